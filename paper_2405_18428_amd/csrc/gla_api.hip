@@ -132,10 +132,13 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
         fast = false;
         *use_fast = false;
     }
-    const int cps = plan_chunks_per_span(p.B * p.H, nchunks, use_mfma, fast ? fast_groups_per_cu(p) : 2, fast);
+    // (the token-by-token engine's epilogue pass is one group per span, like the plan of the bf16 hi/lo engine)
+    const size_t bh = (size_t)p.B * p.H;
+    const int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
+                  ? recurrent_chunks_per_span(p)
+                  : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma, fast ? fast_groups_per_cu(p) : 2, fast);
     p.span_len = cps * kChunk;
     p.nspans = (nchunks + cps - 1) / cps;
-    const size_t bh = (size_t)p.B * p.H;
     p.ws_state = static_cast<float *>(workspace);
     p.ws_lgam = reinterpret_cast<float *>(static_cast<char *>(workspace) +
                                           align_up(bh * p.nspans * p.dk * p.dv * sizeof(float), 256));

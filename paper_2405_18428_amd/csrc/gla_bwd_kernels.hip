@@ -1,27 +1,17 @@
-// Kernels that exist only for the backward pass of the GLA recurrence
-// (DiG paper, Sec. 3.1 Eq. (attn_gla) rows 1-3 with beta = 1, differentiated).
+// The gate gradient of the backward pass of the GLA recurrence
+// (DiG paper, Sec. 3.1 Eq. (attn_gla) rows 1-3, differentiated).
 //
 // With S_s the state after scan step s and G_s = dL/dS_s (which obeys the same kind
 // of recurrence walked backwards, G_s = q_s^T dO_s + diag(alpha_{s+1}) G_{s+1}):
 //     dq_s[c] = sum_n S_s[c,n] dO_s[n]        dk_s[c] = sum_n G_s[c,n] v_s[n]
 //     dv_s    = k_s G_s                        (a forward pass with q, k, v := k, q, dO)
 //     dlog_alpha_s = sum_{s' >= s} (q_s' * dq_s' - k_s' * dk_s')      (reverse cumulative sum)
-// dq and dk read the state along its value axis, which the forward engines (they read
-// it along the key axis) do not do.  For bf16 inputs with head sizes the MFMA engine
-// takes, that read runs in chunk form on the MFMA units (gla_mfma_bwd.hip).  The
-// row_read_kernel of this file covers everything else (fp32 inputs, odd head sizes):
-// it walks one span token by token in fp32 with the state rows in registers, thread c
-// of a wave owning row c of half of the value columns.  The state entering the span
-// comes from the span plan of the forward pass (span-state pass + carry kernel).
-// The two kernels of the gate gradient (the reverse cumulative sum) serve both paths.
+// The two kernels here form the last line from the first two, which the row-read kernels
+// of gla_mfma_bwd.hip (MFMA engine) or gla_recurrent.hip (token by token) have written.
 #include "gla_common.h"
 
 namespace gla {
 namespace {
-
-constexpr int kTile = 16;          // tokens staged per round
-constexpr int kRowWaves = 2;       // waves per work-group; each owns half of the value columns
-constexpr int kColsPerWave = kMaxDv / kRowWaves;
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
@@ -31,170 +21,6 @@ template <> __device__ inline float load_elem<float>(const void *base, size_t id
 }
 template <> __device__ inline float load_elem<uint16_t>(const void *base, size_t idx) {
     return bf16_bits_to_float(static_cast<const uint16_t *>(base)[idx]);
-}
-
-// r_s[c] = sum_n S_s[c,n] w_s[n] for the scan steps of one span; S follows (p.k, p.v, p.log_alpha).
-// p.q is not used; `w` has the layout of p.v, `r` (fp32) that of p.k.
-// A tile of kTile tokens is staged in LDS (alpha and k per channel; v and w interleaved in groups of four
-// columns, as fp32; fetched one tile ahead), then walked token by token: the rows v_s and w_s are the same for all lanes and are read
-// as broadcasts, 16 bytes of each per ds_read_b128 pair.
-// BETA: the state element (c, n) decays by alpha[c] * beta[n] (two-sided gate, p.log_beta).
-template <typename TIn, bool BETA>
-__global__ __launch_bounds__(kRowWaves * 64) void row_read_kernel(Params p, const void *w, float *r) {
-    __shared__ __attribute__((aligned(16))) float s_bq[BETA ? kTile : 1][BETA ? kMaxDv / 4 : 1][4];   // beta per column
-    __shared__ float s_a[kTile][kMaxDk];
-    __shared__ float s_k[kTile][kMaxDk];
-    __shared__ __attribute__((aligned(16))) float s_vw[kTile][kMaxDv / 4][8];   // [token][column quad][v0..v3, w0..w3]
-    __shared__ float s_r[kRowWaves][kTile][kMaxDk];
-    __shared__ int s_tok[kTile];
-
-    const int tid = threadIdx.x;
-    const int c = tid & 63;                                     // state row (key channel) of this lane
-    const int half = __builtin_amdgcn_readfirstlane(tid >> 6);  // which value columns
-    const int bh = blockIdx.x / p.nspans;
-    const int sp = blockIdx.x - bh * p.nspans;
-    const int dk = p.dk, dv = p.dv, T = p.T;
-    const int s_begin = sp * p.span_len;
-    const int s_end = min(T, s_begin + p.span_len);
-    const size_t base_k = slab_k(p, bh), base_v = slab_v(p, bh);
-    const size_t st_k = (size_t)p.st_k, st_v = (size_t)p.st_v;
-    // column quads of this wave: [quad_lo, quad_hi)
-    const int nquads = (dv + 3) / 4;
-    const int per_wave = (nquads + kRowWaves - 1) / kRowWaves;
-    const int quad_lo = half * per_wave;
-    const int quad_hi = min(nquads, quad_lo + per_wave);
-    const bool row_active = c < dk;
-
-    float S[kColsPerWave];
-#pragma unroll
-    for (int n = 0; n < kColsPerWave; ++n) S[n] = 0.f;
-    if (p.nspans > 1 && row_active) {
-        const float *s0 = p.ws_state + ((size_t)bh * p.nspans + sp) * dk * dv + (size_t)c * dv;
-#pragma unroll
-        for (int n = 0; n < kColsPerWave; ++n)
-            if (4 * quad_lo + n < dv && n < 4 * (quad_hi - quad_lo)) S[n] = s0[4 * quad_lo + n];
-    }
-
-    // The rows of a tile are fetched into registers one tile ahead (the loads of tile t + 1 are in flight while
-    // tile t is walked) and reach LDS, gates exponentiated, at the start of their own round.  Slots: the key side
-    // has token rows half, half + 2, ... of channel c; the value side has (token row, column quad) pairs
-    // tid, tid + 128, ... as 8- or 16-byte pieces when the row pitch allows it, element by element otherwise.
-    constexpr int kKSlots = kTile / kRowWaves;
-    constexpr int kVSlots = kTile * (kMaxDv / 4) / (kRowWaves * 64);
-    const bool vec = (dv % 4 == 0) && (st_v % 4 == 0) && (base_v % 4 == 0);   // uniform
-    float ra[kKSlots], rk[kKSlots];
-    f32x4 rv[kVSlots], rw[kVSlots], rb[kVSlots];
-    auto fetch = [&](int t0) {
-#pragma unroll
-        for (int m = 0; m < kKSlots; ++m) {
-            const int j = half + kRowWaves * m;
-            const bool valid = t0 + j < s_end;
-            const int sc = min(t0 + j, s_end - 1);
-            ra[m] = 0.f;      // a step past the span leaves the state alone: alpha = 1, k = 0
-            rk[m] = 0.f;
-            if (valid && row_active) {
-                const int n = scan_token(p.scan_dir, sc, T, p.grid_h, p.grid_w);
-                const int ng = scan_token(p.scan_dir, max(sc - p.gate_shift, 0), T, p.grid_h, p.grid_w);
-                ra[m] = p.log_alpha[base_k + (size_t)ng * st_k + c];
-                rk[m] = load_elem<TIn>(p.k, base_k + (size_t)n * st_k + c);
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < kVSlots; ++m) {
-            const int idx = tid + kRowWaves * 64 * m;
-            const int j = idx / nquads, col = 4 * (idx - j * nquads);
-            rv[m] = rw[m] = rb[m] = f32x4{0.f, 0.f, 0.f, 0.f};     // zero past dv and past the span (beta = 1)
-            if (j < kTile && t0 + j < s_end) {
-                const int sc = t0 + j;
-                const int n = scan_token(p.scan_dir, sc, T, p.grid_h, p.grid_w);
-                const size_t e = base_v + (size_t)n * st_v + col;
-                size_t eg = e;
-                if (BETA) eg = base_v + (size_t)scan_token(p.scan_dir, max(sc - p.gate_shift, 0), T, p.grid_h, p.grid_w) * st_v + col;
-                if (vec) {
-                    if constexpr (sizeof(TIn) == 4) {
-                        rv[m] = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(p.v) + e);
-                        rw[m] = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(w) + e);
-                    } else {
-                        const uint2 tv = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(p.v) + e);
-                        const uint2 tw = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(w) + e);
-                        rv[m] = f32x4{__builtin_bit_cast(float, tv.x << 16), __builtin_bit_cast(float, tv.x & 0xffff0000u),
-                                      __builtin_bit_cast(float, tv.y << 16), __builtin_bit_cast(float, tv.y & 0xffff0000u)};
-                        rw[m] = f32x4{__builtin_bit_cast(float, tw.x << 16), __builtin_bit_cast(float, tw.x & 0xffff0000u),
-                                      __builtin_bit_cast(float, tw.y << 16), __builtin_bit_cast(float, tw.y & 0xffff0000u)};
-                    }
-                    if constexpr (BETA) rb[m] = *reinterpret_cast<const f32x4 *>(p.log_beta + eg);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (col + i < dv) {
-                            rv[m][i] = load_elem<TIn>(p.v, e + i);
-                            rw[m][i] = load_elem<TIn>(w, e + i);
-                            if constexpr (BETA) rb[m][i] = p.log_beta[eg + i];
-                        }
-                    }
-                }
-            }
-        }
-    };
-    fetch(s_begin);
-
-    for (int t0 = s_begin; t0 < s_end; t0 += kTile) {
-        __syncthreads();
-        if (tid < kTile)
-            s_tok[tid] = (t0 + tid < s_end) ? scan_token(p.scan_dir, t0 + tid, T, p.grid_h, p.grid_w) : -1;
-        if (row_active) {
-#pragma unroll
-            for (int m = 0; m < kKSlots; ++m) {
-                s_a[half + kRowWaves * m][c] = expf(ra[m]);
-                s_k[half + kRowWaves * m][c] = rk[m];
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < kVSlots; ++m) {
-            const int idx = tid + kRowWaves * 64 * m;
-            const int j = idx / nquads, qd = idx - j * nquads;
-            if (j < kTile) {
-                *reinterpret_cast<f32x4 *>(&s_vw[j][qd][0]) = rv[m];
-                *reinterpret_cast<f32x4 *>(&s_vw[j][qd][4]) = rw[m];
-                if constexpr (BETA)
-                    *reinterpret_cast<f32x4 *>(&s_bq[j][qd][0]) =
-                        f32x4{expf(rb[m][0]), expf(rb[m][1]), expf(rb[m][2]), expf(rb[m][3])};
-            }
-        }
-        if (t0 + kTile < s_end) fetch(t0 + kTile);
-        __syncthreads();
-        for (int j = 0; j < kTile; ++j) {
-            const float a = s_a[j][c], kc = s_k[j][c];
-            float acc = 0.f;
-#pragma unroll
-            for (int qd = 0; qd < kColsPerWave / 4; ++qd) {
-                if (quad_lo + qd < quad_hi) {   // uniform
-                    const f32x4 vq = *reinterpret_cast<const f32x4 *>(&s_vw[j][quad_lo + qd][0]);
-                    const f32x4 wq = *reinterpret_cast<const f32x4 *>(&s_vw[j][quad_lo + qd][4]);
-                    f32x4 bq = f32x4{1.f, 1.f, 1.f, 1.f};
-                    if constexpr (BETA) bq = *reinterpret_cast<const f32x4 *>(&s_bq[j][quad_lo + qd][0]);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        S[4 * qd + i] = fmaf(BETA ? a * bq[i] : a, S[4 * qd + i], kc * vq[i]);
-                        acc = fmaf(S[4 * qd + i], wq[i], acc);
-                    }
-                }
-            }
-            s_r[half][j][c] = acc;
-        }
-        __syncthreads();
-        // sum the partial reads of the waves and store the tile
-        for (int idx = tid; idx < kTile * dk; idx += kRowWaves * 64) {
-            const int j = idx / dk, cc = idx - j * dk;
-            const int n = s_tok[j];
-            if (n >= 0) {
-                float x = 0.f;
-#pragma unroll
-                for (int h = 0; h < kRowWaves; ++h) x += s_r[h][j][cc];
-                r[base_k + (size_t)n * st_k + cc] = x;
-            }
-        }
-    }
 }
 
 // ---- dlog_alpha: reverse cumulative sum over the scan order of (q * dq - k * dk), in two kernels ----
@@ -400,19 +226,6 @@ hipError_t launch_dg(const Params &p, const float *dq, const float *dk_grad, flo
 }
 
 }  // namespace
-
-hipError_t launch_row_read(const Params &p, const void *w, float *r, hipStream_t stream) {
-    dim3 grid((unsigned)(p.B * p.H * p.nspans)), block(kRowWaves * 64);
-    const bool bf16 = p.qkv_dtype == GLA_DT_BF16;
-    if (p.log_beta != nullptr) {
-        if (bf16) hipLaunchKernelGGL((row_read_kernel<uint16_t, true>), grid, block, 0, stream, p, w, r);
-        else hipLaunchKernelGGL((row_read_kernel<float, true>), grid, block, 0, stream, p, w, r);
-    } else {
-        if (bf16) hipLaunchKernelGGL((row_read_kernel<uint16_t, false>), grid, block, 0, stream, p, w, r);
-        else hipLaunchKernelGGL((row_read_kernel<float, false>), grid, block, 0, stream, p, w, r);
-    }
-    return hipGetLastError();
-}
 
 int dg_spans(int T) { return (T + kDgSpan - 1) / kDgSpan; }
 
