@@ -111,7 +111,9 @@ int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_c
 // Engine for the span passes (p.qkv_dtype, sizes and strides must be set) and the span plan with its workspace.
 // use_fast (optional): the caller is the plain forward pass and would take the fp16 output pass where it covers
 // the call; on return, whether it does (the span plan is then sized for that kernel's residency).
-int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use_fast = nullptr) {
+// ws_limit: room for the plan where the workspace is not sized for every plan.
+int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use_fast = nullptr,
+                           size_t ws_limit = ~(size_t)0) {
     if (g_opt_engine == GLA_ENGINE_RECURRENT) {
         use_mfma = false;
     } else if (g_opt_engine == GLA_ENGINE_MFMA || g_opt_engine == GLA_ENGINE_MFMA_FP16) {
@@ -134,9 +136,21 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     }
     // (the token-by-token engine's epilogue pass is one group per span, like the plan of the bf16 hi/lo engine)
     const size_t bh = (size_t)p.B * p.H;
-    const int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
+    int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
                   ? recurrent_chunks_per_span(p)
                   : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma, fast ? fast_groups_per_cu(p) : 2, fast);
+    // A last span of one ragged chunk: some of the fp16 engine's lanes see no token in it, so it raises the flag of
+    // every sequence, and each would be walked again by one work-group of the bf16 hi/lo kernel.  Those kernels then
+    // take the whole call, on their own span plan (32 sequences of 2745 tokens at 36 / 72 channels: 160 us with the
+    // fallback, 35 us).
+    if (fast && g_opt_engine != GLA_ENGINE_MFMA_FP16 && p.T % kChunk != 0 && (nchunks - 1) % cps == 0) {
+        const int hilo = plan_chunks_per_span(p.B * p.H, nchunks, true);
+        if (plan_workspace_bytes(bh, (size_t)((nchunks + hilo - 1) / hilo), p.dk, p.dv) <= ws_limit) {
+            fast = false;
+            *use_fast = false;
+            cps = hilo;
+        }
+    }
     p.span_len = cps * kChunk;
     p.nspans = (nchunks + cps - 1) / cps;
     p.ws_state = static_cast<float *>(workspace);
@@ -409,7 +423,7 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
     }
 
     bool use_mfma, use_fast = false;
-    st = choose_engine_and_plan(p, workspace, use_mfma, &use_fast);
+    st = choose_engine_and_plan(p, workspace, use_mfma, &use_fast, plan_sized_workspace ? ws_bytes : ~(size_t)0);
     if (st != GLA_OK) return st;
     if (plan_sized_workspace && ws_bytes < plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv))
         return GLA_ERR_WORKSPACE;
@@ -477,7 +491,7 @@ size_t static_plan_bytes(int B, int H, int T, int dk, int dv) {
     bool use_mfma;
     alignas(256) static unsigned char layout_base[256];   // only offsets from it are formed, nothing is accessed
     bool use_fast = false;
-    if (choose_engine_and_plan(p, layout_base, use_mfma, &use_fast) != GLA_OK) return ~(size_t)0;
+    if (choose_engine_and_plan(p, layout_base, use_mfma, &use_fast, kStaticScratchBytes) != GLA_OK) return ~(size_t)0;
     return plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv);
 }
 

@@ -279,3 +279,21 @@ def test_gate_prologue_contract_workloads(name, scan):
     e_out, e_fin = rel_err(out, ref), rel_err(fin, ref_fin)
     print(f"  {name} scan={scan}: err(out)={e_out:.3e} err(state)={e_fin:.3e}", flush=True)
     assert e_out <= TOL_BF16 and e_fin <= TOL_BF16
+
+
+@pytest.mark.parametrize("gh,gw,cps", [(45, 61, 0), (45, 61, 3), (17, 19, 1), (17, 19, 5), (25, 41, 8)])
+def test_one_ragged_chunk_in_the_last_span(gh, gw, cps):
+    """The fp16 engine cannot vouch for a last span of one ragged chunk: such a call runs on the bf16 hi/lo kernels
+    as a whole.  Bar: 1e-4 of the RMS, twice those kernels' error and 30 times below the fp16 operands'."""
+    gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, cps)
+    B, H, dk, dv = 2, 16, 36, 72
+    d = gi.make_inputs(B, H, gh * gw, dk, dv, "bf16", seed=gw)
+    x = upload(d)
+    for scan in (1, 2):
+        ro, rf = oracle(d, gh, gw, scan)
+        out = torch.empty(B, H, gh * gw, dv, device="cuda")
+        fin = torch.empty(B, H, dk, dv, device="cuda")
+        for o, f in (gla.gla_fwd_ex(*x, gh, gw, scan), gla.gla_fwd_static(*x, gh, gw, scan, out, fin)):
+            torch.cuda.synchronize()
+            assert rel_err(o.cpu().numpy(), ro) <= 1e-4
+            assert rel_err(f.cpu().numpy(), rf) <= 1e-4
