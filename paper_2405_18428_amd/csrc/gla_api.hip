@@ -97,7 +97,7 @@ int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_c
         }
     }
     if (cps <= 0) {
-        // no more work-groups than are resident at once (two per compute unit); sequences of up to four chunks are
+        // no more work-groups than are resident at once; sequences of up to four chunks are
         // walked in one pass (a second kernel costs more than the chunks it would save)
         const long long resident_groups = 256LL * groups_per_cu;
         cps = (int)(((long long)bh * nchunks + resident_groups - 1) / resident_groups);
@@ -138,13 +138,14 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     const size_t bh = (size_t)p.B * p.H;
     int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
                   ? recurrent_chunks_per_span(p)
-                  : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma, fast ? fast_groups_per_cu(p) : 2, fast);
+                  : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma,
+                                         fast ? fast_groups_per_cu(p) : (use_mfma ? mfma_groups_per_cu(p) : 2), fast);
     // A last span of one ragged chunk: some of the fp16 engine's lanes see no token in it, so it raises the flag of
     // every sequence, and each would be walked again by one work-group of the bf16 hi/lo kernel.  Those kernels then
     // take the whole call, on their own span plan (32 sequences of 2745 tokens at 36 / 72 channels: 160 us with the
     // fallback, 35 us).
     if (fast && g_opt_engine != GLA_ENGINE_MFMA_FP16 && p.T % kChunk != 0 && (nchunks - 1) % cps == 0) {
-        const int hilo = plan_chunks_per_span(p.B * p.H, nchunks, true);
+        const int hilo = plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p));
         if (plan_workspace_bytes(bh, (size_t)((nchunks + hilo - 1) / hilo), p.dk, p.dv) <= ws_limit) {
             fast = false;
             *use_fast = false;

@@ -136,6 +136,7 @@ bool mfma_engine_supports(const Params &p);
 // compute unit holds, and its launcher
 bool fast_engine_supports(const Params &p);
 int fast_groups_per_cu(const Params &p);
+int mfma_groups_per_cu(const Params &p);     // the same for the bf16 hi/lo kernels that walk the sequence once more
 hipError_t launch_fast_output(const Params &p, hipStream_t stream);
 hipError_t launch_fast_state(const Params &p, hipStream_t stream);   // its span-state pass (phase 1)
 // backward-only kernels: r_s[c] = sum_n S_s[c,n] w_s[n] over the states of (p.k, p.v, p.log_alpha); and

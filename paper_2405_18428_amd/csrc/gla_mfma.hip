@@ -1103,6 +1103,10 @@ bool mfma_engine_supports(const Params &p) {
            slab < (1LL << 31);
 }
 
+// The output pass and the backward pass's row reads: two work-groups fit a compute unit's LDS up to 40 key channels
+// and 80 value columns, one with larger heads and with the two-sided gate's extra rows.
+int mfma_groups_per_cu(const Params &p) { return two_sided(p) || p.dk > 40 || p.dv > 80 ? 1 : 2; }
+
 hipError_t launch_mfma_span(const Params &p, SpanMode mode, hipStream_t stream) {
     return mode == kModeState ? launch_mode<kModeState>(p, stream) : launch_mode<kModeOutput>(p, stream);
 }
