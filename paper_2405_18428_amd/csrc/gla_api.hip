@@ -173,6 +173,28 @@ size_t bwd_totals_bytes(int B, int H, int T, int dk) {
     return align_up((size_t)B * H * dg_spans(T) * dk * sizeof(float), 256);
 }
 
+// Room for the forward states at the bounds of the reversed walk's spans, beyond what is left of the span states' room
+// (bounded for one span per chunk, which a default plan only takes while all spans are resident at once).
+size_t bwd_bound_bytes(int B, int H, int T, int dk, int dv) {
+    const size_t chunks = (size_t)B * H * (((size_t)T + kChunk - 1) / kChunk);
+    return align_up((chunks < 512 ? chunks : 512) * dk * dv * sizeof(float), 256);
+}
+
+// Sets base up for gate gradients formed by the reversed walk itself, if its workspace has room for the states at the
+// span bounds: in what the plan leaves of the span states' room, or in the room from `extra` on.
+bool place_bounds(Params &base, void *workspace, size_t state_bytes, size_t extra, size_t ws_bytes) {
+    const size_t bh = (size_t)base.B * base.H;
+    base.bounds = base.nspans - 1;
+    base.bound_len = base.span_len;
+    if (base.bounds == 0) return true;
+    const size_t need = bh * base.bounds * base.dk * base.dv * sizeof(float);
+    size_t at = plan_workspace_bytes(bh, (size_t)base.nspans, base.dk, base.dv);
+    if (at + need > state_bytes) at = extra;
+    if (at + need > (at == extra ? ws_bytes : state_bytes)) return false;
+    base.ws_bound = reinterpret_cast<float *>(static_cast<char *>(workspace) + at);
+    return true;
+}
+
 // Backward pass (see gla_bwd_kernels.hip for the formulas): three walks over the sequence on the span plan of
 // the forward pass, then the reverse cumulative sum for the gate gradient.
 int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha, const void *d_out,
@@ -211,6 +233,9 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
     base.chain_in_output = use_mfma && base.nspans > 1 &&
                            (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
                             (g_opt_carry == GLA_CARRY_AUTO && base.nspans <= kMaxChainedSpans));
+    // one reversed walk for dk, dv and the gate gradient (MFMA engine)
+    const bool one_walk = use_mfma && !g_opt_bwd_split;
+    const bool with_gates = one_walk && place_bounds(base, workspace, state_bytes, state_bytes + bwd_totals_bytes(B, H, T, dk), ws_bytes);
     auto span = [&](const Params &p, SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
     };
@@ -254,14 +279,21 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
     Params pb = base;
     pb.q = k; pb.k = q; pb.v = d_out; pb.log_alpha = log_alpha; pb.scan_dir = scan_dir ^ 1; pb.gate_shift = 1;
     pb.out = dv_grad;
+    if (with_gates) {
+        pb.span_shift = pb.nspans * pb.span_len - T;
+        pb.fwd_dq = dq;
+        pb.dlog_alpha = dlog_alpha;
+    }
     if (states(pb) != hipSuccess) return GLA_ERR_HIP;
-    if (use_mfma && !g_opt_bwd_split) {
+    if (one_walk) {
         // one walk over the chunks of G for both dk_s = G_s v_s (row read) and dv_s = k_s G_s (outputs with q := k)
         if (launch_mfma_row_read(pb, v, dk_grad, stream, true) != hipSuccess) return GLA_ERR_HIP;
     } else {
         if (span(pb, kModeOutput) != hipSuccess) return GLA_ERR_HIP;             // dv_s = k_s G_s
         if (row_read(pb, v, dk_grad) != hipSuccess) return GLA_ERR_HIP;          // dk_s = G_s v_s
     }
+
+    if (with_gates) return GLA_OK;
 
     // 3. dlog_alpha = reverse cumulative sum of q * dq - k * dk along the scan
     Params pc = base;
@@ -308,6 +340,9 @@ int run_bwd_gates(const void *q, const void *k, const void *v, const float *log_
     base.chain_in_output = use_mfma && base.nspans > 1 &&
                            (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
                             (g_opt_carry == GLA_CARRY_AUTO && base.nspans <= kMaxChainedSpans));
+    const bool one_walk = use_mfma && !g_opt_bwd_split;     // one reversed walk for dk, dv and both gate gradients
+    const bool with_gates = one_walk && place_bounds(base, workspace, state_bytes,
+                                                     state_bytes + totals_bytes + bwd_gates_out_bytes(B, H, T, dv), ws_bytes);
     auto span = [&](const Params &p, SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
     };
@@ -334,14 +369,23 @@ int run_bwd_gates(const void *q, const void *k, const void *v, const float *log_
     //    gates): dv_s = k_s G_s (outputs with q := k), dk_s = G_s v_s
     Params pb = base;
     pb.q = k; pb.k = q; pb.v = d_out; pb.scan_dir = scan_dir ^ 1; pb.gate_shift = 1; pb.out = dv_grad;
+    if (with_gates) {
+        pb.span_shift = pb.nspans * pb.span_len - T;
+        pb.fwd_dq = dq;
+        pb.fwd_out = out_fwd ? out_fwd : o_buf;
+        pb.dlog_alpha = dlog_alpha;
+        pb.dlog_beta = dlog_beta;
+    }
     if (states(pb) != hipSuccess) return GLA_ERR_HIP;
-    if (use_mfma && !g_opt_bwd_split) {
+    if (one_walk) {
         // one walk over the chunks of G for both dk (row read) and dv (outputs with q := k)
         if (launch_mfma_row_read(pb, v, dk_grad, stream, true) != hipSuccess) return GLA_ERR_HIP;
     } else {
         if (span(pb, kModeOutput) != hipSuccess) return GLA_ERR_HIP;
         if (row_read(pb, v, dk_grad) != hipSuccess) return GLA_ERR_HIP;
     }
+
+    if (with_gates) return GLA_OK;
 
     // 3. gate gradients: reverse cumulative sums of q * dq - k * dk (key side) and of dO * o - v * dv (value
     //    side: the same kernels over the dv columns, with dO, v in the places of q, k)
@@ -624,7 +668,7 @@ size_t gla_bwd_gates_workspace_bytes(int B, int H, int T, int dk, int dv, int qk
     (void)qkv_dtype;
     if (B <= 0 || H <= 0 || T <= 0 || dk <= 0 || dv <= 0) return 0;
     return workspace_bytes(B, H, T, dk, dv) + bwd_totals_bytes(B, H, T, dk > dv ? dk : dv) +
-           bwd_gates_out_bytes(B, H, T, dv);
+           bwd_gates_out_bytes(B, H, T, dv) + bwd_bound_bytes(B, H, T, dk, dv);
 }
 
 int gla_bwd_gates(const void *q, const void *k, const void *v, const float *log_alpha, const float *log_beta,
@@ -639,7 +683,7 @@ int gla_bwd_gates(const void *q, const void *k, const void *v, const float *log_
 size_t gla_bwd_workspace_bytes(int B, int H, int T, int dk, int dv, int qkv_dtype) {
     if (B <= 0 || H <= 0 || T <= 0 || dk <= 0 || dv <= 0) return 0;
     if (qkv_dtype != GLA_DT_F32 && qkv_dtype != GLA_DT_BF16) return 0;
-    return workspace_bytes(B, H, T, dk, dv) + bwd_totals_bytes(B, H, T, dk);
+    return workspace_bytes(B, H, T, dk, dv) + bwd_totals_bytes(B, H, T, dk) + bwd_bound_bytes(B, H, T, dk, dv);
 }
 
 int gla_fwd(const void *q, const void *k, const void *v, const float *log_alpha,

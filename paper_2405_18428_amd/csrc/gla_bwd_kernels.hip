@@ -7,7 +7,9 @@
 //     dv_s    = k_s G_s                        (a forward pass with q, k, v := k, q, dO)
 //     dlog_alpha_s = sum_{s' >= s} (q_s' * dq_s' - k_s' * dk_s')      (reverse cumulative sum)
 // The two kernels here form the last line from the first two, which the row-read kernels
-// of gla_mfma_bwd.hip (MFMA engine) or gla_recurrent.hip (token by token) have written.
+// of gla_mfma_bwd.hip (MFMA engine) or gla_recurrent.hip (token by token) have written.  They serve the token-by-token
+// engine, GLA_OPT_BWD_SPLIT, and workspaces without room for the states at the span bounds; elsewhere the reversed walk
+// of gla_mfma_bwd.hip forms the gate gradients itself.
 #include "gla_common.h"
 
 namespace gla {

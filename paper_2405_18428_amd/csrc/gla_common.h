@@ -46,6 +46,9 @@ struct Params {
     int B, H, T, dk, dv, grid_h, grid_w, scan_dir;
     int nspans;             // spans per (batch, head)
     int span_len;           // tokens per span, a multiple of kChunk
+    int span_shift;         // span sp is steps [sp * span_len - span_shift, (sp + 1) * span_len - span_shift) of the
+                            //    sequence (MFMA engine; the reversed walk of the backward pass: its spans then begin
+                            //    where those of the forward walk end, and the first one is the short one)
     int gate_shift;         // 1: scan step s uses the log_alpha row of the token visited at step s-1 (the
                             //    reverse-mode recurrence dS_s = diag(alpha_{s+1}) dS_{s+1} + q_s^T dO_s walked backwards)
     int chain_in_output;    // 1: no phase-2 kernel; the output pass chains U_0..U_{r-1} itself and phase 1
@@ -73,7 +76,24 @@ struct Params {
     int *ws_fail;           // [B*H, nspans of the fp16 engine's plan]
     int only_flagged;
     int fail_spans;         // flags per (batch, head) when only_flagged is set
+    // backward pass on the MFMA engine: the state after every bound_len scan steps, which the walk for dq leaves in
+    // ws_bound ([B*H, bounds, dk, dv]) and the reversed walk for dk, dv starts its gate gradients from; and what that
+    // walk needs to form them (dlog_alpha; dlog_beta with the two-sided gate)
+    float *ws_bound;
+    int bound_len, bounds;
+    const float *fwd_dq, *fwd_out;
+    float *dlog_alpha, *dlog_beta;
 };
+
+// first scan step of span sp, and the step after its last
+__host__ __device__ inline int span_begin(const Params &p, int sp) {
+    const int s = sp * p.span_len - p.span_shift;
+    return s > 0 ? s : 0;
+}
+__host__ __device__ inline int span_end(const Params &p, int sp) {
+    const int s = (sp + 1) * p.span_len - p.span_shift;
+    return s < p.T ? s : p.T;
+}
 
 // the gate has a value-side factor
 __host__ __device__ inline bool two_sided(const Params &p) { return p.log_beta != nullptr || p.z_beta != nullptr; }

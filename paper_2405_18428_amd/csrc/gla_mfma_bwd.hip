@@ -48,9 +48,8 @@ struct RLayout {
     static constexpr int kRowV = kChunk * kVStride * 2;
     static constexpr int kSt = 16 * kNct * kVStride * 2;
 
-    static constexpr int oTok = 0;                                        // int[3][64]
-    static constexpr int oTokG = oTok + 3 * kChunk * 4;                   // int[3][64]
-    static constexpr int oGam = oTokG + 3 * kChunk * 4;                   // float[64] exp(b_C)
+    static constexpr int oTok = 0;                                        // int[4][64]
+    static constexpr int oGam = oTok + 4 * kChunk * 4;                    // float[64] exp(b_C)
     static constexpr int oLa = oGam + 64 * 4;
     static constexpr int oKHi = oLa + kChunk * kLaStride * 4;
     static constexpr int oKLo = oKHi + kRowK;
@@ -67,7 +66,11 @@ struct RLayout {
     static constexpr int oVLo = oLb + kChunk * kLbStride * 4;
     static constexpr int oWLo = oVLo + kRowV;
     static constexpr int oGamB = oWLo + kRowV;                            // float[kDvp]
-    static constexpr int kBytes = BETA ? oGamB + kDvp * 4 : oEndAlpha;
+    // with DV, the gate gradients: sums of the waves' 16 tokens [4], and the sum over all later scan steps [2]
+    static constexpr int oTot = BETA ? oGamB + kDvp * 4 : oEndAlpha;      // float[4 + 2][kDkp]
+    static constexpr int oTotB = oTot + (DV ? 6 * kDkp * 4 : 0);          // float[4 + 2][kDvp]
+    static constexpr int kBytes = oTotB + (DV && BETA ? 6 * kDvp * 4 : 0);
+    static_assert(kBytes % 16 == 0, "cleared in 16-byte pieces");
 };
 
 template <int N>
@@ -82,6 +85,14 @@ using int_c = std::integral_constant<int, N>;
 //     r_j = E_j * ( sum_{i<=j} (w~_j . v~_i) k~_i + S_0 w~_j ),   S_C = diag(E_C) (S_0 + K~^T V~) diag(F_C):
 // the same contractions with v~ and w~ (bf16 hi/lo pairs, all four products) in the places of v and w; with DV the
 // outputs are o_j = F_j * (sum_{i<=j} (q~_j . k~_i) v~_i + q~_j S_0) (F_j is left in place of the raw log_beta row).
+// Gate gradients (DV, p.dlog_alpha): dlog_alpha_s = sum_{s' >= s} (q dq - k dk) runs along this very walk (it visits the
+// last scan step first), so the kernel forms it from the dk rows it holds and the dq rows of the walk before, instead of
+// two more kernels over q, k, dq, dk and the result (29.6 + 17 us at the size below; this kernel takes 21 us more, and
+// the call 205 -> 182 us on MI355X: 16 sequences of 16384 steps, 36 / 72 channels).  The part of the sum that lies
+// before the span is a product of two states (see the prologue), not a chain over spans; its error is five times
+// smaller than that of a sum over all steps (2.7e-5 against 1.5e-4).  With the two-sided gate both gradients (4
+// images of 1024 tokens): 244 -> 192 us for a training step, which includes that the chain of the span states keeps
+// 4 instead of 16 spans in flight there and no longer spills.
 template <int NDK8, int NDV16, int MINW, bool DV, bool BETA = false>
 __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, const void *w_in, float *r_out) {
     using L = RLayout<NDK8, NDV16, DV, BETA>;
@@ -91,12 +102,11 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
     constexpr int NCT = L::kNct;
     constexpr int KSV = (NDV16 * 2 + 3) / 4;        // 32-column steps of the contractions over value columns
     constexpr int TPW = (NDV16 + NW - 1) / NW;      // value-column tiles of the state per wave
-    constexpr int NTB = 3;
+    constexpr int NTB = 4;       // token maps: the chunk before (its last token may be row 0's gate), this one, the next two
     static_assert(16 * NCT <= CHS, "channel tiles must fit the operand row");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int *s_tok = reinterpret_cast<int *>(smem + L::oTok);
-    int *s_tokg = reinterpret_cast<int *>(smem + L::oTokG);
     float *s_gam = reinterpret_cast<float *>(smem + L::oGam);
     float *s_la = reinterpret_cast<float *>(smem + L::oLa);
     uint16_t *s_khi = reinterpret_cast<uint16_t *>(smem + L::oKHi);
@@ -111,6 +121,8 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
     uint16_t *s_vlo = reinterpret_cast<uint16_t *>(smem + L::oVLo);
     uint16_t *s_wlo = reinterpret_cast<uint16_t *>(smem + L::oWLo);
     float *s_gamb = reinterpret_cast<float *>(smem + L::oGamB);
+    float *s_tot = reinterpret_cast<float *>(smem + L::oTot), *s_later = s_tot + 4 * L::kDkp;         // DV
+    float *s_totb = reinterpret_cast<float *>(smem + L::oTotB), *s_laterb = s_totb + 4 * L::kDvp;     // DV, BETA
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -131,8 +143,8 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
     if (p.chain_in_output && (bh & 1)) sp_ = p.nspans - 1 - sp_;
     const int sp = sp_;
     const int dk = p.dk, dv = p.dv, T = p.T;
-    const int s_begin = sp * p.span_len;
-    const int s_end = min(T, s_begin + p.span_len);
+    const int s_begin = span_begin(p, sp);
+    const int s_end = span_end(p, sp);
     const int nch = (s_end - s_begin + kChunk - 1) / kChunk;
 
     const size_t base_k = slab_k(p, bh), base_v = slab_v(p, bh);
@@ -144,6 +156,10 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
     const char *gq = static_cast<const char *>(p.q) + base_k * 2;
     const char *glb = reinterpret_cast<const char *>(p.log_beta) + base_v * 4;
     char *gout = static_cast<char *>(p.out) + base_v * 4;
+    const char *gdq = reinterpret_cast<const char *>(p.fwd_dq) + base_k * 4;          // DV: the gate gradients
+    const char *gof = reinterpret_cast<const char *>(p.fwd_out) + base_v * 4;
+    char *gdla = reinterpret_cast<char *>(p.dlog_alpha) + base_k * 4;
+    char *gdlb = reinterpret_cast<char *>(p.dlog_beta) + base_v * 4;
 
     // ---- state tiles of this wave, transposed: acc[i][ct][r] = S[c = 16 ct + lm][n = 16 (w + 4 i) + 4 g + r] ----
     f32x4 acc[TPW][NCT];
@@ -158,7 +174,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
         const bool chain = p.chain_in_output && sp > 0;   // uniform over the group
         if (chain) {
             constexpr int kV4 = (L::kDkp * L::kDvp / 4 + NTHR - 1) / NTHR;  // float4 per thread
-            constexpr int kBudget = MINW >= 2 ? 32 : 64;                    // float4 in flight
+            constexpr int kBudget = BETA ? 16 : 32;                         // float4 in flight (BETA: as many of log_beta)
             constexpr int kRun = kBudget / kV4 > 0 ? kBudget / kV4 : 1;     // spans in flight
             chain_span_states<NTHR, kV4, kRun, BETA>(p, bh, sp, tid, reinterpret_cast<float *>(smem));
         }
@@ -198,7 +214,65 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
         const int s = s_begin + tid;
         const int sc = (s < s_end) ? s : s_begin;
         s_tok[tid] = scan_token(p.scan_dir, sc, T, p.grid_h, p.grid_w);
-        s_tokg[tid] = scan_token(p.scan_dir, max(sc - p.gate_shift, 0), T, p.grid_h, p.grid_w);
+    }
+    const int tok_before = scan_token(p.scan_dir, max(s_begin - 1, 0), T, p.grid_h, p.grid_w);   // the step before the span
+    if (tid == 0) s_tok[NTB * kChunk - 1] = tok_before;
+    if constexpr (DV) {
+        // The gate gradients are sums over all later scan steps, i.e. over the steps this walk has made before:
+        // those before the span add up to the gradient of the gate between it and them,
+        //     sum_{s' >= b} (q dq - k dk)[c] = sum_n alpha_b[c] beta_b[n] G_b[c,n] S_{b-1}[c,n]
+        // (and the sum over c for beta_b[n]), G_b being the state that enters this walk (acc) and S_{b-1} the one that
+        // the forward walk left at the same place.
+        if (p.dlog_alpha != nullptr && sp > 0) {       // (uniform)
+            const float *sb = p.ws_bound + ((size_t)bh * p.bounds + (T - s_begin) / p.bound_len - 1) * (size_t)(dk * dv);
+            const float *la_b = reinterpret_cast<const float *>(gla_) + (size_t)tok_before * p.st_k;
+            const float *lb_b = reinterpret_cast<const float *>(glb) + (size_t)tok_before * p.st_v;
+            float row_sum[NCT];
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) row_sum[ct] = 0.f;
+#pragma unroll
+            for (int i = 0; i < TPW; ++i) {
+                const int n = 16 * (w + NW * i) + 4 * g;
+                f32x4 col_sum = f32x4{0.f, 0.f, 0.f, 0.f}, fb = f32x4{1.f, 1.f, 1.f, 1.f};
+                if constexpr (BETA) {
+                    if (n < dv) {
+                        const f32x4 lb4 = *reinterpret_cast<const f32x4 *>(lb_b + n);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) fb[r] = exp2_fast(lb4[r] * kLog2e);
+                    }
+                }
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    const int c = 16 * ct + lm;
+                    if (c < dk && n < dv) {
+                        const f32x4 s4 = *reinterpret_cast<const f32x4 *>(sb + c * dv + n);
+                        const float a = exp2_fast(la_b[c] * kLog2e);
+                        const f32x4 x = acc[i][ct] * s4 * fb * a;
+                        row_sum[ct] += (x[0] + x[1]) + (x[2] + x[3]);
+                        if constexpr (BETA) col_sum += x;
+                    }
+                }
+                if constexpr (BETA) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float x = col_sum[r];
+                        for (int m = 1; m < 16; m *= 2) x += __shfl_xor(x, m);
+                        col_sum[r] = x;
+                    }
+                    if (lm == 0 && n < dv) *reinterpret_cast<f32x4 *>(s_laterb + n) = col_sum;
+                }
+            }
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) {
+                float x = row_sum[ct];
+                x += __shfl_xor(x, 16);
+                x += __shfl_xor(x, 32);
+                if (g == 0 && 16 * ct + lm < dk) s_tot[w * L::kDkp + 16 * ct + lm] = x;
+            }
+            __syncthreads();
+            if (tid < dk)
+                s_later[tid] = (s_tot[tid] + s_tot[L::kDkp + tid]) + (s_tot[2 * L::kDkp + tid] + s_tot[3 * L::kDkp + tid]);
+        }
     }
     __syncthreads();
 
@@ -232,13 +306,15 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
     u32x4 r_v[kVF], r_w[kVF];
     f32x4 r_lb[BETA ? kVF : 1][2];   // log_beta of the same 8 columns as the v piece
     auto load_chunk = [&](int chunk) {
-        const int *tok = s_tok + (chunk % NTB) * kChunk;
-        const int *tokg = s_tokg + (chunk % NTB) * kChunk;
+        const int first = (chunk % NTB) * kChunk;
+        const int *tok = s_tok + first;
+        // token whose gate row `row` uses: with gate_shift the one visited a step earlier
+        auto tokg = [&](int row) { return s_tok[(first + row - p.gate_shift) & (NTB * kChunk - 1)]; };
 #pragma unroll
         for (int m = 0; m < kF; ++m) {
             const int row = frp[m] >> 8;
             const uint32_t pc = 8u * (uint32_t)(frp[m] & 255);
-            r_la[m] = *reinterpret_cast<const f32x4 *>(gla_ + 2u * ((uint32_t)tokg[row] * dk2 + pc));
+            r_la[m] = *reinterpret_cast<const f32x4 *>(gla_ + 2u * ((uint32_t)tokg(row) * dk2 + pc));
             r_k[m] = *reinterpret_cast<const u32x2 *>(gk + (uint32_t)tok[row] * dk2 + pc);
             if constexpr (DV) r_q[m] = *reinterpret_cast<const u32x2 *>(gq + (uint32_t)tok[row] * dk2 + pc);
         }
@@ -248,7 +324,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             r_v[m] = *reinterpret_cast<const u32x4 *>(gv + e2);
             r_w[m] = *reinterpret_cast<const u32x4 *>(gw + e2);
             if constexpr (BETA) {
-                const char *lbp = glb + 2u * ((uint32_t)tokg[fvrp[m] >> 8] * dv2 + 16u * (uint32_t)(fvrp[m] & 255));
+                const char *lbp = glb + 2u * ((uint32_t)tokg(fvrp[m] >> 8) * dv2 + 16u * (uint32_t)(fvrp[m] & 255));
                 r_lb[m][0] = *reinterpret_cast<const f32x4 *>(lbp);
                 r_lb[m][1] = *reinterpret_cast<const f32x4 *>(lbp + 16);
             }
@@ -322,8 +398,6 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             const int s = s_begin + (chunk + 2) * kChunk + lane;
             const int sc = (s < s_end) ? s : s_begin;
             s_tok[((chunk + 2) % NTB) * kChunk + lane] = scan_token(p.scan_dir, sc, T, p.grid_h, p.grid_w);
-            s_tokg[((chunk + 2) % NTB) * kChunk + lane] =
-                scan_token(p.scan_dir, max(sc - p.gate_shift, 0), T, p.grid_h, p.grid_w);
         }
         __syncthreads();
 
@@ -431,6 +505,22 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                     ktl[q][ct] = u32x4{l0[0], l0[1], l1[0], l1[1]};
                 }
             };
+            // rows of the gate gradient (key side), fetched now so that they have arrived when dk is there
+            const int row = 16 * IT + lm;
+            u32x2 raw_k[DV ? NCT : 1], raw_q[DV ? NCT : 1];
+            f32x4 row_dq[DV ? NCT : 1];
+            if constexpr (DV) {
+                if (p.dlog_alpha != nullptr) {
+                    const uint32_t first = (uint32_t)tok[row] * (uint32_t)p.st_k;    // (rows past the span: a valid token's)
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct) {
+                        const uint32_t e = first + (uint32_t)min(16 * ct + 4 * g, dk - 4);
+                        raw_k[ct] = *reinterpret_cast<const u32x2 *>(gk + 2u * e);
+                        raw_q[ct] = *reinterpret_cast<const u32x2 *>(gq + 2u * e);
+                        row_dq[ct] = *reinterpret_cast<const f32x4 *>(gdq + 4u * e);
+                    }
+                }
+            }
             f32x4 rr[NCT];
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) rr[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -490,7 +580,6 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                 }
             }
             // scale by E and store: lane (lm, g) holds channels 16 ct + 4 g .. + 3 of token 16 IT + lm
-            const int row = 16 * IT + lm;
             if (row < nvalid) {
                 char *orow = gr + ((uint32_t)tok[row] * (uint32_t)p.st_k + 4u * (uint32_t)g) * 4u;
 #pragma unroll
@@ -501,6 +590,30 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
 #pragma unroll
                         for (int r = 0; r < 4; ++r) o[r] *= e[r];
                         *reinterpret_cast<f32x4 *>(orow + 64 * ct) = o;
+                        if constexpr (DV) rr[ct] = o;
+                    }
+                }
+            }
+            // Gate gradient, key side: x_s = q_s * dq_s - k_s * dk_s summed over the steps walked so far (in this walk
+            // the rows called k are q, those called q are k).  The sums inside the wave's 16 tokens take the place of
+            // E in its rows; what the other waves' tokens and the earlier chunks add follows after the next barrier.
+            if constexpr (DV) {
+                if (p.dlog_alpha != nullptr) {
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct) {
+                        float x[4] = {0.f, 0.f, 0.f, 0.f};
+                        if (row < nvalid && 16 * ct + 4 * g < dk) {
+                            x[0] = fmaf(bf16_lo_as_float(raw_k[ct][0]), row_dq[ct][0], -bf16_lo_as_float(raw_q[ct][0]) * rr[ct][0]);
+                            x[1] = fmaf(bf16_hi_as_float(raw_k[ct][0]), row_dq[ct][1], -bf16_hi_as_float(raw_q[ct][0]) * rr[ct][1]);
+                            x[2] = fmaf(bf16_lo_as_float(raw_k[ct][1]), row_dq[ct][2], -bf16_lo_as_float(raw_q[ct][1]) * rr[ct][2]);
+                            x[3] = fmaf(bf16_hi_as_float(raw_k[ct][1]), row_dq[ct][3], -bf16_hi_as_float(raw_q[ct][1]) * rr[ct][3]);
+                        }
+                        row_scan16x4(x[0], x[1], x[2], x[3]);
+                        if (16 * ct + 4 * g < dk) {
+                            const f32x4 x4 = f32x4{x[0], x[1], x[2], x[3]};
+                            *reinterpret_cast<f32x4 *>(s_la + row * LAS + 16 * ct + 4 * g) = x4;
+                            if (lm == 15) *reinterpret_cast<f32x4 *>(s_tot + IT * L::kDkp + 16 * ct + 4 * g) = x4;
+                        }
                     }
                 }
             }
@@ -609,6 +722,33 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                         }
                     }
                 }
+                if (p.dlog_alpha != nullptr) {
+                    if constexpr (BETA) {
+                        // value side: y_s = o_s * dO_s - v_s * dv_s (dO are the rows called v, v those called w), the
+                        // sums in the place of F
+                        const uint32_t first = (uint32_t)tok[row] * (uint32_t)p.st_v;
+#pragma unroll
+                        for (int x = 0; x < NX; ++x) {
+                            const uint32_t e = first + (uint32_t)min(16 * x + 4 * g, dv - 4);
+                            const u32x2 rv = *reinterpret_cast<const u32x2 *>(gv + 2u * e);
+                            const u32x2 rw = *reinterpret_cast<const u32x2 *>(gw + 2u * e);
+                            const f32x4 of = *reinterpret_cast<const f32x4 *>(gof + 4u * e);
+                            const bool there = row < nvalid && 16 * x + 4 * g < dv;
+                            float y[4];
+                            y[0] = fmaf(bf16_lo_as_float(rv[0]), of[0], -bf16_lo_as_float(rw[0]) * o[x][0]);
+                            y[1] = fmaf(bf16_hi_as_float(rv[0]), of[1], -bf16_hi_as_float(rw[0]) * o[x][1]);
+                            y[2] = fmaf(bf16_lo_as_float(rv[1]), of[2], -bf16_lo_as_float(rw[1]) * o[x][2]);
+                            y[3] = fmaf(bf16_hi_as_float(rv[1]), of[3], -bf16_hi_as_float(rw[1]) * o[x][3]);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) y[r] = there ? y[r] : 0.f;
+                            row_scan16x4(y[0], y[1], y[2], y[3]);
+                            const f32x4 y4 = f32x4{y[0], y[1], y[2], y[3]};
+                            *reinterpret_cast<f32x4 *>(s_lb + row * LBS + 16 * x + 4 * g) = y4;
+                            if (lm == 15) *reinterpret_cast<f32x4 *>(s_totb + IT * L::kDvp + 16 * x + 4 * g) = y4;
+                        }
+                    }
+                    __syncthreads();     // the sums of all four waves' tokens are there
+                }
             }
             // state update on this wave's tiles: S^T += V^T K~, then the chunk's decay per channel
 #pragma unroll
@@ -652,12 +792,54 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                     }
                 }
             }
+            if constexpr (DV) {
+                if (p.dlog_alpha != nullptr) {
+                    // sums over all later scan steps: the wave's own rows + the waves before it + everything before
+                    // this chunk; the last wave leaves the total for the next chunk
+                    auto finish = [&](auto pitch_c, auto stride_c, float *rows, const float *tot, float *later, char *dst,
+                                      int stride, int width) {
+                        constexpr int P = decltype(pitch_c)::value, RS = decltype(stride_c)::value;
+#pragma unroll
+                        for (int x = 0; x < P / 16 + (P % 16 != 0); ++x) {
+                            const int c = 16 * x + 4 * g;
+                            if (c < width) {
+                                f32x4 add = *reinterpret_cast<const f32x4 *>(later + (chunk & 1) * P + c);
+#pragma unroll
+                                for (int u = 0; u < IT; ++u) add += *reinterpret_cast<const f32x4 *>(tot + u * P + c);
+                                if (row < nvalid)
+                                    *reinterpret_cast<f32x4 *>(dst + ((uint32_t)tok[row] * (uint32_t)stride + (uint32_t)c) * 4u) =
+                                        *reinterpret_cast<const f32x4 *>(rows + row * RS + c) + add;
+                                if (IT == NW - 1 && lm == 0)
+                                    *reinterpret_cast<f32x4 *>(later + ((chunk + 1) & 1) * P + c) =
+                                        add + *reinterpret_cast<const f32x4 *>(tot + IT * P + c);
+                            }
+                        }
+                    };
+                    finish(int_c<L::kDkp>{}, int_c<LAS>{}, s_la, s_tot, s_later, gdla, p.st_k, dk);
+                    if constexpr (BETA) finish(int_c<L::kDvp>{}, int_c<LBS>{}, s_lb, s_totb, s_laterb, gdlb, p.st_v, dv);
+                }
+            }
         };
         switch (w) {
         case 0: contract(int_c<0>{}); break;
         case 1: contract(int_c<1>{}); break;
         case 2: contract(int_c<2>{}); break;
         default: contract(int_c<3>{}); break;
+        }
+        if constexpr (!DV) {
+            const int done = s_begin + (chunk + 1) * kChunk;       // scan steps walked: a bound of the reversed walk's spans?
+            if (p.ws_bound != nullptr && done < T && done % p.bound_len == 0) {
+                float *dst = p.ws_bound + ((size_t)bh * p.bounds + done / p.bound_len - 1) * (size_t)(dk * dv);
+#pragma unroll
+                for (int i = 0; i < TPW; ++i) {
+                    const int n = 16 * (w + NW * i) + 4 * g;
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct) {
+                        const int c = 16 * ct + lm;
+                        if (c < dk && n < dv) *reinterpret_cast<f32x4 *>(dst + c * dv + n) = acc[i][ct];
+                    }
+                }
+            }
         }
         __syncthreads();
     }

@@ -1,0 +1,60 @@
+"""Gate gradients formed inside the reversed walk of the backward pass: span bounds of ragged sequences, slowly decaying
+gates (the start of every span then carries most of the sum), and workspaces without room for the states at the bounds
+(the separate reverse-cumulative-sum kernels).  Bar 2e-2 x RMS as for every bf16 call; the two routes differ by the
+rounding of sums of T terms, at most T 2^-24 of their largest partial sum (about 1e-3 of the RMS here)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_2405_18428_amd as gla
+from paper_2405_18428_amd import inputs as gi
+from oracle import gla_oracle as orc
+from oracle import gla_oracle_gates as og
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+@pytest.fixture(autouse=True)
+def _plan():
+    yield
+    gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, 0)
+
+
+def _err(got, ref, floor):
+    rms = max(float(np.sqrt(np.mean(np.square(ref)))), floor)
+    return float(np.abs(got.cpu().numpy().astype(np.float64) - ref).max() / rms)
+
+
+@pytest.mark.parametrize("gh,gw,cps", [(1, 64, 1), (1, 65, 1), (5, 77, 2), (19, 31, 3), (16, 40, 2), (1, 1023, 5)])
+@pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
+@pytest.mark.parametrize("z_mean", [0.0, 3.0])
+def test_span_bounds(gh, gw, cps, dk, dv, z_mean):
+    B, H, T = 1, 3, gh * gw
+    gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, cps)
+    d = gi.make_gate_inputs(B, H, T, dk, dv, "bf16", seed=T + dk, z_mean=z_mean)
+    bits = gi.round_to_bf16_bits(np.random.Generator(np.random.PCG64(5)).standard_normal((B, H, T, dv), dtype=np.float32))
+    w = gi.bf16_bits_to_f32(bits)
+    up = lambda b: torch.from_numpy(b.view(np.int16)).cuda().view(torch.bfloat16)  # noqa: E731
+    q, k, v = (up(d[n + "_bits"]) for n in "qkv")
+    dw = up(bits)
+    la, lb = (torch.from_numpy(d[n]).cuda() for n in ("log_alpha", "log_beta"))
+    chunks = (T + 63) // 64
+    bounds = (min(B * H * chunks, 512) * dk * dv * 4 + 255) // 256 * 256      # what the states at the bounds may add
+    for scan in (0, 3):
+        ref = orc.gla_bwd(d["q"], d["k"], d["v"], d["log_alpha"], w, gh, gw, scan)
+        floor = float(np.sqrt(np.mean(np.square(d["q"] * ref[0]))))
+        routes = []
+        for less in (0, bounds):
+            ws = torch.empty(gla.gla_bwd_workspace_bytes(B, H, T, dk, dv) - less, dtype=torch.uint8, device="cuda")
+            got = gla.gla_bwd(q, k, v, la, dw, gh, gw, scan, workspace=ws)
+            assert max(_err(g, r, f) for g, r, f in zip(got, ref, (0, 0, 0, floor))) <= TOL
+            routes.append(got[3].cpu().numpy().astype(np.float64))
+        assert _err(torch.from_numpy(routes[0]), routes[1], floor) <= 2e-3
+        ref = og.gla_bwd_gates(d["q"], d["k"], d["v"], d["log_alpha"], d["log_beta"], w, gh, gw, scan)
+        floors = (0, 0, 0, float(np.sqrt(np.mean(np.square(d["q"] * ref[0])))), float(np.sqrt(np.mean(np.square(d["v"] * ref[2])))))
+        for less in (0, bounds):
+            n = gla.gla_bwd_gates_workspace_bytes(B, H, T, dk, dv) - less
+            got = gla.gla_bwd_gates(q, k, v, la, lb, dw, gh, gw, scan, workspace=torch.empty(n, dtype=torch.uint8, device="cuda"))
+            assert max(_err(g, r, f) for g, r, f in zip(got, ref, floors)) <= TOL
