@@ -89,6 +89,25 @@ using int_c = std::integral_constant<int, N>;
 // waves (the wave with the most score tiles then owns none); the state-only pass has nothing else to balance
 // against and splits its waves over the row tiles as evenly as they divide (row tile ct: waves NW ct / NCT up to
 // NW (ct + 1) / NCT), and the waves of a row tile take its value-column tiles in turn.
+// (8 waves in the output pass: the two waves of a 16-token tile each own what its columns hold of the tiles above.)
+template <bool ROW_OWNED, int NW, int NCT, int NDV16>
+struct TileMap;
+template <int NCT, int NDV16>
+struct TileMap<true, 8, NCT, NDV16> {
+    static constexpr int WPC = 4 / NCT;
+    static constexpr int kHalf = (NDV16 + 1) / 2;              // column tiles of the first wave
+    static constexpr int kPerWave = (kHalf + WPC - 1) / WPC;
+    __host__ __device__ static constexpr int ct(int w, int = 0) { return (w & 3) / WPC; }
+    __host__ __device__ static constexpr int nt(int w, int i) { return (w >> 2) * kHalf + (w & 3) % WPC + WPC * i; }
+    __host__ __device__ static constexpr bool valid(int w, int i) {
+        return ct(w) < NCT && nt(w, i) < (w < 4 ? kHalf : NDV16);
+    }
+    __host__ __device__ static constexpr int count(int w) {
+        int n = 0;
+        for (int i = 0; i < kPerWave; ++i) n += valid(w, i) ? 1 : 0;
+        return n;
+    }
+};
 template <bool ROW_OWNED, int NW, int NCT, int NDV16>
 struct TileMap {
     static_assert(ROW_OWNED || NW >= NCT, "state pass: at least one wave per row tile");
@@ -139,7 +158,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
     // valid piece), so that the number of younger loads is a constant and the waits can leave them in flight.
     constexpr bool UNCOND = OUT || DEPTH > 1;
     constexpr int NTB = DEPTH + 2;              // token-map buffers in LDS
-    static_assert(NW == 4 || (NW == 8 && !OUT), "4 waves, or 8 in the state pass");
+    static_assert(NW == 4 || (NW == 8 && !(OUT && FUSE)), "4 or 8 waves (the epilogue wants a token's row in one wave)");
     static_assert(DEPTH == 1 || (DEPTH == 2 && !OUT), "two register sets only in the state pass");
     static_assert(NTB <= 4 && (DEPTH + 1) * kChunk <= NTHR, "token maps: four buffers, first ones filled in one go");
     static_assert(16 * NCT <= CHS, "state tiles must fit the operand row");
@@ -230,7 +249,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
         const bool chain = p.chain_in_output && (sp > 0 || p.initial_state != nullptr);  // uniform over the group
         if (chain) {
             constexpr int kV4 = (L::kDkp * L::kDvp / 4 + NTHR - 1) / NTHR;  // float4 per thread
-            constexpr int kBudget = MINW >= 4 ? 16 : 32;                    // float4 in flight: 64 or 128 registers of U
+            constexpr int kBudget = MINW >= 4 || BETA ? 16 : 32;            // float4 in flight: 64 or 128 registers of U (BETA: as many of log_beta)
             constexpr int kRun = kBudget / kV4 > 0 ? kBudget / kV4 : 1;     // spans in flight
             chain_span_states<NTHR, kV4, kRun, BETA>(p, bh, sp, tid, reinterpret_cast<float *>(smem));
         }
@@ -680,7 +699,10 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
             };
 
             if constexpr (OUT) {
-                constexpr int NX = NDV16;          // this wave's 16 output rows span all value-column tiles
+                // the value-column tiles of this wave's 16 output rows: all, or with 8 waves one of two shares (the score
+                // tiles are then computed by both waves of the rows)
+                constexpr int X0 = NW == 8 && W >= 4 ? (NDV16 + 1) / 2 : 0;
+                constexpr int NX = (NW == 8 && W < 4 ? (NDV16 + 1) / 2 : NDV16) - X0;
                 const uint16_t *qrow_h = s_qhi + (16 * IT + lm) * CHS, *qrow_l = s_qlo + (16 * IT + lm) * CHS;
                 // When the last 32-channel step holds a single 8-channel group (dk = 33..40, or dk <= 8), its four
                 // products hi*hi, hi*lo, lo*hi, lo*lo share one MFMA: lane groups g = 0..3 of the gated operand and
@@ -712,11 +734,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
                 auto load_v = [&](int q32) {
 #pragma unroll
                     for (int x = 0; x < NX; ++x) {
-                        vt[q32][x][0] = lds_read_tr(vrow + 32 * q32 * VS + 16 * x);
-                        vt[q32][x][1] = lds_read_tr(vrow + (32 * q32 + 16) * VS + 16 * x);
+                        vt[q32][x][0] = lds_read_tr(vrow + 32 * q32 * VS + 16 * (X0 + x));
+                        vt[q32][x][1] = lds_read_tr(vrow + (32 * q32 + 16) * VS + 16 * (X0 + x));
                         if constexpr (BETA) {
-                            vtl[q32][x][0] = lds_read_tr(vrow_l + 32 * q32 * VS + 16 * x);
-                            vtl[q32][x][1] = lds_read_tr(vrow_l + (32 * q32 + 16) * VS + 16 * x);
+                            vtl[q32][x][0] = lds_read_tr(vrow_l + 32 * q32 * VS + 16 * (X0 + x));
+                            vtl[q32][x][1] = lds_read_tr(vrow_l + (32 * q32 + 16) * VS + 16 * (X0 + x));
                         }
                     }
                 };
@@ -733,9 +755,9 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
 #pragma unroll
                     for (int x = 0; x < NX; ++x) {
                         if (PT && ks == KS - 1) {
-                            sth[buf][x] = *reinterpret_cast<const u32x4 *>(sttail + (16 * x + lm) * CHS);
+                            sth[buf][x] = *reinterpret_cast<const u32x4 *>(sttail + (16 * (X0 + x) + lm) * CHS);
                         } else {
-                            const int srow = (16 * x + lm) * CHS + colk[ks];
+                            const int srow = (16 * (X0 + x) + lm) * CHS + colk[ks];
                             sth[buf][x] = *reinterpret_cast<const u32x4 *>(s_sthi + srow);
                             stl[buf][x] = *reinterpret_cast<const u32x4 *>(s_stlo + srow);
                         }
@@ -813,7 +835,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
                     const char *prow_ = gout + ((uint32_t)tok[16 * IT + lm] * (uint32_t)p.st_v + 4u * (uint32_t)g) * 4u;
 #pragma unroll
                     for (int x = 0; x < NX; ++x)
-                        prev[x] = (4 * g + 16 * x < dv) ? *reinterpret_cast<const f32x4 *>(prow_ + 64 * x)
+                        prev[x] = (4 * g + 16 * (X0 + x) < dv) ? *reinterpret_cast<const f32x4 *>(prow_ + 64 * (X0 + x))
                                                         : f32x4{0.f, 0.f, 0.f, 0.f};
                 }
                 ph[1] = u32x2{0, 0};
@@ -864,8 +886,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
                     const float *erow = s_lb + (16 * IT + lm) * LBS + 4 * g;
 #pragma unroll
                     for (int x = 0; x < NX; ++x) {
-                        if (4 * g + 16 * x < dv) {
-                            const f32x4 e4 = *reinterpret_cast<const f32x4 *>(erow + 16 * x);
+                        if (4 * g + 16 * (X0 + x) < dv) {
+                            const f32x4 e4 = *reinterpret_cast<const f32x4 *>(erow + 16 * (X0 + x));
 #pragma unroll
                             for (int r = 0; r < 4; ++r) o[x][r] *= e4[r];
                         }
@@ -919,7 +941,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
                 }
                 const int row = 16 * IT + lm;
                 if (row < nvalid) {
-                    const int col0 = 4 * g;
+                    const int col0 = 4 * g + 16 * X0;
                     char *orow = gout + ((uint32_t)tok[row] * (uint32_t)p.st_v + (uint32_t)col0) * (uint32_t)sizeof(TOut);
 #pragma unroll
                     for (int x = 0; x < NX; ++x) {
@@ -934,8 +956,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
                 }
 #pragma unroll
                 for (int i = 0; i < NTW; ++i)
-                    update_state(0, i, v_frag(0, TM::nt(W, i)), v_frag(1, TM::nt(W, i)), v_frag_lo(0, TM::nt(W, i)),
-                                 v_frag_lo(1, TM::nt(W, i)));
+                    update_state(0, i, v_frag(0, TM::nt(W, i) - X0), v_frag(1, TM::nt(W, i) - X0),
+                                 v_frag_lo(0, TM::nt(W, i) - X0), v_frag_lo(1, TM::nt(W, i) - X0));
             } else {
                 // state pass: K~ of the wave's row tile once, V of tile i+1 read while tile i is contracted
                 u32x2 uv[2][2][2];                              // [buffer][32-token step][half]
@@ -1022,19 +1044,9 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
     }
 }
 
-template <int MODE, int NDK8, int NDV16, int DEPTH, bool FUSE, bool ACC, typename TOut, bool BETA>
-hipError_t launch_depth(const Params &p, hipStream_t stream) {
+template <int MODE, int NDK8, int NDV16, int NW, int MINW, int DEPTH, bool FUSE, bool ACC, typename TOut, bool BETA>
+hipError_t launch_waves(const Params &p, hipStream_t stream) {
     using L = Layout<MODE, NDK8, NDV16, BETA>;
-    if constexpr (L::kBytes > 160 * 1024) {
-        return hipErrorInvalidConfiguration;   // (two-sided gate at the largest head sizes: mfma_engine_supports says no)
-    } else {
-    // The state pass is light on registers and runs best with 8 waves (4 per SIMD at two work-groups per compute
-    // unit); the output pass needs the 256-register budget of 4-wave groups for its operand batches.
-    constexpr int NW = (MODE == kModeState) ? 8 : 4;
-    // register cap: no tighter than the waves per SIMD that the LDS footprint lets a compute unit hold anyway
-    constexpr int kGroupsPerCu = (160 * 1024) / L::kBytes;
-    constexpr int kWavesPerSimd = kGroupsPerCu * NW / 4;
-    constexpr int MINW = kWavesPerSimd >= 4 ? 4 : (kWavesPerSimd >= 2 ? 2 : 1);
     auto kernel = mfma_span_kernel<MODE, NDK8, NDV16, NW, MINW, DEPTH, FUSE, ACC, TOut, BETA>;
     static std::atomic<bool> configured[kMaxDevices] = {};  // per instantiation and device
     {
@@ -1045,6 +1057,32 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     dim3 grid((unsigned)(p.B * p.H * spans)), block(NW * 64);
     hipLaunchKernelGGL(kernel, grid, block, L::kBytes, stream, p);
     return hipGetLastError();
+}
+
+template <int MODE, int NDK8, int NDV16, int DEPTH, bool FUSE, bool ACC, typename TOut, bool BETA>
+hipError_t launch_depth(const Params &p, hipStream_t stream) {
+    using L = Layout<MODE, NDK8, NDV16, BETA>;
+    if constexpr (L::kBytes > 160 * 1024) {
+        return hipErrorInvalidConfiguration;   // (two-sided gate at the largest head sizes: mfma_engine_supports says no)
+    } else {
+    // The state pass is light on registers and runs best with 8 waves (4 per SIMD at two work-groups per compute
+    // unit); the output pass needs the 256-register budget of 4-wave groups for its operand batches.  It takes 8 waves
+    // with that budget where the LDS holds one group per compute unit anyway (two-sided gate, 64 sequences of 1024
+    // tokens at 36 / 72: 35.0 -> 30.3 us; 64 / 128 channels, two scan orders summed: 70 -> 57 us a call), or where there
+    // are no more groups than compute units and the gate stage's 4-channel units come out even over 8 waves (dk <= 32:
+    // 48 sequences of 256 tokens 13.0 -> 12.4 us; at dk = 36 the ninth unit takes the first wave a second round, 18.7 ->
+    // 20.0 us).  With two 8-wave groups per compute unit the 128 registers spill (32 -> 77 us, two 1024 px images).
+    constexpr int NW = (MODE == kModeState) ? 8 : 4;
+    // register cap: no tighter than the waves per SIMD that the LDS footprint lets a compute unit hold anyway
+    constexpr int kGroupsPerCu = (160 * 1024) / L::kBytes;
+    constexpr int kWavesPerSimd = kGroupsPerCu * NW / 4;
+    constexpr int MINW = kWavesPerSimd >= 4 ? 4 : (kWavesPerSimd >= 2 ? 2 : 1);
+    if constexpr (MODE == kModeOutput && !FUSE) {
+        // (the range fallback's groups mostly return at once: fewer waves to start)
+        if (kGroupsPerCu < 2 || (NDK8 <= 4 && !p.only_flagged && (long long)p.B * p.H * p.nspans <= 256))
+            return launch_waves<MODE, NDK8, NDV16, 8, 2, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
+    }
+    return launch_waves<MODE, NDK8, NDV16, NW, MINW, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
     }
 }
 

@@ -93,17 +93,28 @@ using int_c = std::integral_constant<int, N>;
 // smaller than that of a sum over all steps (2.7e-5 against 1.5e-4).  With the two-sided gate both gradients (4
 // images of 1024 tokens): 244 -> 192 us for a training step, which includes that the chain of the span states keeps
 // 4 instead of 16 spans in flight there and no longer spills.
-template <int NDK8, int NDV16, int MINW, bool DV, bool BETA = false>
-__global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, const void *w_in, float *r_out) {
+//
+// NW = 4: the waves own 16 tokens each.  NW = 8, where a group has its compute unit to itself anyway (the LDS of the
+// large classes, or no more groups than compute units): two waves per 16 tokens, one for the row read (with DV; without,
+// the channel tiles are shared), one for the outputs, so that a SIMD has a second wave to issue from.  MI355X: 256
+// sequences of 256 steps at 36 / 72 channels, dk and dv 34.4 -> 28.2 us; two-sided gate, 64 sequences of 1024 steps,
+// dk and dv 65.9 -> 50.7 us, dq 33.7 -> 31.8 us; 8 sequences of 2304 steps at 64 / 128, whole backward 105 -> 62 us.
+template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA = false>
+__global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, const void *w_in, float *r_out) {
     using L = RLayout<NDK8, NDV16, DV, BETA>;
     constexpr int LBS = L::kLbStride;
-    constexpr int NW = 4, NTHR = 256;
+    constexpr int NTHR = NW * 64;
+    static_assert(NW == 4 || NW == 8, "one or two waves per 16 tokens");
     constexpr int CHS = L::kChStride, VS = L::kVStride, LAS = L::kLaStride;
     constexpr int NCT = L::kNct;
     constexpr int KSV = (NDV16 * 2 + 3) / 4;        // 32-column steps of the contractions over value columns
     constexpr int TPW = (NDV16 + NW - 1) / NW;      // value-column tiles of the state per wave
     constexpr int NTB = 4;       // token maps: the chunk before (its last token may be row 0's gate), this one, the next two
     static_assert(16 * NCT <= CHS, "channel tiles must fit the operand row");
+    static_assert(NW * L::kDkp <= kChunk * LAS, "scratch of the prologue");
+    // value-column tile of the state that is the i-th of wave w (8 waves without DV: the second waves of the tokens,
+    // which have fewer channel tiles of the row read, take the first four)
+    auto state_tile = [](int w, int i) { return (NW == 8 && !DV ? (w + 4) % 8 : w) + NW * i; };
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int *s_tok = reinterpret_cast<int *>(smem + L::oTok);
@@ -161,7 +172,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
     char *gdla = reinterpret_cast<char *>(p.dlog_alpha) + base_k * 4;
     char *gdlb = reinterpret_cast<char *>(p.dlog_beta) + base_v * 4;
 
-    // ---- state tiles of this wave, transposed: acc[i][ct][r] = S[c = 16 ct + lm][n = 16 (w + 4 i) + 4 g + r] ----
+    // ---- state tiles of this wave, transposed: acc[i][ct][r] = S[c = 16 ct + lm][n = 16 state_tile(w, i) + 4 g + r] ----
     f32x4 acc[TPW][NCT];
 #pragma unroll
     for (int i = 0; i < TPW; ++i)
@@ -183,7 +194,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             const float *s_chain = reinterpret_cast<const float *>(smem);
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
-                const int n = 16 * (w + NW * i) + 4 * g;
+                const int n = 16 * state_tile(w, i) + 4 * g;
 #pragma unroll
                 for (int ct = 0; ct < NCT; ++ct) {
                     const int c = 16 * ct + lm;
@@ -196,7 +207,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             const float *s0 = p.ws_state + ((size_t)bh * p.nspans + sp) * dk * dv;
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
-                const int n = 16 * (w + NW * i) + 4 * g;
+                const int n = 16 * state_tile(w, i) + 4 * g;
 #pragma unroll
                 for (int ct = 0; ct < NCT; ++ct) {
                     const int c = 16 * ct + lm;
@@ -232,7 +243,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             for (int ct = 0; ct < NCT; ++ct) row_sum[ct] = 0.f;
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
-                const int n = 16 * (w + NW * i) + 4 * g;
+                const int n = 16 * state_tile(w, i) + 4 * g;
                 f32x4 col_sum = f32x4{0.f, 0.f, 0.f, 0.f}, fb = f32x4{1.f, 1.f, 1.f, 1.f};
                 if constexpr (BETA) {
                     if (n < dv) {
@@ -267,11 +278,15 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                 float x = row_sum[ct];
                 x += __shfl_xor(x, 16);
                 x += __shfl_xor(x, 32);
-                if (g == 0 && 16 * ct + lm < dk) s_tot[w * L::kDkp + 16 * ct + lm] = x;
+                if (g == 0 && 16 * ct + lm < dk) s_la[w * L::kDkp + 16 * ct + lm] = x;
             }
             __syncthreads();
-            if (tid < dk)
-                s_later[tid] = (s_tot[tid] + s_tot[L::kDkp + tid]) + (s_tot[2 * L::kDkp + tid] + s_tot[3 * L::kDkp + tid]);
+            if (tid < dk) {
+                float x = 0.f;
+#pragma unroll
+                for (int u = 0; u < NW; ++u) x += s_la[u * L::kDkp + tid];
+                s_later[tid] = x;
+            }
         }
     }
     __syncthreads();
@@ -381,13 +396,13 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             const int ln = recompute_per_chunk(lane), lm2 = ln & 15, g2 = ln >> 4;
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
-                if (w + NW * i < NDV16) {
+                if (state_tile(w, i) < NDV16) {
 #pragma unroll
                     for (int ct = 0; ct < NCT; ++ct) {
                         u32x2 hi, lo;
                         SPLIT_PAIR(acc[i][ct][0], acc[i][ct][1], hi[0], lo[0]);
                         SPLIT_PAIR(acc[i][ct][2], acc[i][ct][3], hi[1], lo[1]);
-                        const int off = (16 * ct + lm2) * VS + 16 * (w + NW * i) + 4 * g2;
+                        const int off = (16 * ct + lm2) * VS + 16 * state_tile(w, i) + 4 * g2;
                         *reinterpret_cast<u32x2 *>(s_sthi + off) = hi;
                         *reinterpret_cast<u32x2 *>(s_stlo + off) = lo;
                     }
@@ -480,7 +495,12 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
         for (int ks = 0; ks < KSV; ++ks) coln[ks] = (4 * ks + g3 < 2 * NDV16) ? 8 * (4 * ks + g3) : L::kZeroCol;
         const int tr_row = lm3 >> 2, tr_col = 4 * (lm3 & 3);
         auto contract = [&](auto wave_c) {
-            constexpr int IT = decltype(wave_c)::value;   // 16-token tile of this wave
+            constexpr int W = decltype(wave_c)::value;
+            constexpr int IT = W & 3;                     // 16-token tile of this wave
+            // what the wave does of the tile's work: the row read on channel tiles [CT0, CT1), the outputs
+            constexpr bool READ = !(NW == 8 && DV) || W < 4, OUTPUTS = DV && (NW == 4 || W >= 4);
+            constexpr int CT0 = NW == 8 && !DV && W >= 4 ? (NCT + 1) / 2 : 0;
+            constexpr int CT1 = !READ ? 0 : (NW == 8 && !DV && W < 4 ? (NCT + 1) / 2 : NCT);
             constexpr int NQ = IT / 2 + 1;                // 32-token steps that hold tokens <= the tile's
             const int lm = lm3, g = g3;
             const uint16_t *krow_h = s_khi + (4 * g + tr_row) * CHS + tr_col;
@@ -489,7 +509,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             const uint16_t *vrow_l = s_vlo + (4 * g + tr_row) * VS + tr_col;   // BETA
             u32x4 wf[KSV], wfl[BETA ? KSV : 1];
 #pragma unroll
-            for (int ks = 0; ks < KSV; ++ks) {
+            for (int ks = 0; ks < (CT0 < CT1 ? KSV : 0); ++ks) {
                 wf[ks] = *reinterpret_cast<const u32x4 *>(s_w + (16 * IT + lm) * VS + coln[ks]);
                 if constexpr (BETA) wfl[ks] = *reinterpret_cast<const u32x4 *>(s_wlo + (16 * IT + lm) * VS + coln[ks]);
             }
@@ -509,7 +529,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             const int row = 16 * IT + lm;
             u32x2 raw_k[DV ? NCT : 1], raw_q[DV ? NCT : 1];
             f32x4 row_dq[DV ? NCT : 1];
-            if constexpr (DV) {
+            if constexpr (DV && READ) {
                 if (p.dlog_alpha != nullptr) {
                     const uint32_t first = (uint32_t)tok[row] * (uint32_t)p.st_k;    // (rows past the span: a valid token's)
 #pragma unroll
@@ -524,8 +544,9 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             f32x4 rr[NCT];
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) rr[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+            constexpr bool OWNS = (NW == 8 && !DV ? (W + 4) % 8 : W) < NDV16;   // state tiles of this wave
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
+            for (int q = 0; q < (CT0 < CT1 ? NQ : 0); ++q) {
                 u32x2 ph[2] = {u32x2{0, 0}, u32x2{0, 0}}, pl[2] = {u32x2{0, 0}, u32x2{0, 0}};
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
@@ -557,7 +578,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                 const u32x4 bh_ = u32x4{ph[0][0], ph[0][1], ph[1][0], ph[1][1]};
                 const u32x4 bl_ = u32x4{pl[0][0], pl[0][1], pl[1][0], pl[1][1]};
 #pragma unroll
-                for (int ct = 0; ct < NCT; ++ct) {
+                for (int ct = CT0; ct < CT1; ++ct) {
                     rr[ct] = mfma(kth[q][ct], bh_, rr[ct]);
                     rr[ct] = mfma(kth[q][ct], bl_, rr[ct]);
                     rr[ct] = mfma(ktl[q][ct], bh_, rr[ct]);
@@ -567,7 +588,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
 #pragma unroll
             for (int ks = 0; ks < KSV; ++ks) {
 #pragma unroll
-                for (int ct = 0; ct < NCT; ++ct) {
+                for (int ct = CT0; ct < CT1; ++ct) {
                     const int srow = (16 * ct + lm) * VS + coln[ks];
                     const u32x4 sh = *reinterpret_cast<const u32x4 *>(s_sthi + srow);
                     const u32x4 sl = *reinterpret_cast<const u32x4 *>(s_stlo + srow);
@@ -583,7 +604,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             if (row < nvalid) {
                 char *orow = gr + ((uint32_t)tok[row] * (uint32_t)p.st_k + 4u * (uint32_t)g) * 4u;
 #pragma unroll
-                for (int ct = 0; ct < NCT; ++ct) {
+                for (int ct = CT0; ct < CT1; ++ct) {
                     if (16 * ct + 4 * g < dk) {   // dk is a multiple of 4: all four channels or none
                         const f32x4 e = *reinterpret_cast<const f32x4 *>(s_la + row * LAS + 16 * ct + 4 * g);
                         f32x4 o = rr[ct];
@@ -597,7 +618,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
             // Gate gradient, key side: x_s = q_s * dq_s - k_s * dk_s summed over the steps walked so far (in this walk
             // the rows called k are q, those called q are k).  The sums inside the wave's 16 tokens take the place of
             // E in its rows; what the other waves' tokens and the earlier chunks add follows after the next barrier.
-            if constexpr (DV) {
+            if constexpr (DV && READ) {
                 if (p.dlog_alpha != nullptr) {
 #pragma unroll
                     for (int ct = 0; ct < NCT; ++ct) {
@@ -617,7 +638,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                     }
                 }
             }
-            if constexpr (DV) {
+            if constexpr (OUTPUTS) {
                 // ---- outputs of the wave's 16 tokens: O^T[n][i], lane (lm, g) holds o[x][r] = O[i = 16 IT + lm][n = 16 x + 4 g + r]
                 constexpr int NX = NDV16;
                 constexpr int KS = (NDK8 + 3) / 4;            // 32-channel steps
@@ -747,18 +768,20 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                             if (lm == 15) *reinterpret_cast<f32x4 *>(s_totb + IT * L::kDvp + 16 * x + 4 * g) = y4;
                         }
                     }
-                    __syncthreads();     // the sums of all four waves' tokens are there
                 }
+            }
+            if constexpr (DV) {
+                if (p.dlog_alpha != nullptr) __syncthreads();     // the sums of all waves' tokens are there
             }
             // state update on this wave's tiles: S^T += V^T K~, then the chunk's decay per channel
 #pragma unroll
-            for (int q = NQ; q < 2; ++q) load_k(q);
+            for (int q = CT0 < CT1 ? NQ : 0; q < (OWNS ? 2 : 0); ++q) load_k(q);
             float gm[NCT];
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) gm[ct] = s_gam[16 * ct + lm];
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
-                const int nt = IT + NW * i;
+                const int nt = (NW == 8 && !DV ? (W + 4) % 8 : W) + NW * i;
                 if (nt < NDV16) {
                     u32x4 vt[2], vtl[BETA ? 2 : 1];
 #pragma unroll
@@ -809,14 +832,14 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                                 if (row < nvalid)
                                     *reinterpret_cast<f32x4 *>(dst + ((uint32_t)tok[row] * (uint32_t)stride + (uint32_t)c) * 4u) =
                                         *reinterpret_cast<const f32x4 *>(rows + row * RS + c) + add;
-                                if (IT == NW - 1 && lm == 0)
+                                if (IT == 3 && lm == 0)
                                     *reinterpret_cast<f32x4 *>(later + ((chunk + 1) & 1) * P + c) =
                                         add + *reinterpret_cast<const f32x4 *>(tot + IT * P + c);
                             }
                         }
                     };
-                    finish(int_c<L::kDkp>{}, int_c<LAS>{}, s_la, s_tot, s_later, gdla, p.st_k, dk);
-                    if constexpr (BETA) finish(int_c<L::kDvp>{}, int_c<LBS>{}, s_lb, s_totb, s_laterb, gdlb, p.st_v, dv);
+                    if constexpr (READ) finish(int_c<L::kDkp>{}, int_c<LAS>{}, s_la, s_tot, s_later, gdla, p.st_k, dk);
+                    if constexpr (BETA && OUTPUTS) finish(int_c<L::kDvp>{}, int_c<LBS>{}, s_lb, s_totb, s_laterb, gdlb, p.st_v, dv);
                 }
             }
         };
@@ -824,7 +847,11 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
         case 0: contract(int_c<0>{}); break;
         case 1: contract(int_c<1>{}); break;
         case 2: contract(int_c<2>{}); break;
-        default: contract(int_c<3>{}); break;
+        case 3: contract(int_c<3>{}); break;
+        case 4: if constexpr (NW > 4) contract(int_c<4>{}); break;
+        case 5: if constexpr (NW > 4) contract(int_c<5>{}); break;
+        case 6: if constexpr (NW > 4) contract(int_c<6>{}); break;
+        default: if constexpr (NW > 4) contract(int_c<7>{}); break;
         }
         if constexpr (!DV) {
             const int done = s_begin + (chunk + 1) * kChunk;       // scan steps walked: a bound of the reversed walk's spans?
@@ -832,7 +859,7 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
                 float *dst = p.ws_bound + ((size_t)bh * p.bounds + done / p.bound_len - 1) * (size_t)(dk * dv);
 #pragma unroll
                 for (int i = 0; i < TPW; ++i) {
-                    const int n = 16 * (w + NW * i) + 4 * g;
+                    const int n = 16 * state_tile(w, i) + 4 * g;
 #pragma unroll
                     for (int ct = 0; ct < NCT; ++ct) {
                         const int c = 16 * ct + lm;
@@ -845,20 +872,28 @@ __global__ __launch_bounds__(256, MINW) void mfma_row_read_kernel(Params p, cons
     }
 }
 
-template <int NDK8, int NDV16, bool DV, bool BETA = false>
-hipError_t launch_one(const Params &p, const void *w, float *r, hipStream_t stream) {
+template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA>
+hipError_t launch_waves(const Params &p, const void *w, float *r, hipStream_t stream) {
     using L = RLayout<NDK8, NDV16, DV, BETA>;
-    constexpr int kGroupsPerCu = (160 * 1024) / L::kBytes;
-    constexpr int MINW = kGroupsPerCu >= 2 ? 2 : 1;
-    auto kernel = mfma_row_read_kernel<NDK8, NDV16, MINW, DV, BETA>;
+    auto kernel = mfma_row_read_kernel<NDK8, NDV16, NW, MINW, DV, BETA>;
     static std::atomic<bool> configured[kMaxDevices] = {};  // per instantiation and device
     {
         hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), L::kBytes, configured);
         if (e != hipSuccess) return e;
     }
-    dim3 grid((unsigned)(p.B * p.H * p.nspans)), block(256);
+    dim3 grid((unsigned)(p.B * p.H * p.nspans)), block(NW * 64);
     hipLaunchKernelGGL(kernel, grid, block, L::kBytes, stream, p, w, r);
     return hipGetLastError();
+}
+
+template <int NDK8, int NDV16, bool DV, bool BETA = false>
+hipError_t launch_one(const Params &p, const void *w, float *r, hipStream_t stream) {
+    // 8 waves where a compute unit holds one group anyway: by its LDS, or because there are no more groups than units
+    constexpr int kGroupsPerCu = (160 * 1024) / RLayout<NDK8, NDV16, DV, BETA>::kBytes;
+    if constexpr (kGroupsPerCu >= 2) {
+        if ((long long)p.B * p.H * p.nspans > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA>(p, w, r, stream);
+    }
+    return launch_waves<NDK8, NDV16, 8, 2, DV, BETA>(p, w, r, stream);
 }
 
 template <bool DV>
