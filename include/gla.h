@@ -253,9 +253,9 @@ int gla_fwd_gates(const void *q, const void *k, const void *v, const float *log_
  *   q, k, v, d_out   DEVICE, qkv_dtype (d_out = dL/d out, shaped like v)              (read)
  *   log_alpha        DEVICE, fp32                                                     (read)
  *   dq, dk_grad, dlog_alpha   DEVICE, fp32 [B,H,T,dk];  dv_grad  DEVICE, fp32 [B,H,T,dv]   (written)
- *   workspace        DEVICE, 16-byte aligned, gla_bwd_workspace_bytes(...) bytes.  (The part of it that holds states
- *                    at the bounds of the spans may be left out, up to 512 dk dv floats: the gate gradient then
- *                    takes two kernels more.)
+ *   workspace        DEVICE, 16-byte aligned, gla_bwd_workspace_bytes(...) bytes.  (From fwd_workspace_bytes plus
+ *                    4 dk B H ceil(T / 256) bytes, both rounded up to 256, on the call works as well; where what one
+ *                    walk leaves for the other then has no room it takes three kernels more.)
  *
  * Same status codes as gla_fwd_ex.  Never allocates.
  */

@@ -173,25 +173,47 @@ size_t bwd_totals_bytes(int B, int H, int T, int dk) {
     return align_up((size_t)B * H * dg_spans(T) * dk * sizeof(float), 256);
 }
 
-// Room for the forward states at the bounds of the reversed walk's spans, beyond what is left of the span states' room
-// (bounded for one span per chunk, which a default plan only takes while all spans are resident at once).
+// Room for the forward states at the bounds of the reversed walk's spans and for that walk's own span states, beyond what
+// is left of the span states' room (which a default plan fills only while about all spans are resident at once).
 size_t bwd_bound_bytes(int B, int H, int T, int dk, int dv) {
-    const size_t chunks = (size_t)B * H * (((size_t)T + kChunk - 1) / kChunk);
-    return align_up((chunks < 512 ? chunks : 512) * dk * dv * sizeof(float), 256);
+    const size_t bh = (size_t)B * H, chunks = bh * (((size_t)T + kChunk - 1) / kChunk);
+    return 2 * plan_workspace_bytes(1, chunks < 512 + bh ? chunks : 512 + bh, dk, dv);
 }
 
-// Sets base up for gate gradients formed by the reversed walk itself, if its workspace has room for the states at the
-// span bounds: in what the plan leaves of the span states' room, or in the room from `extra` on.
-bool place_bounds(Params &base, void *workspace, size_t state_bytes, size_t extra, size_t ws_bytes) {
-    const size_t bh = (size_t)base.B * base.H;
-    base.bounds = base.nspans - 1;
-    base.bound_len = base.span_len;
-    if (base.bounds == 0) return true;
-    const size_t need = bh * base.bounds * base.dk * base.dv * sizeof(float);
-    size_t at = plan_workspace_bytes(bh, (size_t)base.nspans, base.dk, base.dv);
-    if (at + need > state_bytes) at = extra;
-    if (at + need > (at == extra ? ws_bytes : state_bytes)) return false;
-    base.ws_bound = reinterpret_cast<float *>(static_cast<char *>(workspace) + at);
+// The span states' arrays of a plan, from `at` on
+void place_states(Params &p, char *at) {
+    const size_t spans = (size_t)p.B * p.H * p.nspans;
+    p.ws_state = reinterpret_cast<float *>(at);
+    at += align_up(spans * p.dk * p.dv * sizeof(float), 256);
+    p.ws_lgam = reinterpret_cast<float *>(at);
+    at += align_up(spans * p.dk * sizeof(float), 256);
+    p.ws_lgam_b = reinterpret_cast<float *>(at);
+}
+
+// Sets the two walks of the backward pass (fwd for dq, rev for dk and dv, on one span plan) up so that the first leaves
+// what the second starts from - the forward states at the span bounds and the local states of the reversed recurrence -
+// if the workspace has room: in the span states' room behind the fwd walk's own (`used` bytes of it), else from `extra`.
+bool place_walks(Params &fwd, Params &rev, void *workspace, size_t used, size_t state_bytes, size_t extra, size_t ws_bytes) {
+    if (rev.nspans == 1) return true;
+    char *ws = static_cast<char *>(workspace);
+    const size_t bh = (size_t)rev.B * rev.H;
+    const size_t bound = align_up(bh * (rev.nspans - 1) * rev.dk * rev.dv * sizeof(float), 256);
+    const size_t states = plan_workspace_bytes(bh, (size_t)rev.nspans, rev.dk, rev.dv);
+    size_t at_bound, at_states;
+    auto take = [&](size_t bytes, size_t &at) {
+        if (used + bytes <= state_bytes) { at = used; used += bytes; return true; }
+        if (extra + bytes <= ws_bytes) { at = extra; extra += bytes; return true; }
+        return false;
+    };
+    if (!take(states, at_states) || !take(bound, at_bound)) return false;
+    place_states(rev, ws + at_states);
+    rev.span_shift = rev.nspans * rev.span_len - rev.T;
+    fwd.ws_gstate = rev.ws_state;
+    fwd.ws_glgam = rev.ws_lgam;
+    fwd.ws_glgam_b = rev.ws_lgam_b;
+    fwd.ws_bound = rev.ws_bound = reinterpret_cast<float *>(ws + at_bound);
+    fwd.bound_len = rev.bound_len = rev.span_len;
+    fwd.bounds = rev.bounds = rev.nspans - 1;
     return true;
 }
 
@@ -233,9 +255,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
     base.chain_in_output = use_mfma && base.nspans > 1 &&
                            (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
                             (g_opt_carry == GLA_CARRY_AUTO && base.nspans <= kMaxChainedSpans));
-    // one reversed walk for dk, dv and the gate gradient (MFMA engine)
-    const bool one_walk = use_mfma && !g_opt_bwd_split;
-    const bool with_gates = one_walk && place_bounds(base, workspace, state_bytes, state_bytes + bwd_totals_bytes(B, H, T, dk), ws_bytes);
+    const bool one_walk = use_mfma && !g_opt_bwd_split;     // one reversed walk for dk, dv and the gate gradient
     auto span = [&](const Params &p, SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
     };
@@ -251,8 +271,9 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
 
     // 1. states of the forward recurrence (k, v, log_alpha); dq_s = S_s dO_s
     Params pa = base;
-    pa.k = k; pa.v = v; pa.log_alpha = log_alpha; pa.scan_dir = scan_dir; pa.gate_shift = 0;
-    if (fwd_workspace && pa.nspans > 1) {
+    pa.q = q; pa.k = k; pa.v = v; pa.log_alpha = log_alpha; pa.scan_dir = scan_dir; pa.gate_shift = 0;
+    const bool reuse = fwd_workspace && pa.nspans > 1;
+    if (reuse) {
         // The forward call on the same tensors ran this very state pass.  Its workspace holds either the chained
         // states S_start(r) (carry kernel) or the local states U_r and log Gamma_r (chained inside its output
         // pass), by the rule that also sets base.chain_in_output.
@@ -269,20 +290,33 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         pa.chain_in_output = use_mfma && pa.nspans > 1 &&
                              (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
                               (g_opt_carry == GLA_CARRY_AUTO && pa.nspans <= kMaxChainedSpans));
-    } else if (states(pa) != hipSuccess) {
-        return GLA_ERR_HIP;
     }
-    if (row_read(pa, d_out, dq) != hipSuccess) return GLA_ERR_HIP;
 
     // 2. states of the reversed recurrence G_s = q_s^T dO_s + diag(alpha_{s+1}) G_{s+1}: the forward recurrence
-    //    with k, v := q, dO, walked from the last scan step, each step using the previous step's gate
+    //    with k, v := q, dO, walked from the last scan step, each step using the previous step's gate.
+    //    With one reversed walk for dk, dv and the gate gradient, the walk for dq leaves its local states.
     Params pb = base;
     pb.q = k; pb.k = q; pb.v = d_out; pb.log_alpha = log_alpha; pb.scan_dir = scan_dir ^ 1; pb.gate_shift = 1;
     pb.out = dv_grad;
+    bool with_gates = false;
+    if (one_walk) {
+        Params rev = pb;        // (on the plan of the walk for dq, which may be the forward call's)
+        rev.nspans = pa.nspans;
+        rev.span_len = pa.span_len;
+        rev.chain_in_output = pa.chain_in_output;
+        const size_t used = reuse ? 0 : plan_workspace_bytes((size_t)B * H, (size_t)pa.nspans, dk, dv);
+        with_gates = place_walks(pa, rev, workspace, used, state_bytes, state_bytes + bwd_totals_bytes(B, H, T, dk), ws_bytes);
+        if (with_gates) pb = rev;
+    }
     if (with_gates) {
-        pb.span_shift = pb.nspans * pb.span_len - T;
         pb.fwd_dq = dq;
         pb.dlog_alpha = dlog_alpha;
+    }
+    if (!reuse && states(pa) != hipSuccess) return GLA_ERR_HIP;
+    if (row_read(pa, d_out, dq) != hipSuccess) return GLA_ERR_HIP;
+    if (with_gates) {
+        if (pb.nspans > 1 && !pb.chain_in_output && launch_carry(pb, stream) != hipSuccess) return GLA_ERR_HIP;
+        return launch_mfma_row_read(pb, v, dk_grad, stream, true) == hipSuccess ? GLA_OK : GLA_ERR_HIP;
     }
     if (states(pb) != hipSuccess) return GLA_ERR_HIP;
     if (one_walk) {
@@ -292,8 +326,6 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         if (span(pb, kModeOutput) != hipSuccess) return GLA_ERR_HIP;             // dv_s = k_s G_s
         if (row_read(pb, v, dk_grad) != hipSuccess) return GLA_ERR_HIP;          // dk_s = G_s v_s
     }
-
-    if (with_gates) return GLA_OK;
 
     // 3. dlog_alpha = reverse cumulative sum of q * dq - k * dk along the scan
     Params pc = base;
@@ -341,8 +373,6 @@ int run_bwd_gates(const void *q, const void *k, const void *v, const float *log_
                            (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
                             (g_opt_carry == GLA_CARRY_AUTO && base.nspans <= kMaxChainedSpans));
     const bool one_walk = use_mfma && !g_opt_bwd_split;     // one reversed walk for dk, dv and both gate gradients
-    const bool with_gates = one_walk && place_bounds(base, workspace, state_bytes,
-                                                     state_bytes + totals_bytes + bwd_gates_out_bytes(B, H, T, dv), ws_bytes);
     auto span = [&](const Params &p, SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
     };
@@ -361,20 +391,26 @@ int run_bwd_gates(const void *q, const void *k, const void *v, const float *log_
     //    dq_s = S_s dO_s
     Params pa = base;
     pa.q = q; pa.k = k; pa.v = v; pa.scan_dir = scan_dir; pa.gate_shift = 0; pa.out = o_buf;
+    Params pb = base;
+    pb.q = k; pb.k = q; pb.v = d_out; pb.scan_dir = scan_dir ^ 1; pb.gate_shift = 1; pb.out = dv_grad;
+    const bool with_gates = one_walk && place_walks(pa, pb, workspace, plan_workspace_bytes((size_t)B * H, (size_t)pa.nspans, dk, dv),
+                                                    state_bytes, state_bytes + totals_bytes + bwd_gates_out_bytes(B, H, T, dv), ws_bytes);
+    if (with_gates) {
+        pb.fwd_dq = dq;
+        pb.fwd_out = out_fwd ? out_fwd : o_buf;
+        pb.dlog_alpha = dlog_alpha;
+        pb.dlog_beta = dlog_beta;
+    }
     if (states(pa) != hipSuccess) return GLA_ERR_HIP;
     if (!out_fwd && span(pa, kModeOutput) != hipSuccess) return GLA_ERR_HIP;   // (the caller may still hold o)
     if (row_read(pa, d_out, dq) != hipSuccess) return GLA_ERR_HIP;
 
     // 2. adjoint recurrence (k, v := q, dO; walked from the last scan step, each step with the previous step's
-    //    gates): dv_s = k_s G_s (outputs with q := k), dk_s = G_s v_s
-    Params pb = base;
-    pb.q = k; pb.k = q; pb.v = d_out; pb.scan_dir = scan_dir ^ 1; pb.gate_shift = 1; pb.out = dv_grad;
+    //    gates): dv_s = k_s G_s (outputs with q := k), dk_s = G_s v_s.  With one reversed walk for everything, the
+    //    walk for dq has left its local states.
     if (with_gates) {
-        pb.span_shift = pb.nspans * pb.span_len - T;
-        pb.fwd_dq = dq;
-        pb.fwd_out = out_fwd ? out_fwd : o_buf;
-        pb.dlog_alpha = dlog_alpha;
-        pb.dlog_beta = dlog_beta;
+        if (pb.nspans > 1 && !pb.chain_in_output && launch_carry(pb, stream) != hipSuccess) return GLA_ERR_HIP;
+        return launch_mfma_row_read(pb, v, dk_grad, stream, true) == hipSuccess ? GLA_OK : GLA_ERR_HIP;
     }
     if (states(pb) != hipSuccess) return GLA_ERR_HIP;
     if (one_walk) {
@@ -384,8 +420,6 @@ int run_bwd_gates(const void *q, const void *k, const void *v, const float *log_
         if (span(pb, kModeOutput) != hipSuccess) return GLA_ERR_HIP;
         if (row_read(pb, v, dk_grad) != hipSuccess) return GLA_ERR_HIP;
     }
-
-    if (with_gates) return GLA_OK;
 
     // 3. gate gradients: reverse cumulative sums of q * dq - k * dk (key side) and of dO * o - v * dv (value
     //    side: the same kernels over the dv columns, with dO, v in the places of q, k)

@@ -81,6 +81,9 @@ struct Params {
     // walk needs to form them (dlog_alpha; dlog_beta with the two-sided gate)
     float *ws_bound;
     int bound_len, bounds;
+    // the walk for dq also leaves the local states of the reversed recurrence and their log decays here (laid out like
+    // ws_state, ws_lgam, ws_lgam_b, spans counted in the reversed order), if set
+    float *ws_gstate, *ws_glgam, *ws_glgam_b;
     const float *fwd_dq, *fwd_out;
     float *dlog_alpha, *dlog_beta;
 };

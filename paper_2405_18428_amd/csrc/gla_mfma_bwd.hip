@@ -32,7 +32,7 @@
 namespace gla {
 namespace {
 
-template <int NDK8, int NDV16, bool DV, bool BETA = false>
+template <int NDK8, int NDV16, bool DV, bool BETA, bool GS>
 struct RLayout {
     static constexpr int kDkp = NDK8 * 8;
     static constexpr int kDvp = NDV16 * 16;
@@ -57,9 +57,9 @@ struct RLayout {
     static constexpr int oW = oV + kRowV;
     static constexpr int oStHi = oW + kRowV;
     static constexpr int oStLo = oStHi + kSt;
-    static constexpr int oQHi = oStLo + kSt;                              // with DV: raw q rows, then q~ hi / lo
+    static constexpr int oQHi = oStLo + kSt;                              // with DV or GS: raw q rows, then q~ hi / lo
     static constexpr int oQLo = oQHi + kRowK;
-    static constexpr int oEndAlpha = DV ? oQLo + kRowK : oStLo + kSt;
+    static constexpr int oEndAlpha = DV || GS ? oQLo + kRowK : oStLo + kSt;
     // two-sided gate: raw log_beta rows, the bf16 remainders of the gated v and w rows, exp(c_C) per value column
     static constexpr int kLbStride = kDvp + 4;
     static constexpr int oLb = oEndAlpha;
@@ -69,7 +69,10 @@ struct RLayout {
     // with DV, the gate gradients: sums of the waves' 16 tokens [4], and the sum over all later scan steps [2]
     static constexpr int oTot = BETA ? oGamB + kDvp * 4 : oEndAlpha;      // float[4 + 2][kDkp]
     static constexpr int oTotB = oTot + (DV ? 6 * kDkp * 4 : 0);          // float[4 + 2][kDvp]
-    static constexpr int kBytes = oTotB + (DV && BETA ? 6 * kDvp * 4 : 0);
+    // with GS, the chunk's b_C and c_C (base 2)
+    static constexpr int oLg = oTotB + (DV && BETA ? 6 * kDvp * 4 : 0);   // float[64]
+    static constexpr int oLgB = oLg + (GS ? 64 * 4 : 0);                  // float[kDvp]
+    static constexpr int kBytes = oLgB + (GS && BETA ? kDvp * 4 : 0);
     static_assert(kBytes % 16 == 0, "cleared in 16-byte pieces");
 };
 
@@ -99,9 +102,19 @@ using int_c = std::integral_constant<int, N>;
 // the channel tiles are shared), one for the outputs, so that a SIMD has a second wave to issue from.  MI355X: 256
 // sequences of 256 steps at 36 / 72 channels, dk and dv 34.4 -> 28.2 us; two-sided gate, 64 sequences of 1024 steps,
 // dk and dv 65.9 -> 50.7 us, dq 33.7 -> 31.8 us; 8 sequences of 2304 steps at 64 / 128, whole backward 105 -> 62 us.
-template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA = false>
+//
+// GS (the walk for dq): the local states of the reversed recurrence come along, so that it needs no state pass of its
+// own (which would read q, dO and the gates once more; of these only q is new here).  From a zero state its span over
+// the steps a .. b - 1 ends in
+//     U[c,n] = sum_s prod_{a < u <= s} alpha_u[c] beta_u[n] q_s[c] dO_s[n],
+// which a forward walk can sum chunk by chunk: the decay from a to the chunk times (q~^T dO~ of the chunk).  MI355X: the
+// walk for dq takes 59 instead of 45 us (16 sequences of 16384 steps, 36 / 72 channels) and the state pass of 31 us
+// goes, 182 -> 167 us for the call; two-sided gate, 64 sequences of 1024 steps: 32 -> 36 us, without a state pass of 21.
+template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA, bool GS>
 __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, const void *w_in, float *r_out) {
-    using L = RLayout<NDK8, NDV16, DV, BETA>;
+    using L = RLayout<NDK8, NDV16, DV, BETA, GS>;
+    static_assert(!(DV && GS), "either walk");
+    constexpr bool Q = DV || GS;     // q~ rows are needed
     constexpr int LBS = L::kLbStride;
     constexpr int NTHR = NW * 64;
     static_assert(NW == 4 || NW == 8, "one or two waves per 16 tokens");
@@ -112,6 +125,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
     constexpr int NTB = 4;       // token maps: the chunk before (its last token may be row 0's gate), this one, the next two
     static_assert(16 * NCT <= CHS, "channel tiles must fit the operand row");
     static_assert(NW * L::kDkp <= kChunk * LAS, "scratch of the prologue");
+    auto gstate_tile = [](int w, int i) { return (w + NW - 1) % NW + NW * i; };     // GS: the same for U
     // value-column tile of the state that is the i-th of wave w (8 waves without DV: the second waves of the tokens,
     // which have fewer channel tiles of the row read, take the first four)
     auto state_tile = [](int w, int i) { return (NW == 8 && !DV ? (w + 4) % 8 : w) + NW * i; };
@@ -133,6 +147,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
     uint16_t *s_wlo = reinterpret_cast<uint16_t *>(smem + L::oWLo);
     float *s_gamb = reinterpret_cast<float *>(smem + L::oGamB);
     float *s_tot = reinterpret_cast<float *>(smem + L::oTot), *s_later = s_tot + 4 * L::kDkp;         // DV
+    float *s_lg = reinterpret_cast<float *>(smem + L::oLg), *s_lgb = reinterpret_cast<float *>(smem + L::oLgB);   // GS
     float *s_totb = reinterpret_cast<float *>(smem + L::oTotB), *s_laterb = s_totb + 4 * L::kDvp;     // DV, BETA
 
     const int tid = threadIdx.x;
@@ -178,6 +193,16 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
     for (int i = 0; i < TPW; ++i)
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) acc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // GS: the tiles of U this wave sums, the log2 of the decay from the span's first step to the current chunk
+    f32x4 accg[GS ? TPW : 1][NCT];
+    float decay[NCT];
+    f32x4 decay_b[GS && BETA ? TPW : 1];
+    if constexpr (GS) {
+#pragma unroll
+        for (int i = 0; i < TPW; ++i)
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) accg[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     // The state entering the span: what the carry kernel left in the workspace, or (chain_in_output) chained here
     // from the local states of the spans before it (chain_span_states: nearest span first, until the accumulated
     // decay makes the rest vanish in fp32); the result goes through LDS into the accumulator layout.
@@ -228,6 +253,22 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
     }
     const int tok_before = scan_token(p.scan_dir, max(s_begin - 1, 0), T, p.grid_h, p.grid_w);   // the step before the span
     if (tid == 0) s_tok[NTB * kChunk - 1] = tok_before;
+    if constexpr (GS) {
+        // (the first step's own gate does not act on its q^T dO, but is part of the chunk's prefix sums)
+        const int tok_first = scan_token(p.scan_dir, s_begin, T, p.grid_h, p.grid_w);
+        const float *la_a = reinterpret_cast<const float *>(gla_) + (size_t)tok_first * p.st_k;
+        const float *lb_a = reinterpret_cast<const float *>(glb) + (size_t)tok_first * p.st_v;
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct) decay[ct] = fminf(-la_a[min(16 * ct + lm, dk - 1)] * kLog2e, kMaxExp2);
+        if constexpr (BETA) {
+#pragma unroll
+            for (int i = 0; i < TPW; ++i) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(lb_a + min(16 * gstate_tile(w, i) + 4 * g, dv - 4));
+#pragma unroll
+                for (int r = 0; r < 4; ++r) decay_b[i][r] = fminf(-x[r] * kLog2e, kMaxExp2);
+            }
+        }
+    }
     if constexpr (DV) {
         // The gate gradients are sums over all later scan steps, i.e. over the steps this walk has made before:
         // those before the span add up to the gradient of the gate between it and them,
@@ -317,7 +358,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
 
     f32x4 r_la[kF];
     u32x2 r_k[kF];
-    u32x2 r_q[DV ? kF : 1];
+    u32x2 r_q[Q ? kF : 1];
     u32x4 r_v[kVF], r_w[kVF];
     f32x4 r_lb[BETA ? kVF : 1][2];   // log_beta of the same 8 columns as the v piece
     auto load_chunk = [&](int chunk) {
@@ -331,7 +372,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
             const uint32_t pc = 8u * (uint32_t)(frp[m] & 255);
             r_la[m] = *reinterpret_cast<const f32x4 *>(gla_ + 2u * ((uint32_t)tokg(row) * dk2 + pc));
             r_k[m] = *reinterpret_cast<const u32x2 *>(gk + (uint32_t)tok[row] * dk2 + pc);
-            if constexpr (DV) r_q[m] = *reinterpret_cast<const u32x2 *>(gq + (uint32_t)tok[row] * dk2 + pc);
+            if constexpr (Q) r_q[m] = *reinterpret_cast<const u32x2 *>(gq + (uint32_t)tok[row] * dk2 + pc);
         }
 #pragma unroll
         for (int m = 0; m < kVF; ++m) {
@@ -357,7 +398,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                 if ((frp[m] >> 8) >= nvalid) {
                     r_la[m] = f32x4{0.f, 0.f, 0.f, 0.f};
                     r_k[m] = u32x2{0, 0};
-                    if constexpr (DV) r_q[m] = u32x2{0, 0};
+                    if constexpr (Q) r_q[m] = u32x2{0, 0};
                 }
             }
 #pragma unroll
@@ -375,7 +416,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                 const int row = frp[m] >> 8, ch = 4 * (frp[m] & 255);
                 *reinterpret_cast<f32x4 *>(s_la + row * LAS + ch) = r_la[m];
                 *reinterpret_cast<u32x2 *>(s_khi + row * CHS + ch) = r_k[m];
-                if constexpr (DV) *reinterpret_cast<u32x2 *>(s_qhi + row * CHS + ch) = r_q[m];
+                if constexpr (Q) *reinterpret_cast<u32x2 *>(s_qhi + row * CHS + ch) = r_q[m];
             }
         }
 #pragma unroll
@@ -437,7 +478,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                            bf16_hi_as_float(kr[1]) * exp2_fast(fminf(-bb[3], kMaxExp2)), khi[1], klo[1]);
                 *reinterpret_cast<u32x2 *>(s_khi + j * CHS + c0) = khi;
                 *reinterpret_cast<u32x2 *>(s_klo + j * CHS + c0) = klo;
-                if constexpr (DV) {
+                if constexpr (Q) {
                     const u32x2 qr = *reinterpret_cast<const u32x2 *>(s_qhi + j * CHS + c0);
                     u32x2 qhi, qlo;
                     SPLIT_PAIR(bf16_lo_as_float(qr[0]) * e[0], bf16_hi_as_float(qr[0]) * e[1], qhi[0], qlo[0]);
@@ -446,7 +487,10 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                     *reinterpret_cast<u32x2 *>(s_qlo + j * CHS + c0) = qlo;
                 }
                 *reinterpret_cast<f32x4 *>(s_la + j * LAS + c0) = e;      // E_j in place of the raw gates
-                if (lane == 63) *reinterpret_cast<f32x4 *>(s_gam + c0) = e;
+                if (lane == 63) {
+                    *reinterpret_cast<f32x4 *>(s_gam + c0) = e;
+                    if constexpr (GS) *reinterpret_cast<f32x4 *>(s_lg + c0) = f32x4{bb[0], bb[1], bb[2], bb[3]};
+                }
             }
             if constexpr (BETA) {
                 // value side, 8-column units dealt from the last wave: v~ = v / F and w~ = w F as bf16 hi/lo
@@ -481,7 +525,10 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                     }
                     if (lane == 63) {
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) s_gamb[c0 + i] = f[i];
+                        for (int i = 0; i < 8; ++i) {
+                            s_gamb[c0 + i] = f[i];
+                            if constexpr (GS) s_lgb[c0 + i] = cc[i];
+                        }
                     }
                 }
             }
@@ -815,6 +862,79 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                     }
                 }
             }
+            if constexpr (GS) {
+                // U += (decay from the span's first step) * Q~^T dO, transposed like the state
+                constexpr int G0 = (W + NW - 1) % NW;
+                if constexpr (G0 < NDV16) {
+                    const uint16_t *qrow_h = s_qhi + (4 * g + tr_row) * CHS + tr_col;
+                    const uint16_t *qrow_l = s_qlo + (4 * g + tr_row) * CHS + tr_col;
+                    const uint16_t *wrow = s_w + (4 * g + tr_row) * VS + tr_col;
+                    const uint16_t *wrow_l = s_wlo + (4 * g + tr_row) * VS + tr_col;   // BETA
+                    u32x4 qth[2][NCT], qtl[2][NCT];
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+#pragma unroll
+                        for (int ct = 0; ct < NCT; ++ct) {
+                            const u32x2 h0 = lds_read_tr(qrow_h + 32 * q * CHS + 16 * ct);
+                            const u32x2 h1 = lds_read_tr(qrow_h + (32 * q + 16) * CHS + 16 * ct);
+                            const u32x2 l0 = lds_read_tr(qrow_l + 32 * q * CHS + 16 * ct);
+                            const u32x2 l1 = lds_read_tr(qrow_l + (32 * q + 16) * CHS + 16 * ct);
+                            qth[q][ct] = u32x4{h0[0], h0[1], h1[0], h1[1]};
+                            qtl[q][ct] = u32x4{l0[0], l0[1], l1[0], l1[1]};
+                        }
+                    float fac[NCT];
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct) {
+                        fac[ct] = exp2_fast(decay[ct]);
+                        decay[ct] += s_lg[16 * ct + lm];
+                    }
+#pragma unroll
+                    for (int i = 0; i < TPW; ++i) {
+                        const int nt = G0 + NW * i;
+                        if (nt < NDV16) {
+                            u32x4 wt[2], wtl[BETA ? 2 : 1];
+#pragma unroll
+                            for (int q = 0; q < 2; ++q) {
+                                const u32x2 v0 = lds_read_tr(wrow + 32 * q * VS + 16 * nt);
+                                const u32x2 v1 = lds_read_tr(wrow + (32 * q + 16) * VS + 16 * nt);
+                                wt[q] = u32x4{v0[0], v0[1], v1[0], v1[1]};
+                                if constexpr (BETA) {
+                                    const u32x2 l0 = lds_read_tr(wrow_l + 32 * q * VS + 16 * nt);
+                                    const u32x2 l1 = lds_read_tr(wrow_l + (32 * q + 16) * VS + 16 * nt);
+                                    wtl[q] = u32x4{l0[0], l0[1], l1[0], l1[1]};
+                                }
+                            }
+                            f32x4 fb = f32x4{1.f, 1.f, 1.f, 1.f};
+                            if constexpr (BETA) {
+                                const f32x4 lb4 = *reinterpret_cast<const f32x4 *>(s_lgb + 16 * nt + 4 * g);
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) fb[r] = exp2_fast(decay_b[i][r]);
+                                decay_b[i] += lb4;
+                            }
+#pragma unroll
+                            for (int ct = 0; ct < NCT; ++ct) {
+                                f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                                for (int q = 0; q < 2; ++q) {
+                                    a = mfma(wt[q], qth[q][ct], a);
+                                    a = mfma(wt[q], qtl[q][ct], a);
+                                    if constexpr (BETA) {
+                                        a = mfma(wtl[q], qth[q][ct], a);
+                                        a = mfma(wtl[q], qtl[q][ct], a);
+                                    }
+                                }
+                                f32x4 u = accg[i][ct];
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) u[r] = fmaf(BETA ? fac[ct] * fb[r] : fac[ct], a[r], u[r]);
+                                accg[i][ct] = u;
+                            }
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct) decay[ct] += s_lg[16 * ct + lm];
+                }
+            }
             if constexpr (DV) {
                 if (p.dlog_alpha != nullptr) {
                     // sums over all later scan steps: the wave's own rows + the waves before it + everything before
@@ -870,12 +990,41 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
         }
         __syncthreads();
     }
+
+    if constexpr (GS) {
+        // U of the reversed walk's span, and the log of its decay: the gates of the steps a + 1 .. b (with gate_shift the
+        // walk's first step decays by the gate of step b, the first one after this span)
+        const size_t span = (size_t)bh * p.nspans + (p.nspans - 1 - sp);
+        const int tok_after = scan_token(p.scan_dir, min(s_end, T - 1), T, p.grid_h, p.grid_w);
+        float *u = p.ws_gstate + span * (size_t)(dk * dv);
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+            const int n = 16 * gstate_tile(w, i) + 4 * g;
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) {
+                const int c = 16 * ct + lm;
+                if (c < dk && n < dv) *reinterpret_cast<f32x4 *>(u + c * dv + n) = accg[i][ct];
+            }
+            if constexpr (BETA) {
+                if (lm == 0 && n < dv) {
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(glb) + (size_t)tok_after * p.st_v + n);
+                    *reinterpret_cast<f32x4 *>(p.ws_glgam_b + span * dv + n) = decay_b[i] * kLn2 + x;
+                }
+            }
+        }
+        if (w == 0 && g == 0) {
+            const float *la = reinterpret_cast<const float *>(gla_) + (size_t)tok_after * p.st_k;
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct)
+                if (16 * ct + lm < dk) p.ws_glgam[span * dk + 16 * ct + lm] = decay[ct] * kLn2 + la[16 * ct + lm];
+        }
+    }
 }
 
-template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA>
+template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA, bool GS>
 hipError_t launch_waves(const Params &p, const void *w, float *r, hipStream_t stream) {
-    using L = RLayout<NDK8, NDV16, DV, BETA>;
-    auto kernel = mfma_row_read_kernel<NDK8, NDV16, NW, MINW, DV, BETA>;
+    using L = RLayout<NDK8, NDV16, DV, BETA, GS>;
+    auto kernel = mfma_row_read_kernel<NDK8, NDV16, NW, MINW, DV, BETA, GS>;
     static std::atomic<bool> configured[kMaxDevices] = {};  // per instantiation and device
     {
         hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), L::kBytes, configured);
@@ -886,27 +1035,27 @@ hipError_t launch_waves(const Params &p, const void *w, float *r, hipStream_t st
     return hipGetLastError();
 }
 
-template <int NDK8, int NDV16, bool DV, bool BETA = false>
+template <int NDK8, int NDV16, bool DV, bool BETA, bool GS>
 hipError_t launch_one(const Params &p, const void *w, float *r, hipStream_t stream) {
     // 8 waves where a compute unit holds one group anyway: by its LDS, or because there are no more groups than units
-    constexpr int kGroupsPerCu = (160 * 1024) / RLayout<NDK8, NDV16, DV, BETA>::kBytes;
+    constexpr int kGroupsPerCu = (160 * 1024) / RLayout<NDK8, NDV16, DV, BETA, GS>::kBytes;
     if constexpr (kGroupsPerCu >= 2) {
-        if ((long long)p.B * p.H * p.nspans > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA>(p, w, r, stream);
+        if ((long long)p.B * p.H * p.nspans > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA, GS>(p, w, r, stream);
     }
-    return launch_waves<NDK8, NDV16, 8, 2, DV, BETA>(p, w, r, stream);
+    return launch_waves<NDK8, NDV16, 8, 2, DV, BETA, GS>(p, w, r, stream);
 }
 
-template <bool DV>
+template <bool DV, bool GS>
 hipError_t launch_sizes(const Params &p, const void *w, float *r, hipStream_t stream) {
     const int ndk8 = (p.dk + 7) / 8, ndv16 = (p.dv + 15) / 16;
     if (p.log_beta != nullptr) {   // two-sided gate: the head sizes whose extra rows fit the LDS (dk <= 40, dv <= 80)
-        if (ndk8 <= 4 && ndv16 <= 4) return launch_one<4, 4, DV, true>(p, w, r, stream);
-        if (ndk8 <= 5 && ndv16 <= 5) return launch_one<5, 5, DV, true>(p, w, r, stream);
+        if (ndk8 <= 4 && ndv16 <= 4) return launch_one<4, 4, DV, true, GS>(p, w, r, stream);
+        if (ndk8 <= 5 && ndv16 <= 5) return launch_one<5, 5, DV, true, GS>(p, w, r, stream);
         return hipErrorInvalidConfiguration;
     }
-    if (ndk8 <= 4 && ndv16 <= 4) return launch_one<4, 4, DV>(p, w, r, stream);
-    if (ndk8 <= 5 && ndv16 <= 5) return launch_one<5, 5, DV>(p, w, r, stream);
-    return launch_one<8, 8, DV>(p, w, r, stream);
+    if (ndk8 <= 4 && ndv16 <= 4) return launch_one<4, 4, DV, false, GS>(p, w, r, stream);
+    if (ndk8 <= 5 && ndv16 <= 5) return launch_one<5, 5, DV, false, GS>(p, w, r, stream);
+    return launch_one<8, 8, DV, false, GS>(p, w, r, stream);
 }
 
 }  // namespace
@@ -914,7 +1063,8 @@ hipError_t launch_sizes(const Params &p, const void *w, float *r, hipStream_t st
 // Same conditions as the forward MFMA engine (bf16 rows, dk % 4 == 0, dv % 8 == 0, 32-bit offsets).
 // with_outputs: also write o_j = q_j S_j (p.q, fp32 rows to p.out).
 hipError_t launch_mfma_row_read(const Params &p, const void *w, float *r, hipStream_t stream, bool with_outputs) {
-    return with_outputs ? launch_sizes<true>(p, w, r, stream) : launch_sizes<false>(p, w, r, stream);
+    if (with_outputs) return launch_sizes<true, false>(p, w, r, stream);
+    return p.ws_gstate != nullptr ? launch_sizes<false, true>(p, w, r, stream) : launch_sizes<false, false>(p, w, r, stream);
 }
 
 }  // namespace gla

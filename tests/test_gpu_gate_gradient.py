@@ -1,6 +1,6 @@
 """Gate gradients formed inside the reversed walk of the backward pass: span bounds of ragged sequences, slowly decaying
-gates (the start of every span then carries most of the sum), and workspaces without room for the states at the bounds
-(the separate reverse-cumulative-sum kernels).  Bar 2e-2 x RMS as for every bf16 call; the two routes differ by the
+gates (the start of every span then carries most of the sum), and workspaces without room for what the walk for dq leaves
+(a state pass of the reversed recurrence and the separate reverse-cumulative-sum kernels).  Bar 2e-2 x RMS as for every bf16 call; the two routes differ by the
 rounding of sums of T terms, at most T 2^-24 of their largest partial sum (about 1e-3 of the RMS here)."""
 import numpy as np
 import pytest
@@ -40,21 +40,23 @@ def test_span_bounds(gh, gw, cps, dk, dv, z_mean):
     q, k, v = (up(d[n + "_bits"]) for n in "qkv")
     dw = up(bits)
     la, lb = (torch.from_numpy(d[n]).cuda() for n in ("log_alpha", "log_beta"))
-    chunks = (T + 63) // 64
-    bounds = (min(B * H * chunks, 512) * dk * dv * 4 + 255) // 256 * 256      # what the states at the bounds may add
+    # the least a workspace may hold: the span states, and the totals of the reverse cumulative sums (256 steps each)
+    totals = lambda width: (B * H * ((T + 255) // 256) * width * 4 + 255) // 256 * 256  # noqa: E731
+    least = gla.gla_fwd_workspace_bytes(B, H, T, dk, dv) + totals(dk)
+    least_gates = gla.gla_fwd_workspace_bytes(B, H, T, dk, dv) + totals(dv) + (B * H * T * dv * 4 + 255) // 256 * 256
     for scan in (0, 3):
         ref = orc.gla_bwd(d["q"], d["k"], d["v"], d["log_alpha"], w, gh, gw, scan)
         floor = float(np.sqrt(np.mean(np.square(d["q"] * ref[0]))))
         routes = []
-        for less in (0, bounds):
-            ws = torch.empty(gla.gla_bwd_workspace_bytes(B, H, T, dk, dv) - less, dtype=torch.uint8, device="cuda")
+        for room in (gla.gla_bwd_workspace_bytes(B, H, T, dk, dv), least):
+            ws = torch.empty(room, dtype=torch.uint8, device="cuda")
             got = gla.gla_bwd(q, k, v, la, dw, gh, gw, scan, workspace=ws)
             assert max(_err(g, r, f) for g, r, f in zip(got, ref, (0, 0, 0, floor))) <= TOL
             routes.append(got[3].cpu().numpy().astype(np.float64))
         assert _err(torch.from_numpy(routes[0]), routes[1], floor) <= 2e-3
         ref = og.gla_bwd_gates(d["q"], d["k"], d["v"], d["log_alpha"], d["log_beta"], w, gh, gw, scan)
         floors = (0, 0, 0, float(np.sqrt(np.mean(np.square(d["q"] * ref[0])))), float(np.sqrt(np.mean(np.square(d["v"] * ref[2])))))
-        for less in (0, bounds):
-            n = gla.gla_bwd_gates_workspace_bytes(B, H, T, dk, dv) - less
-            got = gla.gla_bwd_gates(q, k, v, la, lb, dw, gh, gw, scan, workspace=torch.empty(n, dtype=torch.uint8, device="cuda"))
+        for room in (gla.gla_bwd_gates_workspace_bytes(B, H, T, dk, dv), least_gates):
+            ws = torch.empty(room, dtype=torch.uint8, device="cuda")
+            got = gla.gla_bwd_gates(q, k, v, la, lb, dw, gh, gw, scan, workspace=ws)
             assert max(_err(g, r, f) for g, r, f in zip(got, ref, floors)) <= TOL
