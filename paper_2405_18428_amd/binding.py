@@ -6,6 +6,7 @@ the current stream, nothing else.  Every arithmetic step runs inside
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 import re
@@ -141,9 +142,33 @@ def _check(status: int) -> None:
         raise GlaError(status, gla_status_string(status))
 
 
+_torch_module = None
+_raw_stream = None              # device ordinal -> hipStream_t of its current stream
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module, _raw_stream
+    if _torch_module is None:
+        import torch
+        # torch.cuda.current_stream() builds a Stream object on every call (3.0 us against 0.1 us)
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+            (lambda ordinal: torch.cuda.current_stream(ordinal).cuda_stream)
+        _torch_module = torch
+    return _torch_module
+
+
+_HERE = contextlib.nullcontext()
+
+
+def _on_device_of(t):
+    """Context in which the tensor's device is the current one; nothing to do where it already is (1.4 us less)."""
+    torch = _torch()
+    return _HERE if torch.cuda.current_device() == t.get_device() else torch.cuda.device(t.device)
+
+
+def _like(t, dtype):
+    torch = _torch()
+    return torch.empty_like(t, dtype=dtype, memory_format=torch.contiguous_format)
 
 
 def _dt(t) -> int:
@@ -174,10 +199,12 @@ def _prep(q, k, v, log_alpha, grid_h, grid_w):
     return B, H, T, dk, v.shape[3]
 
 
-def _stream_ptr(stream) -> int:
+def _stream_ptr(stream, t=None) -> int:
+    """The given stream, or the current one of the tensor's device (of the current device without a tensor)."""
+    if stream is not None:
+        return int(stream.cuda_stream)
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    return int(_raw_stream(torch.cuda.current_device() if t is None else t.get_device()))
 
 
 def gla_fwd(q, k, v, log_alpha, grid_h, grid_w, scan_dir=SCAN_ROW_FWD,
@@ -189,14 +216,14 @@ def gla_fwd(q, k, v, log_alpha, grid_h, grid_w, scan_dir=SCAN_ROW_FWD,
     if q.dtype != torch.bfloat16:
         raise TypeError("gla_fwd takes bf16 q/k/v; use gla_fwd_ex for fp32")
     if out is None:
-        out = torch.empty((B, H, T, dv), dtype=torch.float32, device=q.device)
+        out = _like(v, torch.float32)
     if final_state is None and want_final_state:
-        final_state = torch.empty((B, H, dk, dv), dtype=torch.float32, device=q.device)
-    with torch.cuda.device(q.device):
+        final_state = q.new_empty((B, H, dk, dv), dtype=torch.float32)
+    with _on_device_of(q):
         _check(lib.gla_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(),
                            B, H, T, dk, dv, grid_h, grid_w, scan_dir,
                            out.data_ptr(), final_state.data_ptr() if final_state is not None else None,
-                           _stream_ptr(stream)))
+                           _stream_ptr(stream, q)))
     return out, final_state
 
 
@@ -211,11 +238,11 @@ def gla_fwd_static(q, k, v, log_alpha, grid_h, grid_w, scan_dir=SCAN_ROW_FWD, ou
         raise TypeError("gla_fwd_static takes bf16 q/k/v")
     if out is None or out.dtype != torch.float32 or tuple(out.shape) != (B, H, T, dv) or not out.is_contiguous():
         raise ValueError("out must be a contiguous fp32 GPU tensor [B,H,T,dv]")
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         _check(lib.gla_fwd_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(),
                                   B, H, T, dk, dv, grid_h, grid_w, scan_dir,
                                   out.data_ptr(), final_state.data_ptr() if final_state is not None else None,
-                                  _stream_ptr(stream)))
+                                  _stream_ptr(stream, q)))
     return out, final_state
 
 
@@ -229,17 +256,17 @@ def gla_fwd_ex(q, k, v, log_alpha, grid_h, grid_w, scan_dir=SCAN_ROW_FWD,
     qdt = _dt(q)
     if out is None:
         odt = torch.float32 if out_dtype is None else out_dtype
-        out = torch.empty((B, H, T, dv), dtype=odt, device=q.device)
+        out = _like(v, odt)
     if final_state is None and want_final_state:
-        final_state = torch.empty((B, H, dk, dv), dtype=torch.float32, device=q.device)
+        final_state = q.new_empty((B, H, dk, dv), dtype=torch.float32)
     if workspace is None:
         nbytes = gla_fwd_workspace_bytes(B, H, T, dk, dv, qdt)
         workspace = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         _check(lib.gla_fwd_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(),
                               B, H, T, dk, dv, grid_h, grid_w, scan_dir, qdt, _dt(out),
                               out.data_ptr(), final_state.data_ptr() if final_state is not None else None,
-                              workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+                              workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q)))
     return out, final_state
 
 
@@ -271,18 +298,18 @@ def gla_fwd_layout(q, k, v, log_alpha, grid_h, grid_w, scan_dir=SCAN_ROW_FWD, la
             raise ValueError("initial_state must be a contiguous fp32 GPU tensor [B,H,dk,dv]")
     if out is None:
         odt = torch.float32 if out_dtype is None else out_dtype
-        out = torch.empty(tuple(v.shape), dtype=odt, device=q.device)
+        out = _like(v, odt)
     if final_state is None and want_final_state:
-        final_state = torch.empty((B, H, dk, dv), dtype=torch.float32, device=q.device)
+        final_state = q.new_empty((B, H, dk, dv), dtype=torch.float32)
     if workspace is None:
         nbytes = gla_fwd_workspace_bytes(B, H, T, dk, dv, qdt)
         workspace = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         _check(lib.gla_fwd_layout(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(),
                                   B, H, T, dk, dv, grid_h, grid_w, scan_dir, qdt, _dt(out), layout,
                                   initial_state.data_ptr() if initial_state is not None else None,
                                   out.data_ptr(), final_state.data_ptr() if final_state is not None else None,
-                                  workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+                                  workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q)))
     return out, final_state
 
 
@@ -312,18 +339,18 @@ def gla_fwd_gates(q, k, v, log_alpha, log_beta, grid_h, grid_w, scan_dir=SCAN_RO
                 or not initial_state.is_contiguous() or not initial_state.is_cuda):
             raise ValueError("initial_state must be a contiguous fp32 GPU tensor [B,H,dk,dv]")
     if out is None:
-        out = torch.empty(tuple(v.shape), dtype=torch.float32 if out_dtype is None else out_dtype, device=q.device)
+        out = _like(v, torch.float32 if out_dtype is None else out_dtype)
     if final_state is None and want_final_state:
-        final_state = torch.empty((B, H, dk, dv), dtype=torch.float32, device=q.device)
+        final_state = q.new_empty((B, H, dk, dv), dtype=torch.float32)
     if workspace is None:
         nbytes = gla_fwd_workspace_bytes(B, H, T, dk, dv, qdt)
         workspace = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         _check(lib.gla_fwd_gates(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(), log_beta.data_ptr(),
                                  B, H, T, dk, dv, grid_h, grid_w, scan_dir, qdt, _dt(out), layout,
                                  initial_state.data_ptr() if initial_state is not None else None,
                                  out.data_ptr(), final_state.data_ptr() if final_state is not None else None,
-                                 workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+                                 workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q)))
     return out, final_state
 
 
@@ -343,9 +370,9 @@ def gla_srem_dwconv(x, weight, bias, grid_h, grid_w, orient=0, out_dtype=None, o
         raise ValueError("bias must be a contiguous fp32 GPU tensor [D]")
     if out is None:
         out = torch.empty_like(x, dtype=x.dtype if out_dtype is None else out_dtype)
-    with torch.cuda.device(x.device):
+    with _on_device_of(x):
         _check(lib.gla_srem_dwconv(x.data_ptr(), weight.data_ptr(), bias.data_ptr() if bias is not None else None,
-                                   B, grid_h, grid_w, D, orient, _dt(x), _dt(out), out.data_ptr(), _stream_ptr(stream)))
+                                   B, grid_h, grid_w, D, orient, _dt(x), _dt(out), out.data_ptr(), _stream_ptr(stream, x)))
     return out
 
 
@@ -370,14 +397,14 @@ def gla_fwd_multi(q, k, v, log_alpha, grid_h, grid_w, scan_dirs=(SCAN_ROW_FWD, S
     dv = v.shape[3]
     qdt = _dt(q)
     if out is None:
-        out = torch.empty(tuple(v.shape), dtype=torch.float32, device=q.device)
+        out = _like(v, torch.float32)
     if workspace is None:
         nbytes = gla_fwd_workspace_bytes(B, H, T, dk, dv, qdt)
         workspace = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         _check(lib.gla_fwd_multi(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(),
                                  B, H, T, dk, dv, grid_h, grid_w, mask, qdt, out.data_ptr(),
-                                 workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+                                 workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q)))
     return out
 
 
@@ -412,16 +439,16 @@ def gla_fwd_fused(q, k, v, z_alpha, tau, grid_h, grid_w, scan_dir=SCAN_ROW_FWD, 
     qdt = _dt(q)
     if out is None:
         odt = torch.float32 if out_dtype is None else out_dtype
-        out = torch.empty(tuple(v.shape), dtype=odt, device=q.device)
+        out = _like(v, odt)
     if final_state is None and want_final_state:
-        final_state = torch.empty((B, H, dk, dv), dtype=torch.float32, device=q.device)
+        final_state = q.new_empty((B, H, dk, dv), dtype=torch.float32)
     if workspace is None:
         nbytes = gla_fwd_workspace_bytes(B, H, T, dk, dv, qdt)
         workspace = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=q.device)
     ptr = lambda t: t.data_ptr() if t is not None else None
     tail = (ptr(r_pre), ptr(ln_weight), ptr(ln_bias), float(ln_eps), B, H, T, dk, dv, grid_h, grid_w, scan_dir, qdt,
-            _dt(out), out.data_ptr(), ptr(final_state), workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
-    with torch.cuda.device(q.device):
+            _dt(out), out.data_ptr(), ptr(final_state), workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q))
+    with _on_device_of(q):
         if _z_beta is not None:
             _check(lib.gla_fwd_fused_gates(q.data_ptr(), k.data_ptr(), v.data_ptr(), z_alpha.data_ptr(),
                                            _z_beta.data_ptr(), float(tau), *tail))
@@ -460,18 +487,17 @@ def gla_bwd_gates(q, k, v, log_alpha, log_beta, d_out, grid_h, grid_w, scan_dir=
     if out_fwd is not None and (out_fwd.dtype != torch.float32 or out_fwd.shape != v.shape or not out_fwd.is_cuda
                                 or not out_fwd.is_contiguous()):
         raise ValueError("out_fwd must be a contiguous fp32 GPU tensor shaped like v")
-    f32 = dict(dtype=torch.float32, device=q.device)
-    dq, dk_g, dla = (torch.empty((B, H, T, dk), **f32) for _ in range(3))
-    dv_g, dlb = (torch.empty((B, H, T, dv), **f32) for _ in range(2))
+    dq, dk_g, dla = (_like(q, torch.float32) for _ in range(3))
+    dv_g, dlb = (_like(v, torch.float32) for _ in range(2))
     if workspace is None:
         nbytes = int(lib.gla_bwd_gates_workspace_bytes(B, H, T, dk, dv, qdt))
         workspace = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         _check(lib.gla_bwd_gates(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(), log_beta.data_ptr(),
                                  d_out.data_ptr(), out_fwd.data_ptr() if out_fwd is not None else None,
                                  B, H, T, dk, dv, grid_h, grid_w, scan_dir, qdt,
                                  dq.data_ptr(), dk_g.data_ptr(), dv_g.data_ptr(), dla.data_ptr(), dlb.data_ptr(),
-                                 workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+                                 workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q)))
     return dq, dk_g, dv_g, dla, dlb
 
 
@@ -503,19 +529,18 @@ def gla_bwd_layout(q, k, v, log_alpha, d_out, grid_h, grid_w, scan_dir=SCAN_ROW_
         B, T, H, dk = q.shape
     dv = v.shape[3]
     qdt = _dt(q)
-    f32 = dict(dtype=torch.float32, device=q.device)
-    dq, dk_, dg = (torch.empty(tuple(q.shape), **f32) for _ in range(3))
-    dv_ = torch.empty(tuple(v.shape), **f32)
+    dq, dk_, dg = (_like(q, torch.float32) for _ in range(3))
+    dv_ = _like(v, torch.float32)
     if workspace is None:
         nbytes = gla_bwd_workspace_bytes(B, H, T, dk, dv, qdt)
         workspace = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         _check(lib.gla_bwd_layout(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(), d_out.data_ptr(),
                                   B, H, T, dk, dv, grid_h, grid_w, scan_dir, qdt, layout,
                                   fwd_workspace.data_ptr() if fwd_workspace is not None else None,
                                   fwd_workspace.numel() if fwd_workspace is not None else 0,
                                   dq.data_ptr(), dk_.data_ptr(), dv_.data_ptr(), dg.data_ptr(),
-                                  workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+                                  workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q)))
     return dq, dk_, dv_, dg
 
 
@@ -531,24 +556,23 @@ def gla_bwd(q, k, v, log_alpha, d_out, grid_h, grid_w, scan_dir=SCAN_ROW_FWD, wo
     if d_out.shape != v.shape or d_out.dtype != v.dtype or not d_out.is_cuda or not d_out.is_contiguous():
         raise ValueError("d_out must be a contiguous GPU tensor shaped and typed like v")
     qdt = _dt(q)
-    f32 = dict(dtype=torch.float32, device=q.device)
-    dq, dk_ = torch.empty((B, H, T, dk), **f32), torch.empty((B, H, T, dk), **f32)
-    dg, dv_ = torch.empty((B, H, T, dk), **f32), torch.empty((B, H, T, dv), **f32)
+    dq, dk_, dg = (_like(q, torch.float32) for _ in range(3))
+    dv_ = _like(v, torch.float32)
     if workspace is None:
         nbytes = gla_bwd_workspace_bytes(B, H, T, dk, dv, qdt)
         workspace = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         if fwd_workspace is None:
             _check(lib.gla_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(), d_out.data_ptr(),
                                B, H, T, dk, dv, grid_h, grid_w, scan_dir, qdt,
                                dq.data_ptr(), dk_.data_ptr(), dv_.data_ptr(), dg.data_ptr(),
-                               workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+                               workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q)))
         else:
             _check(lib.gla_bwd_reuse(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(), d_out.data_ptr(),
                                      B, H, T, dk, dv, grid_h, grid_w, scan_dir, qdt,
                                      fwd_workspace.data_ptr(), fwd_workspace.numel(),
                                      dq.data_ptr(), dk_.data_ptr(), dv_.data_ptr(), dg.data_ptr(),
-                                     workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+                                     workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q)))
     return dq, dk_, dv_, dg
 
 
@@ -567,10 +591,10 @@ def gla_fwd_timed(q, k, v, log_alpha, grid_h, grid_w, scan_dir, out, final_state
     lib = load_library()
     B, H, T, dk, dv = _prep(q, k, v, log_alpha, grid_h, grid_w)
     ms = (ctypes.c_float * 4)()
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         _check(lib.gla_fwd_timed(q.data_ptr(), k.data_ptr(), v.data_ptr(), log_alpha.data_ptr(),
                                  B, H, T, dk, dv, grid_h, grid_w, scan_dir, _dt(q), _dt(out),
                                  out.data_ptr(), final_state.data_ptr() if final_state is not None else None,
-                                 workspace.data_ptr(), workspace.numel(), _stream_ptr(stream),
+                                 workspace.data_ptr(), workspace.numel(), _stream_ptr(stream, q),
                                  int(iters), ms))
     return [float(x) for x in ms]
