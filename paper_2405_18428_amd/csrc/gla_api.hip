@@ -102,6 +102,19 @@ int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_c
         const long long resident_groups = 256LL * groups_per_cu;
         cps = (int)(((long long)bh * nchunks + resident_groups - 1) / resident_groups);
         if (cps < 1) cps = 1;
+        // The last span of a sequence may be short, so that many spans of this length can still be a few more than are
+        // resident: a second round of all but idle compute units.  Then longer spans, if they fit into fewer rounds
+        // (a group's prologue counts as two chunks).  24 sequences of 64 chunks at 32 / 64 channels, backward: 22 spans
+        // of 3 chunks are 528 groups, 80 us; 16 of 4 68 us.
+        long long best = -1;
+        for (int c = cps, first = cps; mfma_engine && c <= nchunks && c <= 2 * first + 2; ++c) {
+            const long long groups = (long long)bh * ((nchunks + c - 1) / c);
+            const long long cost = (groups + resident_groups - 1) / resident_groups * (c + 2);
+            if (best < 0 || cost < best) {
+                best = cost;
+                cps = c;
+            }
+        }
         if (mfma_engine && nchunks <= 4) cps = nchunks;
     }
     if (cps > nchunks) cps = nchunks;
