@@ -46,9 +46,9 @@ struct Params {
     int B, H, T, dk, dv, grid_h, grid_w, scan_dir;
     int nspans;             // spans per (batch, head)
     int span_len;           // tokens per span, a multiple of kChunk
-    int span_shift;         // span sp is steps [sp * span_len - span_shift, (sp + 1) * span_len - span_shift) of the
-                            //    sequence (MFMA engine; the reversed walk of the backward pass: its spans then begin
-                            //    where those of the forward walk end, and the first one is the short one)
+    int span_shift;         // row reads of the MFMA engine: span sp is steps [sp * span_len - span_shift,
+                            //    (sp + 1) * span_len - span_shift) of the sequence (the reversed walk of the backward
+                            //    pass: its spans then begin where those of the forward walk end, the first is the short one)
     int gate_shift;         // 1: scan step s uses the log_alpha row of the token visited at step s-1 (the
                             //    reverse-mode recurrence dS_s = diag(alpha_{s+1}) dS_{s+1} + q_s^T dO_s walked backwards)
     int chain_in_output;    // 1: no phase-2 kernel; the output pass chains U_0..U_{r-1} itself and phase 1

@@ -219,8 +219,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
         }
     }
     const int dk = p.dk, dv = p.dv, T = p.T;
-    const int s_begin = span_begin(p, sp);
-    const int s_end = span_end(p, sp);
+    const int s_begin = sp * p.span_len;
+    const int s_end = min(T, s_begin + p.span_len);
     const int nch = (s_end - s_begin + kChunk - 1) / kChunk;
 
     // per-(batch, head) bases; everything below is a 32-bit byte offset from them
