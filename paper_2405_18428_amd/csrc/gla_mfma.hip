@@ -611,8 +611,10 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
                         SPLIT_PAIR(bf16_lo_as_float(vr[h]) * exp2_fast(fminf(-cc[2 * h], kMaxExp2)),
                                    bf16_hi_as_float(vr[h]) * exp2_fast(fminf(-cc[2 * h + 1], kMaxExp2)),
                                    vh[h], vl[h]);
-                        ev[2 * h] = exp2_fast(cc[2 * h]);
-                        ev[2 * h + 1] = exp2_fast(cc[2 * h + 1]);
+                        if constexpr (OUT) {      // (the state pass needs the last token's only)
+                            ev[2 * h] = exp2_fast(cc[2 * h]);
+                            ev[2 * h + 1] = exp2_fast(cc[2 * h + 1]);
+                        }
                     }
                     *reinterpret_cast<u32x4 *>(s_v + j * VS + c0) = vh;
                     *reinterpret_cast<u32x4 *>(s_vlo + j * VS + c0) = vl;
@@ -623,7 +625,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
                     if (lane == 63) {
 #pragma unroll
                         for (int i = 0; i < 8; ++i) {
-                            s_gamb[c0 + i] = ev[i];
+                            s_gamb[c0 + i] = OUT ? ev[i] : exp2_fast(cc[i]);
                             if constexpr (!OUT) s_lgb[c0 + i] += cc[i];
                         }
                     }
@@ -1076,7 +1078,9 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     // register cap: no tighter than the waves per SIMD that the LDS footprint lets a compute unit hold anyway
     constexpr int kGroupsPerCu = (160 * 1024) / L::kBytes;
     constexpr int kWavesPerSimd = kGroupsPerCu * NW / 4;
-    constexpr int MINW = kWavesPerSimd >= 4 ? 4 : (kWavesPerSimd >= 2 ? 2 : 1);
+    // (two-sided gate: the plan is for the output pass's one group per compute unit, so the state pass has one, too:
+    // 22.8 -> 18.3 us at 64 sequences of 1024 steps, 36 / 72 channels, without spills; a second chunk in flight 20.0 us)
+    constexpr int MINW = kWavesPerSimd >= 4 && !BETA ? 4 : (kWavesPerSimd >= 2 ? 2 : 1);
     if constexpr (MODE == kModeOutput && !FUSE) {
         // (the range fallback's groups mostly return at once: fewer waves to start)
         if (kGroupsPerCu < 2 || (NDK8 <= 4 && !p.only_flagged && (long long)p.B * p.H * p.nspans <= 256))
