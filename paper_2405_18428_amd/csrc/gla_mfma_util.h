@@ -173,11 +173,15 @@ __device__ inline void chain_span_states(const Params &p, int bh, int sp, int ti
     f32x4 st[kV4];
     float wl[kV4];      // log2 of the weight of the next span to add
     f32x4 wb[BETA ? kV4 : 1];   // BETA: its value-side part per column
+    float ref[BETA ? kV4 : 1];  // BETA: wl behind the nearest spans that were all zero
 #pragma unroll
     for (int m = 0; m < kV4; ++m) {
         st[m] = f32x4{0.f, 0.f, 0.f, 0.f};
         wl[m] = 0.f;
-        if constexpr (BETA) wb[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (BETA) {
+            wb[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+            ref[m] = 0.f;
+        }
     }
     auto run = [&](auto n_c, int r_hi) {   // spans r_hi, r_hi - 1, ..., r_hi - n + 1 (those below 0 do not exist)
         constexpr int N = decltype(n_c)::value;
@@ -211,18 +215,24 @@ __device__ inline void chain_span_states(const Params &p, int bh, int sp, int ti
                         for (int x = 0; x < 4; ++x) st[m][x] = fmaf(wgt, u[i][m][x], st[m][x]);
                     }
                     wl[m] += lg[i][m] * kLog2e;    // the workspace keeps natural logarithms
+                    if constexpr (BETA) {
+                        const bool zero = st[m][0] == 0.f && st[m][1] == 0.f && st[m][2] == 0.f && st[m][3] == 0.f;
+                        ref[m] = zero ? wl[m] : ref[m];
+                    }
                 }
             }
         }
     };
     // a piece goes on while its accumulated decay is above 2^-40, and also while everything it has summed is
     // exactly zero (all-zero k or v over the nearer spans, e.g. a padded tail: then even a strongly decayed
-    // earlier state is the whole result)
+    // earlier state is the whole result).  BETA, whose runs are shorter (registers): 2^-40 counts from there, so that the
+    // spans behind the zeros are added up whatever the length of a run
     auto alive = [&]() {
         bool a = false;
 #pragma unroll
         for (int m = 0; m < kV4; ++m)
-            a = a || wl[m] > -40.f || (st[m][0] == 0.f && st[m][1] == 0.f && st[m][2] == 0.f && st[m][3] == 0.f);
+            if constexpr (BETA) a = a || wl[m] > ref[m] - 40.f;
+            else a = a || wl[m] > -40.f || (st[m][0] == 0.f && st[m][1] == 0.f && st[m][2] == 0.f && st[m][3] == 0.f);
         return a;
     };
     int r = sp - 1;

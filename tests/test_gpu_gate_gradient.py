@@ -60,3 +60,25 @@ def test_span_bounds(gh, gw, cps, dk, dv, z_mean):
             ws = torch.empty(room, dtype=torch.uint8, device="cuda")
             got = gla.gla_bwd_gates(q, k, v, la, lb, dw, gh, gw, scan, workspace=ws)
             assert max(_err(g, r, f) for g, r, f in zip(got, ref, floors)) <= TOL
+
+
+@pytest.mark.parametrize("zeros", [3, 9, 20])
+def test_two_sided_chain_behind_a_zero_tail(zeros):
+    """k = 0 over the last chunks: the state entering a span behind them is the decayed sum of many earlier spans, all of
+    them added up however far the zeros have decayed them (one chunk per span, chained by the output pass); the carry
+    kernel, which has no cut-off, as second opinion.  Bar 1e-4 x RMS, twice the hi/lo kernels' error."""
+    B, H, gh, gw, dk, dv = 1, 2, 64, 64, 36, 72
+    d = gi.make_gate_inputs(B, H, gh * gw, dk, dv, "bf16", seed=zeros, z_mean=1.5)
+    d["k"][:, :, (64 - zeros) * 64:] = 0.0
+    d["k_bits"] = gi.round_to_bf16_bits(d["k"])
+    q, k, v = (torch.from_numpy(d[n + "_bits"].view(np.int16)).cuda().view(torch.bfloat16) for n in "qkv")
+    la, lb = (torch.from_numpy(d[n]).cuda() for n in ("log_alpha", "log_beta"))
+    gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, 1)
+    ref, ref_fin = og.gla_fwd_gates(d["q"], d["k"], d["v"], d["log_alpha"], d["log_beta"], gh, gw, 0)
+    try:
+        for carry in (gla.CARRY_KERNEL, gla.CARRY_IN_OUTPUT_PASS):
+            gla.gla_set_option(gla.OPT_CARRY, carry)
+            out, fin = gla.gla_fwd_gates(q, k, v, la, lb, gh, gw, 0)
+            assert _err(out, ref, 0) <= 1e-4 and _err(fin, ref_fin, 0) <= 1e-4, carry
+    finally:
+        gla.gla_set_option(gla.OPT_CARRY, gla.CARRY_AUTO)
