@@ -460,7 +460,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
         // ================= (b) gates: lane = token, units of 4 channels dealt to the waves =================
         {
             const int j = lane;
-            for (int u = w; u < pcs; u += NW) {
+            // (8 waves: a last round of at most half as many units as waves is dealt channel by channel below, 19.4 -> 18.1
+            // and 28.2 -> 26.7 us for dq and dk, dv of 256 sequences of 256 steps at dk = 36; with 4 waves it costs registers
+            // that spill, and with the two-sided gate the units of the value side, dealt from the last wave, even it out)
+            const int rest = NW == 8 && !BETA && pcs % NW <= NW / 2 ? pcs % NW : 0, units = pcs - rest;
+            for (int u = w; u < units; u += NW) {
                 const int c0 = 4 * u;
                 const f32x4 x = *reinterpret_cast<const f32x4 *>(s_la + j * LAS + c0);
                 const u32x2 kr = *reinterpret_cast<const u32x2 *>(s_khi + j * CHS + c0);
@@ -490,6 +494,25 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                 if (lane == 63) {
                     *reinterpret_cast<f32x4 *>(s_gam + c0) = e;
                     if constexpr (GS) *reinterpret_cast<f32x4 *>(s_lg + c0) = f32x4{bb[0], bb[1], bb[2], bb[3]};
+                }
+            }
+            if constexpr (NW == 8 && !BETA) for (int c = 4 * units + w; c < dk; c += NW) {
+                const float b = wave_inclusive_scan(s_la[j * LAS + c] * kLog2e);
+                const float e = exp2_fast(b);
+                const float kx = bf16_bits_to_float(s_khi[j * CHS + c]) * exp2_fast(fminf(-b, kMaxExp2));
+                const float qx = Q ? bf16_bits_to_float(s_qhi[j * CHS + c]) * e : 0.f;
+                uint32_t h2, l2;
+                SPLIT_PAIR(kx, qx, h2, l2);
+                s_khi[j * CHS + c] = (uint16_t)(h2 & 0xffffu);
+                s_klo[j * CHS + c] = (uint16_t)(l2 & 0xffffu);
+                if constexpr (Q) {
+                    s_qhi[j * CHS + c] = (uint16_t)(h2 >> 16);
+                    s_qlo[j * CHS + c] = (uint16_t)(l2 >> 16);
+                }
+                s_la[j * LAS + c] = e;
+                if (lane == 63) {
+                    s_gam[c] = e;
+                    if constexpr (GS) s_lg[c] = b;
                 }
             }
             if constexpr (BETA) {
@@ -817,9 +840,6 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                     }
                 }
             }
-            if constexpr (DV) {
-                if (p.dlog_alpha != nullptr) __syncthreads();     // the sums of all waves' tokens are there
-            }
             // state update on this wave's tiles: S^T += V^T K~, then the chunk's decay per channel
 #pragma unroll
             for (int q = CT0 < CT1 ? NQ : 0; q < (OWNS ? 2 : 0); ++q) load_k(q);
@@ -937,29 +957,37 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
             }
             if constexpr (DV) {
                 if (p.dlog_alpha != nullptr) {
-                    // sums over all later scan steps: the wave's own rows + the waves before it + everything before
-                    // this chunk; the last wave leaves the total for the next chunk
-                    auto finish = [&](auto pitch_c, auto stride_c, float *rows, const float *tot, float *later, char *dst,
-                                      int stride, int width) {
-                        constexpr int P = decltype(pitch_c)::value, RS = decltype(stride_c)::value;
+                    // Sums over all later scan steps: the wave's own rows + the waves before it + everything before
+                    // this chunk; the last wave leaves the total for the next chunk.  The barrier stands behind the state
+                    // update, so that the waves with fewer causal tiles, which own the odd state tiles, have no less to
+                    // do before it; and since only registers and the sums are read after it, it is also the one that
+                    // lets the next chunk's rows into LDS.
+                    constexpr int NA = READ ? NCT : 0, NB = BETA && OUTPUTS ? NDV16 : 0;
+                    f32x4 xs[NA > 0 ? NA : 1], ys[NB > 0 ? NB : 1];
 #pragma unroll
-                        for (int x = 0; x < P / 16 + (P % 16 != 0); ++x) {
-                            const int c = 16 * x + 4 * g;
-                            if (c < width) {
-                                f32x4 add = *reinterpret_cast<const f32x4 *>(later + (chunk & 1) * P + c);
+                    for (int x = 0; x < NA; ++x) xs[x] = *reinterpret_cast<const f32x4 *>(s_la + row * LAS + min(16 * x + 4 * g, L::kDkp - 4));
 #pragma unroll
-                                for (int u = 0; u < IT; ++u) add += *reinterpret_cast<const f32x4 *>(tot + u * P + c);
-                                if (row < nvalid)
-                                    *reinterpret_cast<f32x4 *>(dst + ((uint32_t)tok[row] * (uint32_t)stride + (uint32_t)c) * 4u) =
-                                        *reinterpret_cast<const f32x4 *>(rows + row * RS + c) + add;
-                                if (IT == 3 && lm == 0)
-                                    *reinterpret_cast<f32x4 *>(later + ((chunk + 1) & 1) * P + c) =
-                                        add + *reinterpret_cast<const f32x4 *>(tot + IT * P + c);
-                            }
+                    for (int x = 0; x < NB; ++x) ys[x] = *reinterpret_cast<const f32x4 *>(s_lb + row * LBS + 16 * x + 4 * g);
+                    const uint32_t my_tok = (uint32_t)tok[row];
+                    __syncthreads();
+                    auto finish = [&](auto pitch_c, const f32x4 &sum, int x, const float *tot, float *later, char *dst, int stride, int width) {
+                        constexpr int P = decltype(pitch_c)::value;
+                        const int c = 16 * x + 4 * g;
+                        if (c < width) {
+                            f32x4 add = *reinterpret_cast<const f32x4 *>(later + (chunk & 1) * P + c);
+#pragma unroll
+                            for (int u = 0; u < IT; ++u) add += *reinterpret_cast<const f32x4 *>(tot + u * P + c);
+                            if (row < nvalid)
+                                *reinterpret_cast<f32x4 *>(dst + (my_tok * (uint32_t)stride + (uint32_t)c) * 4u) = sum + add;
+                            if (IT == 3 && lm == 0)
+                                *reinterpret_cast<f32x4 *>(later + ((chunk + 1) & 1) * P + c) =
+                                    add + *reinterpret_cast<const f32x4 *>(tot + IT * P + c);
                         }
                     };
-                    if constexpr (READ) finish(int_c<L::kDkp>{}, int_c<LAS>{}, s_la, s_tot, s_later, gdla, p.st_k, dk);
-                    if constexpr (BETA && OUTPUTS) finish(int_c<L::kDvp>{}, int_c<LBS>{}, s_lb, s_totb, s_laterb, gdlb, p.st_v, dv);
+#pragma unroll
+                    for (int x = 0; x < NA; ++x) finish(int_c<L::kDkp>{}, xs[x], x, s_tot, s_later, gdla, p.st_k, dk);
+#pragma unroll
+                    for (int x = 0; x < NB; ++x) finish(int_c<L::kDvp>{}, ys[x], x, s_totb, s_laterb, gdlb, p.st_v, dv);
                 }
             }
         };
@@ -988,7 +1016,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
                 }
             }
         }
-        __syncthreads();
+        if (!(DV && p.dlog_alpha != nullptr)) __syncthreads();
     }
 
     if constexpr (GS) {
