@@ -1078,9 +1078,9 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     // register cap: no tighter than the waves per SIMD that the LDS footprint lets a compute unit hold anyway
     constexpr int kGroupsPerCu = (160 * 1024) / L::kBytes;
     constexpr int kWavesPerSimd = kGroupsPerCu * NW / 4;
-    // (two-sided gate: the plan is for the output pass's one group per compute unit, so the state pass has one, too:
+    // (two-sided gate from its logarithms: the plan is for the output pass's one group per compute unit, so the state pass has one, too:
     // 22.8 -> 18.3 us at 64 sequences of 1024 steps, 36 / 72 channels, without spills; a second chunk in flight 20.0 us)
-    constexpr int MINW = kWavesPerSimd >= 4 && !BETA ? 4 : (kWavesPerSimd >= 2 ? 2 : 1);
+    constexpr int MINW = kWavesPerSimd >= 4 && (!BETA || FUSE) ? 4 : (kWavesPerSimd >= 2 ? 2 : 1);
     if constexpr (MODE == kModeOutput && !FUSE) {
         // (the range fallback's groups mostly return at once: fewer waves to start)
         if (kGroupsPerCu < 2 || (NDK8 <= 4 && !p.only_flagged && (long long)p.B * p.H * p.nspans <= 256))
@@ -1146,8 +1146,13 @@ bool mfma_engine_supports(const Params &p) {
 }
 
 // The output pass and the backward pass's row reads: two work-groups fit a compute unit's LDS up to 40 key channels
-// and 80 value columns, one with larger heads and with the two-sided gate's extra rows.
-int mfma_groups_per_cu(const Params &p) { return two_sided(p) || p.dk > 40 || p.dv > 80 ? 1 : 2; }
+// and 80 value columns, one with larger heads and with the two-sided gate's extra rows.  With both gates from
+// pre-activations the spans are cut for two all the same: that output pass has no 8-wave form, and the state pass, which
+// does fit twice, gains more than the output pass loses (16 sequences of 16384 steps at 36 / 72: 182 us against 193).
+int mfma_groups_per_cu(const Params &p) {
+    if (p.dk > 40 || p.dv > 80) return 1;
+    return two_sided(p) && p.z_beta == nullptr ? 1 : 2;
+}
 
 hipError_t launch_mfma_span(const Params &p, SpanMode mode, hipStream_t stream) {
     return mode == kModeState ? launch_mode<kModeState>(p, stream) : launch_mode<kModeOutput>(p, stream);
