@@ -379,12 +379,14 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_span_kernel(Params p) {
 
     // ---- gate work of this wave: whole UW-channel units w, w+NW, ..., then single left-over channels ----
     constexpr int UW = 32 / NW;                       // channels per unit: 16-byte LDS rows accesses for 4 waves
-    const int nunits = dk / UW;
+    // (8 waves in the output pass: a last round of at most half as many units as waves is dealt channel by channel, too)
+    const int all_units = dk / UW;
+    const int nunits = OUT && NW == 8 && all_units % NW <= NW / 2 ? all_units - all_units % NW : all_units;
     const int upw = (nunits + NW - 1) / NW;           // units of the busiest wave
     const int left0 = UW * nunits;                    // first left-over channel (none with 4-channel units)
     const int lpw = (dk - left0 + NW - 1) / NW;       // left-over channels per wave
     constexpr int kMaxUnits = (kMaxDk / UW + NW - 1) / NW;
-    constexpr int kMaxLeft = (UW - 4 + NW - 1) / NW;
+    constexpr int kMaxLeft = OUT && NW == 8 ? UW * (NW / 2) / NW : (UW - 4 + NW - 1) / NW;
 
     load_chunk(0, int_c<0>{});
     if constexpr (DEPTH == 2) {
@@ -1071,9 +1073,10 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     // unit); the output pass needs the 256-register budget of 4-wave groups for its operand batches.  It takes 8 waves
     // with that budget where the LDS holds one group per compute unit anyway (two-sided gate, 64 sequences of 1024
     // tokens at 36 / 72: 35.0 -> 30.3 us; 64 / 128 channels, two scan orders summed: 70 -> 57 us a call), or where there
-    // are no more groups than compute units and the gate stage's 4-channel units come out even over 8 waves (dk <= 32:
-    // 48 sequences of 256 tokens 13.0 -> 12.4 us; at dk = 36 the ninth unit takes the first wave a second round, 18.7 ->
-    // 20.0 us).  With two 8-wave groups per compute unit the 128 registers spill (32 -> 77 us, two 1024 px images).
+    // are no more groups than compute units: dk <= 32, 48 sequences of 256 tokens 13.0 -> 12.4 us; at dk = 36, whose ninth
+    // gate unit is then dealt channel by channel, only up to half as many (96 sequences of 253 tokens 16.5 -> 15.7 us a call,
+    // a training step of 256 sequences of 256 tokens 59.2 -> 60.1 us).  With two 8-wave groups per compute unit the 128
+    // registers spill (32 -> 77 us, two 1024 px images).
     constexpr int NW = (MODE == kModeState) ? 8 : 4;
     // register cap: no tighter than the waves per SIMD that the LDS footprint lets a compute unit hold anyway
     constexpr int kGroupsPerCu = (160 * 1024) / L::kBytes;
@@ -1083,7 +1086,7 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     constexpr int MINW = kWavesPerSimd >= 4 && (!BETA || FUSE) ? 4 : (kWavesPerSimd >= 2 ? 2 : 1);
     if constexpr (MODE == kModeOutput && !FUSE) {
         // (the range fallback's groups mostly return at once: fewer waves to start)
-        if (kGroupsPerCu < 2 || (NDK8 <= 4 && !p.only_flagged && (long long)p.B * p.H * p.nspans <= 256))
+        if (kGroupsPerCu < 2 || (NDK8 <= 5 && !p.only_flagged && (long long)p.B * p.H * p.nspans <= (NDK8 <= 4 ? 256 : 128)))
             return launch_waves<MODE, NDK8, NDV16, 8, 2, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
     }
     return launch_waves<MODE, NDK8, NDV16, NW, MINW, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
