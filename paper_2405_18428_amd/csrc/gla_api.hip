@@ -206,7 +206,7 @@ void place_states(Params &p, char *at) {
 // Sets the two walks of the backward pass (fwd for dq, rev for dk and dv, on one span plan) up so that the first leaves
 // what the second starts from - the forward states at the span bounds and the local states of the reversed recurrence -
 // if the workspace has room: in the span states' room behind the fwd walk's own (`used` bytes of it), else from `extra`.
-bool place_walks(Params &fwd, Params &rev, void *workspace, size_t used, size_t state_bytes, size_t extra, size_t ws_bytes) {
+bool place_walks(WalkParams &fwd, WalkParams &rev, void *workspace, size_t used, size_t state_bytes, size_t extra, size_t ws_bytes) {
     if (rev.nspans == 1) return true;
     char *ws = static_cast<char *>(workspace);
     const size_t bh = (size_t)rev.B * rev.H;
@@ -272,7 +272,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
     auto span = [&](const Params &p, SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
     };
-    auto row_read = [&](const Params &p, const void *w, float *r) {
+    auto row_read = [&](const WalkParams &p, const void *w, float *r) {
         return use_mfma ? launch_mfma_row_read(p, w, r, stream) : launch_row_read(p, w, r, stream);
     };
     auto states = [&](const Params &p) {   // span-local states, then chained in place
@@ -283,7 +283,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
     };
 
     // 1. states of the forward recurrence (k, v, log_alpha); dq_s = S_s dO_s
-    Params pa = base;
+    WalkParams pa{base};
     pa.q = q; pa.k = k; pa.v = v; pa.log_alpha = log_alpha; pa.scan_dir = scan_dir; pa.gate_shift = 0;
     const bool reuse = fwd_workspace && pa.nspans > 1;
     if (reuse) {
@@ -308,12 +308,12 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
     // 2. states of the reversed recurrence G_s = q_s^T dO_s + diag(alpha_{s+1}) G_{s+1}: the forward recurrence
     //    with k, v := q, dO, walked from the last scan step, each step using the previous step's gate.
     //    With one reversed walk for dk, dv and the gate gradient, the walk for dq leaves its local states.
-    Params pb = base;
+    WalkParams pb{base};
     pb.q = k; pb.k = q; pb.v = d_out; pb.log_alpha = log_alpha; pb.scan_dir = scan_dir ^ 1; pb.gate_shift = 1;
     pb.out = dv_grad;
     bool with_gates = false;
     if (one_walk) {
-        Params rev = pb;        // (on the plan of the walk for dq, which may be the forward call's)
+        WalkParams rev = pb;        // (on the plan of the walk for dq, which may be the forward call's)
         rev.nspans = pa.nspans;
         rev.span_len = pa.span_len;
         rev.chain_in_output = pa.chain_in_output;
@@ -396,15 +396,15 @@ int run_bwd_gates(const void *q, const void *k, const void *v, const float *log_
         return launch_carry(p, stream);
     };
     // value-axis reads of the state: chunk form on the MFMA units where the engine covers the case
-    auto row_read = [&](const Params &p, const void *w, float *r) {
+    auto row_read = [&](const WalkParams &p, const void *w, float *r) {
         return use_mfma ? launch_mfma_row_read(p, w, r, stream) : launch_row_read(p, w, r, stream);
     };
 
     // 1. forward recurrence: states entering the spans, the outputs o (for the value-side gate gradient),
     //    dq_s = S_s dO_s
-    Params pa = base;
+    WalkParams pa{base};
     pa.q = q; pa.k = k; pa.v = v; pa.scan_dir = scan_dir; pa.gate_shift = 0; pa.out = o_buf;
-    Params pb = base;
+    WalkParams pb{base};
     pb.q = k; pb.k = q; pb.v = d_out; pb.scan_dir = scan_dir ^ 1; pb.gate_shift = 1; pb.out = dv_grad;
     const bool with_gates = one_walk && place_walks(pa, pb, workspace, plan_workspace_bytes((size_t)B * H, (size_t)pa.nspans, dk, dv),
                                                     state_bytes, state_bytes + totals_bytes + bwd_gates_out_bytes(B, H, T, dv), ws_bytes);

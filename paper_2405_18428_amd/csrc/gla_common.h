@@ -46,9 +46,6 @@ struct Params {
     int B, H, T, dk, dv, grid_h, grid_w, scan_dir;
     int nspans;             // spans per (batch, head)
     int span_len;           // tokens per span, a multiple of kChunk
-    int span_shift;         // row reads of the MFMA engine: span sp is steps [sp * span_len - span_shift,
-                            //    (sp + 1) * span_len - span_shift) of the sequence (the reversed walk of the backward
-                            //    pass: its spans then begin where those of the forward walk end, the first is the short one)
     int gate_shift;         // 1: scan step s uses the log_alpha row of the token visited at step s-1 (the
                             //    reverse-mode recurrence dS_s = diag(alpha_{s+1}) dS_{s+1} + q_s^T dO_s walked backwards)
     int chain_in_output;    // 1: no phase-2 kernel; the output pass chains U_0..U_{r-1} itself and phase 1
@@ -76,9 +73,20 @@ struct Params {
     int *ws_fail;           // [B*H, nspans of the fp16 engine's plan]
     int only_flagged;
     int fail_spans;         // flags per (batch, head) when only_flagged is set
-    // backward pass on the MFMA engine: the state after every bound_len scan steps, which the walk for dq leaves in
-    // ws_bound ([B*H, bounds, dk, dv]) and the reversed walk for dk, dv starts its gate gradients from; and what that
-    // walk needs to form them (dlog_alpha; dlog_beta with the two-sided gate)
+};
+
+static_assert(sizeof(Params) <= 264, "what only some kernels need belongs into a struct of theirs, see WalkParams");
+
+// The backward walks of the MFMA engine (mfma_row_read_kernel) take more.  Only they do: every kernel loads its arguments
+// at its start, and with these among them the 4-wave hi/lo forward pass took 0.16 us more a launch on MI355X (160 to 256
+// sequences of 256 tokens at 36 / 72 channels, 16.8 us, 16.7 without).
+struct WalkParams : Params {
+    int span_shift;         // span sp is steps [sp * span_len - span_shift, (sp + 1) * span_len - span_shift) of the
+                            //    sequence (the reversed walk: its spans then begin where those of the forward walk end,
+                            //    the first is the short one)
+    // the state after every bound_len scan steps, which the walk for dq leaves in ws_bound ([B*H, bounds, dk, dv]) and
+    // the reversed walk for dk, dv starts its gate gradients from; and what that walk needs to form them (dlog_alpha;
+    // dlog_beta with the two-sided gate)
     float *ws_bound;
     int bound_len, bounds;
     // the walk for dq also leaves the local states of the reversed recurrence and their log decays here (laid out like
@@ -89,11 +97,11 @@ struct Params {
 };
 
 // first scan step of span sp, and the step after its last
-__host__ __device__ inline int span_begin(const Params &p, int sp) {
+__host__ __device__ inline int span_begin(const WalkParams &p, int sp) {
     const int s = sp * p.span_len - p.span_shift;
     return s > 0 ? s : 0;
 }
-__host__ __device__ inline int span_end(const Params &p, int sp) {
+__host__ __device__ inline int span_end(const WalkParams &p, int sp) {
     const int s = (sp + 1) * p.span_len - p.span_shift;
     return s < p.T ? s : p.T;
 }
@@ -166,7 +174,7 @@ hipError_t launch_fast_state(const Params &p, hipStream_t stream);   // its span
 // dlog_alpha = reverse cumulative sum of q * dq - k * dk (totals: [B*H, dg_spans(T), dk] floats of scratch)
 hipError_t launch_row_read(const Params &p, const void *w, float *r, hipStream_t stream);
 // the same on the MFMA units (chunk form); needs what mfma_engine_supports() checks
-hipError_t launch_mfma_row_read(const Params &p, const void *w, float *r, hipStream_t stream,
+hipError_t launch_mfma_row_read(const WalkParams &p, const void *w, float *r, hipStream_t stream,
                                 bool with_outputs = false);   // with_outputs: also o_j = q_j S_j (p.q) to p.out, fp32
 hipError_t launch_dlog_alpha(const Params &p, const float *dq, const float *dk_grad, float *dg, float *totals,
                              hipStream_t stream);

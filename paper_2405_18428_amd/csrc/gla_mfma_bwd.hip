@@ -111,7 +111,7 @@ using int_c = std::integral_constant<int, N>;
 // walk for dq takes 59 instead of 45 us (16 sequences of 16384 steps, 36 / 72 channels) and the state pass of 31 us
 // goes, 182 -> 167 us for the call; two-sided gate, 64 sequences of 1024 steps: 32 -> 36 us, without a state pass of 21.
 template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA, bool GS>
-__global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, const void *w_in, float *r_out) {
+__global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(WalkParams p, const void *w_in, float *r_out) {
     using L = RLayout<NDK8, NDV16, DV, BETA, GS>;
     static_assert(!(DV && GS), "either walk");
     constexpr bool Q = DV || GS;     // q~ rows are needed
@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(Params p, 
 }
 
 template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA, bool GS>
-hipError_t launch_waves(const Params &p, const void *w, float *r, hipStream_t stream) {
+hipError_t launch_waves(const WalkParams &p, const void *w, float *r, hipStream_t stream) {
     using L = RLayout<NDK8, NDV16, DV, BETA, GS>;
     auto kernel = mfma_row_read_kernel<NDK8, NDV16, NW, MINW, DV, BETA, GS>;
     static std::atomic<bool> configured[kMaxDevices] = {};  // per instantiation and device
@@ -1064,7 +1064,7 @@ hipError_t launch_waves(const Params &p, const void *w, float *r, hipStream_t st
 }
 
 template <int NDK8, int NDV16, bool DV, bool BETA, bool GS>
-hipError_t launch_one(const Params &p, const void *w, float *r, hipStream_t stream) {
+hipError_t launch_one(const WalkParams &p, const void *w, float *r, hipStream_t stream) {
     // 8 waves where a compute unit holds one group anyway: by its LDS, or because there are no more groups than units
     constexpr int kGroupsPerCu = (160 * 1024) / RLayout<NDK8, NDV16, DV, BETA, GS>::kBytes;
     if constexpr (kGroupsPerCu >= 2) {
@@ -1074,7 +1074,7 @@ hipError_t launch_one(const Params &p, const void *w, float *r, hipStream_t stre
 }
 
 template <bool DV, bool GS>
-hipError_t launch_sizes(const Params &p, const void *w, float *r, hipStream_t stream) {
+hipError_t launch_sizes(const WalkParams &p, const void *w, float *r, hipStream_t stream) {
     const int ndk8 = (p.dk + 7) / 8, ndv16 = (p.dv + 15) / 16;
     if (p.log_beta != nullptr) {   // two-sided gate: the head sizes whose extra rows fit the LDS (dk <= 40, dv <= 80)
         if (ndk8 <= 4 && ndv16 <= 4) return launch_one<4, 4, DV, true, GS>(p, w, r, stream);
@@ -1090,7 +1090,7 @@ hipError_t launch_sizes(const Params &p, const void *w, float *r, hipStream_t st
 
 // Same conditions as the forward MFMA engine (bf16 rows, dk % 4 == 0, dv % 8 == 0, 32-bit offsets).
 // with_outputs: also write o_j = q_j S_j (p.q, fp32 rows to p.out).
-hipError_t launch_mfma_row_read(const Params &p, const void *w, float *r, hipStream_t stream, bool with_outputs) {
+hipError_t launch_mfma_row_read(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs) {
     if (with_outputs) return launch_sizes<true, false>(p, w, r, stream);
     return p.ws_gstate != nullptr ? launch_sizes<false, true>(p, w, r, stream) : launch_sizes<false, false>(p, w, r, stream);
 }
