@@ -149,8 +149,11 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     }
     // (the token-by-token engine's epilogue pass is one group per span, like the plan of the bf16 hi/lo engine)
     const size_t bh = (size_t)p.B * p.H;
+    // most spans that surely fit the workspace (its arrays begin at multiples of 256 bytes)
+    const size_t per_span = bh * ((size_t)p.dk * p.dv + p.dk + p.dv + 1) * sizeof(float);
+    const size_t max_spans = ws_limit > 1024 ? (ws_limit - 1024) / per_span : 0;
     int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
-                  ? recurrent_chunks_per_span(p)
+                  ? recurrent_chunks_per_span(p, (long long)(max_spans < (size_t)nchunks ? max_spans : nchunks))
                   : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma,
                                          fast ? fast_groups_per_cu(p) : (use_mfma ? mfma_groups_per_cu(p) : 2), fast);
     // A last span of one ragged chunk: some of the fp16 engine's lanes see no token in it, so it raises the flag of

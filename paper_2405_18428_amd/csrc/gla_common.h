@@ -159,7 +159,7 @@ inline hipError_t allow_dynamic_lds(const void *kernel, int bytes, std::atomic<b
 // Launchers (defined in the .hip files); each enqueues on `stream` and returns
 // hipGetLastError().
 hipError_t launch_recurrent_span(const Params &p, SpanMode mode, hipStream_t stream);
-int recurrent_chunks_per_span(const Params &p);   // span plan of the token-by-token engine
+int recurrent_chunks_per_span(const Params &p, long long max_spans);   // span plan of the token-by-token engine
 hipError_t launch_mfma_span(const Params &p, SpanMode mode, hipStream_t stream);
 hipError_t launch_carry(const Params &p, hipStream_t stream);
 bool mfma_engine_supports(const Params &p);

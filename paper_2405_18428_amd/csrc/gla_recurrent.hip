@@ -572,7 +572,7 @@ hipError_t launch_row_read(const Params &p, const void *w, float *r, hipStream_t
     return bf16 ? launch_read<false, uint16_t>(p, w, r, stream) : launch_read<false, float>(p, w, r, stream);
 }
 
-int recurrent_chunks_per_span(const Params &p) {
+int recurrent_chunks_per_span(const Params &p, long long max_spans) {
     const int nchunks = (p.T + kChunk - 1) / kChunk;
     // scan steps per round of a work-group, from the span-state pass's configuration (the other passes' differ by at
     // most a factor of two where gates on both axes or a long value axis take more LDS)
@@ -587,6 +587,7 @@ int recurrent_chunks_per_span(const Params &p) {
     int best_rounds = rounds;
     for (int r = 1; r < rounds; ++r) {                                 // rounds per span
         const long long spans = (rounds + r - 1) / r;
+        if (spans > max_spans) continue;                               // (no room for their states)
         const long long cost = 2 * ((groups * spans + 255) / 256 * r) + kLaunches;
         if (cost < best) {
             best = cost;

@@ -111,3 +111,19 @@ def test_static_scratch_rejects_oversize_on_the_host():
     # 4096 sequences of 1024 chunks, one span each: 4096 * (64 * 128 + 64 + 128) floats, far beyond 16 MiB
     assert lib.gla_fwd_static(ok, ok, ok, ok, 64, 64, 65536, 64, 128, 256, 256, 0, ok, None, None) == 5
     assert lib.gla_fwd_static(None, ok, ok, ok, 1, 1, 4, 8, 8, 2, 2, 0, ok, None, None) == 1
+
+
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="passes addresses that no GPU may be given")
+@pytest.mark.parametrize("engine", [gla.ENGINE_AUTO, gla.ENGINE_RECURRENT])
+@pytest.mark.parametrize("B,H,T,dk,dv", [(1, 16, 16384, 36, 70), (1, 16, 16384, 33, 64), (1, 16, 16384, 36, 72),
+                                         (4, 4, 65536, 36, 70)])
+def test_static_scratch_takes_long_sequences(engine, B, H, T, dk, dv):
+    """Long sequences on the token-by-token engine: of the span plans that fit the static array one is taken, so the
+    call gets as far as asking for the device (status 6 where there is none) instead of refusing the plan (5)."""
+    lib = gla.load_library()
+    ok = ctypes.c_void_p(4096)
+    gla.gla_set_option(gla.OPT_ENGINE, engine)
+    try:
+        assert lib.gla_fwd_static(ok, ok, ok, ok, B, H, T, dk, dv, T // 64, 64, 0, ok, None, None) == 6
+    finally:
+        gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)

@@ -50,3 +50,13 @@ def test_static_scratch_two_calls_second_smaller(oracle):
     # several spans per head (the scratch holds span states), then a smaller problem that reuses the array
     _one_call(torch, oracle, 2, 16, 64, 64, 36, 72, gla.SCAN_COL_REV, seed=11)
     _one_call(torch, oracle, 1, 6, 28, 20, 32, 64, gla.SCAN_ROW_FWD, seed=12)
+
+
+def test_static_scratch_long_odd_heads(oracle):
+    """16 sequences of 16384 steps on the token-by-token engine: its cheapest span plan (128 spans a sequence, 21 MB of
+    states) does not fit the array, one of fewer spans does."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    gla.load_library()
+    _one_call(torch, oracle, 1, 16, 128, 128, 36, 70, gla.SCAN_COL_FWD, seed=13)
