@@ -377,12 +377,13 @@ __global__ __launch_bounds__((TokenCfg<GS, PER, ROWREAD, BETA, STATE>::kMaxWaves
 // Output pass with the epilogue (Eq. (attn_gla) rows 4-5 up to the projection): y = Swish(r) * LN(o) needs a token's
 // whole row of o, so one work-group walks the span with thread n owning column n of the state in registers; q, k and
 // alpha of a tile of tokens are staged in LDS and read as wave-wide broadcasts.  RP = padded number of key channels:
-// the padding is staged as zeros, so a step has no branch per channel.
+// the padding is staged as zeros, so a step has no branch per channel.  Without the epilogue it takes the sequences of a
+// few steps (few_steps).
 constexpr int kThreads = 128;  // >= kMaxDv
 constexpr int kTile = 16;      // tokens staged per round
 
 template <int RP, typename TIn, typename TOut, bool BETA>
-__global__ __launch_bounds__(kThreads) void epilogue_span_kernel(Params p) {
+__global__ __launch_bounds__(kThreads) void column_span_kernel(Params p) {
     __shared__ float s_b[BETA ? kTile : 1][BETA ? kMaxDv : 1];   // log_beta rows of the tile
     __shared__ __attribute__((aligned(16))) float s_q[kTile][RP], s_k[kTile][RP], s_a[kTile][RP];
     __shared__ float s_v[kTile][kMaxDv];
@@ -463,7 +464,17 @@ __global__ __launch_bounds__(kThreads) void epilogue_span_kernel(Params p) {
             }
         }
         __syncthreads();
-        {   // 8 threads per token of the tile
+        if (p.r_pre == nullptr) {     // (uniform)
+            for (int idx = tid; idx < kTile * dv; idx += kThreads) {
+                const int j = idx / dv, n2 = idx - j * dv;
+                const int n = s_tok[j];
+                if (n < 0) break;
+                const size_t e = base_v + (size_t)n * st_v + n2;
+                float o = s_o[j][n2];
+                if (p.accumulate) o += static_cast<const float *>(p.out)[e];   // fp32 rows (host checks)
+                store_elem<TOut>(p.out, e, o);
+            }
+        } else {   // 8 threads per token of the tile
             const int j = tid >> 3, sub = tid & 7;
             const int n = s_tok[j];
             const float inv_n = 1.f / (float)dv;
@@ -518,7 +529,7 @@ hipError_t launch_token(const Params &p, const void *w, float *r, hipStream_t st
 }
 
 template <bool BETA, typename TIn>
-hipError_t launch_epilogue(const Params &p, hipStream_t stream) {
+hipError_t launch_columns(const Params &p, hipStream_t stream) {
     const bool out_bf16 = p.out_dtype == GLA_DT_BF16;
     dim3 grid((unsigned)(p.B * p.H * p.nspans)), block(kThreads);
     auto launch = [&](auto kernel) {
@@ -526,8 +537,24 @@ hipError_t launch_epilogue(const Params &p, hipStream_t stream) {
         return hipGetLastError();
     };
     if (p.dk <= 32)
-        return out_bf16 ? launch(epilogue_span_kernel<32, TIn, uint16_t, BETA>) : launch(epilogue_span_kernel<32, TIn, float, BETA>);
-    return out_bf16 ? launch(epilogue_span_kernel<64, TIn, uint16_t, BETA>) : launch(epilogue_span_kernel<64, TIn, float, BETA>);
+        return out_bf16 ? launch(column_span_kernel<32, TIn, uint16_t, BETA>) : launch(column_span_kernel<32, TIn, float, BETA>);
+    return out_bf16 ? launch(column_span_kernel<64, TIn, uint16_t, BETA>) : launch(column_span_kernel<64, TIn, float, BETA>);
+}
+
+// Sequences of a few steps (a state carried on token by token): a wave of token_span_kernel walks 8 or 16 steps whether
+// they are there or not and stages their rows once per 16 columns, column_span_kernel only what there is.  The less work a
+// compute unit has and the fewer columns, the sooner the first is the faster one all the same.  MI355X, fp32 with an
+// initial state, token_span_kernel against column_span_kernel, us a call:
+//   4096 sequences at 36 / 72 channels   1 step 81.7  43.9   4 steps 83.8  60.7   6 steps 87.5  74.2   8 steps 89.9  90.2
+//   3072 sequences at 32 / 64            1 step 28.0  21.3   4 steps 28.5  26.2   6 steps 29.5  30.3
+//   512 sequences at 36 / 72             1 step 17.0  11.5   4 steps 17.1  15.0   5 steps 17.2  16.3
+//   16 sequences at 36 / 72              2 steps 12.2 11.6   3 steps 11.9  12.3   4 steps 12.2  13.4
+//   4096 sequences at 64 / 64            1 step 93.0  61.8   4 steps 94.3  79.5   6 steps 95.6  92.5
+//   4096 sequences at 36 / 48            1 step 51.9  39.0   4 steps 52.4  52.4   6 steps 53.0  63.0
+bool few_steps(const Params &p) {
+    if (p.nspans > 1 || p.gate_shift || p.dv <= (p.dk > 32 ? 32 : 48)) return false;
+    const long long sequences = (long long)p.B * p.H;
+    return p.T <= 2 || (p.T <= 4 && sequences >= 512) || (p.T <= 6 && p.dk > 32 && p.dv > 64 && sequences >= 1024);
 }
 
 template <int GS, int PER, bool BETA, typename TIn>
@@ -542,7 +569,7 @@ hipError_t launch_span_class(const Params &p, SpanMode mode, hipStream_t stream)
 // the next power of two would do 1.6 and 1.8 times the arithmetic.
 template <bool BETA, typename TIn>
 hipError_t launch_span(const Params &p, SpanMode mode, hipStream_t stream) {
-    if (mode == kModeOutput && p.r_pre != nullptr) return launch_epilogue<BETA, TIn>(p, stream);
+    if (mode == kModeOutput && (p.r_pre != nullptr || few_steps(p))) return launch_columns<BETA, TIn>(p, stream);
     if (p.dk <= 32) return launch_span_class<4, 4, BETA, TIn>(p, mode, stream);
     if (p.dk <= 40) return launch_span_class<8, 5, BETA, TIn>(p, mode, stream);
     return launch_span_class<8, 8, BETA, TIn>(p, mode, stream);

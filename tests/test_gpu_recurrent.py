@@ -62,6 +62,31 @@ def test_edges(grid, dk, dv, cps):
             assert _err(got, r, f) < TOL
 
 
+@pytest.mark.parametrize("B,H,grid,dk,dv", [
+    # on both sides of the bounds up to which one thread per column walks a sequence of a few steps
+    (1, 2, (1, 1), 36, 72), (1, 2, (2, 1), 32, 49), (1, 2, (1, 2), 33, 33), (1, 2, (1, 3), 36, 72), (32, 16, (2, 2), 64, 128),
+    (32, 16, (1, 3), 31, 50), (32, 16, (1, 5), 36, 72), (64, 16, (2, 3), 36, 72), (64, 16, (1, 7), 40, 80)])
+def test_few_steps(B, H, grid, dk, dv):
+    gh, gw = grid
+    T = gh * gw
+    d = gi.make_gate_inputs(B, H, T, dk, dv, "f32", seed=T + dk)
+    init = np.random.Generator(np.random.PCG64(8)).standard_normal((B, H, dk, dv), dtype=np.float32)
+    host = [d[n] for n in ("q", "k", "v", "log_alpha")]
+    up = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    x, lb, s0 = [up(t) for t in host], up(d["log_beta"]), up(init)
+    for scan in (0, 3):
+        ref = orc.gla_fwd(*host, gh, gw, scan, initial_state=init)
+        for got, r in zip(gla.gla_fwd_layout(*x, gh, gw, scan, initial_state=s0), ref):
+            assert _err(got, r) < TOL
+        bthd = [up(t.transpose(0, 2, 1, 3)) for t in host]
+        out, fin = gla.gla_fwd_layout(*bthd, gh, gw, scan, layout=gla.LAYOUT_BTHD, initial_state=s0, out_dtype=torch.bfloat16)
+        assert _err(out.float().transpose(1, 2), ref[0]) < 0.05 and _err(fin, ref[1]) < TOL    # (bf16: 2^-9 of the largest)
+        for got, r in zip(gla.gla_fwd_gates(*x, lb, gh, gw, scan, initial_state=s0),
+                          og.gla_fwd_gates(*host, d["log_beta"], gh, gw, scan, initial_state=init)):
+            assert _err(got, r) < TOL
+    assert _err(gla.gla_fwd_multi(*x, gh, gw, scan_dirs=(0, 1, 2, 3)), orc.gla_fwd_multi(*host, gh, gw, (0, 1, 2, 3))) < TOL
+
+
 def test_closed_gates_stay_exact():
     """alpha = 0 (log alpha = -inf) and gates far below any factorised range, at steps on both sides of a wave's cut."""
     d = gi.make_inputs(1, 2, 80, 32, 20, "f32", seed=3)
