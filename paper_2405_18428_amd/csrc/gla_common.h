@@ -156,6 +156,10 @@ inline hipError_t allow_dynamic_lds(const void *kernel, int bytes, std::atomic<b
     return hipSuccess;
 }
 
+// HIP launches fewer than 2^32 threads along one dimension; where more work-groups than that are wanted of a wide kernel, a
+// narrower one takes them.
+inline bool launch_fits(long long groups, int threads) { return groups * threads < (1LL << 32); }
+
 // Launchers (defined in the .hip files); each enqueues on `stream` and returns
 // hipGetLastError().
 hipError_t launch_recurrent_span(const Params &p, SpanMode mode, hipStream_t stream);

@@ -1086,7 +1086,8 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     constexpr int MINW = kWavesPerSimd >= 4 && (!BETA || FUSE) ? 4 : (kWavesPerSimd >= 2 ? 2 : 1);
     if constexpr (MODE == kModeOutput && !FUSE) {
         // (the range fallback's groups mostly return at once: fewer waves to start)
-        if (kGroupsPerCu < 2 || (NDK8 <= 5 && !p.only_flagged && (long long)p.B * p.H * p.nspans <= (NDK8 <= 4 ? 256 : 128)))
+        const long long groups = (long long)p.B * p.H * p.nspans;
+        if (kGroupsPerCu < 2 ? launch_fits(groups, 512) : NDK8 <= 5 && !p.only_flagged && groups <= (NDK8 <= 4 ? 256 : 128))
             return launch_waves<MODE, NDK8, NDV16, 8, 2, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
     }
     return launch_waves<MODE, NDK8, NDV16, NW, MINW, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);

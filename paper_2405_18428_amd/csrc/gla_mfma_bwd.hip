@@ -1067,8 +1067,11 @@ template <int NDK8, int NDV16, bool DV, bool BETA, bool GS>
 hipError_t launch_one(const WalkParams &p, const void *w, float *r, hipStream_t stream) {
     // 8 waves where a compute unit holds one group anyway: by its LDS, or because there are no more groups than units
     constexpr int kGroupsPerCu = (160 * 1024) / RLayout<NDK8, NDV16, DV, BETA, GS>::kBytes;
+    const long long groups = (long long)p.B * p.H * p.nspans;
     if constexpr (kGroupsPerCu >= 2) {
-        if ((long long)p.B * p.H * p.nspans > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA, GS>(p, w, r, stream);
+        if (groups > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA, GS>(p, w, r, stream);
+    } else {
+        if (!launch_fits(groups, 512)) return launch_waves<NDK8, NDV16, 4, 1, DV, BETA, GS>(p, w, r, stream);
     }
     return launch_waves<NDK8, NDV16, 8, 2, DV, BETA, GS>(p, w, r, stream);
 }

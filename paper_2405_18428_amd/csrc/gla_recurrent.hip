@@ -522,6 +522,7 @@ hipError_t launch_token(const Params &p, const void *w, float *r, hipStream_t st
     const int steps = p.T < p.span_len ? p.T : p.span_len;
     int waves = (steps + C::kSteps - 1) / C::kSteps;
     if (waves > C::kMaxWaves) waves = C::kMaxWaves;
+    while (waves > 1 && !launch_fits((long long)p.B * p.H * p.nspans, waves * 64)) --waves;      // (more rounds instead)
     const int cols = ((ROWREAD ? p.dk : p.dv) + kCols - 1) / kCols;
     dim3 grid((unsigned)(p.B * p.H * p.nspans), (unsigned)cols), block(waves * 64);
     hipLaunchKernelGGL(kernel, grid, block, C::bytes(waves), stream, p, w, r);
