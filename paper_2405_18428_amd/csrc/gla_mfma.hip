@@ -1074,8 +1074,8 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     // with that budget where the LDS holds one group per compute unit anyway (two-sided gate, 64 sequences of 1024
     // tokens at 36 / 72: 35.0 -> 30.3 us; 64 / 128 channels, two scan orders summed: 70 -> 57 us a call), or where there
     // are no more groups than compute units: dk <= 32, 48 sequences of 256 tokens 13.0 -> 12.4 us; at dk = 36, whose ninth
-    // gate unit is then dealt channel by channel, only up to half as many (96 sequences of 253 tokens 16.5 -> 15.7 us a call,
-    // a training step of 256 sequences of 256 tokens 59.2 -> 60.1 us).  With two 8-wave groups per compute unit the 128
+    // gate unit is then dealt channel by channel, only up to 224 (sequences of 256 tokens, us a call with 4 and 8 waves: 144
+    // groups 16.5 and 16.0, 192 16.9 and 16.5, 224 17.2 and 17.0, 240 17.3 and 17.3, 256 17.4 and 17.6).  With two 8-wave groups per compute unit the 128
     // registers spill (32 -> 77 us, two 1024 px images).
     constexpr int NW = (MODE == kModeState) ? 8 : 4;
     // register cap: no tighter than the waves per SIMD that the LDS footprint lets a compute unit hold anyway
@@ -1087,7 +1087,7 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     if constexpr (MODE == kModeOutput && !FUSE) {
         // (the range fallback's groups mostly return at once: fewer waves to start)
         const long long groups = (long long)p.B * p.H * p.nspans;
-        if (kGroupsPerCu < 2 ? launch_fits(groups, 512) : NDK8 <= 5 && !p.only_flagged && groups <= (NDK8 <= 4 ? 256 : 128))
+        if (kGroupsPerCu < 2 ? launch_fits(groups, 512) : NDK8 <= 5 && !p.only_flagged && groups <= (NDK8 <= 4 ? 256 : 224))
             return launch_waves<MODE, NDK8, NDV16, 8, 2, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
     }
     return launch_waves<MODE, NDK8, NDV16, NW, MINW, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
