@@ -1,7 +1,8 @@
 """Gate gradients formed inside the reversed walk of the backward pass: span bounds of ragged sequences, slowly decaying
 gates (the start of every span then carries most of the sum), and workspaces without room for what the walk for dq leaves
-(a state pass of the reversed recurrence and the separate reverse-cumulative-sum kernels).  Bar 2e-2 x RMS as for every bf16 call; the two routes differ by the
-rounding of sums of T terms, at most T 2^-24 of their largest partial sum (about 1e-3 of the RMS here)."""
+(a state pass of the reversed recurrence and the separate reverse-cumulative-sum kernels).  Bar 2e-2 x RMS as for every
+bf16 call.  The two routes differ by the rounding of sums of T terms, at most T 2^-24 of their largest partial sum (about
+1e-3 of the RMS here)."""
 import numpy as np
 import pytest
 
@@ -27,11 +28,14 @@ def _err(got, ref, floor):
     return float(np.abs(got.cpu().numpy().astype(np.float64) - ref).max() / rms)
 
 
-@pytest.mark.parametrize("gh,gw,cps", [(1, 64, 1), (1, 65, 1), (5, 77, 2), (19, 31, 3), (16, 40, 2), (1, 1023, 5)])
+@pytest.mark.parametrize("B,H,gh,gw,cps", [
+    (1, 3, 1, 64, 1), (1, 3, 1, 65, 1), (1, 3, 5, 77, 2), (1, 3, 19, 31, 3), (1, 3, 16, 40, 2), (1, 3, 1, 1023, 5),
+    # more than 256 work-groups, which the kernels of 4 waves walk: one wave for the row read and the outputs
+    (6, 16, 5, 77, 1), (6, 16, 5, 77, 2), (9, 16, 3, 43, 1), (65, 4, 1, 61, 1)])
 @pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
 @pytest.mark.parametrize("z_mean", [0.0, 3.0])
-def test_span_bounds(gh, gw, cps, dk, dv, z_mean):
-    B, H, T = 1, 3, gh * gw
+def test_span_bounds(B, H, gh, gw, cps, dk, dv, z_mean):
+    T = gh * gw
     gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, cps)
     d = gi.make_gate_inputs(B, H, T, dk, dv, "bf16", seed=T + dk, z_mean=z_mean)
     bits = gi.round_to_bf16_bits(np.random.Generator(np.random.PCG64(5)).standard_normal((B, H, T, dv), dtype=np.float32))
@@ -56,10 +60,14 @@ def test_span_bounds(gh, gw, cps, dk, dv, z_mean):
         assert _err(torch.from_numpy(routes[0]), routes[1], floor) <= 2e-3
         ref = og.gla_bwd_gates(d["q"], d["k"], d["v"], d["log_alpha"], d["log_beta"], w, gh, gw, scan)
         floors = (0, 0, 0, float(np.sqrt(np.mean(np.square(d["q"] * ref[0])))), float(np.sqrt(np.mean(np.square(d["v"] * ref[2])))))
+        routes = []
         for room in (gla.gla_bwd_gates_workspace_bytes(B, H, T, dk, dv), least_gates):
             ws = torch.empty(room, dtype=torch.uint8, device="cuda")
             got = gla.gla_bwd_gates(q, k, v, la, lb, dw, gh, gw, scan, workspace=ws)
             assert max(_err(g, r, f) for g, r, f in zip(got, ref, floors)) <= TOL
+            routes.append([g.cpu().numpy().astype(np.float64) for g in got[3:]])
+        for a, b, f in zip(*routes, floors[3:]):
+            assert _err(torch.from_numpy(a), b, f) <= 2e-3
 
 
 @pytest.mark.parametrize("zeros", [3, 9, 20])
