@@ -57,7 +57,9 @@
  *    whenever z > -20).  GLA_ENGINE_RECURRENT has no such limit.
  *  - fp16 MFMA engine (what GLA_ENGINE_AUTO takes for the plain forward pass, and for
  *    gla_fwd_fused without the output epilogue, on bf16 inputs with 17..64 key
- *    channels and more than four chunks): its operands
+ *    channels and more than four chunks, unless the last span of the launch plan would
+ *    be a single chunk of fewer than 64 tokens: such calls run on the bf16 hi/lo
+ *    kernels, see gla_engine): its operands
  *    cover a decay of at most 2^-11 per key channel over 32 consecutive scan steps
  *    (alpha above about 0.79 on average; sigmoid(z)^(1/16) with z > -3.7) and
  *    inputs whose largest |q|, |k| lie in [2^-8, 8] and |v| in [2^-8, 2^14].  This
@@ -71,7 +73,9 @@
  *    below 2^-40: what is left out is at most 2^-40 of what those earlier states
  *    hold.  The bound is relative to the earlier states, not to the sum so far
  *    (a thread whose sum is still exactly zero, e.g. behind a padded tail of
- *    all-zero k or v, does go on): sequences whose later spans are many orders
+ *    all-zero k or v, does go on: with the two-sided gate the 2^-40 then count from
+ *    behind the zeros, with one gate it stops after the group of up to 32 spans that
+ *    ended them): sequences whose later spans are many orders
  *    of magnitude smaller than the earlier ones lose the decayed remainder of
  *    the earlier ones.  GLA_CARRY_KERNEL has no cut-off.
  *
@@ -125,7 +129,10 @@ typedef enum {
 typedef enum {
     GLA_ENGINE_AUTO = 0,      /* bf16 inputs with dk % 4 == 0 and dv % 8 == 0 -> an MFMA engine (the fp16 one for the
                                  plain forward pass and for gla_fwd_fused without r_pre, with 17..64 key channels
-                                 and more than four chunks, else the bf16 hi/lo one), otherwise recurrent */
+                                 and more than four chunks, else the bf16 hi/lo one), otherwise recurrent.  A call
+                                 whose last span would be one chunk of fewer than 64 tokens (T % 64 != 0, and 64-token
+                                 chunks before it that the plan's chunks per span divide) runs on the bf16 hi/lo kernels
+                                 instead of the fp16 ones, in gla_fwd_static only if their plan fits its array */
     GLA_ENGINE_RECURRENT = 1, /* fp32 token-by-token arithmetic inside each span; any dtype, any gates */
     GLA_ENGINE_MFMA = 2,      /* bf16 hi/lo MFMA chunk form (Sec. 3.5) in every pass; bf16 inputs only */
     GLA_ENGINE_MFMA_FP16 = 3  /* fp16 operands in both passes of the plain forward call and of gla_fwd_fused without
@@ -277,7 +284,9 @@ size_t gla_bwd_workspace_bytes(int B, int H, int T, int dk, int dv, int qkv_dtyp
  *   out_fwd          DEVICE, fp32 [B,H,T,dv]: `out` of gla_fwd_gates on the same inputs, or NULL
  *                    (the outputs are then recomputed, one more pass over the sequence)          (read)
  *   dlog_beta        DEVICE, fp32 [B,H,T,dv]                                           (written)
- *   workspace        DEVICE, 16-byte aligned, at least gla_bwd_gates_workspace_bytes(...) bytes
+ *   workspace        DEVICE, 16-byte aligned, gla_bwd_gates_workspace_bytes(...) bytes.  (From fwd_workspace_bytes plus
+ *                    4 max(dk, dv) B H ceil(T / 256) bytes plus 4 dv B H T bytes, each rounded up to 256, on the call
+ *                    works as well; where what one walk leaves for the other then has no room it takes more kernels.)
  *
  * Everything else as gla_bwd.  Engines as gla_fwd_gates (MFMA chunk form for bf16 rows with
  * dk % 4 == 0, dv % 8 == 0, dk <= 40, dv <= 80; token by token in fp32 otherwise).  Never allocates.

@@ -233,8 +233,10 @@ bool place_walks(WalkParams &fwd, WalkParams &rev, void *workspace, size_t used,
     return true;
 }
 
-// Backward pass (see gla_bwd_kernels.hip for the formulas): three walks over the sequence on the span plan of
-// the forward pass, then the reverse cumulative sum for the gate gradient.
+// Backward pass (see gla_bwd_kernels.hip for the formulas), on the span plan of the forward pass.  MFMA engine: the state
+// pass of S, the walk for dq, which leaves what the reversed walk starts from, and the reversed walk for dk, dv and the
+// gate gradient.  Token by token, with GLA_OPT_BWD_SPLIT, or where the workspace has no room for what the first walk would
+// leave: the state pass of G as well, and the gate gradient's reverse cumulative sum behind the walks.
 int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha, const void *d_out,
             int B, int H, int T, int dk, int dv, int grid_h, int grid_w, int scan_dir, int qkv_dtype,
             float *dq, float *dk_grad, float *dv_grad, float *dlog_alpha,

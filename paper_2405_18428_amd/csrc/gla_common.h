@@ -63,7 +63,7 @@ struct Params {
     const float *ln_weight, *ln_bias;
     float ln_eps;
     // value-side gate (Eq. (gate_gla_2)): if log_beta is set ([B,H,T,dv] fp32, laid out like v), the state element
-    // (c, n) decays by alpha_t[c] * beta_t[n]; token-by-token engine only
+    // (c, n) decays by alpha_t[c] * beta_t[n]
     const float *log_beta;
     const void *z_beta;     // or (with z_gate) its pre-activation: log beta = logsigmoid(z_beta) * inv_tau, like v
     float *ws_lgam_b;       // [B*H, nspans, dv]  summed log_beta of each span (phase 1 -> phase 2)

@@ -1150,7 +1150,10 @@ bool mfma_engine_supports(const Params &p) {
 }
 
 // The output pass and the backward pass's row reads: two work-groups fit a compute unit's LDS up to 40 key channels
-// and 80 value columns, one with larger heads and with the two-sided gate's extra rows.  With both gates from
+// and 80 value columns, one with larger heads and with the two-sided gate's extra rows.  Up to 32 / 64 channels the output
+// pass with those rows would fit twice (79 KB) and the walks of the backward pass once (95 and 97 KB); planned for two, the
+// forward call of 12 sequences of 4096 steps takes 32.8 us instead of 35.3, of 6 sequences of 16384 50.7 instead of 49.5,
+// and a training step of these 124 instead of 111 and 198 instead of 166: one.  With both gates from
 // pre-activations the spans are cut for two all the same: that output pass has no 8-wave form, and the state pass, which
 // does fit twice, gains more than the output pass loses (16 sequences of 16384 steps at 36 / 72: 182 us against 193).
 int mfma_groups_per_cu(const Params &p) {

@@ -15,8 +15,9 @@
 // R = E * (P K~ + W S_0^T),  S += K~^T V then scaled.  P, K~ and S_0 are split into a bf16 "hi" part
 // and a bf16 "lo" remainder (three products where two split operands meet, two otherwise).
 //
-// One work-group of 4 waves walks the chunks of its span; wave i owns the 16 tokens 16i..16i+15 of a
-// chunk (all channels of R) and the state tiles of the value-column tiles i, i+4.  The state is kept
+// One work-group walks the chunks of its span.  With 4 waves, wave i owns the 16 tokens 16i..16i+15 of a
+// chunk (all channels of R) and the state tiles of the value-column tiles i, i+4; with 8, waves i and i+4
+// share those tokens and the state tiles go round over all of them (see the kernel).  The state is kept
 // transposed, S^T[n][c], in fp32 accumulators: a lane then holds four consecutive value columns of one
 // channel, which is (a) a 16-byte load from the [dk][dv] state the carry kernel left in the workspace,
 // (b) an 8-byte LDS write of the bf16 parts as the channel-major rows that the S_0 term reads as its A
@@ -74,6 +75,8 @@ struct RLayout {
     static constexpr int oLgB = oLg + (GS ? 64 * 4 : 0);                  // float[kDvp]
     static constexpr int kBytes = oLgB + (GS && BETA ? kDvp * 4 : 0);
     static_assert(kBytes % 16 == 0, "cleared in 16-byte pieces");
+    // (the span plan and the choice of waves count on it; 81,600 bytes of 81,920 for 5 x 5 with DV)
+    static_assert(BETA || NDK8 > 5 || kBytes <= 80 * 1024, "two groups per compute unit up to 40 / 80 channels");
 };
 
 template <int N>
@@ -335,7 +338,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(WalkParams
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): keeps later reads of acc from waiting on the row prefetch
 
     // ---- HBM pieces staged by this thread: the 16-byte pieces of log_alpha (8-byte pieces of k) of a chunk and the
-    // 16-byte pieces of v and w are numbered row by row; slot m of a thread is piece tid + 256 m, so that a wave's
+    // 16-byte pieces of v and w are numbered row by row; slot m of a thread is piece tid + NTHR m, so that a wave's
     // request covers neighbouring pieces of neighbouring rows.  Slots past the last piece repeat it (the load stays
     // in bounds; nothing is written to LDS for them) ----
     constexpr int kF = (kChunk * NDK8 * 2 + NTHR - 1) / NTHR;

@@ -602,8 +602,12 @@ hipError_t launch_row_read(const Params &p, const void *w, float *r, hipStream_t
 
 int recurrent_chunks_per_span(const Params &p, long long max_spans) {
     const int nchunks = (p.T + kChunk - 1) / kChunk;
-    // scan steps per round of a work-group, from the span-state pass's configuration (the other passes' differ by at
-    // most a factor of two where gates on both axes or a long value axis take more LDS)
+    // Scan steps per round of a work-group, from the span-state pass with one gate.  The output pass has as many, half
+    // with both gates up to 32 key channels.  The row reads of the backward pass have 256 up to 32 value columns (128 with
+    // both gates), 128 up to 64, else 64 (32 with both gates), and their columns are the key channels.  A backward call
+    // keeps the forward call's plan all the same, so with long rows it is planned on up to four (both gates: eight) times
+    // the steps that its rounds take: too few spans where sequences are few (8 sequences of 1024 steps at 64 / 128
+    // channels, MI355X: 372 us on the one span planned, 157 us on 8).
     const int round = p.dk <= 32 ? TokenCfg<4, 4, false, false, true>::kRound : TokenCfg<8, 8, false, false, true>::kRound;
     const int chunks = round / kChunk;                                 // chunks per round
     const long long groups = (long long)p.B * p.H * ((p.dv + kCols - 1) / kCols);
