@@ -52,6 +52,11 @@ struct Params {
                             //    skips the last span of every (batch, head) (nobody reads its U)
     int qkv_dtype, out_dtype;
     int accumulate;         // 1: the output pass adds its rows to what `out` (fp32) holds (sums over scan orders)
+    int span_shift;         // row reads of the MFMA engine: span sp is steps [sp * span_len - span_shift,
+                            //    (sp + 1) * span_len - span_shift) of the sequence (the reversed walk of the backward
+                            //    pass: its spans then begin where those of the forward walk end, the first is the short one).
+                            //    Here, where it takes no room (the next field is a pointer), rather than behind the others:
+                            //    a span's bounds are the first thing that its group works out
     // gate prologue (Eq. (gate_gla)): if z_gate is set, log_alpha is not read; the gate of a row is
     // logsigmoid(z) * inv_tau, z in the element type of q, k, v and laid out like log_alpha
     const void *z_gate;
@@ -81,9 +86,6 @@ static_assert(sizeof(Params) <= 264, "what only some kernels need belongs into a
 // at its start, and with these among them the 4-wave hi/lo forward pass took 0.16 us more a launch on MI355X (160 to 256
 // sequences of 256 tokens at 36 / 72 channels, 16.8 us, 16.7 without).
 struct WalkParams : Params {
-    int span_shift;         // span sp is steps [sp * span_len - span_shift, (sp + 1) * span_len - span_shift) of the
-                            //    sequence (the reversed walk: its spans then begin where those of the forward walk end,
-                            //    the first is the short one)
     // the state after every bound_len scan steps, which the walk for dq leaves in ws_bound ([B*H, bounds, dk, dv]) and
     // the reversed walk for dk, dv starts its gate gradients from; and what that walk needs to form them (dlog_alpha;
     // dlog_beta with the two-sided gate)
@@ -97,11 +99,11 @@ struct WalkParams : Params {
 };
 
 // first scan step of span sp, and the step after its last
-__host__ __device__ inline int span_begin(const WalkParams &p, int sp) {
+__host__ __device__ inline int span_begin(const Params &p, int sp) {
     const int s = sp * p.span_len - p.span_shift;
     return s > 0 ? s : 0;
 }
-__host__ __device__ inline int span_end(const WalkParams &p, int sp) {
+__host__ __device__ inline int span_end(const Params &p, int sp) {
     const int s = (sp + 1) * p.span_len - p.span_shift;
     return s < p.T ? s : p.T;
 }
