@@ -158,9 +158,56 @@ inline hipError_t allow_dynamic_lds(const void *kernel, int bytes, std::atomic<b
     return hipSuccess;
 }
 
-// HIP launches fewer than 2^32 threads along one dimension; where more work-groups than that are wanted of a wide kernel, a
-// narrower one takes them.
+// HIP launches fewer than 2^32 threads along one dimension.
 inline bool launch_fits(long long groups, int threads) { return groups * threads < (1LL << 32); }
+
+// The nb batch elements from b on, or (nb = 1) the nh heads from h on of one, as a call of its own (bf16 rows).
+inline void move_to_part(Params &p, int b, int nb, int h, int nh) {
+    const size_t seq = (size_t)b * p.H + h;
+    const size_t ek = (size_t)b * p.sb_k + (size_t)h * p.sh_k, ev = (size_t)b * p.sb_v + (size_t)h * p.sh_v;
+    auto shift = [](auto *&x, size_t bytes) {
+        if (x != nullptr) x = reinterpret_cast<std::remove_reference_t<decltype(x)>>(reinterpret_cast<uintptr_t>(x) + bytes);
+    };
+    const size_t row = 2, f32 = sizeof(float), ne = (size_t)p.dk * p.dv, spans = seq * p.nspans;
+    shift(p.q, ek * row); shift(p.k, ek * row); shift(p.z_gate, ek * row); shift(p.log_alpha, ek * f32);
+    shift(p.v, ev * row); shift(p.r_pre, ev * row); shift(p.z_beta, ev * row); shift(p.log_beta, ev * f32);
+    shift(p.out, ev * (p.out_dtype == GLA_DT_BF16 ? 2 : 4));
+    shift(p.final_state, seq * ne * f32); shift(p.initial_state, seq * ne * f32);
+    shift(p.ws_state, spans * ne * f32); shift(p.ws_lgam, spans * p.dk * f32); shift(p.ws_lgam_b, spans * p.dv * f32);
+    shift(p.ws_fail, (p.only_flagged ? seq * p.fail_spans : spans) * sizeof(int));
+    shift(p.ln_weight, (size_t)h * p.dv * f32); shift(p.ln_bias, (size_t)h * p.dv * f32);
+    p.B = nb;
+    p.H = nh;
+}
+inline void move_to_part(WalkParams &p, int b, int nb, int h, int nh) {
+    const size_t seq = (size_t)b * p.H + h, ne = (size_t)p.dk * p.dv, spans = seq * p.nspans;
+    const size_t ek = (size_t)b * p.sb_k + (size_t)h * p.sh_k, ev = (size_t)b * p.sb_v + (size_t)h * p.sh_v;
+    move_to_part(static_cast<Params &>(p), b, nb, h, nh);
+    auto shift = [](auto *&x, size_t elems) { if (x != nullptr) x += elems; };
+    shift(p.ws_bound, seq * p.bounds * ne);
+    shift(p.ws_gstate, spans * ne); shift(p.ws_glgam, spans * p.dk); shift(p.ws_glgam_b, spans * p.dv);
+    shift(p.fwd_dq, ek); shift(p.fwd_out, ev); shift(p.dlog_alpha, ek); shift(p.dlog_beta, ev);
+}
+
+// launch(part, b, h) for the whole call, or for parts of its sequences (from batch element b and head h on) where it would
+// be too many threads at once: `spans` work-groups of `threads` threads a sequence.
+template <typename P, typename F>
+hipError_t launch_in_parts(const P &p, int spans, int threads, F launch) {
+    const long long most = ((1LL << 32) - 1) / threads / (spans > 0 ? spans : 1);      // sequences of one launch
+    if ((long long)p.B * p.H <= most || most == 0) return launch(p, 0, 0);
+    const int nb = p.H <= most ? (int)(most / p.H) : 1, nh = p.H <= most ? p.H : (int)most;
+    for (int b = 0; b < p.B; b += nb) {
+        for (int h = 0; h < p.H; h += nh) {
+            P part = p;
+            move_to_part(part, b, p.B - b < nb ? p.B - b : nb, h, p.H - h < nh ? p.H - h : nh);
+            const hipError_t e = launch(part, b, h);
+            if (e != hipSuccess) return e;
+            if (p.H - h <= nh) break;         // (h + nh may be past the largest int)
+        }
+        if (p.B - b <= nb) break;
+    }
+    return hipSuccess;
+}
 
 // Launchers (defined in the .hip files); each enqueues on `stream` and returns
 // hipGetLastError().

@@ -1058,9 +1058,11 @@ hipError_t launch_waves(const Params &p, hipStream_t stream) {
         if (e != hipSuccess) return e;
     }
     const int spans = (MODE == kModeState && p.chain_in_output) ? p.nspans - 1 : p.nspans;
-    dim3 grid((unsigned)(p.B * p.H * spans)), block(NW * 64);
-    hipLaunchKernelGGL(kernel, grid, block, L::kBytes, stream, p);
-    return hipGetLastError();
+    return launch_in_parts(p, spans, NW * 64, [&](const Params &part, int, int) {
+        dim3 grid((unsigned)(part.B * part.H * spans)), block(NW * 64);
+        hipLaunchKernelGGL(kernel, grid, block, L::kBytes, stream, part);
+        return hipGetLastError();
+    });
 }
 
 template <int MODE, int NDK8, int NDV16, int DEPTH, bool FUSE, bool ACC, typename TOut, bool BETA>
@@ -1087,7 +1089,7 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     if constexpr (MODE == kModeOutput && !FUSE) {
         // (the range fallback's groups mostly return at once: fewer waves to start)
         const long long groups = (long long)p.B * p.H * p.nspans;
-        if (kGroupsPerCu < 2 ? launch_fits(groups, 512) : NDK8 <= 5 && !p.only_flagged && groups <= (NDK8 <= 4 ? 256 : 224))
+        if (kGroupsPerCu < 2 || (NDK8 <= 5 && !p.only_flagged && groups <= (NDK8 <= 4 ? 256 : 224)))
             return launch_waves<MODE, NDK8, NDV16, 8, 2, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
     }
     return launch_waves<MODE, NDK8, NDV16, NW, MINW, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);

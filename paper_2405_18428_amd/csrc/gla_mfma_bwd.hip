@@ -1061,20 +1061,20 @@ hipError_t launch_waves(const WalkParams &p, const void *w, float *r, hipStream_
         hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), L::kBytes, configured);
         if (e != hipSuccess) return e;
     }
-    dim3 grid((unsigned)(p.B * p.H * p.nspans)), block(NW * 64);
-    hipLaunchKernelGGL(kernel, grid, block, L::kBytes, stream, p, w, r);
-    return hipGetLastError();
+    return launch_in_parts(p, p.nspans, NW * 64, [&](const WalkParams &part, int b, int h) {
+        dim3 grid((unsigned)(part.B * part.H * p.nspans)), block(NW * 64);
+        const void *wp = static_cast<const char *>(w) + 2 * ((size_t)b * p.sb_v + (size_t)h * p.sh_v);
+        hipLaunchKernelGGL(kernel, grid, block, L::kBytes, stream, part, wp, r + (size_t)b * p.sb_k + (size_t)h * p.sh_k);
+        return hipGetLastError();
+    });
 }
 
 template <int NDK8, int NDV16, bool DV, bool BETA, bool GS>
 hipError_t launch_one(const WalkParams &p, const void *w, float *r, hipStream_t stream) {
     // 8 waves where a compute unit holds one group anyway: by its LDS, or because there are no more groups than units
     constexpr int kGroupsPerCu = (160 * 1024) / RLayout<NDK8, NDV16, DV, BETA, GS>::kBytes;
-    const long long groups = (long long)p.B * p.H * p.nspans;
     if constexpr (kGroupsPerCu >= 2) {
-        if (groups > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA, GS>(p, w, r, stream);
-    } else {
-        if (!launch_fits(groups, 512)) return launch_waves<NDK8, NDV16, 4, 1, DV, BETA, GS>(p, w, r, stream);
+        if ((long long)p.B * p.H * p.nspans > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA, GS>(p, w, r, stream);
     }
     return launch_waves<NDK8, NDV16, 8, 2, DV, BETA, GS>(p, w, r, stream);
 }

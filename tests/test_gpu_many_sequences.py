@@ -42,9 +42,23 @@ def test_token_by_token():
         assert float((got_fin[b:b + 1000] - fin).abs().max()) <= 1e-5 * float(fin.abs().max())
 
 
+@pytest.mark.parametrize("layout", [gla.LAYOUT_BHTD, gla.LAYOUT_BTHD])
+def test_large_heads_one_batch_element(layout):
+    """The same with all sequences in one batch element (heads are cut, not batch elements), an initial state, bf16 out."""
+    H, n, T, dk, dv = 1024, 8200, 1, 44, 8
+    q, k, v, la, _ = (t.transpose(1, 2).contiguous() if layout else t for t in _block(H, T, dk, dv, 2))
+    s0 = torch.randn(1, H, dk, dv, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    kw = dict(layout=layout, out_dtype=torch.bfloat16)
+    ref, fin = gla.gla_fwd_layout(q, k, v, la, 1, 1, 0, initial_state=s0, **kw)
+    many = [t.repeat(1, 1, n, 1) if layout else t.repeat(1, n, 1, 1) for t in (q, k, v, la)]
+    got, got_fin = gla.gla_fwd_layout(*many, 1, 1, 0, initial_state=s0.repeat(1, n, 1, 1), **kw)
+    _same(got.view(n, 1, H, T, dv) if not layout else got.view(n, 1, T, H, dv), ref, "out")
+    _same(got_fin.view(n, 1, H, dk, dv), fin, "state")
+
+
 def test_large_heads():
     """8.4 million sequences of one step at 44 / 8 channels, forward and backward: eight waves a work-group would be
-    4.3e9 threads.  The 4-wave kernels sum in the same order."""
+    4.3e9 threads, so there are two launches of each kernel."""
     n, H = 8200, 1024
     *x, dout = _block(H, 1, 44, 8, 1)
     refs = (*gla.gla_fwd_ex(*x, 1, 1), *gla.gla_bwd(*x, dout, 1, 1))
