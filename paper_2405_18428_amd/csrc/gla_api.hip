@@ -73,8 +73,27 @@ int validate(const void *q, const void *k, const void *v, const float *log_alpha
 // per-work-group prologue; short spans give the 256 compute units more
 // work-groups.  Two resident work-groups per compute unit is the sweet spot
 // measured on MI355X for the output pass.
-int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_cu = 2, bool fp16_engine = false) {
+int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_cu = 2, bool fp16_engine = false, bool hilo = false) {
     int cps = g_opt_chunks_per_span;
+    if (cps <= 0 && hilo) {
+        // bf16 hi/lo kernels with the rows in registers, forward calls: in units of the time one group alone on its compute
+        // unit takes for a chunk of both passes (3 us at 36 / 72 channels on MI355X), a span of c chunks costs 5.3 + 1.06 c
+        // with a unit to itself, 5.85 + 1.92 c where two groups share it (calls of 32 x 64, 64 x 16, 32 x 43 and 16 x 256
+        // chunks, one and two groups a unit: 40.4 / 38.6, 27.8 / 28.9, 33.4 / 34.0, 70.2 / 64.6 us), and what does not fit
+        // at once starts again.  Sequences of up to four chunks are one pass (256 sequences: 16.0 us, in two spans 23.2).
+        double best = 0.0;
+        for (int c = 1; c <= nchunks; ++c) {
+            const long long groups = (long long)bh * ((nchunks + c - 1) / c);
+            const long long rounds = (groups + 511) / 512;
+            const double cost = groups <= 256 ? 5.3 + 1.06 * c : (double)rounds * (4.0 + 1.92 * c) + 1.85;
+            if (cps <= 0 || cost < best - 1e-9) {
+                best = cost;
+                cps = c;
+            }
+            if (groups <= 128) break;     // longer spans only idle more compute units
+        }
+        if (nchunks <= 4) cps = nchunks;
+    }
     if (cps <= 0 && fp16_engine) {
         // fp16 engine: a work-group spends about three chunk periods on its prologue (span-state chain, pipeline
         // fill) whatever the span length, and a chunk period is about 0.62 as long when the group has its compute
@@ -152,20 +171,22 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     // most spans that surely fit the workspace (its arrays begin at multiples of 256 bytes)
     const size_t per_span = bh * ((size_t)p.dk * p.dv + p.dk + p.dv + 1) * sizeof(float);
     const size_t max_spans = ws_limit > 1024 ? (ws_limit - 1024) / per_span : 0;
+    // (the backward pass passes no use_fast; its walks have a plan of their own)
+    const bool hilo = use_mfma && use_fast != nullptr && hilo_kernels_cover(p);
     int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
                   ? recurrent_chunks_per_span(p, (long long)(max_spans < (size_t)nchunks ? max_spans : nchunks))
                   : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma,
-                                         fast ? fast_groups_per_cu(p) : (use_mfma ? mfma_groups_per_cu(p) : 2), fast);
+                                         fast ? fast_groups_per_cu(p) : (use_mfma ? mfma_groups_per_cu(p) : 2), fast, hilo && !fast);
     // A last span of one ragged chunk: some of the fp16 engine's lanes see no token in it, so it raises the flag of
     // every sequence, and each would be walked again by one work-group of the bf16 hi/lo kernel.  Those kernels then
     // take the whole call, on their own span plan (32 sequences of 2745 tokens at 36 / 72 channels: 160 us with the
     // fallback, 35 us).
     if (fast && g_opt_engine != GLA_ENGINE_MFMA_FP16 && p.T % kChunk != 0 && (nchunks - 1) % cps == 0) {
-        const int hilo = plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p));
-        if (plan_workspace_bytes(bh, (size_t)((nchunks + hilo - 1) / hilo), p.dk, p.dv) <= ws_limit) {
+        const int other = plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p), false, hilo);
+        if (plan_workspace_bytes(bh, (size_t)((nchunks + other - 1) / other), p.dk, p.dv) <= ws_limit) {
             fast = false;
             *use_fast = false;
-            cps = hilo;
+            cps = other;
         }
     }
     p.span_len = cps * kChunk;

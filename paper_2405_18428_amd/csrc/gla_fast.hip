@@ -60,14 +60,6 @@ __device__ inline f32x4 mfma_h32(u32x4 a, u32x4 b, f32x4 c) {
 __device__ inline f32x4 mfma_h16(u32x2 a, u32x2 b, f32x4 c) {
     return mfma_h32(u32x4{a[0], a[1], 0u, 0u}, u32x4{b[0], b[1], 0u, 0u}, c);
 }
-// inclusive prefix sum over the 16 lanes of a DPP row
-__device__ inline float row_scan16(float v) {
-    v += dpp_move<0x111, 0xF, true>(v);  // row_shr:1
-    v += dpp_move<0x112, 0xF, true>(v);  // row_shr:2
-    v += dpp_move<0x114, 0xF, true>(v);  // row_shr:4
-    v += dpp_move<0x118, 0xF, true>(v);  // row_shr:8
-    return v;
-}
 
 // Head-size classes.  NK32 = 32-channel MFMA steps, TAIL = one more 16-channel step, NCT = 16-channel units
 // (= row tiles of the state), NDV16 = 16-column tiles of the values.  Row strides (in 16-bit elements) are chosen so

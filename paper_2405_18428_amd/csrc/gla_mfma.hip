@@ -1107,37 +1107,29 @@ hipError_t launch_one(const Params &p, hipStream_t stream) {
     return launch_depth<MODE, NDK8, NDV16, 1, FUSE, ACC, TOut, BETA>(p, stream);
 }
 
-template <int MODE, int NDK8, int NDV16>
+// BETA: two-sided gate.  (One-sided calls of up to 36 key channels and 80 value columns run on the kernels in gla_hilo.hip.)
+template <int MODE, int NDK8, int NDV16, bool BETA>
 hipError_t launch_dt(const Params &p, hipStream_t stream) {
-    if (p.z_gate != nullptr && p.z_beta != nullptr) {   // both gates from pre-activations (+ optional epilogue)
-        if (MODE == kModeOutput && p.out_dtype == GLA_DT_BF16)
-            return launch_one<MODE, NDK8, NDV16, true, false, uint16_t, true>(p, stream);
-        return launch_one<MODE, NDK8, NDV16, true, false, float, true>(p, stream);
-    }
-    if (p.log_beta != nullptr) {   // two-sided gate from its logarithms (the host keeps it apart from the accumulation)
-        if (MODE == kModeOutput && p.out_dtype == GLA_DT_BF16)
-            return launch_one<MODE, NDK8, NDV16, false, false, uint16_t, true>(p, stream);
-        return launch_one<MODE, NDK8, NDV16, false, false, float, true>(p, stream);
-    }
-    if (p.z_gate != nullptr) {
-        if (MODE == kModeOutput && p.out_dtype == GLA_DT_BF16)
-            return launch_one<MODE, NDK8, NDV16, true, false, uint16_t>(p, stream);
-        return launch_one<MODE, NDK8, NDV16, true, false, float>(p, stream);
-    }
-    if constexpr (MODE == kModeOutput) {
+    const bool bf16_out = MODE == kModeOutput && p.out_dtype == GLA_DT_BF16;
+    if (p.z_gate != nullptr)        // gates from pre-activations (+ optional epilogue)
+        return bf16_out ? launch_one<MODE, NDK8, NDV16, true, false, uint16_t, BETA>(p, stream)
+                        : launch_one<MODE, NDK8, NDV16, true, false, float, BETA>(p, stream);
+    if constexpr (MODE == kModeOutput && !BETA) {    // (the host keeps the two-sided gate apart from the accumulation)
         if (p.accumulate) return launch_one<MODE, NDK8, NDV16, false, true, float>(p, stream);   // host checks fp32 out
     }
-    if (MODE == kModeOutput && p.out_dtype == GLA_DT_BF16)
-        return launch_one<MODE, NDK8, NDV16, false, false, uint16_t>(p, stream);
-    return launch_one<MODE, NDK8, NDV16, false, false, float>(p, stream);
+    return bf16_out ? launch_one<MODE, NDK8, NDV16, false, false, uint16_t, BETA>(p, stream)
+                    : launch_one<MODE, NDK8, NDV16, false, false, float, BETA>(p, stream);
 }
 
 template <int MODE>
 hipError_t launch_mode(const Params &p, hipStream_t stream) {
     const int ndk8 = (p.dk + 7) / 8, ndv16 = (p.dv + 15) / 16;
-    if (ndk8 <= 4 && ndv16 <= 4) return launch_dt<MODE, 4, 4>(p, stream);
-    if (ndk8 <= 5 && ndv16 <= 5) return launch_dt<MODE, 5, 5>(p, stream);
-    return launch_dt<MODE, 8, 8>(p, stream);
+    if (two_sided(p)) {
+        if (ndk8 <= 4 && ndv16 <= 4) return launch_dt<MODE, 4, 4, true>(p, stream);
+        return launch_dt<MODE, 5, 5, true>(p, stream);     // (mfma_engine_supports: no larger ones)
+    }
+    if (ndk8 <= 5 && ndv16 <= 5) return launch_dt<MODE, 5, 5, false>(p, stream);
+    return launch_dt<MODE, 8, 8, false>(p, stream);
 }
 
 }  // namespace
@@ -1164,6 +1156,7 @@ int mfma_groups_per_cu(const Params &p) {
 }
 
 hipError_t launch_mfma_span(const Params &p, SpanMode mode, hipStream_t stream) {
+    if (hilo_kernels_cover(p)) return launch_hilo_span(p, mode, stream);
     return mode == kModeState ? launch_mode<kModeState>(p, stream) : launch_mode<kModeOutput>(p, stream);
 }
 

@@ -145,6 +145,15 @@ __device__ inline void row_scan16x4(float &a, float &b, float &c, float &d) {
         : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
 }
 
+// inclusive prefix sum over the 16 lanes of a DPP row
+__device__ inline float row_scan16(float v) {
+    v += dpp_move<0x111, 0xF, true>(v);  // row_shr:1
+    v += dpp_move<0x112, 0xF, true>(v);  // row_shr:2
+    v += dpp_move<0x114, 0xF, true>(v);  // row_shr:4
+    v += dpp_move<0x118, 0xF, true>(v);  // row_shr:8
+    return v;
+}
+
 // State entering span `sp` of (batch, head) `bh`, formed from the local states U_r and the log decays of the
 // spans before it (phase 2 of the span plan, done by the work-group that needs the result):
 //     S_start(sp) = U_{sp-1} + Gamma_{sp-1} U_{sp-2} + Gamma_{sp-1} Gamma_{sp-2} U_{sp-3} + ... (+ the decayed initial state)
@@ -157,7 +166,7 @@ __device__ inline void row_scan16x4(float &a, float &b, float &c, float &d) {
 // The result is written to s_chain[dk * dv] (LDS, row-major [dk][dv]).
 // BETA (two-sided gate): element (c, n) also decays by the value-side sums of the spans (ws_lgam_b, per column n);
 // the stopping rule stays the key-side one (the value side only makes the skipped terms smaller).
-template <int NTHR, int kV4, int kRun, bool BETA = false>
+template <int NTHR, int kV4, int kRun, bool BETA = false, bool REF = BETA>
 __device__ inline void chain_span_states(const Params &p, int bh, int sp, int tid, float *s_chain) {
     const int dk = p.dk, dv = p.dv, ne = dk * dv, ne4 = ne >> 2;
     const float *ub = p.ws_state + (size_t)bh * p.nspans * ne;
@@ -173,15 +182,13 @@ __device__ inline void chain_span_states(const Params &p, int bh, int sp, int ti
     f32x4 st[kV4];
     float wl[kV4];      // log2 of the weight of the next span to add
     f32x4 wb[BETA ? kV4 : 1];   // BETA: its value-side part per column
-    float ref[BETA ? kV4 : 1];  // BETA: wl behind the nearest spans that were all zero
+    float ref[REF ? kV4 : 1];   // REF: wl behind the nearest spans that were all zero
 #pragma unroll
     for (int m = 0; m < kV4; ++m) {
         st[m] = f32x4{0.f, 0.f, 0.f, 0.f};
         wl[m] = 0.f;
-        if constexpr (BETA) {
-            wb[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-            ref[m] = 0.f;
-        }
+        if constexpr (BETA) wb[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (REF) ref[m] = 0.f;
     }
     auto run = [&](auto n_c, int r_hi) {   // spans r_hi, r_hi - 1, ..., r_hi - n + 1 (those below 0 do not exist)
         constexpr int N = decltype(n_c)::value;
@@ -215,7 +222,7 @@ __device__ inline void chain_span_states(const Params &p, int bh, int sp, int ti
                         for (int x = 0; x < 4; ++x) st[m][x] = fmaf(wgt, u[i][m][x], st[m][x]);
                     }
                     wl[m] += lg[i][m] * kLog2e;    // the workspace keeps natural logarithms
-                    if constexpr (BETA) {
+                    if constexpr (REF) {
                         const bool zero = st[m][0] == 0.f && st[m][1] == 0.f && st[m][2] == 0.f && st[m][3] == 0.f;
                         ref[m] = zero ? wl[m] : ref[m];
                     }
@@ -225,13 +232,13 @@ __device__ inline void chain_span_states(const Params &p, int bh, int sp, int ti
     };
     // a piece goes on while its accumulated decay is above 2^-40, and also while everything it has summed is
     // exactly zero (all-zero k or v over the nearer spans, e.g. a padded tail: then even a strongly decayed
-    // earlier state is the whole result).  BETA, whose runs are shorter (registers): 2^-40 counts from there, so that the
-    // spans behind the zeros are added up whatever the length of a run
+    // earlier state is the whole result).  REF, for kernels whose runs are shorter (registers): 2^-40 counts from there,
+    // so that the spans behind the zeros are added up whatever the length of a run
     auto alive = [&]() {
         bool a = false;
 #pragma unroll
         for (int m = 0; m < kV4; ++m)
-            if constexpr (BETA) a = a || wl[m] > ref[m] - 40.f;
+            if constexpr (REF) a = a || wl[m] > ref[m] - 40.f;
             else a = a || wl[m] > -40.f || (st[m][0] == 0.f && st[m][1] == 0.f && st[m][2] == 0.f && st[m][3] == 0.f);
         return a;
     };
@@ -260,6 +267,26 @@ __device__ inline void chain_span_states(const Params &p, int bh, int sp, int ti
     for (int m = 0; m < kV4; ++m)
         if (tid + NTHR * m < ne4) *reinterpret_cast<f32x4 *>(s_chain + 4 * e4[m]) = st[m];
 }
+
+// Buffer accesses: 32-bit offsets into the view of one (batch, head); an offset past its end loads zero and stores nothing,
+// so that rows past a span's end, channels past dk and columns past dv need neither masks nor branches (and the number of
+// accesses in flight is a constant, which the waits count on).  A view is smaller than 2^31 bytes (2^30 of bf16).
+constexpr uint32_t kNowhere = 0x80000000u;        // such an offset; half of it in units of bf16 rows
+using Rsrc = __amdgpu_buffer_rsrc_t;
+__device__ inline Rsrc view(const void *base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00027000);
+}
+template <typename V>
+__device__ inline V fetch(Rsrc r, uint32_t at) {
+    if constexpr (sizeof(V) == 16) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, 0, 0));
+    else if constexpr (sizeof(V) == 8) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, (int)at, 0, 0));
+    else if constexpr (sizeof(V) == 4) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, (int)at, 0, 0));
+    else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b16(r, (int)at, 0, 0));
+}
+__device__ inline void put(Rsrc r, uint32_t at, f32x4 x) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), r, (int)at, 0, 0);
+}
+__device__ inline void put(Rsrc r, uint32_t at, u32x2 x) { __builtin_amdgcn_raw_buffer_store_b64(x, r, (int)at, 0, 0); }
 
 }  // namespace
 }  // namespace gla

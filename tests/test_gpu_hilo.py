@@ -1,0 +1,50 @@
+"""The bf16 hi/lo kernels that keep a chunk's rows in registers, at the edges of what they cover: numbers of key channels
+around the 16-channel units and the tail, value columns around the 16-column tiles, chunks that are one token long or one
+short, one span and several, both memory orders, an initial state.
+
+Tolerance: the split operands carry 16 bits, so a product is off by at most 4 * 2^-17 of itself and an output, whose largest
+value is about six times its RMS, by 2e-4 of the RMS; a bf16 store adds at most half a unit of its eighth bit, 2^-8 of the largest value."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2405_18428_amd as gla
+from paper_2405_18428_amd import inputs as gi
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-4
+
+
+@pytest.fixture(autouse=True)
+def defaults():
+    gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_MFMA)
+    yield
+    gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
+    gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, 0)
+
+
+def upload(d, name):
+    return torch.from_numpy(d[name + "_bits"].view(np.int16)).cuda().view(torch.bfloat16)
+
+
+@pytest.mark.parametrize("dk,dv", [(4, 8), (16, 64), (20, 24), (32, 64), (28, 72), (36, 8), (36, 72), (36, 80)])
+@pytest.mark.parametrize("gh,gw", [(1, 1), (7, 9), (8, 8), (5, 13), (16, 16), (17, 19), (9, 50)])
+def test_edges(dk, dv, gh, gw):
+    from oracle import gla_oracle
+    B, H, T = 2, 3, gh * gw
+    d = gi.make_inputs(B, H, T, dk, dv, "bf16", seed=dk + dv)
+    s0 = np.random.default_rng(5).standard_normal((B, H, dk, dv)).astype(np.float32)
+    for cps, scan, layout, out_dtype in ((0, 0, 0, torch.float32), (1, 3, 1, torch.float32), (2, 2, 0, torch.bfloat16),
+                                         (3, 1, 1, torch.float32)):
+        gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, cps)
+        ref, ref_fin = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, scan, initial_state=s0)
+        t = [upload(d, n) for n in ("q", "k", "v")] + [torch.from_numpy(d["log_alpha"]).cuda()]
+        if layout == 1:
+            t = [x.transpose(1, 2).contiguous() for x in t]
+        out, fin = gla.gla_fwd_layout(*t, gh, gw, scan, layout=layout, initial_state=torch.from_numpy(s0).cuda(),
+                                      out_dtype=out_dtype)
+        got = out.float().cpu().numpy() if layout == 0 else out.float().transpose(1, 2).cpu().numpy()
+        rms = np.sqrt(np.mean(ref ** 2))
+        tol = TOL * max(1.0, np.abs(ref).max() / rms / 6) + (2.0 ** -8 * np.abs(ref).max() / rms if out_dtype == torch.bfloat16 else 0.0)
+        assert np.abs(got - ref).max() / rms <= tol, (cps, scan, layout)
+        assert np.abs(fin.cpu().numpy() - ref_fin).max() / np.sqrt(np.mean(ref_fin ** 2)) <= TOL, (cps, scan, layout)
