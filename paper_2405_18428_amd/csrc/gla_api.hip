@@ -173,10 +173,17 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     const size_t max_spans = ws_limit > 1024 ? (ws_limit - 1024) / per_span : 0;
     // (the backward pass passes no use_fast; its walks have a plan of their own)
     const bool hilo = use_mfma && use_fast != nullptr && hilo_kernels_cover(p);
+    // Backward pass: spans for one group a compute unit where that is what the plan comes to (and the sums over a span, whose
+    // error grows with its square root, get no longer than twice what they would be with two groups; launch_mfma_row_read)
+    int bwd_groups = mfma_groups_per_cu(p);
+    if (use_fast == nullptr && use_mfma && hilo_kernels_cover(p) && bwd_groups > 1) {
+        const int one = plan_chunks_per_span(p.B * p.H, nchunks, true, 1), two = plan_chunks_per_span(p.B * p.H, nchunks, true, bwd_groups);
+        if ((long long)p.B * p.H * ((nchunks + one - 1) / one) <= 256 && one <= 2 * two) bwd_groups = 1;
+    }
     int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
                   ? recurrent_chunks_per_span(p, (long long)(max_spans < (size_t)nchunks ? max_spans : nchunks))
                   : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma,
-                                         fast ? fast_groups_per_cu(p) : (use_mfma ? mfma_groups_per_cu(p) : 2), fast, hilo && !fast);
+                                         fast ? fast_groups_per_cu(p) : (use_mfma ? bwd_groups : 2), fast, hilo && !fast);
     // A last span of one ragged chunk: some of the fp16 engine's lanes see no token in it, so it raises the flag of
     // every sequence, and each would be walked again by one work-group of the bf16 hi/lo kernel.  Those kernels then
     // take the whole call, on their own span plan (32 sequences of 2745 tokens at 36 / 72 channels: 160 us with the

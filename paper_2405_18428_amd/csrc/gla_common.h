@@ -220,6 +220,7 @@ bool mfma_engine_supports(const Params &p);
 // the kernels of the bf16 hi/lo engine that hold a chunk's rows in registers (gla_hilo.hip; the others: gla_mfma.hip)
 bool hilo_kernels_cover(const Params &p);
 hipError_t launch_hilo_span(const Params &p, SpanMode mode, hipStream_t stream);
+hipError_t launch_hilo_walk(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs);  // (gla_hilo_bwd.hip)
 // fp16 output pass with the pipelined chunk loop (gla_fast.hip): what it covers, how many of its work-groups a
 // compute unit holds, and its launcher
 bool fast_engine_supports(const Params &p);

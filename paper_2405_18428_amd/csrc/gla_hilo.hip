@@ -24,6 +24,10 @@
 // vector instructions of the gating stand between the matrix instructions of the contraction (both are chains of dependent
 // instructions, and a SIMD holds two waves: 76 KB a group, two groups a compute unit).
 //
+// LDS rows are 160 bytes (40 banks) long, and the 16-byte units of rows 8 .. 15 of every 16 change places in pairs: the
+// reads of 16 rows (8- and 16-byte pieces, transposing or not) then fall into different banks.  (With rows an odd number of
+// 16-byte units long the transposing reads of 8 rows overlapped in twos.)
+//
 // What bounds it on MI355X: up to 1024 px the instruction streams (one group alone on a compute unit: 5300 clocks a chunk at
 // 36 / 72 channels, 6500 when two share it), at 2048 px the memory (output pass 195 MB in 30 us once the pipeline is filled).
 // Before, with the rows staged through LDS, three barriers a chunk and single sets (output pass / state pass of 2048 chunks
@@ -43,10 +47,10 @@ using int_c = std::integral_constant<int, N>;
 
 template <bool OUT, int DT, int NDV16, bool FUSE>
 struct HLayout {
+    static_assert(64 + 16 * DT <= 80 && 16 * NDV16 <= 80, "rows of 160 bytes");
     static constexpr int NV = 8 + DT;                         // gate values per lane and chunk
     static constexpr int kTotStride = DT == 0 ? 8 : 12;       // floats per (tile, g) of the tile totals
-    static constexpr int kRow = 64 + 16 * DT + 8;             // bf16 per row of k~ and P: an odd number of 16-byte units
-    static constexpr int kVRow = 16 * NDV16 + 8;              // bf16 per row of v: likewise
+    static constexpr int kRow = 80, kVRow = 80;               // bf16 per row of k~ and P, of v (see swz)
     static constexpr int kTotBuf = 4 * 4 * kTotStride;        // floats per chunk: [tile][g][NV]
     static constexpr int oTot = 0;                            // three chunks
     static constexpr int oLn = oTot + 3 * kTotBuf * 4;        // float[2][16 NDV16]: LayerNorm weight, bias (FUSE)
@@ -68,8 +72,7 @@ struct Owned {
     static constexpr int NCT = 2 + DT, kTiles = NCT * NDV16;
     __host__ __device__ static constexpr int start(int w) {
         if (!OUT) return kTiles * w / 4;
-        // (15 tiles: 6, 5, 2, 2; 8 tiles: 3, 3, 1, 1)
-        return w == 0 ? 0 : (w == 1 ? (kTiles * 2 + 2) / 5 : (w == 2 ? (kTiles * 3 + 3) / 4 - (DT == 0 ? 0 : 1) : (w == 3 ? kTiles - (kTiles + 7) / 12 : kTiles)));
+        return w == 0 ? 0 : (w == 1 ? kTiles * 2 / 5 : (w == 2 ? kTiles * 3 / 4 : (w == 3 ? kTiles - 1 : kTiles)));   // (15: 6, 5, 3, 1)
     }
     __host__ __device__ static constexpr int count(int w) { return start(w + 1) - start(w); }
     static constexpr int kMost = OUT ? count(0) : (kTiles + 3) / 4;
@@ -104,6 +107,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15;
     const int g = lane >> 4;
+    const int swz = 8 * (lm >> 3);            // of the rows 16 i + lm
 
     // contiguous ranges of spans per XCD; odd heads walk their spans backwards where the span states are chained here
     // (a long and a short chain then share a compute unit)
@@ -193,11 +197,10 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
     auto issue_la = [&](GateRow &dst, int step, int tk) {
         if constexpr (SHIFT) tk = scan_token(p.scan_dir, max(min(step, s_end - 1) - 1, 0), T, p.grid_h, p.grid_w);
         const uint32_t row = step < s_end ? (uint32_t)tk * dk2 : kNowhere / 2;
-        constexpr uint32_t E = FUSE ? 1u : 2u;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) dst.u[u] = fetch<GatePiece>(bg, E * (row + chb[u]));
+        for (int u = 0; u < 2; ++u) dst.u[u] = fetch<GatePiece>(bg, FUSE ? row + chb[u] : f32_at(row, chb[u]));
 #pragma unroll
-        for (int e = 0; e < DT; ++e) dst.t[e] = fetch<GateTail>(bg, E * (row + tcb[e]));
+        for (int e = 0; e < DT; ++e) dst.t[e] = fetch<GateTail>(bg, FUSE ? row + tcb[e] : f32_at(row, tcb[e]));
     };
     auto issue_qkv = [&](int step, int tk) {
         const uint32_t row = step < s_end ? (uint32_t)tk * dk2 : kNowhere / 2;
@@ -315,14 +318,14 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
                 }
             }
         }
-        *reinterpret_cast<u32x4 *>(krow + 8 * g) = kh;
-        *reinterpret_cast<u32x4 *>(krow + 32 + 8 * g) = kl;
+        *reinterpret_cast<u32x4 *>(krow + (8 * g ^ swz)) = kh;
+        *reinterpret_cast<u32x4 *>(krow + 32 + (8 * g ^ swz)) = kl;
 #pragma unroll
         for (int e = 0; e < DT; ++e) {
             const float kx = bf16_lo_as_float(r_k.t[e]) * ek[8 + e];
             const uint32_t hh = pack_bf16(kx, kx);
             const float rem = kx - bf16_lo_as_float(hh);
-            *reinterpret_cast<u32x2 *>(krow + 64 + 16 * e + 4 * g) = u32x2{hh, pack_bf16(rem, rem)};
+            *reinterpret_cast<u32x2 *>(krow + 64 + 16 * e + (4 * g ^ swz)) = u32x2{hh, pack_bf16(rem, rem)};
             if constexpr (OUT) {
                 const float qx = bf16_lo_as_float(r_q.t[e]) * eq[8 + e];
                 const uint32_t qh = pack_bf16(qx, qx);
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
         }
         uint16_t *vrow = s_v + (x & 1) * SET + (16 * W + lm) * VS;
 #pragma unroll
-        for (int i = 0; i < NVP; ++i) *reinterpret_cast<u32x4 *>(vrow + min(8 * (g + 4 * i), 16 * NDV16 - 8)) = r_v[i];
+        for (int i = 0; i < NVP; ++i) *reinterpret_cast<u32x4 *>(vrow + (min(8 * (g + 4 * i), 16 * NDV16 - 8) ^ swz)) = r_v[i];
     };
 
     // ---- state tiles owned by this wave: acc[i][r] of a main tile ct = 0, 1 is S[channel 16 (g & 1) + 4 (2 ct + g / 2) + r]
@@ -384,8 +387,8 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
                     u32x2 hi, lo;
                     SPLIT_PAIR(acc[i][0], acc[i][1], hi[0], lo[0]);
                     SPLIT_PAIR(acc[i][2], acc[i][3], hi[1], lo[1]);
-                    *reinterpret_cast<u32x2 *>(prow + 16 * ct + 4 * g) = hi;
-                    *reinterpret_cast<u32x2 *>(prow + 32 + 16 * ct + 4 * g) = lo;
+                    *reinterpret_cast<u32x2 *>(prow + 16 * ct + (4 * g ^ swz)) = hi;
+                    *reinterpret_cast<u32x2 *>(prow + 32 + 16 * ct + (4 * g ^ swz)) = lo;
                 }
             } else {
                 const int e = ct >= 2 ? ct - 2 : 0;
@@ -394,7 +397,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
                 if constexpr (OUT) {
                     const uint32_t hh = pack_bf16(s, s);
                     const float rem = s - bf16_lo_as_float(hh);
-                    *reinterpret_cast<u32x2 *>(prow + 64 + 16 * e + 4 * g) = u32x2{hh, pack_bf16(rem, rem)};
+                    *reinterpret_cast<u32x2 *>(prow + 64 + 16 * e + (4 * g ^ swz)) = u32x2{hh, pack_bf16(rem, rem)};
                 }
             }
         }
@@ -487,7 +490,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
 
     // Iteration c: contraction of chunk c from one set, gating of chunk c + 1 into the other, scan of chunk c + 2.  (Past the
     // span's end rows are nothing: what is gated and scanned there is not read.)
-    const int tr_row = lm >> 2, tr_col = 4 * (lm & 3);   // transposing reads: token-in-4 and column quad of this lane
+    const int tr_row = lm >> 2, tr_col = (4 * (lm & 3)) ^ (8 * (g >> 1));   // transposing reads: token-in-4 and column quad of this lane
     for (int c = 0; c < nch; ++c) {
         auto step = [&](auto wave_c, int) {
             constexpr int W = decltype(wave_c)::value;
@@ -499,6 +502,16 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
                 const u32x2 lo = lds_read_tr(vtr + 32 * q32 * VS + 16 * x);
                 const u32x2 hi = lds_read_tr(vtr + (32 * q32 + 16) * VS + 16 * x);
                 return u32x4{lo[0], lo[1], hi[0], hi[1]};
+            };
+            auto tail_frag = [&](const uint16_t *at) {
+                u32x4 t = u32x4{0, 0, 0, 0};
+#pragma unroll
+                for (int e = 0; e < DT; ++e) {
+                    const u32x2 y = *reinterpret_cast<const u32x2 *>(at + 16 * e);
+                    t[2 * e] = y[0];
+                    t[2 * e + 1] = y[1];
+                }
+                return t;
             };
             auto k_frag = [&](int q32, int col) {
                 const u32x2 lo = lds_read_tr(ktr + 32 * q32 * RS + col);
@@ -557,69 +570,67 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
                     for (int x = 0; x < NX; ++x)
                         prev[x] = fetch<f32x4>(bo, OE * ocol(x));
                 }
+                // (The products of several tiles go round: each tile's are a chain of dependent instructions.)
                 // ---- score tiles, transposed: lane (lm, g) gets A[i = 16 W + lm][j = 16 jt + 4 g + r] ----
                 u32x4 pah[NQ], pal[NQ];                       // A^T hi, lo: B operand of O^T += V^T A^T
-                auto score = [&](int jt) {
-                    const uint16_t *krow = s_k + (c & 1) * SET + (16 * jt + lm) * RS;
-                    const u32x4 kh = *reinterpret_cast<const u32x4 *>(krow + 8 * g);
-                    const u32x4 kl = *reinterpret_cast<const u32x4 *>(krow + 32 + 8 * g);
-                    f32x4 d = f32x4{0.f, 0.f, 0.f, 0.f};
-                    d = mfma(kh, qf.h, d);
-                    d = mfma(kh, qf.l, d);
-                    d = mfma(kl, qf.h, d);
-                    d = mfma(kl, qf.l, d);
-                    if constexpr (DT > 0) {
-                        u32x4 kt = u32x4{0, 0, 0, 0};
+                {
+                    u32x4 kh[W + 1], kl[W + 1], kt[W + 1];
+                    f32x4 d[W + 1];
 #pragma unroll
-                        for (int e = 0; e < DT; ++e) {
-                            const u32x2 x = *reinterpret_cast<const u32x2 *>(krow + 64 + 16 * e + 4 * g);
-                            kt[2 * e] = x[0];
-                            kt[2 * e + 1] = x[1];
-                        }
-                        d = mfma(kt, qf.t, d);
+                    for (int jt = 0; jt <= W; ++jt) {
+                        const uint16_t *krow = s_k + (c & 1) * SET + (16 * jt + lm) * RS;
+                        kh[jt] = *reinterpret_cast<const u32x4 *>(krow + (8 * g ^ swz));
+                        kl[jt] = *reinterpret_cast<const u32x4 *>(krow + 32 + (8 * g ^ swz));
+                        kt[jt] = tail_frag(krow + 64 + (4 * g ^ swz));
+                        d[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
                     }
-                    if (jt == W)      // causal mask of the diagonal tile
-                        d = f32x4{4 * g + 0 > lm ? 0.f : d[0], 4 * g + 1 > lm ? 0.f : d[1], 4 * g + 2 > lm ? 0.f : d[2],
-                                  4 * g + 3 > lm ? 0.f : d[3]};
-                    const int h = 2 * (jt & 1);
-                    SPLIT_PAIR(d[0], d[1], pah[jt / 2][h], pal[jt / 2][h]);
-                    SPLIT_PAIR(d[2], d[3], pah[jt / 2][h + 1], pal[jt / 2][h + 1]);
-                };
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) pah[q] = pal[q] = u32x4{0, 0, 0, 0};
+                    for (int m = 0; m < 4 + (DT > 0 ? 1 : 0); ++m)
 #pragma unroll
-                for (int jt = 0; jt <= W; ++jt) score(jt);
+                        for (int jt = 0; jt <= W; ++jt)
+                            d[jt] = mfma(m == 4 ? kt[jt] : (m < 2 ? kh[jt] : kl[jt]), m == 4 ? qf.t : ((m & 1) ? qf.l : qf.h), d[jt]);
+                    // causal mask of the diagonal tile
+                    d[W] = f32x4{4 * g + 0 > lm ? 0.f : d[W][0], 4 * g + 1 > lm ? 0.f : d[W][1], 4 * g + 2 > lm ? 0.f : d[W][2],
+                                 4 * g + 3 > lm ? 0.f : d[W][3]};
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) pah[q] = pal[q] = u32x4{0, 0, 0, 0};
+#pragma unroll
+                    for (int jt = 0; jt <= W; ++jt) {
+                        const int h = 2 * (jt & 1);
+                        SPLIT_PAIR(d[jt][0], d[jt][1], pah[jt / 2][h], pal[jt / 2][h]);
+                        SPLIT_PAIR(d[jt][2], d[jt][3], pah[jt / 2][h + 1], pal[jt / 2][h + 1]);
+                    }
+                }
                 // ---- O^T = P^T Q~^T + V^T A^T: lane (lm, g) accumulates O[i = 16 W + lm][n = 16 x + 4 g + r] ----
+                constexpr int GX = (NX + 1) / 2;
 #pragma unroll
-                for (int x = 0; x < NX; ++x) {
-                    const uint16_t *prow = s_p + (c & 1) * SET + (16 * x + lm) * RS;
-                    const u32x4 ph = *reinterpret_cast<const u32x4 *>(prow + 8 * g);
-                    const u32x4 pl = *reinterpret_cast<const u32x4 *>(prow + 32 + 8 * g);
-                    f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
-                    a = mfma(ph, qf.h, a);
-                    a = mfma(ph, qf.l, a);
-                    a = mfma(pl, qf.h, a);
-                    a = mfma(pl, qf.l, a);
-                    if constexpr (DT > 0) {
-                        u32x4 pt = u32x4{0, 0, 0, 0};
+                for (int x0 = 0; x0 < NX; x0 += GX) {
+                    u32x4 ph[GX], pl[GX], pt[GX];
 #pragma unroll
-                        for (int e = 0; e < DT; ++e) {
-                            const u32x2 y = *reinterpret_cast<const u32x2 *>(prow + 64 + 16 * e + 4 * g);
-                            pt[2 * e] = y[0];
-                            pt[2 * e + 1] = y[1];
-                        }
-                        a = mfma(pt, qf.t, a);
+                    for (int i = 0; i < GX; ++i) {
+                        const uint16_t *prow = s_p + (c & 1) * SET + (16 * min(x0 + i, NX - 1) + lm) * RS;
+                        ph[i] = *reinterpret_cast<const u32x4 *>(prow + (8 * g ^ swz));
+                        pl[i] = *reinterpret_cast<const u32x4 *>(prow + 32 + (8 * g ^ swz));
+                        pt[i] = tail_frag(prow + 64 + (4 * g ^ swz));
                     }
-                    o[x] = a;
+#pragma unroll
+                    for (int m = 0; m < 4 + (DT > 0 ? 1 : 0); ++m)
+#pragma unroll
+                        for (int i = 0; i < GX; ++i)
+                            if (x0 + i < NX)
+                                o[x0 + i] = mfma(m == 4 ? pt[i] : (m < 2 ? ph[i] : pl[i]), m == 4 ? qf.t : ((m & 1) ? qf.l : qf.h),
+                                                 m == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : o[x0 + i]);
                 }
 #pragma unroll
-                for (int q = 0; q < NQ; ++q)
+                for (int q = 0; q < NQ; ++q) {
+                    u32x4 vf[NX];
 #pragma unroll
-                    for (int x = 0; x < NX; ++x) {
-                        const u32x4 vf = v_frag(q, x);
-                        o[x] = mfma(vf, pah[q], o[x]);
-                        o[x] = mfma(vf, pal[q], o[x]);
-                    }
+                    for (int x = 0; x < NX; ++x) vf[x] = v_frag(q, x);
+#pragma unroll
+                    for (int x = 0; x < NX; ++x) o[x] = mfma(vf[x], pah[q], o[x]);
+#pragma unroll
+                    for (int x = 0; x < NX; ++x) o[x] = mfma(vf[x], pal[q], o[x]);
+                }
                 if constexpr (FUSE) {
                     if (epilogue) {
                         // Swish(r) * LN(o): a token's row is spread over the four lanes lm, lm+16, lm+32, lm+48
@@ -748,10 +759,15 @@ hipError_t launch_cls(const Params &p, SpanMode mode, hipStream_t stream) {
 
 }  // namespace
 
-bool hilo_kernels_cover(const Params &p) { return !two_sided(p) && p.dk <= 36 && p.dv <= 80; }
+// One-sided gates, the DiG-XL/2 heads (36 / 72) and what their registers hold.  Heads of up to 32 / 64 channels stay with the
+// kernels in gla_mfma.hip: a chunk has less to overlap there, and those have an 8-wave form for few groups (6 sequences of 432
+// tokens 14.6 us, here 17.0; backward of 42 sequences of 256 steps 27.8 and 30.0; only calls of more than 256 groups would
+// gain, 24 sequences of 6292 tokens with the epilogue 49.8 and 46.6).
+bool hilo_kernels_cover(const Params &p) {
+    return !two_sided(p) && p.dk <= 36 && p.dv <= 80 && (p.dk > 32 || p.dv > 64);
+}
 
 hipError_t launch_hilo_span(const Params &p, SpanMode mode, hipStream_t stream) {
-    if (p.dk <= 32 && p.dv <= 64) return launch_cls<0, 4>(p, mode, stream);
     return launch_cls<1, 5>(p, mode, stream);
 }
 

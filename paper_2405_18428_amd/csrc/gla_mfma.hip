@@ -1107,7 +1107,7 @@ hipError_t launch_one(const Params &p, hipStream_t stream) {
     return launch_depth<MODE, NDK8, NDV16, 1, FUSE, ACC, TOut, BETA>(p, stream);
 }
 
-// BETA: two-sided gate.  (One-sided calls of up to 36 key channels and 80 value columns run on the kernels in gla_hilo.hip.)
+// BETA: two-sided gate.  (One-sided calls with 33 to 36 key channels run on the kernels in gla_hilo.hip.)
 template <int MODE, int NDK8, int NDV16, bool BETA>
 hipError_t launch_dt(const Params &p, hipStream_t stream) {
     const bool bf16_out = MODE == kModeOutput && p.out_dtype == GLA_DT_BF16;
@@ -1128,6 +1128,7 @@ hipError_t launch_mode(const Params &p, hipStream_t stream) {
         if (ndk8 <= 4 && ndv16 <= 4) return launch_dt<MODE, 4, 4, true>(p, stream);
         return launch_dt<MODE, 5, 5, true>(p, stream);     // (mfma_engine_supports: no larger ones)
     }
+    if (ndk8 <= 4 && ndv16 <= 4) return launch_dt<MODE, 4, 4, false>(p, stream);
     if (ndk8 <= 5 && ndv16 <= 5) return launch_dt<MODE, 5, 5, false>(p, stream);
     return launch_dt<MODE, 8, 8, false>(p, stream);
 }

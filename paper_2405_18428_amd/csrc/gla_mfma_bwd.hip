@@ -1097,6 +1097,10 @@ hipError_t launch_sizes(const WalkParams &p, const void *w, float *r, hipStream_
 // Same conditions as the forward MFMA engine (bf16 rows, dk % 4 == 0, dv % 8 == 0, 32-bit offsets).
 // with_outputs: also write o_j = q_j S_j (p.q, fp32 rows to p.out).
 hipError_t launch_mfma_row_read(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs) {
+    // The kernels with the rows in registers take a compute unit per group: where there are more groups (a forward call's plan
+    // adopted by gla_bwd_reuse, more than 256 sequences) those above, two groups a unit, are as fast or faster (16 x 256 chunks
+    // at 36 / 72 channels in 512 spans 162 and 167 us a call, in 256 spans 178 and 155).
+    if (hilo_kernels_cover(p) && (long long)p.B * p.H * p.nspans <= 256) return launch_hilo_walk(p, w, r, stream, with_outputs);
     if (with_outputs) return launch_sizes<true, false>(p, w, r, stream);
     return p.ws_gstate != nullptr ? launch_sizes<false, true>(p, w, r, stream) : launch_sizes<false, false>(p, w, r, stream);
 }

@@ -272,6 +272,8 @@ __device__ inline void chain_span_states(const Params &p, int bh, int sp, int ti
 // so that rows past a span's end, channels past dk and columns past dv need neither masks nor branches (and the number of
 // accesses in flight is a constant, which the waits count on).  A view is smaller than 2^31 bytes (2^30 of bf16).
 constexpr uint32_t kNowhere = 0x80000000u;        // such an offset; half of it in units of bf16 rows
+// the fp32 offset of a row and a piece of it given in bf16 rows (either may be nowhere; twice nowhere must not wrap around)
+__device__ inline uint32_t f32_at(uint32_t row, uint32_t piece) { return 2u * min(row + piece, kNowhere / 2); }
 using Rsrc = __amdgpu_buffer_rsrc_t;
 __device__ inline Rsrc view(const void *base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00027000);
