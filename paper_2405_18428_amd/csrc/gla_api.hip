@@ -188,7 +188,12 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     // every sequence, and each would be walked again by one work-group of the bf16 hi/lo kernel.  Those kernels then
     // take the whole call, on their own span plan (32 sequences of 2745 tokens at 36 / 72 channels: 160 us with the
     // fallback, 35 us).
-    if (fast && g_opt_engine != GLA_ENGINE_MFMA_FP16 && p.T % kChunk != 0 && (nchunks - 1) % cps == 0) {
+    // The same for large calls of the heads that have the hi/lo kernels with the rows in registers: the memory bounds either
+    // engine there, and these need no launch for the range fallback (16 sequences of 16384 tokens, row and column scan: fp16 70.7
+    // and 94.6 us, hi/lo 66 and 90; 16 of 12288 in [B,T,H,d] 69.6 and 62.0; but 32 of 4096 35.8 and 37.5).
+    const bool ragged_span = p.T % kChunk != 0 && (nchunks - 1) % cps == 0;
+    const bool large = hilo && p.z_gate == nullptr && g_opt_chunks_per_span <= 0 && (long long)bh * nchunks >= 3000;
+    if (fast && g_opt_engine != GLA_ENGINE_MFMA_FP16 && (ragged_span || large)) {
         const int other = plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p), false, hilo);
         if (plan_workspace_bytes(bh, (size_t)((nchunks + other - 1) / other), p.dk, p.dv) <= ws_limit) {
             fast = false;
