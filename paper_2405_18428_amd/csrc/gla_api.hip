@@ -184,6 +184,9 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
                   ? recurrent_chunks_per_span(p, (long long)(max_spans < (size_t)nchunks ? max_spans : nchunks))
                   : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma,
                                          fast ? fast_groups_per_cu(p) : (use_mfma ? bwd_groups : 2), fast, hilo && !fast);
+    // that cost model may take more spans than are resident at once; where their states do not fit, the plan without it
+    if (hilo && !fast && (size_t)((nchunks + cps - 1) / cps) > max_spans)
+        cps = plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p));
     // A last span of one ragged chunk: some of the fp16 engine's lanes see no token in it, so it raises the flag of
     // every sequence, and each would be walked again by one work-group of the bf16 hi/lo kernel.  Those kernels then
     // take the whole call, on their own span plan (32 sequences of 2745 tokens at 36 / 72 channels: 160 us with the

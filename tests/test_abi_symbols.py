@@ -114,6 +114,20 @@ def test_static_scratch_rejects_oversize_on_the_host():
 
 
 @pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="passes addresses that no GPU may be given")
+@pytest.mark.parametrize("engine,B,T,dk,dv", [(gla.ENGINE_MFMA, 65, 4096, 36, 72), (gla.ENGINE_MFMA, 150, 2048, 36, 72),
+                                              (gla.ENGINE_AUTO, 150, 4096, 12, 80)])
+def test_static_scratch_takes_many_sequences(engine, B, T, dk, dv):
+    """Many sequences on the bf16 hi/lo engine, whose states fit the static array only in one span a sequence."""
+    lib = gla.load_library()
+    ok = ctypes.c_void_p(4096)
+    gla.gla_set_option(gla.OPT_ENGINE, engine)
+    try:
+        assert lib.gla_fwd_static(ok, ok, ok, ok, B, 8, T, dk, dv, T // 64, 64, 0, ok, None, None) == 6
+    finally:
+        gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
+
+
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="passes addresses that no GPU may be given")
 @pytest.mark.parametrize("engine", [gla.ENGINE_AUTO, gla.ENGINE_RECURRENT])
 @pytest.mark.parametrize("B,H,T,dk,dv", [(1, 16, 16384, 36, 70), (1, 16, 16384, 33, 64), (1, 16, 16384, 36, 72),
                                          (4, 4, 65536, 36, 70)])
