@@ -1,6 +1,6 @@
 // bf16 hi/lo MFMA engine for one span of the GLA recurrence in its chunk form, rows held in registers
 // (DiG paper, Sec. 3.5: chunks of M = 64 tokens computed on-chip; recurrence of Sec. 3.1 Eq. (attn_gla) rows 1-3 with
-// beta = 1; up to 40 key channels and 80 value columns).
+// beta = 1; up to 36 key channels and 80 value columns, see hilo_kernels_cover).
 //
 // Chunk form around a mid-chunk anchor.  With b_j = sum_{i<=j} log2 alpha_i inside a chunk (inclusive, per key channel),
 // b_m its value after the chunk's 32nd token and b_C after its last, and S_0 the state entering the chunk,
@@ -11,9 +11,9 @@
 //
 // Wave w of the four owns tokens 16 w .. 16 w + 15 of every chunk, and fetches their rows straight into the layout of the
 // MFMA operands: lane (lm, g) = (lane % 16, lane / 16) holds, for token 16 w + lm, channels 16 u + 4 g .. + 3 of the units
-// u = 0, 1 (one 32-channel step: slot (g, e) is channel 16 (e / 4) + 4 g + e % 4) and the "tail" channels 32 + g (dk > 32)
-// and 36 + g (dk > 36).  q~ therefore never leaves the wave's registers, the gates' prefix sums are 4-step scans over the
-// 16 lanes of a DPP row plus the totals of the other waves' tiles, and only k~, v and P go through LDS, each written once.
+// u = 0, 1 (one 32-channel step: slot (g, e) is channel 16 (e / 4) + 4 g + e % 4) and the "tail" channel 32 + g.  q~
+// therefore never leaves the wave's registers, the gates' prefix sums are 4-step scans over the 16 lanes of a DPP row plus
+// the totals of the other waves' tiles, and only k~, v and P go through LDS, each written once.
 // A tail channel fills the four contraction slots of its lane group with its four hi/lo products: (hi, hi, lo, lo) on the
 // side of k~ and P, (hi, lo, hi, lo) on that of q~; one MFMA takes them all.  The same 16 columns read over the tokens
 // give the state update of the four tail channels (rows hi, hi, lo, lo of each: the sum of the first and the third).
@@ -22,7 +22,7 @@
 // then 16 for the tail channels, and the operands of two chunks: while the waves contract chunk c from one set, they gate
 // chunk c + 1 and scale the state into the other and scan the gates of chunk c + 2, with one barrier a chunk, so that the
 // vector instructions of the gating stand between the matrix instructions of the contraction (both are chains of dependent
-// instructions, and a SIMD holds two waves: 76 KB a group, two groups a compute unit).
+// instructions, and a SIMD holds two waves: 69 KB a group, two groups a compute unit).
 //
 // LDS rows are 160 bytes (40 banks) long, and the 16-byte units of rows 8 .. 15 of every 16 change places in pairs: the
 // reads of 16 rows (8- and 16-byte pieces, transposing or not) then fall into different banks.  (With rows an odd number of
@@ -31,7 +31,7 @@
 // What bounds it on MI355X: up to 1024 px the instruction streams (one group alone on a compute unit: 5300 clocks a chunk at
 // 36 / 72 channels, 6500 when two share it), at 2048 px the memory (output pass 195 MB in 30 us once the pipeline is filled).
 // Before, with the rows staged through LDS, three barriers a chunk and single sets (output pass / state pass of 2048 chunks
-// in gla_fwd_fused: 36.7 / 16.6 us, here 29 / 12.5): a chunk of a lone group took 6800 clocks and two groups gained little
+// in gla_fwd_fused: 36.7 / 16.6 us, here 30 / 13.9): a chunk of a lone group took 6800 clocks and two groups gained little
 // on each other.  Tried: three groups of 168 registers with single sets (two barriers; 45.3 against 42.6 us a fused call),
 // a chunk loop per wave with the scan inside (45.5), the state's chain with the decays read a run ahead (42.6 -> 43.3).
 #include <type_traits>

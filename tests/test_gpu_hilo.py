@@ -1,6 +1,7 @@
 """The bf16 hi/lo kernels that keep a chunk's rows in registers, at the edges of what they cover: numbers of key channels
 around the 16-channel units and the tail, value columns around the 16-column tiles, chunks that are one token long or one
-short, one span and several, both memory orders, an initial state.
+short, one span and several, both memory orders, an initial state; heads of up to 32 / 64 channels, which stay on the kernels that
+stage rows through LDS, at the same edges.
 
 Tolerance: the split operands carry 16 bits, so a product is off by at most 4 * 2^-17 of itself and an output, whose largest
 value is about six times its RMS, by 2e-4 of the RMS; a bf16 store adds at most half a unit of its eighth bit, 2^-8 of the largest value."""
@@ -48,3 +49,42 @@ def test_edges(dk, dv, gh, gw):
         tol = TOL * max(1.0, np.abs(ref).max() / rms / 6) + (2.0 ** -8 * np.abs(ref).max() / rms if out_dtype == torch.bfloat16 else 0.0)
         assert np.abs(got - ref).max() / rms <= tol, (cps, scan, layout)
         assert np.abs(fin.cpu().numpy() - ref_fin).max() / np.sqrt(np.mean(ref_fin ** 2)) <= TOL, (cps, scan, layout)
+
+
+@pytest.mark.parametrize("dk,dv", [(36, 8), (36, 72), (36, 80), (20, 72)])
+@pytest.mark.parametrize("B,gh,gw", [(1, 1, 1), (1, 7, 9), (1, 8, 8), (1, 5, 13), (1, 17, 19), (1, 9, 50), (86, 5, 13)])
+def test_walk_edges(dk, dv, B, gh, gw):
+    """The backward walks at the same edges, one span and several, both memory orders, and at 258 sequences, where the
+    older kernels take them.  The gate gradient is a sum over up to T steps of terms q dq - k dk, each off by at most TOL of
+    their size: sqrt(T) TOL of it, whatever cancels."""
+    from oracle import gla_oracle
+    H, T = 3, gh * gw
+    d = gi.make_inputs(B, H, T, dk, dv, "bf16", seed=dk + dv + 1)
+    w = torch.from_numpy(np.random.default_rng(9).standard_normal((B, H, T, dv)).astype(np.float32)).bfloat16()
+    for cps, scan, layout in ((0, 0, 0), (1, 3, 1), (2, 2, 0), (3, 1, 0)):
+        gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, cps)
+        ref = gla_oracle.gla_bwd(d["q"], d["k"], d["v"], d["log_alpha"], w.float().numpy(), gh, gw, scan)
+        t = [upload(d, n) for n in ("q", "k", "v")] + [torch.from_numpy(d["log_alpha"]).cuda(), w.cuda()]
+        if layout == 1:
+            t = [x.transpose(1, 2).contiguous() for x in t]
+        got = gla.gla_bwd_layout(*t, gh, gw, scan, layout=layout)
+        got = [(g if layout == 0 else g.transpose(1, 2)).cpu().numpy() for g in got]
+        for g, r in zip(got[:3], ref[:3]):
+            rms = np.sqrt(np.mean(r ** 2))
+            assert np.abs(g - r).max() / rms <= TOL * max(1.0, np.abs(r).max() / rms / 6), (cps, scan, layout)
+        size = max(np.sqrt(np.mean((d["q"].astype(np.float64) * ref[0]) ** 2)), np.sqrt(np.mean(ref[3] ** 2)))
+        assert np.abs(got[3] - ref[3]).max() <= TOL * 6 * np.sqrt(T) * size, (cps, scan, layout)
+
+
+def test_large_call():
+    """3024 chunks: a plain forward call of these heads leaves the fp16 kernels for these, whose accuracy it then has."""
+    from oracle import gla_oracle
+    gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
+    B, H, gh, gw, dk, dv = 3, 16, 63, 64, 36, 72
+    d = gi.make_inputs(B, H, gh * gw, dk, dv, "bf16", seed=3)
+    ref, ref_fin = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, 2)
+    t = [upload(d, n) for n in ("q", "k", "v")] + [torch.from_numpy(d["log_alpha"]).cuda()]
+    out, fin = gla.gla_fwd_layout(*t, gh, gw, 2, out_dtype=torch.float32)
+    rms = np.sqrt(np.mean(ref ** 2))
+    assert np.abs(out.cpu().numpy() - ref).max() / rms <= TOL * max(1.0, np.abs(ref).max() / rms / 6)
+    assert np.abs(fin.cpu().numpy() - ref_fin).max() / np.sqrt(np.mean(ref_fin ** 2)) <= TOL
