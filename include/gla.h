@@ -58,8 +58,8 @@
  *  - fp16 MFMA engine (what GLA_ENGINE_AUTO takes for the plain forward pass, and for
  *    gla_fwd_fused without the output epilogue, on bf16 inputs with 17..64 key
  *    channels and more than four chunks, unless the last span of the launch plan would
- *    be a single chunk of fewer than 64 tokens: such calls run on the bf16 hi/lo
- *    kernels, see gla_engine): its operands
+ *    be a single chunk of fewer than 64 tokens, or the call is a large column scan or
+ *    [B,T,H,d] call of 33 to 36 key channels: such calls run on the bf16 hi/lo kernels, see gla_engine): its operands
  *    cover a decay of at most 2^-11 per key channel over 32 consecutive scan steps
  *    (alpha above about 0.79 on average; sigmoid(z)^(1/16) with z > -3.7) and
  *    inputs whose largest |q|, |k| lie in [2^-8, 8] and |v| in [2^-8, 2^14].  This
@@ -132,7 +132,9 @@ typedef enum {
                                  and more than four chunks, else the bf16 hi/lo one), otherwise recurrent.  A call
                                  whose last span would be one chunk of fewer than 64 tokens (T % 64 != 0, and 64-token
                                  chunks before it that the plan's chunks per span divide) runs on the bf16 hi/lo kernels
-                                 instead of the fp16 ones, in gla_fwd_static only if their plan fits its array */
+                                 instead of the fp16 ones, and so does the plain forward pass with 33 to 36 key channels
+                                 (or up to 36 and 65 to 80 value columns) of a column scan or of [B,T,H,d] tensors from
+                                 3000 chunks of 64 tokens on, over all batches and heads; in gla_fwd_static only if their plan fits its array */
     GLA_ENGINE_RECURRENT = 1, /* fp32 token-by-token arithmetic inside each span; any dtype, any gates */
     GLA_ENGINE_MFMA = 2,      /* bf16 hi/lo MFMA chunk form (Sec. 3.5) in every pass; bf16 inputs only */
     GLA_ENGINE_MFMA_FP16 = 3  /* fp16 operands in both passes of the plain forward call and of gla_fwd_fused without

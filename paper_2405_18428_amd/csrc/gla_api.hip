@@ -144,8 +144,10 @@ int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_c
 // use_fast (optional): the caller is the plain forward pass and would take the fp16 output pass where it covers
 // the call; on return, whether it does (the span plan is then sized for that kernel's residency).
 // ws_limit: room for the plan where the workspace is not sized for every plan.
+// plain_plan: the plan of the plain forward pass, whatever kernels the call itself runs on (the last scan order of a sum, whose
+// span states gla_bwd_reuse takes on that plan).
 int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use_fast = nullptr,
-                           size_t ws_limit = ~(size_t)0) {
+                           size_t ws_limit = ~(size_t)0, bool plain_plan = false) {
     if (g_opt_engine == GLA_ENGINE_RECURRENT) {
         use_mfma = false;
     } else if (g_opt_engine == GLA_ENGINE_MFMA || g_opt_engine == GLA_ENGINE_MFMA_FP16) {
@@ -158,7 +160,12 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     if (use_fast != nullptr) {
         fast = use_mfma && g_opt_engine != GLA_ENGINE_MFMA && fast_engine_supports(p);
         if (g_opt_engine == GLA_ENGINE_MFMA_FP16 && !fast) return GLA_ERR_UNSUPPORTED;
-        *use_fast = fast;
+        if (plain_plan && p.accumulate) {
+            Params plain = p;
+            plain.accumulate = 0;
+            fast = use_mfma && g_opt_engine != GLA_ENGINE_MFMA && fast_engine_supports(plain);
+        }
+        *use_fast = fast && !p.accumulate;
     }
     const int nchunks = (p.T + kChunk - 1) / kChunk;
     // short sequences are one span on the bf16 hi/lo kernel: a single pass, and no launch for the range fallback
@@ -191,11 +198,14 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     // every sequence, and each would be walked again by one work-group of the bf16 hi/lo kernel.  Those kernels then
     // take the whole call, on their own span plan (32 sequences of 2745 tokens at 36 / 72 channels: 160 us with the
     // fallback, 35 us).
-    // The same for large calls of the heads that have the hi/lo kernels with the rows in registers: the memory bounds either
-    // engine there, and these need no launch for the range fallback (16 sequences of 16384 tokens, row and column scan: fp16 70.7
-    // and 94.6 us, hi/lo 66 and 90; 16 of 12288 in [B,T,H,d] 69.6 and 62.0; but 32 of 4096 35.8 and 37.5).
+    // The same for large calls of the heads that have the hi/lo kernels with the rows in registers, where the rows of
+    // neighbouring scan steps lie apart (column scans, [B,T,H,d]): lines fetched more than once bound either engine there, and
+    // these need no launch for the range fallback (16 sequences of 16384 tokens, column scan: fp16 94.4 us, hi/lo 90.3, from
+    // one buffer set 82.1 and 79.5, with bf16 results 87.8 and 83.5; [B,T,H,d] 97.7 and 90.3).  A row scan of [B,H,T,d] gains
+    // nothing (71.6 and 71.6; from one buffer set 56.9 and 60.2, with bf16 results 64.8 and 66.4), nor do smaller calls.
     const bool ragged_span = p.T % kChunk != 0 && (nchunks - 1) % cps == 0;
-    const bool large = hilo && p.z_gate == nullptr && g_opt_chunks_per_span <= 0 && (long long)bh * nchunks >= 3000;
+    const bool apart = p.scan_dir >= GLA_SCAN_COL_FWD || p.st_k != p.dk;
+    const bool large = hilo && apart && p.z_gate == nullptr && g_opt_chunks_per_span <= 0 && (long long)bh * nchunks >= 3000;
     if (fast && g_opt_engine != GLA_ENGINE_MFMA_FP16 && (ragged_span || large)) {
         const int other = plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p), false, hilo);
         if (plan_workspace_bytes(bh, (size_t)((nchunks + other - 1) / other), p.dk, p.dv) <= ws_limit) {
@@ -332,6 +342,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         // states S_start(r) (carry kernel) or the local states U_r and log Gamma_r (chained inside its output
         // pass), by the rule that also sets base.chain_in_output.
         Params pf = base;
+        pf.scan_dir = scan_dir;
         bool same_engine, fwd_fast = false;
         if (choose_engine_and_plan(pf, const_cast<void *>(fwd_workspace), same_engine, &fwd_fast) != GLA_OK)
             return GLA_ERR_HIP;
@@ -536,7 +547,7 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
     p.initial_state = initial_state;
     if (accumulate && out_dtype != GLA_DT_F32) return GLA_ERR_UNSUPPORTED;
     if (accumulate && (log_beta || (fused && fused->z_beta))) return GLA_ERR_UNSUPPORTED;
-    p.accumulate = accumulate;
+    p.accumulate = accumulate != 0;     // (2: the last scan order of a sum)
     if (fused) {
         p.log_alpha = nullptr;
         p.z_gate = fused->z;
@@ -556,7 +567,7 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
     }
 
     bool use_mfma, use_fast = false;
-    st = choose_engine_and_plan(p, workspace, use_mfma, &use_fast, plan_sized_workspace ? ws_bytes : ~(size_t)0);
+    st = choose_engine_and_plan(p, workspace, use_mfma, &use_fast, plan_sized_workspace ? ws_bytes : ~(size_t)0, accumulate == 2);
     if (st != GLA_OK) return st;
     if (plan_sized_workspace && ws_bytes < plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv))
         return GLA_ERR_WORKSPACE;
@@ -737,7 +748,7 @@ int gla_fwd_multi(const void *q, const void *k, const void *v, const float *log_
         // the first scan order writes `out`, the others add to it; the workspace is reused in stream order
         const int st = run(q, k, v, log_alpha, B, H, T, dk, dv, grid_h, grid_w, d, qkv_dtype, GLA_DT_F32, out,
                            nullptr, workspace, workspace_bytes_, static_cast<hipStream_t>(stream), nullptr,
-                           GLA_LAYOUT_BHTD, nullptr, nullptr, first ? 0 : 1);
+                           GLA_LAYOUT_BHTD, nullptr, nullptr, first ? 0 : (scan_mask >> (d + 1) ? 1 : 2));
         if (st != GLA_OK) return st;   // argument errors show on the first pass, before any launch
         first = 0;
     }

@@ -88,3 +88,26 @@ def test_large_call():
     rms = np.sqrt(np.mean(ref ** 2))
     assert np.abs(out.cpu().numpy() - ref).max() / rms <= TOL * max(1.0, np.abs(ref).max() / rms / 6)
     assert np.abs(fin.cpu().numpy() - ref_fin).max() / np.sqrt(np.mean(ref_fin ** 2)) <= TOL
+
+
+@pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
+@pytest.mark.parametrize("B,gh,gw,scans", [(2, 64, 64, (0, 1)), (2, 64, 64, (2,)), (1, 112, 112, (0, 3)), (3, 63, 64, (2,)), (3, 63, 64, (0, 1))])
+def test_reuse_takes_the_plan_of_the_forward_call(dk, dv, B, gh, gw, scans):
+    """Span states of a forward call (several scan orders: of the last one) give the gradients that a call of its own states
+    gives, also where the kernels that wrote them have span plans of their own; two sums over other spans, 2 TOL."""
+    gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
+    H, T = 16 if gh < 100 else 6, gh * gw
+    d = gi.make_inputs(B, H, T, dk, dv, "bf16", seed=4)
+    t = [upload(d, n) for n in ("q", "k", "v")] + [torch.from_numpy(d["log_alpha"]).cuda()]
+    w = torch.from_numpy(np.random.default_rng(9).standard_normal((B, H, T, dv)).astype(np.float32)).bfloat16().cuda()
+    ws = torch.full((gla.gla_fwd_workspace_bytes(B, H, T, dk, dv, gla.DT_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+    if len(scans) == 1:
+        gla.gla_fwd_layout(*t, gh, gw, scans[0], workspace=ws)
+    else:
+        gla.gla_fwd_multi(*t, gh, gw, scan_dirs=scans, workspace=ws)
+    ref = gla.gla_bwd(*t, w, gh, gw, scans[-1])
+    got = gla.gla_bwd(*t, w, gh, gw, scans[-1], fwd_workspace=ws)
+    # a plain call's states may come from the fp16 kernels, whose operands carry 11 bits where the hi/lo pairs carry 16
+    tol = 2 * TOL if len(scans) > 1 else 32 * TOL
+    for g, r in zip(got[:3], ref[:3]):
+        assert float((g - r).abs().max() / r.square().mean().sqrt()) <= tol * max(1.0, float(r.abs().max() / r.square().mean().sqrt()) / 6)
