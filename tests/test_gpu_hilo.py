@@ -77,7 +77,7 @@ def test_walk_edges(dk, dv, B, gh, gw):
 
 
 def test_large_call():
-    """3024 chunks: a plain forward call of these heads leaves the fp16 kernels for these, whose accuracy it then has."""
+    """3024 chunks: a column scan of these heads leaves the fp16 kernels for these, whose accuracy it then has."""
     from oracle import gla_oracle
     gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
     B, H, gh, gw, dk, dv = 3, 16, 63, 64, 36, 72
