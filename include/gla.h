@@ -54,7 +54,9 @@
  * limits of the engines (see gla_engine):
  *  - bf16 hi/lo MFMA engine: the summed |log_alpha| over any 64 consecutive scan
  *    steps of one key channel stays below 80 (true for alpha = sigmoid(z)^(1/16)
- *    whenever z > -20).  GLA_ENGINE_RECURRENT has no such limit.
+ *    whenever z > -20).  GLA_ENGINE_RECURRENT has no such limit.  Beyond it, up to a gate
+ *    of exactly zero (log_alpha = -inf), what that channel adds inside the 64-step chunk is
+ *    lost or wrong, but finite: later chunks lack it as far as it would not have decayed.
  *  - fp16 MFMA engine (what GLA_ENGINE_AUTO takes for the plain forward pass, and for
  *    gla_fwd_fused without the output epilogue, on bf16 inputs with 17..64 key
  *    channels and more than four chunks, unless the last span of the launch plan would

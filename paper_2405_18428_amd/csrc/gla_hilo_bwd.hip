@@ -303,11 +303,16 @@ __global__ __launch_bounds__(512, 2) void hilo_walk_kernel(WalkParams p, const v
     };
     // prefix sums of the gates of chunk x inside this wave's tile; tile totals to LDS
     auto scan = [&](int x, FRow &b) {
-        b.u[0] = r_la.u[0] * kLog2e;
-        b.u[1] = r_la.u[1] * kLog2e;
 #pragma unroll
-        for (int e = 0; e < DT; ++e) b.t[e] = r_la.t[e] * kLog2e;
-        scan_rows(b);
+        for (int u = 0; u < 2; ++u) {
+            float l[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) l[i] = r_la.u[u][i] * kLog2e;
+            row_scan16x4_least(l[0], l[1], l[2], l[3], kLeastGate2);
+            b.u[u] = f32x4{l[0], l[1], l[2], l[3]};
+        }
+#pragma unroll
+        for (int e = 0; e < DT; ++e) b.t[e] = row_scan16(fmaxf(r_la.t[e] * kLog2e, kLeastGate2));
         if constexpr (READ) put_tot(s_tot + (ring(x) * 4 + w) * 4 * TS, b);
     };
 

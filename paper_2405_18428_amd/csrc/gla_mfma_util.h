@@ -21,6 +21,9 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kMaxExp2 = 120.f;       // clamp of -b (base 2) before exp2: keeps k~ finite
+// Where the prefix sums of a chunk are taken relative to its middle, a gate of exactly zero (log alpha = -inf) would make them
+// inf - inf: no gate counts for less than this (base 2), whose factor is zero in fp32 all the same
+constexpr float kLeastGate2 = -2.f * kMaxExp2;
 
 __device__ inline f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
@@ -143,6 +146,36 @@ __device__ inline void row_scan16x4(float &a, float &b, float &c, float &d) {
         "v_add_f32_dpp %3, %3, %3 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         "s_nop 1"      // and before whatever reads the results through DPP next
         : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
+
+// The same of max(x, least): the four maxima stand in the wait states before the first step (two after the instruction that
+// wrote a DPP source, five after one that wrote EXEC).
+__device__ inline void row_scan16x4_least(float &a, float &b, float &c, float &d, float least) {
+    asm volatile(
+        "v_max_f32 %0, %4, %0\n\t"
+        "v_max_f32 %1, %4, %1\n\t"
+        "v_max_f32 %2, %4, %2\n\t"
+        "v_max_f32 %3, %4, %3\n\t"
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "s_nop 1"      // and before whatever reads the results through DPP next
+        : "+v"(a), "+v"(b), "+v"(c), "+v"(d)
+        : "s"(least));
 }
 
 // inclusive prefix sum over the 16 lanes of a DPP row

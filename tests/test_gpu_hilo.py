@@ -111,3 +111,34 @@ def test_reuse_takes_the_plan_of_the_forward_call(dk, dv, B, gh, gw, scans):
     tol = 2 * TOL if len(scans) > 1 else 32 * TOL
     for g, r in zip(got[:3], ref[:3]):
         assert float((g - r).abs().max() / r.square().mean().sqrt()) <= tol * max(1.0, float(r.abs().max() / r.square().mean().sqrt()) / 6)
+
+
+@pytest.mark.parametrize("engine", [gla.ENGINE_AUTO, gla.ENGINE_MFMA])
+@pytest.mark.parametrize("step", [0, 5, 20, 31, 40, 63])
+def test_gate_of_exactly_zero(engine, step):
+    """log_alpha = -inf on some channels at one step of a chunk, and a step whose pre-activation is as low: the limits of the
+    engines do not cover it, but no output is lost to NaN, and six chunks later, where the steps of that chunk have decayed to
+    less than TOL, the results are right again."""
+    from oracle import gla_oracle
+    gla.gla_set_option(gla.OPT_ENGINE, engine)
+    B, H, gh, gw, dk, dv = 1, 3, 16, 48, 36, 72
+    T, at = gh * gw, 2 * 64 + step
+    d = gi.make_inputs(B, H, T, dk, dv, "bf16", seed=7)
+    d["log_alpha"][:, :, at, [0, 5, 17, 33, 35]] = -np.inf
+    t = [upload(d, n) for n in ("q", "k", "v")] + [torch.from_numpy(d["log_alpha"]).cuda()]
+    w = torch.from_numpy(np.random.default_rng(9).standard_normal((B, H, T, dv)).astype(np.float32)).bfloat16()
+    z = torch.from_numpy(np.random.default_rng(8).standard_normal((B, H, T, dk)).astype(np.float32))
+    z[:, :, at, [0, 5, 17, 33, 35]] = -3e38
+    for cps in (0, 3, 12):
+        gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, cps)
+        ref, ref_fin = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, 0)
+        out, fin = gla.gla_fwd_layout(*t, gh, gw, 0, out_dtype=torch.float32)
+        out, fin = out.cpu().numpy(), fin.cpu().numpy()
+        assert np.isfinite(out).all() and np.isfinite(fin).all()
+        rms = np.sqrt(np.mean(ref ** 2))
+        assert np.abs(out - ref)[:, :, 9 * 64:].max() / rms <= TOL * max(1.0, np.abs(ref).max() / rms / 6)
+        assert np.abs(fin - ref_fin).max() / np.sqrt(np.mean(ref_fin ** 2)) <= TOL
+        for g in gla.gla_bwd(*t, w.cuda(), gh, gw, 0):
+            assert bool(torch.isfinite(g).all())
+        fused, fin = gla.gla_fwd_fused(*t[:3], z.bfloat16().cuda(), 16.0, gh, gw, 0)
+        assert bool(torch.isfinite(fused).all()) and bool(torch.isfinite(fin).all())
