@@ -181,11 +181,14 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     // (the backward pass passes no use_fast; its walks have a plan of their own)
     const bool hilo = use_mfma && use_fast != nullptr && hilo_kernels_cover(p);
     // Backward pass: spans for one group a compute unit where that is what the plan comes to (and the sums over a span, whose
-    // error grows with its square root, get no longer than twice what they would be with two groups; launch_mfma_row_read)
+    // error grows with its square root, get no longer than twice what they would be with two groups; launch_mfma_row_read),
+    // but where long sequences of one chunk a span are a few groups more than compute units (32 x 9 chunks: 288 groups
+    // 37.7 us, 160 of two chunks 38.1; 16 x 17 37.1 and 41.5; but 16 x 20 40.9 and 39.4, 48 x 6 37.3 and 35.5)
     int bwd_groups = mfma_groups_per_cu(p);
     if (use_fast == nullptr && use_mfma && hilo_kernels_cover(p) && bwd_groups > 1) {
         const int one = plan_chunks_per_span(p.B * p.H, nchunks, true, 1), two = plan_chunks_per_span(p.B * p.H, nchunks, true, bwd_groups);
-        if ((long long)p.B * p.H * ((nchunks + one - 1) / one) <= 256 && one <= 2 * two) bwd_groups = 1;
+        const long long bhn = (long long)p.B * p.H;
+        if (bhn * ((nchunks + one - 1) / one) <= 256 && one <= 2 * two && (two > 1 || bhn * nchunks > 304 || nchunks < 9)) bwd_groups = 1;
     }
     int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
                   ? recurrent_chunks_per_span(p, (long long)(max_spans < (size_t)nchunks ? max_spans : nchunks))

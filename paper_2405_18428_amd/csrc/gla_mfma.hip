@@ -1156,8 +1156,23 @@ int mfma_groups_per_cu(const Params &p) {
     return two_sided(p) && p.z_beta == nullptr ? 1 : 2;
 }
 
+// Whether the kernels with the rows in registers are the faster ones for a pass of a call that they cover.  Their pipeline
+// gates two chunks past a span's end: state passes of up to 3 chunks a span, of which a compute unit holds two groups here and
+// one chunk in flight each, are faster here (15 spans of one chunk 0.5 us of 16.4, of 2 chunks 0.4, of 3 even; from 4 on
+// there, 32 spans of 4 chunks 2 us).  A load of theirs touches 16 rows: where more than 256 groups of one span each share the
+// compute units in twos and the rows are those of [B,T,H,d], sequences of up to 6 chunks are faster here (384 of 4 chunks
+// 0.9 us, 272 of 2 chunks 1.6 us of 16), from 513 groups on only those of up to 2 (768 of 4 chunks 15 % slower here); rows of
+// [B,H,T,d] for sequences of 2 chunks by 1 to 3 %.
+static bool hilo_span_takes(const Params &p, SpanMode mode) {
+    const int chunks = p.span_len / kChunk;
+    if (mode == kModeState) return chunks >= 4;
+    const long long groups = (long long)p.B * p.H * p.nspans;
+    if (p.nspans > 1 || groups <= 256 || p.z_gate != nullptr || p.accumulate) return true;
+    return chunks > (p.st_k != p.dk && groups <= 512 ? 6 : 2);
+}
+
 hipError_t launch_mfma_span(const Params &p, SpanMode mode, hipStream_t stream) {
-    if (hilo_kernels_cover(p)) return launch_hilo_span(p, mode, stream);
+    if (hilo_kernels_cover(p) && hilo_span_takes(p, mode)) return launch_hilo_span(p, mode, stream);
     return mode == kModeState ? launch_mode<kModeState>(p, stream) : launch_mode<kModeOutput>(p, stream);
 }
 

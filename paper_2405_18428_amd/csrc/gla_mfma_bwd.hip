@@ -113,7 +113,9 @@ using int_c = std::integral_constant<int, N>;
 // which a forward walk can sum chunk by chunk: the decay from a to the chunk times (q~^T dO~ of the chunk).  MI355X: the
 // walk for dq takes 59 instead of 45 us (16 sequences of 16384 steps, 36 / 72 channels) and the state pass of 31 us
 // goes, 182 -> 167 us for the call; two-sided gate, 64 sequences of 1024 steps: 32 -> 36 us, without a state pass of 21.
-template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA, bool GS>
+// FOUR: lo times lo as well where two split operands meet, for calls whose longer spans gla_hilo_bwd.hip walks that way (errors
+// of dq and dk 4.3e-6 -> 3.5e-6, of dlog_alpha 1.4e-5 -> 1.0e-5 at two chunks a span; 0.3 % of a call).
+template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA, bool GS, bool FOUR>
 __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(WalkParams p, const void *w_in, float *r_out) {
     using L = RLayout<NDK8, NDV16, DV, BETA, GS>;
     static_assert(!(DV && GS), "either walk");
@@ -655,6 +657,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(WalkParams
                     rr[ct] = mfma(kth[q][ct], bh_, rr[ct]);
                     rr[ct] = mfma(kth[q][ct], bl_, rr[ct]);
                     rr[ct] = mfma(ktl[q][ct], bh_, rr[ct]);
+                    if constexpr (FOUR) rr[ct] = mfma(ktl[q][ct], bl_, rr[ct]);
                 }
             }
             // + W S_0^T
@@ -743,6 +746,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(WalkParams
                                 d = mfma(kh, qfh[ks], d);
                                 d = mfma(kh, qfl[ks], d);
                                 d = mfma(kl, qfh[ks], d);
+                                if constexpr (FOUR) d = mfma(kl, qfl[ks], d);
                             }
                             if (jt == IT) {
 #pragma unroll
@@ -800,6 +804,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(WalkParams
                         o[x] = mfma(sh, qsh, o[x]);
                         o[x] = mfma(sh, qsl, o[x]);
                         o[x] = mfma(sl, qsh, o[x]);
+                        if constexpr (FOUR) o[x] = mfma(sl, qsl, o[x]);
                     }
                 }
                 if (row < nvalid) {
@@ -1052,10 +1057,10 @@ __global__ __launch_bounds__(NW * 64, MINW) void mfma_row_read_kernel(WalkParams
     }
 }
 
-template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA, bool GS>
+template <int NDK8, int NDV16, int NW, int MINW, bool DV, bool BETA, bool GS, bool FOUR = false>
 hipError_t launch_waves(const WalkParams &p, const void *w, float *r, hipStream_t stream) {
     using L = RLayout<NDK8, NDV16, DV, BETA, GS>;
-    auto kernel = mfma_row_read_kernel<NDK8, NDV16, NW, MINW, DV, BETA, GS>;
+    auto kernel = mfma_row_read_kernel<NDK8, NDV16, NW, MINW, DV, BETA, GS, FOUR>;
     static std::atomic<bool> configured[kMaxDevices] = {};  // per instantiation and device
     {
         hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), L::kBytes, configured);
@@ -1075,6 +1080,9 @@ hipError_t launch_one(const WalkParams &p, const void *w, float *r, hipStream_t 
     constexpr int kGroupsPerCu = (160 * 1024) / RLayout<NDK8, NDV16, DV, BETA, GS>::kBytes;
     if constexpr (kGroupsPerCu >= 2) {
         if ((long long)p.B * p.H * p.nspans > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA, GS>(p, w, r, stream);
+    }
+    if constexpr (NDK8 == 5 && !BETA) {
+        if (hilo_kernels_cover(p)) return launch_waves<NDK8, NDV16, 8, 2, DV, BETA, GS, true>(p, w, r, stream);
     }
     return launch_waves<NDK8, NDV16, 8, 2, DV, BETA, GS>(p, w, r, stream);
 }
@@ -1099,8 +1107,22 @@ hipError_t launch_sizes(const WalkParams &p, const void *w, float *r, hipStream_
 hipError_t launch_mfma_row_read(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs) {
     // The kernels with the rows in registers take a compute unit per group: where there are more groups (a forward call's plan
     // adopted by gla_bwd_reuse, more than 256 sequences) those above, two groups a unit, are as fast or faster (16 x 256 chunks
-    // at 36 / 72 channels in 512 spans 162 and 167 us a call, in 256 spans 178 and 155).
-    if (hilo_kernels_cover(p) && (long long)p.B * p.H * p.nspans <= 256) return launch_hilo_walk(p, w, r, stream, with_outputs);
+    // at 36 / 72 channels in 512 spans 162 and 167 us a call, in 256 spans 178 and 155).  They also pay for a longer prologue
+    // (both kinds of waves read the gates of three chunks) and for loads that touch 16 rows each, which tells where these are
+    // those of [B,T,H,d].  Short spans therefore stay with those above.  Difference of a backward call over 64 to 256 groups,
+    // the means of eleven numbers of sequences and spans (+: faster with the rows in registers), by chunks a span:
+    //     walk for dq      [B,H,T,d] row scans 1: +0.9 %, 2: +3.1, 3: +4.0; column scans +0.6, +2.0, +2.4
+    //                      [B,T,H,d] 2: -0.3 %, 3: 0.0, 4: +0.7, 6: +1.9, 12: +4.3
+    //     walk for dk, dv  [B,H,T,d] row scans 1: -0.7 %, 2: +0.2, 3: +1.9; column scans 2: -0.8, 3: +0.3, 4: +2.0 (grids 64
+    //                      tokens wide 3: -1.0, 4: -0.2, 12: +1.1)
+    //                      [B,T,H,d] 1: -4.3 %, 2: -3.9, 4: -1.8, 8: -0.2, 10: +0.2, 16: +1.2
+    // (one chunk: prologues of up to 15 spans that hardly decay, -2.5 %; row scans of two chunks a span +1.3 to +2.8 % from
+    // four spans on, -0.4 to -3.8 with one or two)
+    const bool heads_inside = p.st_k != p.dk;
+    const int chunks = p.span_len / kChunk;
+    const int least = with_outputs ? (heads_inside ? 10 : (p.scan_dir >= GLA_SCAN_COL_FWD ? 4 : (p.nspans > 2 ? 2 : 3))) : (heads_inside ? 4 : 2);
+    if (hilo_kernels_cover(p) && (long long)p.B * p.H * p.nspans <= 256 && chunks >= least)
+        return launch_hilo_walk(p, w, r, stream, with_outputs);
     if (with_outputs) return launch_sizes<true, false>(p, w, r, stream);
     return p.ws_gstate != nullptr ? launch_sizes<false, true>(p, w, r, stream) : launch_sizes<false, false>(p, w, r, stream);
 }

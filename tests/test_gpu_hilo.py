@@ -142,3 +142,58 @@ def test_gate_of_exactly_zero(engine, step):
             assert bool(torch.isfinite(g).all())
         fused, fin = gla.gla_fwd_fused(*t[:3], z.bfloat16().cuda(), 16.0, gh, gw, 0)
         assert bool(torch.isfinite(fused).all()) and bool(torch.isfinite(fin).all())
+
+
+@pytest.mark.parametrize("cps", [1, 2, 3, 4, 5, 9, 10])
+@pytest.mark.parametrize("scan,layout", [(1, 0), (2, 0), (0, 1), (3, 1)])
+def test_lengths_of_spans(cps, scan, layout):
+    """Four spans (the last one ragged) of the lengths between which the passes change from the kernels that stage rows through
+    LDS to those that hold them in registers, forwards and backwards, also from the forward call's states."""
+    from oracle import gla_oracle
+    B, H, gh, gw, dk, dv = 1, 2, 4 * cps, 61, 36, 72
+    T = gh * gw
+    gla.gla_set_option(gla.OPT_CHUNKS_PER_SPAN, cps)
+    d = gi.make_inputs(B, H, T, dk, dv, "bf16", seed=cps)
+    w = torch.from_numpy(np.random.default_rng(9).standard_normal((B, H, T, dv)).astype(np.float32)).bfloat16()
+    ref, ref_fin = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, scan)
+    grad = gla_oracle.gla_bwd(d["q"], d["k"], d["v"], d["log_alpha"], w.float().numpy(), gh, gw, scan)
+    t = [upload(d, n) for n in ("q", "k", "v")] + [torch.from_numpy(d["log_alpha"]).cuda(), w.cuda()]
+    if layout == 1:
+        t = [x.transpose(1, 2).contiguous() for x in t]
+    ws = torch.full((gla.gla_fwd_workspace_bytes(B, H, T, dk, dv, gla.DT_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+    out, fin = gla.gla_fwd_layout(*t[:4], gh, gw, scan, layout=layout, out_dtype=torch.float32, workspace=ws)
+    back = (lambda x: x.cpu().numpy()) if layout == 0 else (lambda x: x.transpose(1, 2).cpu().numpy())
+
+    def near(got, want):
+        rms = np.sqrt(np.mean(want ** 2))
+        assert np.abs(got - want).max() / rms <= TOL * max(1.0, np.abs(want).max() / rms / 6)
+
+    near(back(out), ref)
+    near(fin.cpu().numpy(), ref_fin)
+    # (the gate gradient as in test_walk_edges)
+    size = max(np.sqrt(np.mean((d["q"].astype(np.float64) * grad[0]) ** 2)), np.sqrt(np.mean(grad[3] ** 2)))
+    for keep in (None, ws):
+        got = [back(g) for g in gla.gla_bwd_layout(*t, gh, gw, scan, layout=layout, fwd_workspace=keep)]
+        for g, r in zip(got[:3], grad[:3]):
+            near(g, r)
+        assert np.abs(got[3] - grad[3]).max() <= TOL * 6 * np.sqrt(T) * size
+
+
+@pytest.mark.parametrize("B", [16, 17, 33])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 6, 7])
+def test_short_sequences_with_the_heads_inside(B, chunks):
+    """[B,T,H,d] rows of 256, 272 and 528 sequences of one span, on either side of the lengths that stay with the kernels that
+    stage rows through LDS: every sequence as in a call of its own, which is on the others."""
+    H, gh, gw, dk, dv = 16, chunks, 63, 36, 72
+    g = torch.Generator(device="cuda").manual_seed(chunks)
+    q, k, v = (torch.randn(B, gh * gw, H, d, generator=g, device="cuda").bfloat16() for d in (dk, dk, dv))
+    la = torch.nn.functional.logsigmoid(torch.randn(B, gh * gw, H, dk, generator=g, device="cuda")) / 16
+    s0 = torch.randn(B, H, dk, dv, generator=g, device="cuda")
+    for scan in (0, 3):
+        out, fin = gla.gla_fwd_layout(q, k, v, la, gh, gw, scan, layout=1, initial_state=s0, out_dtype=torch.float32)
+        for b in (0, B // 2, B - 1):
+            one, last = gla.gla_fwd_layout(*(x[b:b + 1] for x in (q, k, v, la)), gh, gw, scan, layout=1,
+                                           initial_state=s0[b:b + 1], out_dtype=torch.float32)
+            for x, y in ((out[b:b + 1], one), (fin[b:b + 1], last)):
+                rms = float(y.square().mean().sqrt())
+                assert float((x - y).abs().max()) / rms <= 2 * TOL * max(1.0, float(y.abs().max()) / rms / 6), (b, scan)
