@@ -73,27 +73,8 @@ int validate(const void *q, const void *k, const void *v, const float *log_alpha
 // per-work-group prologue; short spans give the 256 compute units more
 // work-groups.  Two resident work-groups per compute unit is the sweet spot
 // measured on MI355X for the output pass.
-int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_cu = 2, bool fp16_engine = false, bool hilo = false) {
+int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_cu = 2, bool fp16_engine = false) {
     int cps = g_opt_chunks_per_span;
-    if (cps <= 0 && hilo) {
-        // bf16 hi/lo kernels with the rows in registers, forward calls: in units of the time one group alone on its compute
-        // unit takes for a chunk of both passes (3 us at 36 / 72 channels on MI355X), a span of c chunks costs 5.3 + 1.06 c
-        // with a unit to itself, 5.85 + 1.92 c where two groups share it (calls of 32 x 64, 64 x 16, 32 x 43 and 16 x 256
-        // chunks, one and two groups a unit: 40.4 / 38.6, 27.8 / 28.9, 33.4 / 34.0, 70.2 / 64.6 us), and what does not fit
-        // at once starts again.  Sequences of up to four chunks are one pass (256 sequences: 16.0 us, in two spans 23.2).
-        double best = 0.0;
-        for (int c = 1; c <= nchunks; ++c) {
-            const long long groups = (long long)bh * ((nchunks + c - 1) / c);
-            const long long rounds = (groups + 511) / 512;
-            const double cost = groups <= 256 ? 5.3 + 1.06 * c : (double)rounds * (4.0 + 1.92 * c) + 1.85;
-            if (cps <= 0 || cost < best - 1e-9) {
-                best = cost;
-                cps = c;
-            }
-            if (groups <= 128) break;     // longer spans only idle more compute units
-        }
-        if (nchunks <= 4) cps = nchunks;
-    }
     if (cps <= 0 && fp16_engine) {
         // fp16 engine: a work-group spends about three chunk periods on its prologue (span-state chain, pipeline
         // fill) whatever the span length, and a chunk period is about 0.62 as long when the group has its compute
@@ -138,6 +119,55 @@ int plan_chunks_per_span(int bh, int nchunks, bool mfma_engine, int groups_per_c
     }
     if (cps > nchunks) cps = nchunks;
     return cps;
+}
+
+// The same for forward calls on the bf16 hi/lo kernels with the rows in registers, from a model of the two passes in us,
+// fitted to calls of 6 to 1024 sequences of 2 to 256 chunks (MI355X, 36 / 72 channels; plain, accumulating and with gate
+// prologue, in both memory orders, and with the output epilogue).  The output pass runs two groups on a compute unit, a group
+// taking 3 us + 4.4 us a chunk (5.1 with the epilogue), and a last round of up to 256 groups, one on a unit, 2.25 us a chunk
+// (3.1).  One span a sequence needs no state pass; else the state pass of all spans but the sequences' last takes three groups
+// a unit, 5 us + 4 us a chunk, and no less than 0.39 of the time a chunk however few they are; of up to 3 chunks, on the
+// staged kernels, two groups a unit, 6.4 us + 2.1 us a chunk.  0.1 us for each span that is chained.  Plans come out within 0.6 %
+// of the fastest on average (15 % at most), those of the rule above within 4.5 %: 256 sequences of 16 chunks 43 us in one span,
+// 58 in two, with the epilogue 58 and 65; 320 of 16 chunks with it 81 in one, 96 in three; 32 of 64 43.3 in spans of 4, 45.5 of 5.
+// Without the epilogue gla_bwd_reuse may walk back over the same spans, which suits a group a compute unit: plans of more
+// groups have to be ahead by 3 % (6 % of up to 3 chunks, but for a few single chunks more than units: 32 sequences of 25 chunks,
+// forward 25.6 us in spans of two, 26.0 of four, but the whole step 74.9 and 70.4), and fewer than 96 sequences are cut (80 of 6
+// chunks 18.8 us in one span, 18.0 in three, the whole step 61 and 49).  Plans of several rounds have to be ahead by 8 %: column scans
+// lose more to the second round than the model knows (48 sequences of 64 chunks in 768 spans 73 us, in 240 67).
+int hilo_chunks_per_span(int bh, int nchunks, bool epilogue) {
+    // (up to four chunks: one launch.  128 sequences of 4: 14.9 us, in four spans 19.5, with the epilogue 19.0 and 21.8; of few
+    // sequences it is as good, 16: 13.3 and 14.1, with the epilogue 18.1 and 16.1)
+    if (nchunks <= 4) return nchunks;
+    const double shared = epilogue ? 5.1 : 4.4, alone = epilogue ? 3.1 : 2.25;
+    auto cost = [&](int c) {
+        const int spans = (nchunks + c - 1) / c;
+        const long long out = (long long)bh * spans, state = (long long)bh * (spans - 1);
+        double t = (double)(out / 512) * (3.0 + shared * c);
+        if (out % 512 != 0) t += 3.0 + (out % 512 <= 256 ? alone : shared) * c;
+        if (spans == 1) return t;
+        const int resident = c >= 4 ? 768 : 512;
+        const double start = c >= 4 ? 5.0 : 6.4, chunk = c >= 4 ? 4.0 : 2.1, least = c >= 4 ? 0.39 : 0.5;
+        const double rest = (double)(state % resident) / resident;
+        t += (double)(state / resident) * (start + chunk * c) + 0.1 * spans;
+        if (rest > 0.0) t += start + chunk * (rest > least ? rest : least) * c;
+        double ahead = 0.0;
+        if (!epilogue && out > 256) ahead = out > 512 ? 0.08 : (c >= 4 ? 0.03 : (c == 1 && out <= 304 ? 0.0 : 0.06));
+        return t + ahead * (t + 5.0);       // (5 us: what every call takes)
+    };
+    int best = 0;
+    double best_cost = 0.0;
+    const long long chunks = (long long)bh * nchunks;
+    for (long long c = (chunks + 1535) / 1536; c <= nchunks; ++c) {
+        if (c == nchunks && bh < 96 && !epilogue && best > 0) break;
+        const double t = cost((int)c);
+        if (best == 0 || t < best_cost) {
+            best_cost = t;
+            best = (int)c;
+        }
+        if (bh * ((nchunks + c - 1) / c) <= 128) break;     // longer spans only idle more compute units
+    }
+    return best > 0 ? best : nchunks;        // (more than 1536 sequences)
 }
 
 // Engine for the span passes (p.qkv_dtype, sizes and strides must be set) and the span plan with its workspace.
@@ -192,9 +222,11 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     }
     int cps = !use_mfma && p.r_pre == nullptr && g_opt_chunks_per_span <= 0
                   ? recurrent_chunks_per_span(p, (long long)(max_spans < (size_t)nchunks ? max_spans : nchunks))
+              : hilo && !fast && g_opt_chunks_per_span <= 0
+                  ? hilo_chunks_per_span(p.B * p.H, nchunks, p.r_pre != nullptr)
                   : plan_chunks_per_span(p.B * p.H, nchunks, use_mfma,
-                                         fast ? fast_groups_per_cu(p) : (use_mfma ? bwd_groups : 2), fast, hilo && !fast);
-    // that cost model may take more spans than are resident at once; where their states do not fit, the plan without it
+                                         fast ? fast_groups_per_cu(p) : (use_mfma ? bwd_groups : 2), fast);
+    // that model may take more spans than are resident at once; where their states do not fit, the plan without it
     if (hilo && !fast && (size_t)((nchunks + cps - 1) / cps) > max_spans)
         cps = plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p));
     // A last span of one ragged chunk: some of the fp16 engine's lanes see no token in it, so it raises the flag of
@@ -210,7 +242,8 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     const bool apart = p.scan_dir >= GLA_SCAN_COL_FWD || p.st_k != p.dk;
     const bool large = hilo && apart && p.z_gate == nullptr && g_opt_chunks_per_span <= 0 && (long long)bh * nchunks >= 3000;
     if (fast && g_opt_engine != GLA_ENGINE_MFMA_FP16 && (ragged_span || large)) {
-        const int other = plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p), false, hilo);
+        const int other = hilo && g_opt_chunks_per_span <= 0 ? hilo_chunks_per_span(p.B * p.H, nchunks, p.r_pre != nullptr)
+                                                             : plan_chunks_per_span(p.B * p.H, nchunks, true, mfma_groups_per_cu(p));
         if (plan_workspace_bytes(bh, (size_t)((nchunks + other - 1) / other), p.dk, p.dv) <= ws_limit) {
             fast = false;
             *use_fast = false;

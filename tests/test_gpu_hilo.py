@@ -144,6 +144,23 @@ def test_gate_of_exactly_zero(engine, step):
         assert bool(torch.isfinite(fused).all()) and bool(torch.isfinite(fin).all())
 
 
+@pytest.mark.parametrize("B,chunks", [(16, 16), (17, 16), (20, 8), (24, 25), (40, 64)])
+def test_many_sequences_are_walked_in_one_pass(B, chunks):
+    """Calls of more sequences than compute units: the state pass that several spans a sequence would need costs more than what
+    they would gain (272 sequences of 16 chunks 65 us in one span, 75 in three), so nothing is left in the workspace."""
+    H, gh, gw, dk, dv = 16, chunks, 64, 36, 72
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn(B, H, gh * gw, d, generator=g, device="cuda").bfloat16() for d in (dk, dk, dv))
+    la = torch.full((B, H, gh * gw, dk), -0.05, device="cuda")
+    ws = torch.full((gla.gla_fwd_workspace_bytes(B, H, gh * gw, dk, dv, gla.DT_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+    gla.gla_fwd_layout(q, k, v, la, gh, gw, 0, workspace=ws)
+    written = int((ws != 0xFF).sum())
+    assert written == 0
+    gla.gla_fwd_fused(q, k, v, la.bfloat16(), 16.0, gh, gw, 0, r_pre=v, workspace=ws)
+    written = int((ws != 0xFF).sum())
+    assert written == 0
+
+
 @pytest.mark.parametrize("cps", [1, 2, 3, 4, 5, 9, 10])
 @pytest.mark.parametrize("scan,layout", [(1, 0), (2, 0), (0, 1), (3, 1)])
 def test_lengths_of_spans(cps, scan, layout):
