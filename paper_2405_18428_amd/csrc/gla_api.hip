@@ -235,9 +235,14 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     // fallback, 35 us).
     // The same for large calls of the heads that have the hi/lo kernels with the rows in registers, where the rows of
     // neighbouring scan steps lie apart (column scans, [B,T,H,d]): lines fetched more than once bound either engine there, and
-    // these need no launch for the range fallback (16 sequences of 16384 tokens, column scan: fp16 94.4 us, hi/lo 90.3, from
-    // one buffer set 82.1 and 79.5, with bf16 results 87.8 and 83.5; [B,T,H,d] 97.7 and 90.3).  A row scan of [B,H,T,d] gains
-    // nothing (71.6 and 71.6; from one buffer set 56.9 and 60.2, with bf16 results 64.8 and 66.4), nor do smaller calls.
+    // these need no launch for the range fallback.  Time of the fp16 kernels over that of these, column scans and [B,T,H,d],
+    // results of both types (sequences x chunks):
+    //     16 x 192 1.08 to 1.12, 16 x 256 1.05 to 1.10, 32 x 100 0.98 to 1.01, 32 x 128 1.07 to 1.08, 48 x 64 0.97 to 1.02,
+    //     48 x 100 1.07 to 1.09, 64 x 50 0.95 to 0.99, 64 x 64 1.08 to 1.09, 96 x 36 1.07 to 1.09, 128 x 25 0.96 to 1.01,
+    //     128 x 36 1.07 to 1.09, 192 x 25 and 256 x 16 1.4, 512 x 8 1.08 to 1.12.
+    // Below 3000 chunks it goes either way (16 x 100, 16 x 128, 32 x 64 0.93 to 0.99; 16 x 25, 48 x 50, 64 x 8, 96 x 25 1.08 to
+    // 1.13; 64 x 16 1.02), by whether the fp16 plan is one long span a compute unit; those calls stay on the fp16 kernels.  So
+    // does a row scan of [B,H,T,d] (16 x 256 1.01, from one buffer set 0.95, with bf16 results 0.98).
     const bool ragged_span = p.T % kChunk != 0 && (nchunks - 1) % cps == 0;
     const bool apart = p.scan_dir >= GLA_SCAN_COL_FWD || p.st_k != p.dk;
     const bool large = hilo && apart && p.z_gate == nullptr && g_opt_chunks_per_span <= 0 && (long long)bh * nchunks >= 3000;

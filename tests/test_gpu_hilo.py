@@ -214,3 +214,26 @@ def test_short_sequences_with_the_heads_inside(B, chunks):
             for x, y in ((out[b:b + 1], one), (fin[b:b + 1], last)):
                 rms = float(y.square().mean().sqrt())
                 assert float((x - y).abs().max()) / rms <= 2 * TOL * max(1.0, float(y.abs().max()) / rms / 6), (b, scan)
+
+
+@pytest.mark.parametrize("scan,out_dtype", [(0, torch.float32), (3, torch.bfloat16)])
+def test_large_call_with_the_heads_inside(scan, out_dtype):
+    """3024 chunks of [B,T,H,d] rows leave the fp16 kernels for these in either kind of scan, and the backward call finds the
+    span states on the plan that this choice gives."""
+    from oracle import gla_oracle
+    gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
+    B, H, gh, gw, dk, dv = 3, 16, 63, 64, 36, 72
+    d = gi.make_inputs(B, H, gh * gw, dk, dv, "bf16", seed=3)
+    ref, ref_fin = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, scan)
+    t = [x.transpose(1, 2).contiguous() for x in [upload(d, n) for n in ("q", "k", "v")] + [torch.from_numpy(d["log_alpha"]).cuda()]]
+    ws = torch.full((gla.gla_fwd_workspace_bytes(B, H, gh * gw, dk, dv, gla.DT_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+    out, fin = gla.gla_fwd_layout(*t, gh, gw, scan, layout=1, out_dtype=out_dtype, workspace=ws)
+    rms = np.sqrt(np.mean(ref ** 2))
+    tol = TOL * max(1.0, np.abs(ref).max() / rms / 6) + (2.0 ** -8 * np.abs(ref).max() / rms if out_dtype == torch.bfloat16 else 0.0)
+    assert np.abs(out.float().transpose(1, 2).cpu().numpy() - ref).max() / rms <= tol
+    assert np.abs(fin.cpu().numpy() - ref_fin).max() / np.sqrt(np.mean(ref_fin ** 2)) <= TOL
+    w = torch.from_numpy(np.random.default_rng(9).standard_normal((B, gh * gw, H, dv)).astype(np.float32)).bfloat16().cuda()
+    own = gla.gla_bwd_layout(*t, w, gh, gw, scan, layout=1)
+    got = gla.gla_bwd_layout(*t, w, gh, gw, scan, layout=1, fwd_workspace=ws)
+    for g, r in zip(got[:3], own[:3]):      # (two sums over other spans)
+        assert float((g - r).abs().max() / r.square().mean().sqrt()) <= 2 * TOL * max(1.0, float(r.abs().max() / r.square().mean().sqrt()) / 6)
