@@ -222,7 +222,6 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
         }
     };
 
-    const float least_z = FUSE ? kLeastGate2 / p.inv_tau : 0.f;     // (kLeastGate2 as a pre-activation)
     auto ring = [](int x) { return x % 3; };
     // prefix sums of log2(alpha) of chunk x inside this wave's tile; tile totals to LDS
     auto scan = [&](int x, const GateRow &la) {
@@ -230,7 +229,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
             // log2(alpha) = log2(sigmoid(z)) / tau = (min(t, 0) - log2(1 + 2^-|t|)) / tau with t = z log2(e)
             auto gate1 = [&](float z) {
                 const float t = z * kLog2e;
-                return (__builtin_amdgcn_fmed3f(t, least_z, 0.f) - __builtin_amdgcn_logf(1.f + exp2_fast(-fabsf(t)))) * p.inv_tau;
+                return (fminf(t, 0.f) - __builtin_amdgcn_logf(1.f + exp2_fast(-fabsf(t)))) * p.inv_tau;
             };
 #pragma unroll
             for (int u = 0; u < 2; ++u)
@@ -250,9 +249,9 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
             for (int e = 0; e < DT; ++e) r_b[8 + e] = fmaxf(la.t[e] * kLog2e, kLeastGate2);
         }
         if constexpr (FUSE) {     // (a row that is not there decays by nothing; the gate of z = 0 is not 1)
-            const bool valid = row_is_token(x);
+            const float least = row_is_token(x) ? kLeastGate2 : 0.f;      // (gates are at most 0)
 #pragma unroll
-            for (int i = 0; i < NV; ++i) r_b[i] = valid ? r_b[i] : 0.f;
+            for (int i = 0; i < NV; ++i) r_b[i] = fmaxf(r_b[i], least);
             row_scan16x4(r_b[0], r_b[1], r_b[2], r_b[3]);
             row_scan16x4(r_b[4], r_b[5], r_b[6], r_b[7]);
         } else {
