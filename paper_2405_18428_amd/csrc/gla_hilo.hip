@@ -45,11 +45,15 @@ namespace {
 template <int N>
 using int_c = std::integral_constant<int, N>;
 
-template <bool OUT, int DT, int NDV16, bool FUSE>
+// What the heads come to: DT groups of four tail channels (33 .. 36), NDV16 tiles of 16 value columns.  (Smaller heads leave the
+// rest of them empty, see hilo_kernels_cover.)
+constexpr int DT = 1, NDV16 = 5;
+
+template <bool OUT, bool FUSE>
 struct HLayout {
     static_assert(64 + 16 * DT <= 80 && 16 * NDV16 <= 80, "rows of 160 bytes");
     static constexpr int NV = 8 + DT;                         // gate values per lane and chunk
-    static constexpr int kTotStride = DT == 0 ? 8 : 12;       // floats per (tile, g) of the tile totals
+    static constexpr int kTotStride = 12;                     // floats per (tile, g) of the tile totals
     static constexpr int kRow = 80, kVRow = 80;               // bf16 per row of k~ and P, of v (see swz)
     static constexpr int kTotBuf = 4 * 4 * kTotStride;        // floats per chunk: [tile][g][NV]
     static constexpr int oTot = 0;                            // three chunks
@@ -67,7 +71,7 @@ struct HLayout {
 
 // Which state tiles (tile t = row tile t % NCT of column tile t / NCT) a wave owns.  A wave's outputs cost more the later
 // its tokens are (causal tiles), so the early waves own most of the state; in the state pass they share it evenly.
-template <bool OUT, int DT, int NDV16>
+template <bool OUT>
 struct Owned {
     static constexpr int NCT = 2 + DT, kTiles = NCT * NDV16;
     __host__ __device__ static constexpr int start(int w) {
@@ -86,10 +90,10 @@ struct Owned {
 // FUSE = the gate prologue (gates from bf16 pre-activations) and, in the output pass, the optional epilogue.
 // ACC = the output pass adds its rows to the fp32 rows already in `out`.
 // SHIFT = p.gate_shift: a step uses the gate of the token visited a step earlier.
-template <bool OUT, int DT, int NDV16, int MINW, bool FUSE, bool ACC, bool SHIFT, typename TOut>
+template <bool OUT, int MINW, bool FUSE, bool ACC, bool SHIFT, typename TOut>
 __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
-    using L = HLayout<OUT, DT, NDV16, FUSE && OUT>;
-    using OW = Owned<OUT, DT, NDV16>;
+    using L = HLayout<OUT, FUSE && OUT>;
+    using OW = Owned<OUT>;
     constexpr int NV = L::NV, NCT = 2 + DT, RS = L::kRow, VS = L::kVRow, TS = L::kTotStride;
     constexpr int NVP = (2 * NDV16 + 3) / 4;          // 16-byte pieces of a v row per lane
     constexpr int NX = NDV16;
@@ -175,24 +179,23 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
     uint32_t chb[2];                     // byte offset of the lane's units in a bf16 row
 #pragma unroll
     for (int u = 0; u < 2; ++u) chb[u] = 16 * u + 4 * g < dk ? 2u * (uint32_t)(16 * u + 4 * g) : kNowhere / 2;
-    constexpr int DT1 = DT > 0 ? DT : 1;
-    uint32_t tcb[DT1];                   // the same for the tail channels
+    uint32_t tcb[DT];                   // the same for the tail channels
 #pragma unroll
     for (int e = 0; e < DT; ++e) tcb[e] = 32 + 4 * e + g < dk ? 2u * (uint32_t)(32 + 4 * e + g) : kNowhere / 2;
     using GatePiece = std::conditional_t<FUSE, u32x2, f32x4>;
     using GateTail = std::conditional_t<FUSE, uint16_t, float>;
     struct GateRow {
         GatePiece u[2];
-        GateTail t[DT1];
+        GateTail t[DT];
     };
     struct ActRow {
         u32x2 u[2];
-        uint32_t t[DT1];
+        uint32_t t[DT];
     };
     GateRow r_la;
     ActRow r_q, r_k;
     u32x4 r_v[NVP];
-    float r_b[8 + DT1];                  // scanned gates (log2, prefix inside the 16-token tile)
+    float r_b[8 + DT];                  // scanned gates (log2, prefix inside the 16-token tile)
 
     auto issue_la = [&](GateRow &dst, int step, int tk) {
         if constexpr (SHIFT) tk = scan_token(p.scan_dir, max(min(step, s_end - 1) - 1, 0), T, p.grid_h, p.grid_w);
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
     auto gate = [&](auto wave_c, int x, QFrag &qn) {
         constexpr int W = decltype(wave_c)::value;
         const float *tot = s_tot + ring(x) * L::kTotBuf + g * TS;        // + tile * 4 * TS
-        float off[8 + DT1];
+        float off[8 + DT];
         if constexpr (W != 2) {
             const float *t1 = tot + (W == 3 ? 2 : 1) * 4 * TS;
 #pragma unroll
@@ -297,7 +300,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
         }
         uint16_t *krow = s_k + (x & 1) * SET + (16 * W + lm) * RS;
         qn.t = u32x4{0, 0, 0, 0};
-        float eq[8 + DT1], ek[8 + DT1];
+        float eq[8 + DT], ek[8 + DT];
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const float ex = W == 2 ? r_b[i] : (W == 3 ? r_b[i] + off[i] : r_b[i] - off[i]);
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
         const float *t_c = s_tot + ring(c + 3) * L::kTotBuf;           // totals of chunk c
         const float *t_n = s_tot + ring(c + 1) * L::kTotBuf;           // totals of chunk c + 1
         f32x4 fac[2];
-        float fact[DT1];
+        float fact[DT];
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) {
             bool used = false;
@@ -526,7 +529,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
                 constexpr int NT_LO = t_lo / NCT, NT_HI = (t_hi - 1) / NCT;
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    u32x4 kf[2 + 2 + DT1];        // hi of ct 0, 1; lo of ct 0, 1; tails
+                    u32x4 kf[2 + 2 + DT];        // hi of ct 0, 1; lo of ct 0, 1; tails
 #pragma unroll
                     for (int ct = 0; ct < NCT; ++ct) {
                         bool used = false;
@@ -588,7 +591,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
                         d[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
                     }
 #pragma unroll
-                    for (int m = 0; m < 4 + (DT > 0 ? 1 : 0); ++m)
+                    for (int m = 0; m < 5; ++m)
 #pragma unroll
                         for (int jt = 0; jt <= W; ++jt)
                             d[jt] = mfma(m == 4 ? kt[jt] : (m < 2 ? kh[jt] : kl[jt]), m == 4 ? qf.t : ((m & 1) ? qf.l : qf.h), d[jt]);
@@ -617,7 +620,7 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
                         pt[i] = tail_frag(prow + 64 + (4 * g ^ swz));
                     }
 #pragma unroll
-                    for (int m = 0; m < 4 + (DT > 0 ? 1 : 0); ++m)
+                    for (int m = 0; m < 5; ++m)
 #pragma unroll
                         for (int i = 0; i < GX; ++i)
                             if (x0 + i < NX)
@@ -725,11 +728,11 @@ __global__ __launch_bounds__(256, MINW) void hilo_span_kernel(Params p) {
     if (!OUT && tid < dk) p.ws_lgam[((size_t)bh * p.nspans + sp) * dk + tid] = lg_sum * kLn2;
 }
 
-template <bool OUT, int DT, int NDV16, bool FUSE, bool ACC, bool SHIFT, typename TOut>
+template <bool OUT, bool FUSE, bool ACC, bool SHIFT, typename TOut>
 hipError_t launch_one(const Params &p, hipStream_t stream) {
-    using L = HLayout<OUT, DT, NDV16, FUSE && OUT>;
+    using L = HLayout<OUT, FUSE && OUT>;
     constexpr int MINW = OUT ? 2 : 3;
-    auto kernel = hilo_span_kernel<OUT, DT, NDV16, MINW, FUSE, ACC, SHIFT, TOut>;
+    auto kernel = hilo_span_kernel<OUT, MINW, FUSE, ACC, SHIFT, TOut>;
     const int spans = (!OUT && p.chain_in_output) ? p.nspans - 1 : p.nspans;
     static std::atomic<bool> configured[kMaxDevices] = {};  // per instantiation and device
     {
@@ -743,26 +746,10 @@ hipError_t launch_one(const Params &p, hipStream_t stream) {
     });
 }
 
-template <int DT, int NDV16>
-hipError_t launch_cls(const Params &p, SpanMode mode, hipStream_t stream) {
-    const bool fuse = p.z_gate != nullptr, bf16 = p.out_dtype == GLA_DT_BF16;
-    if (mode == kModeState) {
-        if (fuse) return launch_one<false, DT, NDV16, true, false, false, float>(p, stream);
-        return p.gate_shift ? launch_one<false, DT, NDV16, false, false, true, float>(p, stream)
-                            : launch_one<false, DT, NDV16, false, false, false, float>(p, stream);
-    }
-    if (fuse)
-        return bf16 ? launch_one<true, DT, NDV16, true, false, false, uint16_t>(p, stream)
-                    : launch_one<true, DT, NDV16, true, false, false, float>(p, stream);
-    if (p.accumulate) return launch_one<true, DT, NDV16, false, true, false, float>(p, stream);   // host checks fp32 out
-    if (p.gate_shift) return launch_one<true, DT, NDV16, false, false, true, float>(p, stream);   // (backward: fp32 rows)
-    return bf16 ? launch_one<true, DT, NDV16, false, false, false, uint16_t>(p, stream)
-                : launch_one<true, DT, NDV16, false, false, false, float>(p, stream);
-}
-
 }  // namespace
 
-// One-sided gates, the DiG-XL/2 heads (36 / 72) and what their registers hold.  Heads of up to 32 / 64 channels stay with the
+// One-sided gates, the DiG-XL/2 heads (36 / 72) and what their registers hold (launch_mfma_span and launch_mfma_row_read leave
+// the shortest spans of these to the kernels that stage rows through LDS).  Heads of up to 32 / 64 channels stay with the
 // kernels in gla_mfma.hip: a chunk has less to overlap there, and those have an 8-wave form for few groups (6 sequences of 432
 // tokens 14.6 us, here 17.0; backward of 42 sequences of 256 steps 27.8 and 30.0; only calls of more than 256 groups would
 // gain, 24 sequences of 6292 tokens with the epilogue 49.8 and 46.6).
@@ -771,7 +758,19 @@ bool hilo_kernels_cover(const Params &p) {
 }
 
 hipError_t launch_hilo_span(const Params &p, SpanMode mode, hipStream_t stream) {
-    return launch_cls<1, 5>(p, mode, stream);
+    const bool fuse = p.z_gate != nullptr, bf16 = p.out_dtype == GLA_DT_BF16;
+    if (mode == kModeState) {
+        if (fuse) return launch_one<false, true, false, false, float>(p, stream);
+        return p.gate_shift ? launch_one<false, false, false, true, float>(p, stream)
+                            : launch_one<false, false, false, false, float>(p, stream);
+    }
+    if (fuse)
+        return bf16 ? launch_one<true, true, false, false, uint16_t>(p, stream)
+                    : launch_one<true, true, false, false, float>(p, stream);
+    if (p.accumulate) return launch_one<true, false, true, false, float>(p, stream);   // host checks fp32 out
+    if (p.gate_shift) return launch_one<true, false, false, true, float>(p, stream);   // (backward: fp32 rows)
+    return bf16 ? launch_one<true, false, false, false, uint16_t>(p, stream)
+                : launch_one<true, false, false, false, float>(p, stream);
 }
 
 }  // namespace gla
