@@ -75,9 +75,10 @@
  *    below 2^-40: what is left out is at most 2^-40 of what those earlier states
  *    hold.  The bound is relative to the earlier states, not to the sum so far
  *    (a thread whose sum is still exactly zero, e.g. behind a padded tail of
- *    all-zero k or v, does go on: with the two-sided gate the 2^-40 then count from
- *    behind the zeros, with one gate it stops after the group of up to 32 spans that
- *    ended them): sequences whose later spans are many orders
+ *    all-zero k or v, does go on: with the two-sided gate, and in the kernels that the
+ *    heads of 33 to 36 key channels have, the 2^-40 then count from behind the zeros;
+ *    in the others with one gate, which these heads share for their shortest spans, it
+ *    stops after the group of up to 32 spans that ended them): sequences whose later spans are many orders
  *    of magnitude smaller than the earlier ones lose the decayed remainder of
  *    the earlier ones.  GLA_CARRY_KERNEL has no cut-off.
  *

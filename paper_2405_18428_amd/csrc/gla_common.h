@@ -84,8 +84,8 @@ static_assert(sizeof(Params) <= 264, "what only some kernels need belongs into a
 
 // The backward walks of the MFMA engine (mfma_row_read_kernel) take more; the other kernels' arguments stay as they are
 // without them.  The order in which the compiler loads the fields of a larger struct shows in short calls on MI355X: with
-// these fields in Params the 4-wave hi/lo output pass took 0.16 us more a launch (160 sequences of 256 tokens at 36 / 72
-// channels 16.83 us, 16.71 without) and its 8-wave form 0.16 us less (128 sequences 15.78, 15.95).
+// these fields in Params the 4-wave output pass of gla_mfma.hip took 0.16 us more a launch (160 sequences of 256 tokens at
+// 36 / 72 channels, when these ran on it, 16.83 us, 16.71 without) and its 8-wave form 0.16 us less (128 sequences 15.78, 15.95).
 struct WalkParams : Params {
     // the state after every bound_len scan steps, which the walk for dq leaves in ws_bound ([B*H, bounds, dk, dv]) and
     // the reversed walk for dk, dv starts its gate gradients from; and what that walk needs to form them (dlog_alpha;

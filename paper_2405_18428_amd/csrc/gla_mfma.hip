@@ -1075,10 +1075,10 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     // unit); the output pass needs the 256-register budget of 4-wave groups for its operand batches.  It takes 8 waves
     // with that budget where the LDS holds one group per compute unit anyway (two-sided gate, 64 sequences of 1024
     // tokens at 36 / 72: 35.0 -> 30.3 us; 64 / 128 channels, two scan orders summed: 70 -> 57 us a call), or where there
-    // are no more groups than compute units: dk <= 32, 48 sequences of 256 tokens 13.0 -> 12.4 us; at dk = 36, whose ninth
-    // gate unit is then dealt channel by channel, only up to 224 (sequences of 256 tokens, us a call with 4 and 8 waves: 144
-    // groups 16.5 and 16.0, 192 16.9 and 16.5, 224 17.2 and 17.0, 240 17.3 and 17.3, 256 17.4 and 17.6).  With two 8-wave groups per compute unit the 128
-    // registers spill (32 -> 77 us, two 1024 px images).
+    // are no more groups than compute units: dk <= 32, 48 sequences of 256 tokens 13.0 -> 12.4 us; dk = 40 (sequences of 256
+    // tokens, us a call with 4 and 8 waves: 144 groups 17.9 and 16.9, 192 18.2 and 17.4, 256 18.7 and 18.5; of 128 tokens 256
+    // groups 12.5 and 12.0; 33 to 36 channels come here with more groups only).  With two 8-wave groups per compute unit the
+    // 128 registers spill (32 -> 77 us, two 1024 px images at 36 / 72).
     constexpr int NW = (MODE == kModeState) ? 8 : 4;
     // register cap: no tighter than the waves per SIMD that the LDS footprint lets a compute unit hold anyway
     constexpr int kGroupsPerCu = (160 * 1024) / L::kBytes;
@@ -1089,7 +1089,7 @@ hipError_t launch_depth(const Params &p, hipStream_t stream) {
     if constexpr (MODE == kModeOutput && !FUSE) {
         // (the range fallback's groups mostly return at once: fewer waves to start)
         const long long groups = (long long)p.B * p.H * p.nspans;
-        if (kGroupsPerCu < 2 || (NDK8 <= 5 && !p.only_flagged && groups <= (NDK8 <= 4 ? 256 : 224)))
+        if (kGroupsPerCu < 2 || (NDK8 <= 5 && !p.only_flagged && groups <= 256))
             return launch_waves<MODE, NDK8, NDV16, 8, 2, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
     }
     return launch_waves<MODE, NDK8, NDV16, NW, MINW, DEPTH, FUSE, ACC, TOut, BETA>(p, stream);
@@ -1107,7 +1107,7 @@ hipError_t launch_one(const Params &p, hipStream_t stream) {
     return launch_depth<MODE, NDK8, NDV16, 1, FUSE, ACC, TOut, BETA>(p, stream);
 }
 
-// BETA: two-sided gate.  (One-sided calls with 33 to 36 key channels run on the kernels in gla_hilo.hip.)
+// BETA: two-sided gate.
 template <int MODE, int NDK8, int NDV16, bool BETA>
 hipError_t launch_dt(const Params &p, hipStream_t stream) {
     const bool bf16_out = MODE == kModeOutput && p.out_dtype == GLA_DT_BF16;
