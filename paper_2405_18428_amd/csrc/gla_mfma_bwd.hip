@@ -1081,9 +1081,6 @@ hipError_t launch_one(const WalkParams &p, const void *w, float *r, hipStream_t 
     if constexpr (kGroupsPerCu >= 2) {
         if ((long long)p.B * p.H * p.nspans > 256) return launch_waves<NDK8, NDV16, 4, 2, DV, BETA, GS>(p, w, r, stream);
     }
-    if constexpr (NDK8 == 5 && !BETA) {
-        if (hilo_kernels_cover(p)) return launch_waves<NDK8, NDV16, 8, 2, DV, BETA, GS, true>(p, w, r, stream);
-    }
     return launch_waves<NDK8, NDV16, 8, 2, DV, BETA, GS>(p, w, r, stream);
 }
 
@@ -1102,6 +1099,8 @@ hipError_t launch_sizes(const WalkParams &p, const void *w, float *r, hipStream_
 
 }  // namespace
 
+static hipError_t launch_four(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs);
+
 // Same conditions as the forward MFMA engine (bf16 rows, dk % 4 == 0, dv % 8 == 0, 32-bit offsets).
 // with_outputs: also write o_j = q_j S_j (p.q, fp32 rows to p.out).
 hipError_t launch_mfma_row_read(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs) {
@@ -1116,15 +1115,27 @@ hipError_t launch_mfma_row_read(const WalkParams &p, const void *w, float *r, hi
     //     walk for dk, dv  [B,H,T,d] row scans 1: -0.7 %, 2: +0.2, 3: +1.9; column scans 2: -0.8, 3: +0.3, 4: +2.0 (grids 64
     //                      tokens wide 3: -1.0, 4: -0.2, 12: +1.1)
     //                      [B,T,H,d] 1: -4.3 %, 2: -3.9, 4: -1.8, 8: -0.2, 10: +0.2, 16: +1.2
-    // (one chunk: prologues of up to 15 spans that hardly decay, -2.5 %; row scans of two chunks a span +1.3 to +2.8 % from
-    // four spans on, -0.4 to -3.8 with one or two)
+    // and of [B,H,T,d] by spans: one chunk in the walk for dq +0.2 to +5 % with 4 to 9 spans (grids 64 tokens wide, column scans
+    // -0.8 to +0.2), -0.7 to -2.4 with two, -2.5 to -4 with 15 that hardly decay; row scans of two chunks in the walk for dk, dv
+    // +1.3 to +2.8 % from four spans on, -0.4 to -3.8 with one or two.
     const bool heads_inside = p.st_k != p.dk;
     const int chunks = p.span_len / kChunk;
-    const int least = with_outputs ? (heads_inside ? 10 : (p.scan_dir >= GLA_SCAN_COL_FWD ? 4 : (p.nspans > 2 ? 2 : 3))) : (heads_inside ? 4 : 2);
-    if (hilo_kernels_cover(p) && (long long)p.B * p.H * p.nspans <= 256 && chunks >= least)
-        return launch_hilo_walk(p, w, r, stream, with_outputs);
+    int least;
+    if (heads_inside) least = with_outputs ? 10 : 4;
+    else if (!with_outputs) least = p.nspans > 2 && p.nspans <= 10 ? 1 : 2;
+    else least = p.scan_dir >= GLA_SCAN_COL_FWD ? 4 : (p.nspans > 2 ? 2 : 3);
+    if (hilo_kernels_cover(p) && (long long)p.B * p.H * p.nspans <= 256)
+        return chunks >= least ? launch_hilo_walk(p, w, r, stream, with_outputs) : launch_four(p, w, r, stream, with_outputs);
     if (with_outputs) return launch_sizes<true, false>(p, w, r, stream);
     return p.ws_gstate != nullptr ? launch_sizes<false, true>(p, w, r, stream) : launch_sizes<false, false>(p, w, r, stream);
+}
+
+// Short spans of the heads of 33 to 36 channels.  (Last in this file, so that the other kernels stay where they are in the code
+// object: a two-sided training step of 64 sequences of 16 chunks takes 143.2 us then, 143.6 with these in between.)
+static hipError_t launch_four(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs) {
+    if (with_outputs) return launch_waves<5, 5, 8, 2, true, false, false, true>(p, w, r, stream);
+    return p.ws_gstate != nullptr ? launch_waves<5, 5, 8, 2, false, false, true, true>(p, w, r, stream)
+                                  : launch_waves<5, 5, 8, 2, false, false, false, true>(p, w, r, stream);
 }
 
 }  // namespace gla
