@@ -59,7 +59,8 @@
  *    lost or wrong, but finite: later chunks lack it as far as it would not have decayed.
  *  - fp16 MFMA engine (what GLA_ENGINE_AUTO takes for the plain forward pass, and for
  *    gla_fwd_fused without the output epilogue, on bf16 inputs with 17..64 key
- *    channels and more than four chunks, unless the last span of the launch plan would
+ *    channels and more than four chunks, unless the single-launch kernels take the call (see gla_engine), or
+ *    the last span of the launch plan would
  *    be a single chunk of fewer than 64 tokens, or the call is a large column scan or
  *    [B,T,H,d] call of 33 to 36 key channels: such calls run on the bf16 hi/lo kernels, see gla_engine): its operands
  *    cover a decay of at most 2^-11 per key channel over 32 consecutive scan steps
@@ -75,7 +76,7 @@
  *    below 2^-40: what is left out is at most 2^-40 of what those earlier states
  *    hold.  The bound is relative to the earlier states, not to the sum so far
  *    (a thread whose sum is still exactly zero, e.g. behind a padded tail of
- *    all-zero k or v, does go on: with the two-sided gate, and in the kernels that the
+ *    all-zero k or v, does go on: with the two-sided gate, in the single-launch kernels, and in the kernels that the
  *    heads of 33 to 36 key channels have, the 2^-40 then count from behind the zeros;
  *    in the others with one gate, which these heads share for their shortest spans, it
  *    stops after the group of up to 32 spans that ended them): sequences whose later spans are many orders
@@ -123,6 +124,10 @@ typedef enum {
     GLA_OPT_CARRY = 2,           /* gla_carry */
     GLA_OPT_BWD_SPLIT = 3,       /* 0 = the backward pass computes dk and dv of a chunk in one kernel (MFMA engine);
                                     1 = in two kernels (the forward output pass for dv, the row read for dk) */
+    GLA_OPT_LOOK_BACK_POLLS = 5, /* how often a wave of the single-launch forward kernels polls for the state of an earlier span
+                                    before it forms the state entering its own from the inputs (default 32768: tens of
+                                    milliseconds, which only runs out where other work keeps the earlier spans off the
+                                    GPU; 0 = never, for tests) */
     GLA_OPT_RANGE_FALLBACK = 4   /* 1 (default) = after the fp16 engine's passes, the (batch, head) sequences that
                                     left its range are recomputed by the bf16 hi/lo kernel (one more launch, whose
                                     work-groups return at once when no flag is raised); 0 = that launch is skipped
@@ -137,9 +142,14 @@ typedef enum {
                                  chunks before it that the plan's chunks per span divide) runs on the bf16 hi/lo kernels
                                  instead of the fp16 ones, and so does the plain forward pass with 33 to 36 key channels
                                  (or up to 36 and 65 to 80 value columns) of a column scan or of [B,T,H,d] tensors from
-                                 3000 chunks of 64 tokens on, over all batches and heads; in gla_fwd_static only if their plan fits its array */
+                                 3000 chunks of 64 tokens on, over all batches and heads; in gla_fwd_static only if their plan fits its array.
+                                 Of heads of 17 to 36 key channels and 33 to 72 value columns, forward calls with one gate from 48 chunks
+                                 (384 with the output epilogue) up to about 2048 chunks, and larger plain ones of up to 128
+                                 sequences up to 4096, run on kernels with the bf16 hi/lo operands that read their inputs
+                                 once, in one launch (from 4 chunks a sequence on; not with GLA_OPT_CHUNKS_PER_SPAN or
+                                 GLA_CARRY_KERNEL set) */
     GLA_ENGINE_RECURRENT = 1, /* fp32 token-by-token arithmetic inside each span; any dtype, any gates */
-    GLA_ENGINE_MFMA = 2,      /* bf16 hi/lo MFMA chunk form (Sec. 3.5) in every pass; bf16 inputs only */
+    GLA_ENGINE_MFMA = 2,      /* bf16 hi/lo MFMA chunk form (Sec. 3.5) in every pass, or in the one there is; bf16 inputs only */
     GLA_ENGINE_MFMA_FP16 = 3  /* fp16 operands in both passes of the plain forward call and of gla_fwd_fused without
                                  r_pre (producer / consumer waves), the bf16 hi/lo kernel as range fallback;
                                  GLA_ERR_UNSUPPORTED where it does not apply (the output epilogue, other entry

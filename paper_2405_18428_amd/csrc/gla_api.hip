@@ -2,6 +2,7 @@
 // plan, library-owned scratch for gla_fwd, and the timing aid.
 #include <atomic>
 #include <mutex>
+#include <random>
 #include <vector>
 
 #include "gla_common.h"
@@ -18,6 +19,7 @@ std::atomic<int> g_opt_engine{GLA_ENGINE_AUTO};
 std::atomic<int> g_opt_carry{GLA_CARRY_AUTO};
 std::atomic<int> g_opt_bwd_split{0};
 std::atomic<int> g_opt_range_fallback{1};
+std::atomic<int> g_opt_look_back_polls{1 << 15};     // (tens of milliseconds)
 
 // Most spans per (batch, head) that the output pass chains by itself: work-group r reads the r local states
 // before it, so the reads grow with the square of the span count while a carry kernel's grow linearly.
@@ -170,6 +172,42 @@ int hilo_chunks_per_span(int bh, int nchunks, bool epilogue) {
     return best > 0 ? best : nchunks;        // (more than 1536 sequences)
 }
 
+// Bytes of the flags of a single-launch plan (two waves a chunk), which lie behind the sums of log alpha
+size_t onepass_flag_bytes(size_t bh, size_t nspans, int chunks) { return align_up(bh * nspans * 2 * chunks * sizeof(unsigned long long), 256); }
+
+// Chunks a work-group of the single-launch forward kernels (4 or 8), or 0 where the call stays on the others: a span is then that
+// many chunks.  Eight chunks fill a compute unit, so up to 2048 are one round of work-groups, all loads in flight at once.  Time of the
+// two-pass kernels over that of these (36 / 72 channels, sequences x chunks; S: 32 / 64 channels, E: with the epilogue):
+//     spans of 4   16 x 4 1.14 (S 1.11, E 1.18), 128 x 4 1.10, but 192 x 4 1.03 and 0.95 to 0.97 for sums and [B,T,H,d], 256 x 4 0.98;
+//                  16 x 5 1.10, 16 x 16 1.03, 6 x 64 1.12, 32 x 32 1.21, 128 x 8 1.29; E: 32 x 8 0.90, 16 x 24 1.03, 16 x 64 1.16;
+//                  two groups on a unit 96 x 17 1.16 to 1.31
+//     spans of 8   16 x 100 1.20, 32 x 64 1.26 (E 1.33), 128 x 16 1.38, 128 x 5 1.13 but 192 x 5 0.87, 256 x 8 0.93 (E 1.20)
+//     two rounds   32 x 100 1.08, 32 x 128 1.11 (E 1.00), 64 x 64 1.14, 96 x 32 1.00, 16 x 256 1.03 (column scan 1.2), but 64 x 43 0.93,
+//                  128 x 17 0.87, 192 x 16 1.05 (column scan 0.85); three and more 0.87 to 1.11
+// Sequences of up to three chunks, which would leave waves idle, take 0.6 to 0.97.  The fewest chunks of a plain call (48) are where
+// its work-groups begin to count: below, either kernel waits for its launches (16.3 us, 13.7 here), and such calls stay with
+// the fp16 engine.
+int onepass_chunks_per_group(const Params &p, int nchunks) {
+    if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || !onepass_covers(p)) return 0;
+    const long long bh = (long long)p.B * p.H, total = bh * nchunks;
+    const bool epilogue = p.r_pre != nullptr;
+    auto groups = [&](int chunks) { return bh * ((nchunks + chunks - 1) / chunks); };
+    if (nchunks <= 4) return nchunks == 4 && bh <= 128 ? 4 : 0;
+    if (total < (epilogue ? 384 : 48)) return 0;
+    if (groups(4) <= 256) return 4;
+    if (bh > 128) return epilogue && groups(8) <= 256 && (nchunks == 7 || nchunks == 8) ? 8 : 0;
+    if (groups(8) <= 256) return 8;
+    if (groups(4) <= 512) return 4;
+    return groups(8) <= 512 && total >= 2990 && p.z_gate == nullptr ? 8 : 0;
+}
+
+// A value that no earlier call's flags hold, nor (but for one chance in 2^64) memory that never held any
+unsigned long long next_nonce() {
+    static std::atomic<unsigned long long> last{(unsigned long long)std::random_device{}() << 32 | std::random_device{}()};
+    const unsigned long long n = ++last;
+    return n != 0 ? n : ++last;       // (0 is what clears them)
+}
+
 // Engine for the span passes (p.qkv_dtype, sizes and strides must be set) and the span plan with its workspace.
 // use_fast (optional): the caller is the plain forward pass and would take the fp16 output pass where it covers
 // the call; on return, whether it does (the span plan is then sized for that kernel's residency).
@@ -177,7 +215,7 @@ int hilo_chunks_per_span(int bh, int nchunks, bool epilogue) {
 // plain_plan: the plan of the plain forward pass, whatever kernels the call itself runs on (the last scan order of a sum, whose
 // span states gla_bwd_reuse takes on that plan).
 int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use_fast = nullptr,
-                           size_t ws_limit = ~(size_t)0, bool plain_plan = false) {
+                           size_t ws_limit = ~(size_t)0, bool plain_plan = false, int *use_onepass = nullptr) {
     if (g_opt_engine == GLA_ENGINE_RECURRENT) {
         use_mfma = false;
     } else if (g_opt_engine == GLA_ENGINE_MFMA || g_opt_engine == GLA_ENGINE_MFMA_FP16) {
@@ -253,6 +291,17 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
             fast = false;
             *use_fast = false;
             cps = other;
+        }
+    }
+    if (use_onepass != nullptr) {
+        // (without flags a sequence of one span needs no room; the bound over all plans holds these)
+        const int c = use_mfma && g_opt_engine != GLA_ENGINE_MFMA_FP16 ? onepass_chunks_per_group(p, nchunks) : 0;
+        const size_t spans = c > 0 ? (size_t)((nchunks + c - 1) / c) : 1;
+        const bool fits = spans == 1 || plan_workspace_bytes(bh, spans, p.dk, p.dv) + onepass_flag_bytes(bh, spans, c) <= ws_limit;
+        *use_onepass = fits ? c : 0;
+        if (*use_onepass > 0) {
+            cps = c;
+            if (use_fast != nullptr) *use_fast = false;
         }
     }
     p.span_len = cps * kChunk;
@@ -385,7 +434,8 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         Params pf = base;
         pf.scan_dir = scan_dir;
         bool same_engine, fwd_fast = false;
-        if (choose_engine_and_plan(pf, const_cast<void *>(fwd_workspace), same_engine, &fwd_fast) != GLA_OK)
+        int fwd_onepass = 0;
+        if (choose_engine_and_plan(pf, const_cast<void *>(fwd_workspace), same_engine, &fwd_fast, ~(size_t)0, false, &fwd_onepass) != GLA_OK)
             return GLA_ERR_HIP;
         // either way the states are read where they are: the row-read kernel chains local states itself.
         // The walk adopts the forward call's span plan (its output pass may have been sized differently).
@@ -608,9 +658,10 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
     }
 
     bool use_mfma, use_fast = false;
-    st = choose_engine_and_plan(p, workspace, use_mfma, &use_fast, plan_sized_workspace ? ws_bytes : ~(size_t)0, accumulate == 2);
+    int use_onepass = 0;
+    st = choose_engine_and_plan(p, workspace, use_mfma, &use_fast, plan_sized_workspace ? ws_bytes : ~(size_t)0, accumulate == 2, &use_onepass);
     if (st != GLA_OK) return st;
-    if (plan_sized_workspace && ws_bytes < plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv))
+    if (plan_sized_workspace && use_onepass == 0 && ws_bytes < plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv))
         return GLA_ERR_WORKSPACE;
     auto span = [&](SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
@@ -625,6 +676,17 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
 
     hipError_t e = hipSuccess;
     mark(0);
+    if (use_onepass > 0) {
+        mark(1);
+        mark(2);
+        OnePassParams pw{p};
+        pw.flags = reinterpret_cast<unsigned long long *>(p.ws_lgam_b);
+        pw.nonce = next_nonce();
+        pw.polls = g_opt_look_back_polls;
+        e = launch_onepass(pw, use_onepass, stream);
+        mark(3);
+        return e == hipSuccess ? GLA_OK : GLA_ERR_HIP;
+    }
     if (p.nspans > 1) {
         e = use_fast ? launch_fast_state(p, stream) : span(kModeState);
         if (e != hipSuccess) return GLA_ERR_HIP;
@@ -676,8 +738,10 @@ size_t static_plan_bytes(int B, int H, int T, int dk, int dv) {
     bool use_mfma;
     alignas(256) static unsigned char layout_base[256];   // only offsets from it are formed, nothing is accessed
     bool use_fast = false;
-    if (choose_engine_and_plan(p, layout_base, use_mfma, &use_fast, kStaticScratchBytes) != GLA_OK) return ~(size_t)0;
-    return plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv);
+    int use_onepass = 0;
+    if (choose_engine_and_plan(p, layout_base, use_mfma, &use_fast, kStaticScratchBytes, false, &use_onepass) != GLA_OK) return ~(size_t)0;
+    // (a single-launch plan has been compared with the room, which its flags need as well)
+    return use_onepass > 0 ? 0 : plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv);
 }
 
 }  // namespace
@@ -999,6 +1063,10 @@ int gla_set_option(int option, int value) {
         if (value < 0 || value > 1) return GLA_ERR_SHAPE;
         g_opt_bwd_split = value;
         return GLA_OK;
+    case GLA_OPT_LOOK_BACK_POLLS:
+        if (value < 0) return GLA_ERR_SHAPE;
+        g_opt_look_back_polls = value;
+        return GLA_OK;
     case GLA_OPT_RANGE_FALLBACK:
         if (value < 0 || value > 1) return GLA_ERR_SHAPE;
         g_opt_range_fallback = value;
@@ -1015,6 +1083,7 @@ int gla_get_option(int option) {
     case GLA_OPT_CARRY: return g_opt_carry;
     case GLA_OPT_BWD_SPLIT: return g_opt_bwd_split;
     case GLA_OPT_RANGE_FALLBACK: return g_opt_range_fallback;
+    case GLA_OPT_LOOK_BACK_POLLS: return g_opt_look_back_polls;
     default: return -1;
     }
 }

@@ -99,6 +99,13 @@ struct WalkParams : Params {
     float *dlog_alpha, *dlog_beta;
 };
 
+// The single-launch forward kernels (gla_onepass.hip): a flag per wave of each span, the value that says a span's state is there
+// (another one for every call), and how often a wave polls for it.
+struct OnePassParams : Params {
+    unsigned long long *flags, nonce;
+    int polls;
+};
+
 // first scan step of span sp, and the step after its last
 __host__ __device__ inline int span_begin(const Params &p, int sp) {
     const int s = sp * p.span_len - p.span_shift;
@@ -220,6 +227,9 @@ bool mfma_engine_supports(const Params &p);
 // the kernels of the bf16 hi/lo engine that hold a chunk's rows in registers (gla_hilo.hip; the others: gla_mfma.hip)
 bool hilo_kernels_cover(const Params &p);
 hipError_t launch_hilo_span(const Params &p, SpanMode mode, hipStream_t stream);
+// the single-launch forward kernels, of 4 or 8 chunks a work-group (gla_onepass.hip)
+bool onepass_covers(const Params &p);
+hipError_t launch_onepass(const OnePassParams &p, int chunks, hipStream_t stream);
 hipError_t launch_hilo_walk(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs);  // (gla_hilo_bwd.hip)
 // fp16 output pass with the pipelined chunk loop (gla_fast.hip): what it covers, how many of its work-groups a
 // compute unit holds, and its launcher

@@ -1,0 +1,132 @@
+"""The single-launch forward kernels (a span's chunks on chip from the first load to the last store, states handed on through
+flags) at their edges: head sizes around the 16-channel units, the tail and the 16-column tiles, spans of 4 and of 8 chunks, ragged
+last chunks and spans, grids whose columns are shorter than a tile, both memory orders, an initial state, slow gates (every
+earlier span is looked at), sums over scan orders, gate prologue and epilogue; a wait that runs out, and replays of a graph.
+
+Tolerance: as for the other kernels with split operands, 2e-4 of the RMS (an operand pair carries 16 bits, a product is off by at
+most 4 * 2^-17 of itself, and an output's largest value is about six times its RMS); a bf16 store adds at most half a unit of its
+eighth bit, 2^-8 of the largest value.  The epilogue divides rows by their spread: 2e-3."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2405_18428_amd as gla
+from paper_2405_18428_amd import inputs as gi
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-4
+POLLS = 1 << 15
+
+
+@pytest.fixture(autouse=True)
+def defaults():
+    yield
+    gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
+    gla.gla_set_option(gla.OPT_LOOK_BACK_POLLS, POLLS)
+
+
+def upload(d, *names):
+    f = lambda n: torch.from_numpy(d[n + "_bits"].view(np.int16)).cuda().view(torch.bfloat16)
+    return [torch.from_numpy(d[n]).cuda() if n == "log_alpha" else f(n) for n in names]
+
+
+def near(got, want, bf16=False, tol=TOL):
+    got, rms, top = got.float().cpu().numpy(), np.sqrt(np.mean(want ** 2)), np.abs(want).max()
+    assert np.abs(got - want).max() / rms <= tol * max(1.0, top / rms / 6) + (2.0 ** -8 * top / rms if bf16 else 0.0)
+
+
+# (sequences as B x H, grid): one span; spans of 4 with a ragged last chunk or a last span of one chunk; the same of 8 (more than
+# 256 groups of 4); two groups on a compute unit; two rounds of groups
+PLANS = [(2, 2, 16, 16), (2, 3, 50, 13), (2, 3, 3, 219), (1, 6, 41, 16), (8, 16, 5, 91), (4, 16, 64, 17), (6, 16, 25, 43), (2, 16, 100, 65)]
+
+
+@pytest.mark.parametrize("dk,dv,B,H,gh,gw", [(*h, *c) for h in ((36, 72), (32, 64)) for c in PLANS] +
+                         [(*h, *c) for h in ((20, 40), (36, 40), (28, 72)) for c in PLANS[:5]])
+def test_plans_and_heads(dk, dv, B, H, gh, gw):
+    from oracle import gla_oracle
+    d = gi.make_inputs(B, H, gh * gw, dk, dv, "bf16", seed=dk + dv + gh, z_mean=3.0 if gw % 2 else 0.0)
+    s0 = np.random.default_rng(5).standard_normal((B, H, dk, dv)).astype(np.float32)
+    for scan, layout, out_dtype in ((1, 0, torch.float32), (2, 1, torch.bfloat16)):
+        ref, ref_fin = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, scan, initial_state=s0)
+        t = upload(d, "q", "k", "v", "log_alpha")
+        if layout == 1:
+            t = [x.transpose(1, 2).contiguous() for x in t]
+        out, fin = gla.gla_fwd_layout(*t, gh, gw, scan, layout=layout, initial_state=torch.from_numpy(s0).cuda(), out_dtype=out_dtype)
+        near(out if layout == 0 else out.transpose(1, 2), ref, out_dtype == torch.bfloat16)
+        near(fin, ref_fin)
+
+
+@pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
+@pytest.mark.parametrize("B,H,gh,gw,scans", [(2, 3, 50, 13, (0, 3)), (2, 16, 64, 64, (1, 2))])
+def test_sums_and_their_states(B, H, gh, gw, scans, dk, dv):
+    """Sums over scan orders; the last order's span states serve the backward call."""
+    from oracle import gla_oracle
+    d = gi.make_inputs(B, H, gh * gw, dk, dv, "bf16", seed=6)
+    t = upload(d, "q", "k", "v", "log_alpha")
+    ws = torch.full((gla.gla_fwd_workspace_bytes(B, H, gh * gw, dk, dv, gla.DT_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = gla.gla_fwd_multi(*t, gh, gw, scan_dirs=scans, workspace=ws)
+    near(out, sum(gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, s)[0] for s in scans))
+    w = torch.randn(B, H, gh * gw, dv, device="cuda").bfloat16()
+    for got, own in zip(gla.gla_bwd(*t, w, gh, gw, scans[-1], fwd_workspace=ws)[:3], gla.gla_bwd(*t, w, gh, gw, scans[-1])[:3]):
+        near(got, own.cpu().numpy(), tol=2 * TOL)       # (two sums over other spans)
+
+
+@pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64), (20, 40)])
+@pytest.mark.parametrize("B,H,gh,gw", [(2, 3, 16, 15), (4, 16, 40, 13), (8, 16, 23, 37), (16, 16, 8, 61)])
+def test_gate_prologue_and_epilogue(B, H, gh, gw, dk, dv):
+    from oracle import gla_oracle_fused as fo
+    d = gi.make_fused_inputs(B, H, gh * gw, dk, dv, "bf16", seed=7)
+    q, k, v, z, r = upload(d, "q", "k", "v", "z", "r")
+    lnw, lnb = (torch.from_numpy(d[n]).cuda() for n in ("ln_w", "ln_b"))
+    for scan, out_dtype in ((0, torch.float32), (3, torch.bfloat16)):
+        ref, ref_fin = fo.gla_fused(d["q"], d["k"], d["v"], d["z"], 16.0, None, None, None, 1e-5, gh, gw, scan)
+        gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_MFMA)
+        out, fin = gla.gla_fwd_fused(q, k, v, z, 16.0, gh, gw, scan, out_dtype=out_dtype)
+        near(out, ref, out_dtype == torch.bfloat16)
+        near(fin, ref_fin)
+        ref, _ = fo.gla_fused(d["q"], d["k"], d["v"], d["z"], 16.0, d["r"], d["ln_w"], d["ln_b"], 1e-5, gh, gw, scan)
+        out, fin = gla.gla_fwd_fused(q, k, v, z, 16.0, gh, gw, scan, r_pre=r, ln_weight=lnw, ln_bias=lnb, ln_eps=1e-5, out_dtype=out_dtype)
+        near(out, ref, out_dtype == torch.bfloat16, tol=2e-3)
+        near(fin, ref_fin)
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("scan", [0, 3])
+def test_a_wait_that_runs_out(scan, fused):
+    """No polls at all: what a span does not find at once it forms from the inputs."""
+    from oracle import gla_oracle
+    B, H, gh, gw, dk, dv = 1, 7, 20, 33, 36, 72
+    d = gi.make_fused_inputs(B, H, gh * gw, dk, dv, "bf16", seed=8)
+    gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_MFMA)
+    gla.gla_set_option(gla.OPT_LOOK_BACK_POLLS, 0)
+    q, k, v, z = upload(d, "q", "k", "v", "z")
+    la = torch.nn.functional.logsigmoid(z.float()) / 16
+    ref, ref_fin = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], la.cpu().numpy(), gh, gw, scan)
+    for _ in range(2):
+        out, fin = gla.gla_fwd_fused(q, k, v, z, 16.0, gh, gw, scan) if fused else gla.gla_fwd_ex(q, k, v, la, gh, gw, scan)
+        near(out, ref)
+        near(fin, ref_fin)
+
+
+def test_replays_do_not_take_old_states():
+    """A recorded call has one nonce for all replays: other inputs in the same buffers, and calls outside the graph on the same
+    workspace, must not be answered from the states that the flags of an earlier replay stand for."""
+    B, H, gh, gw, dk, dv = 2, 16, 45, 61, 36, 72
+    sets = [[x.cuda() for x in upload(gi.make_inputs(B, H, gh * gw, dk, dv, "bf16", seed=s, z_mean=3.0), "q", "k", "v", "log_alpha")] for s in (1, 2)]
+    ws = torch.empty(gla.gla_fwd_workspace_bytes(B, H, gh * gw, dk, dv, gla.DT_BF16), dtype=torch.uint8, device="cuda")
+    want = [[y.clone() for y in gla.gla_fwd_ex(*x, gh, gw, 2, workspace=ws)] for x in sets]
+    t = [x.clone() for x in sets[0]]
+    out, fin = torch.empty_like(want[0][0]), torch.empty_like(want[0][1])
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        gla.gla_fwd_ex(*t, gh, gw, 2, out=out, final_state=fin, workspace=ws, stream=side)
+    for i in (0, 1, 1, 0):
+        for x, y in zip(t, sets[i]):
+            x.copy_(y)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[i][0]) and torch.equal(fin, want[i][1]), i
+        got = gla.gla_fwd_ex(*sets[1 - i], gh, gw, 2, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[1 - i][0])
