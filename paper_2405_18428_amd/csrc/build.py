@@ -8,7 +8,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["gla_api.hip", "gla_carry.hip", "gla_recurrent.hip", "gla_mfma.hip", "gla_hilo.hip", "gla_bwd_kernels.hip",
-           "gla_mfma_bwd.hip", "gla_hilo_bwd.hip", "gla_srem.hip", "gla_fast.hip", "gla_onepass.hip"]
+           "gla_mfma_bwd.hip", "gla_hilo_bwd.hip", "gla_srem.hip", "gla_fast.hip", "gla_onepass.hip", "gla_onepass_bwd.hip"]
 LIB = os.path.join(HERE, "libgla.so")
 
 # -packed-fp32-ops is switched off: the compiler must not form packed fp32 math.

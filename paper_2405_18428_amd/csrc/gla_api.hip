@@ -201,6 +201,21 @@ int onepass_chunks_per_group(const Params &p, int nchunks) {
     return groups(8) <= 512 && total >= 2990 && p.z_gate == nullptr ? 8 : 0;
 }
 
+// Whether the backward pass runs on the kernels that take whole chunks, four on a compute unit (`reuse`: the other kernels would
+// find the forward states in the forward call's workspace).  Time of the walks over that of these (36 / 72 channels, sequences x
+// chunks; S: 32 / 64 channels, R: with the forward call's states, that call included):
+//     one span     16 x 4 1.40 (S 1.31, R 1.27), 256 x 4 1.26 (R 1.21), 512 x 4 1.13 (S 1.02), 16 x 3 1.20, 256 x 3 1.10, 320 x 3 0.98,
+//                  two chunks and fewer leave waves idle: 16 x 2 0.97, 1 chunk 0.7
+//     several      32 x 9 1.07 (S 0.89), 16 x 24 1.12 (S 1.04), 32 x 32 1.27, 16 x 64 1.30, 128 x 8 1.21, but 16 x 16 0.96 and 16 x 5
+//                  0.87, where two launches are all there is (R: 16 x 5 1.09, 16 x 64 1.04, 1 x 32 0.85)
+//     more groups than compute units 0.6 to 0.98: what a group loads and stores has nothing beside it there
+bool onepass_back_takes(const Params &p, bool reuse) {
+    if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || !onepass_covers(p)) return false;
+    const long long bh = (long long)p.B * p.H, nchunks = (p.T + kChunk - 1) / kChunk, total = bh * nchunks;
+    if (nchunks <= 4) return nchunks == 4 ? bh <= 512 : nchunks == 3 && bh <= 256;
+    return bh * ((nchunks + 3) / 4) <= 256 && total >= (reuse ? 64 : (p.dk <= 32 && p.dv <= 64 ? 384 : 288));
+}
+
 // A value that no earlier call's flags hold, nor (but for one chance in 2^64) memory that never held any
 unsigned long long next_nonce() {
     static std::atomic<unsigned long long> last{(unsigned long long)std::random_device{}() << 32 | std::random_device{}()};
@@ -422,6 +437,20 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         if (e != hipSuccess || p.chain_in_output) return e;
         return launch_carry(p, stream);
     };
+
+    if (one_walk && onepass_back_takes(base, fwd_workspace != nullptr)) {
+        BackParams pc{base};
+        const int nchunks = (T + kChunk - 1) / kChunk;
+        pc.q = q; pc.k = k; pc.v = v; pc.log_alpha = log_alpha; pc.scan_dir = scan_dir; pc.d_out = d_out;
+        pc.dq = dq; pc.dk_grad = dk_grad; pc.dv_grad = dv_grad; pc.dlog_alpha = dlog_alpha;
+        pc.nspans = (nchunks + 3) / 4;
+        pc.span_len = 4 * kChunk;
+        const size_t states = align_up((size_t)B * H * pc.nspans * dk * dv * sizeof(float), 256);
+        pc.ws_state = static_cast<float *>(workspace);
+        pc.ws_gstate = reinterpret_cast<float *>(static_cast<char *>(workspace) + states);
+        pc.ws_lgam = reinterpret_cast<float *>(static_cast<char *>(workspace) + 2 * states);
+        return launch_onepass_back(pc, stream) == hipSuccess ? GLA_OK : GLA_ERR_HIP;
+    }
 
     // 1. states of the forward recurrence (k, v, log_alpha); dq_s = S_s dO_s
     WalkParams pa{base};

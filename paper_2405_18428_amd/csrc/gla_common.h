@@ -106,6 +106,13 @@ struct OnePassParams : Params {
     int polls;
 };
 
+// The backward kernels on whole chunks (gla_onepass_bwd.hip): spans of four chunks, local states of both recurrences
+struct BackParams : Params {
+    const void *d_out;
+    float *dq, *dk_grad, *dv_grad, *dlog_alpha;
+    float *ws_gstate;       // [B*H, nspans, dk, dv], like ws_state: what the span adds to the adjoint of the state that enters it
+};
+
 // first scan step of span sp, and the step after its last
 __host__ __device__ inline int span_begin(const Params &p, int sp) {
     const int s = sp * p.span_len - p.span_shift;
@@ -230,6 +237,7 @@ hipError_t launch_hilo_span(const Params &p, SpanMode mode, hipStream_t stream);
 // the single-launch forward kernels, of 4 or 8 chunks a work-group (gla_onepass.hip)
 bool onepass_covers(const Params &p);
 hipError_t launch_onepass(const OnePassParams &p, int chunks, hipStream_t stream);
+hipError_t launch_onepass_back(const BackParams &p, hipStream_t stream);      // (gla_onepass_bwd.hip)
 hipError_t launch_hilo_walk(const WalkParams &p, const void *w, float *r, hipStream_t stream, bool with_outputs);  // (gla_hilo_bwd.hip)
 // fp16 output pass with the pipelined chunk loop (gla_fast.hip): what it covers, how many of its work-groups a
 // compute unit holds, and its launcher

@@ -93,7 +93,7 @@ __device__ inline V afresh(V x) {
 }
 
 // This lane, afresh in every stage: what is derived from it is not carried from one to the next in registers.
-#define LANE const int lane = recompute_per_chunk(threadIdx.x) & 63, lm = lane & 15, g = lane >> 4
+#define LANE [[maybe_unused]] const int lane = recompute_per_chunk(threadIdx.x) & 63, lm = lane & 15, g = lane >> 4
 
 // FUSE = the gate prologue and the optional output epilogue; ACC = rows are added to the fp32 rows already in `out`.
 // The kernel's arguments, loaded where they are used: all of them at once do not fit the scalar registers.
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
 #pragma unroll
                 for (int i = 0; i < KQ; ++i)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) a = a || wl[i][r] > ref[i][r] - 40.f;
+                    for (int r = 0; r < 4; ++r) a = a || (qp.at[i] != kNowhere && wl[i][r] > ref[i][r] - 40.f);
                 return (bool)__any(a);
             };
             constexpr int N = KQ == 1 ? 4 : 2;

@@ -1,4 +1,4 @@
-"""The single-launch forward kernels (a span's chunks on chip from the first load to the last store, states handed on through
+"""The kernels that take whole chunks, forwards and backwards.  The single-launch forward kernels (a span's chunks on chip from the first load to the last store, states handed on through
 flags) at their edges: head sizes around the 16-channel units, the tail and the 16-column tiles, spans of 4 and of 8 chunks, ragged
 last chunks and spans, grids whose columns are shorter than a tile, both memory orders, an initial state, slow gates (every
 earlier span is looked at), sums over scan orders, gate prologue and epilogue; a wait that runs out, and replays of a graph.
@@ -106,6 +106,36 @@ def test_a_wait_that_runs_out(scan, fused):
         out, fin = gla.gla_fwd_fused(q, k, v, z, 16.0, gh, gw, scan) if fused else gla.gla_fwd_ex(q, k, v, la, gh, gw, scan)
         near(out, ref)
         near(fin, ref_fin)
+
+
+# (one span of three and of four chunks, ragged; several spans, with a last one of one token and with one of four chunks; two rounds
+# of one-span groups; short columns)
+BACK = [(2, 3, 14, 13), (2, 3, 3, 84), (1, 6, 16, 16), (18, 16, 5, 37), (8, 16, 11, 35), (2, 16, 9, 57), (4, 16, 64, 15), (16, 16, 32, 7)]
+
+
+@pytest.mark.parametrize("dk,dv,B,H,gh,gw", [(*h, *c) for h in ((36, 72), (32, 64)) for c in BACK] +
+                         [(*h, *c) for h in ((20, 40), (36, 40), (28, 72)) for c in BACK[:5]])
+def test_gradients(dk, dv, B, H, gh, gw):
+    """All four gradients, both memory orders, with and without the forward call's workspace; slow gates in every other case.  The gate
+    gradient sums up to 64 terms q dq - k dk and two states: 64 TOL of their size, whatever cancels."""
+    from oracle import gla_oracle
+    d = gi.make_inputs(B, H, gh * gw, dk, dv, "bf16", seed=dk + dv + gh, z_mean=3.0 if gw % 2 else 0.0)
+    w = torch.from_numpy(np.random.default_rng(9).standard_normal((B, H, gh * gw, dv)).astype(np.float32)).bfloat16()
+    for scan, layout in ((2, 0), (1, 1)):
+        want = gla_oracle.gla_bwd(d["q"], d["k"], d["v"], d["log_alpha"], w.float().numpy(), gh, gw, scan)
+        size = max(np.sqrt(np.mean((d["q"].astype(np.float64) * want[0]) ** 2)), np.sqrt(np.mean(want[3] ** 2)))
+        t = upload(d, "q", "k", "v", "log_alpha") + [w.cuda()]
+        if layout == 1:
+            t = [x.transpose(1, 2).contiguous() for x in t]
+        ws = torch.full((gla.gla_fwd_workspace_bytes(B, H, gh * gw, dk, dv, gla.DT_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+        gla.gla_fwd_layout(*t[:4], gh, gw, scan, layout=layout, workspace=ws)
+        for keep in (None, ws):
+            room = torch.full((gla.gla_bwd_workspace_bytes(B, H, gh * gw, dk, dv, gla.DT_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+            got = gla.gla_bwd_layout(*t, gh, gw, scan, layout=layout, fwd_workspace=keep, workspace=room)
+            got = [g if layout == 0 else g.transpose(1, 2) for g in got]
+            for g, r in zip(got[:3], want[:3]):
+                near(g, r)
+            assert np.abs(got[3].cpu().numpy() - want[3]).max() <= TOL * 64 * size
 
 
 def test_replays_do_not_take_old_states():
