@@ -172,7 +172,7 @@ int hilo_chunks_per_span(int bh, int nchunks, bool epilogue) {
     return best > 0 ? best : nchunks;        // (more than 1536 sequences)
 }
 
-// Bytes of the flags of a single-launch plan (two waves a chunk), which lie behind the sums of log alpha
+// Bytes of the flags of a single-launch plan (two waves a chunk), which lie behind the sums of the gates
 size_t onepass_flag_bytes(size_t bh, size_t nspans, int chunks) { return align_up(bh * nspans * 2 * chunks * sizeof(unsigned long long), 256); }
 
 // Chunks a work-group of the single-launch forward kernels (4 or 8), or 0 where the call stays on the others: a span is then that
@@ -184,6 +184,9 @@ size_t onepass_flag_bytes(size_t bh, size_t nspans, int chunks) { return align_u
 //     spans of 8   16 x 100 1.20, 32 x 64 1.26 (E 1.33), 128 x 16 1.38, 128 x 5 1.13 but 192 x 5 0.87, 256 x 8 0.93 (E 1.20)
 //     two rounds   32 x 100 1.08, 32 x 128 1.11 (E 1.00), 64 x 64 1.14, 96 x 32 1.00, 16 x 256 1.03 (column scan 1.2), but 64 x 43 0.93,
 //                  128 x 17 0.87, 192 x 16 1.05 (column scan 0.85); three and more 0.87 to 1.11
+// The two-sided gate has room for four chunks on a compute unit, in one group: 16 x 4 1.29 (S 1.05), 256 x 4 1.17 (S 1.01), 512 x 4 1.17 (S 0.83),
+// 16 x 16 1.02 (column scan 0.87), 32 x 9 1.28 (S 1.13), 64 x 16 1.73 (S 1.52), and in several rounds 128 x 9 1.17 (S 1.00), 32 x 64 1.43,
+// 16 x 256 1.38, 128 x 32 1.40 (S 1.16), but 192 x 5 0.74 and 256 x 16 0.87, whose sequences the other kernels walk in one pass.
 // Sequences of up to three chunks, which would leave waves idle, take 0.6 to 0.97.  The fewest chunks of a plain call (48) are where
 // its work-groups begin to count: below, either kernel waits for its launches (16.3 us, 13.7 here), and such calls stay with
 // the fp16 engine.
@@ -192,6 +195,10 @@ int onepass_chunks_per_group(const Params &p, int nchunks) {
     const long long bh = (long long)p.B * p.H, total = bh * nchunks;
     const bool epilogue = p.r_pre != nullptr;
     auto groups = [&](int chunks) { return bh * ((nchunks + chunks - 1) / chunks); };
+    if (two_sided(p)) {
+        if (nchunks <= 4) return nchunks == 4 && (bh <= 128 || p.dk > 32 || p.dv > 64) && launch_fits(bh, 512) ? 4 : 0;
+        return bh <= 128 && total >= 288 && groups(4) <= bh * kMaxChainedSpans ? 4 : 0;
+    }
     if (nchunks <= 4) return nchunks == 4 && bh <= 128 ? 4 : 0;
     if (total < (epilogue ? 384 : 48)) return 0;
     if (groups(4) <= 256) return 4;
@@ -210,7 +217,7 @@ int onepass_chunks_per_group(const Params &p, int nchunks) {
 //                  0.87, where two launches are all there is (R: 16 x 5 1.09, 16 x 64 1.04, 1 x 32 0.85)
 //     more groups than compute units 0.6 to 0.98: what a group loads and stores has nothing beside it there
 bool onepass_back_takes(const Params &p, bool reuse) {
-    if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || !onepass_covers(p)) return false;
+    if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || two_sided(p) || !onepass_covers(p)) return false;
     const long long bh = (long long)p.B * p.H, nchunks = (p.T + kChunk - 1) / kChunk, total = bh * nchunks;
     if (nchunks <= 4) return nchunks == 4 ? bh <= 512 : nchunks == 3 && bh <= 256;
     return bh * ((nchunks + 3) / 4) <= 256 && total >= (reuse ? 64 : (p.dk <= 32 && p.dv <= 64 ? 384 : 288));
@@ -709,7 +716,7 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
         mark(1);
         mark(2);
         OnePassParams pw{p};
-        pw.flags = reinterpret_cast<unsigned long long *>(p.ws_lgam_b);
+        pw.flags = reinterpret_cast<unsigned long long *>(p.ws_fail);       // (behind the sums of the gates)
         pw.nonce = next_nonce();
         pw.polls = g_opt_look_back_polls;
         e = launch_onepass(pw, use_onepass, stream);

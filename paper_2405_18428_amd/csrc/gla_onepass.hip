@@ -50,19 +50,22 @@ struct HeadsS {
     static constexpr int DT = 0, NX = 4, NV = 64;
 };
 
-template <typename HD, int NC, bool FUSE>
+template <typename HD, int NC, bool FUSE, bool BETA>
 struct WLayout {
     static constexpr int kRow = 72;                                  // bf16 per row of k~ (32 hi, 32 lo, 4 x (hi, lo))
     static constexpr int kState = 36;                                // floats per value column of a state
     static constexpr int kUBytes = HD::NV * kState * 4;
     static constexpr int kKBytes = kChunk * kRow * 2 > kUBytes ? kChunk * kRow * 2 : kUBytes;   // k~, then U_c, then P_c
-    static constexpr int kVBytes = kChunk * HD::NV * 2;              // v, as it comes in: 16-byte pieces row by row
+    static constexpr int kVRows = kChunk * HD::NV * 2;               // v, as it comes in: 16-byte pieces row by row
+    static constexpr int kVBytes = (BETA ? 2 : 1) * kVRows;          // (v~ of the two-sided gate: hi rows, then lo rows)
     static constexpr int kOne = kKBytes + kVBytes;
     static constexpr int oDecay = NC * kOne;                         // float[NC][4][36]: totals of the tiles, then kDecay ..
-    static constexpr int oPair = oDecay + NC * 4 * kState * 4;       // int[2 NC]: how often a wave has met its partner
+    static constexpr int kCols = 16 * HD::NX;
+    static constexpr int oCols = oDecay + NC * 4 * kState * 4;       // float[NC][4][kCols]: the same of the value columns (BETA)
+    static constexpr int oPair = oCols + (BETA ? NC * 4 * kCols * 4 : 0);    // int[2 NC]: how often a wave has met its partner
     static constexpr int oLn = oPair + 2 * NC * 4;                   // float[2][16 NX]: LayerNorm weight, bias (FUSE)
     static constexpr int kBytes = oLn + (FUSE ? 2 * 16 * HD::NX * 4 : 0);
-    static_assert(kBytes <= 160 * 1024 / (8 / NC), "16 waves on a compute unit");
+    static_assert(kBytes <= 160 * 1024 / (BETA ? 4 / NC : 8 / NC), "16 waves on a compute unit, 8 with the two-sided gate");
 };
 // what the totals of a chunk's tiles become: 2^(b_C), 2^(b_m), 2^(b_C - b_m), b_C
 enum { kDecay, kToAnchor, kFromAnchor, kLogDecay };
@@ -95,15 +98,18 @@ __device__ inline V afresh(V x) {
 // This lane, afresh in every stage: what is derived from it is not carried from one to the next in registers.
 #define LANE [[maybe_unused]] const int lane = recompute_per_chunk(threadIdx.x) & 63, lm = lane & 15, g = lane >> 4
 
-// FUSE = the gate prologue and the optional output epilogue; ACC = rows are added to the fp32 rows already in `out`.
 // The kernel's arguments, loaded where they are used: all of them at once do not fit the scalar registers.
 typedef const __attribute__((address_space(4))) OnePassParams *Args;
 #define ARG afresh(args)
 
-template <typename HD, int NC, bool FUSE, bool ACC, typename TOut>
-__global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) {
+// FUSE = the gate prologue and the optional output epilogue; ACC = rows are added to the fp32 rows already in `out`; BETA = the
+// two-sided gate (log_beta): with c_j the prefix sums of log2 beta per value column, v~_i = v_i 2^(c_m - c_i) takes the place of v as
+// a hi/lo pair, the state decays by 2^(c_C) as well, and output rows are scaled by 2^(c_j - c_m).
+template <typename HD, int NC, bool FUSE, bool ACC, typename TOut, bool BETA>
+__global__ __launch_bounds__(128 * NC, BETA ? 2 : 4) void chunk_pair_kernel(OnePassParams) {
     const Args args = (Args)__builtin_amdgcn_kernarg_segment_ptr();
-    using L = WLayout<HD, NC, FUSE>;
+    using L = WLayout<HD, NC, FUSE, BETA>;
+    static_assert(!BETA || (!FUSE && !ACC), "two-sided gate: from log gates, no sums");
     constexpr int DT = HD::DT, NX = HD::NX, NG = 8 + DT, NT = 128 * NC, NW = 2 * NC;
     constexpr int RS = L::kRow, US = L::kState;
     constexpr int VP = HD::NV / 8;                    // 16-byte pieces of a v row; a chunk's go to LDS 64 at a time
@@ -120,6 +126,7 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
     uint16_t *s_v = reinterpret_cast<uint16_t *>(mine + L::kKBytes);
     float *s_decay = reinterpret_cast<float *>(smem + L::oDecay);
     float *my_decay = s_decay + (w >> 1) * 4 * US;
+    float *s_cols = reinterpret_cast<float *>(smem + L::oCols), *my_cols = s_cols + (w >> 1) * 4 * L::kCols;
     float *s_lnw = reinterpret_cast<float *>(smem + L::oLn), *s_lnb = s_lnw + 16 * NX;
 
     // The two waves of a chunk wait for each other without the group's others (a chunk whose rows have come is not held up by
@@ -200,9 +207,8 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
             for (int r = 0; r < 4; ++r) S[i][r] = fetch<float>(b_init, q.at[i] + r * dv4);
     }
 
-    // (one round, but where a sequence is one span longer than the group's chunks: then the state goes on in S)
-    for (int r_begin = s_begin; r_begin < s_end; r_begin += NC * kChunk) {
-        const int c_begin = r_begin + (w >> 1) * kChunk;
+    {
+        const int c_begin = s_begin + (w >> 1) * kChunk;
         // (Waves whose chunk is not there go along with rows of zeros: straight-line code keeps the registers.)
         using GatePiece = std::conditional_t<FUSE, u32x2, f32x4>;
         using GateTail = std::conditional_t<FUSE, uint16_t, float>;
@@ -234,6 +240,8 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
         float b[2][NG];
         u32x2 rk[2][2], rq[2][2];
         uint32_t rkt[2], rqt[2];
+        u32x2 rv[2][BETA ? NX : 1];                    // BETA: v and the sums of log2 beta, columns 16 x + 4 g .. + 3
+        f32x4 cx[2][BETA ? NX : 1];
         {
             LANE;
             uint32_t chb[2];                     // byte offset of the lane's units in a bf16 row
@@ -248,7 +256,7 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                 row[t] = there ? tk * dk2 : kNowhere / 2;
                 rowv[t] = there ? tk * dv2 : kNowhere / 2;
             }
-            v_to_lds(view_v(ARG->v, 2));       // (a row that is not there meets k~ = 0; columns past dv are not read)
+            if constexpr (!BETA) v_to_lds(view_v(ARG->v, 2));       // (a row that is not there meets k~ = 0; columns past dv are not read)
             const Rsrc bg = FUSE ? view_k(ARG->z_gate, 2) : view_k(ARG->log_alpha, 4), bk = view_k(ARG->k, 2), bq = view_k(ARG->q, 2);
             GatePiece la[2][2];
             GateTail lat[2];
@@ -269,6 +277,18 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
 #pragma unroll
                 for (int u = 0; u < 2; ++u) rq[t][u] = fetch<u32x2>(bq, row[t] + chb[u]);
                 if constexpr (DT) rqt[t] = fetch<uint16_t>(bq, row[t] + tcb);
+            }
+
+            if constexpr (BETA) {
+                const Rsrc bv = view_v(ARG->v, 2), bb = view_v(ARG->log_beta, 4);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int x = 0; x < NX; ++x) {
+                        const uint32_t col = 4 * g + 16 * x < dv ? 8u * (uint32_t)g + 32u * (uint32_t)x : kNowhere / 2;
+                        cx[t][x] = fetch<f32x4>(bb, f32_at(rowv[t], col));
+                        rv[t][x] = fetch<u32x2>(bv, rowv[t] + col);
+                    }
             }
 
             // ---- gates: prefix sums inside the 16-token tiles, totals of the tiles ----
@@ -296,6 +316,15 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                     row_scan16x4_least(b[t][4], b[t][5], b[t][6], b[t][7], kLeastGate2);
                 }
                 if constexpr (DT) b[t][8] = row_scan16(b[t][8]);
+                if constexpr (BETA) {
+#pragma unroll
+                    for (int x = 0; x < NX; ++x) {
+                        float c0 = cx[t][x][0] * kLog2e, c1 = cx[t][x][1] * kLog2e, c2 = cx[t][x][2] * kLog2e, c3 = cx[t][x][3] * kLog2e;
+                        row_scan16x4_least(c0, c1, c2, c3, kLeastGate2);
+                        cx[t][x] = f32x4{c0, c1, c2, c3};
+                        if (lm == 15) *reinterpret_cast<f32x4 *>(my_cols + tile[t] * L::kCols + 16 * x + 4 * g) = cx[t][x];
+                    }
+                }
                 if (lm == 15) {
                     float *d = my_decay + tile[t] * US;
                     *reinterpret_cast<f32x4 *>(d + 4 * g) = f32x4{b[t][0], b[t][1], b[t][2], b[t][3]};
@@ -363,7 +392,35 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                     qt[t] = (qhh & 0xffffu) | (pack_bf16(qrem, qrem) << 16);           // slots hi, lo, hi, lo
                 }
             }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (v is in LDS)
+            if constexpr (BETA) {
+#pragma unroll
+                for (int x = 0; x < NX; ++x) {
+                    const float *d = my_cols + 16 * x + 4 * g;
+                    const f32x4 t0 = *reinterpret_cast<const f32x4 *>(d), t1 = *reinterpret_cast<const f32x4 *>(d + L::kCols),
+                                t2 = *reinterpret_cast<const f32x4 *>(d + 2 * L::kCols);
+                    cx[0][x] -= first * t0 + t1;
+                    cx[1][x] += first * t2;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        f32x4 y;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float vv = r & 1 ? bf16_hi_as_float(rv[t][x][r >> 1]) : bf16_lo_as_float(rv[t][x][r >> 1]);
+                            y[r] = vv * exp2_fast(fminf(-cx[t][x][r], kMaxExp2));
+                        }
+                        u32x2 h, l;
+                        SPLIT_PAIR(y[0], y[1], h[0], l[0]);
+                        SPLIT_PAIR(y[2], y[3], h[1], l[1]);
+                        uint16_t *vrow = s_v + (16 * tile[t] + lm) * HD::NV + ((16 * x) ^ (DT ? 0 : 16 * ((lm >> 1) & 3))) + 4 * g;
+                        if (16 * x + 4 * g < HD::NV) {
+                            *reinterpret_cast<u32x2 *>(vrow) = h;
+                            *reinterpret_cast<u32x2 *>(vrow + kChunk * HD::NV) = l;
+                        }
+                    }
+                }
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (v is in LDS)
+            }
         }
         meet();
         // slots hi, hi, lo, lo of a tail channel's pair
@@ -377,9 +434,10 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
             const int tr_row = lm >> 2, tr_col = 4 * (lm & 3);       // transposing reads: token-in-4 and column quad of this lane
             const uint16_t *vtr = s_v + (4 * g + tr_row) * HD::NV + tr_col;
             const int v_swz = DT ? 0 : 16 * ((2 * g + (tr_row >> 1)) & 3);     // (rows of 128 bytes: tiles change places, see load_to_lds)
-            auto v_frag = [&](int q32, int x) {   // slot (g, e) of step q32 = token 32 q32 + 16 (e / 4) + 4 g + e % 4
-                const u32x2 lo = lds_read_tr(vtr + 32 * q32 * HD::NV + ((16 * x) ^ v_swz));
-                const u32x2 hi = lds_read_tr(vtr + (32 * q32 + 16) * HD::NV + ((16 * x) ^ v_swz));
+            // slot (g, e) of step q32 = token 32 q32 + 16 (e / 4) + 4 g + e % 4; part 1: the lo rows
+            auto v_frag = [&](int q32, int x, int part = 0) {
+                const u32x2 lo = lds_read_tr(vtr + (32 * q32 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz));
+                const u32x2 hi = lds_read_tr(vtr + (32 * q32 + 16 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz));
                 return u32x4{lo[0], lo[1], hi[0], hi[1]};
             };
             // (the totals of the tiles have been read)
@@ -390,6 +448,21 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                 d[kToAnchor * US] = exp2_fast(m);
                 d[kFromAnchor * US] = exp2_fast(e);
                 d[kLogDecay * US] = m + e;
+            }
+            if constexpr (BETA) {
+                if (W == 1) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        if (lane + 64 * i < L::kCols) {
+                            float *d = my_cols + lane + 64 * i;
+                            const float m = d[0] + d[L::kCols], e = d[2 * L::kCols] + d[3 * L::kCols];
+                            d[kDecay * L::kCols] = exp2_fast(m + e);
+                            d[kToAnchor * L::kCols] = exp2_fast(m);
+                            d[kFromAnchor * L::kCols] = exp2_fast(e);
+                            d[kLogDecay * L::kCols] = m + e;
+                        }
+                    }
+                }
             }
             // ---- scores, transposed: lane (lm, g) gets A[i = 16 t + lm][j = 16 jt + 4 g + r]: of tile W with token tile 0, of tile
             // 3 - W with 0, 1, 2, and the last one of its two diagonals: tile 3 with 3 (W = 0), 1 with 1 (W = 1) ----
@@ -468,12 +541,26 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                     if constexpr (DT) acc[i][2] = mfma(kf[4], vf, acc[i][2]);
                     acc[i][0] = mfma(kf[2], vf, acc[i][0]);
                     acc[i][1] = mfma(kf[3], vf, acc[i][1]);
+                    if constexpr (BETA) {
+                        const u32x4 vl = v_frag(q, 2 * i + W, 1);
+                        acc[i][0] = mfma(kf[0], vl, acc[i][0]);
+                        acc[i][1] = mfma(kf[1], vl, acc[i][1]);
+                        if constexpr (DT) acc[i][2] = mfma(kf[4], vl, acc[i][2]);
+                        acc[i][0] = mfma(kf[2], vl, acc[i][0]);
+                        acc[i][1] = mfma(kf[3], vl, acc[i][1]);
+                    }
                 }
                 if constexpr (NX == 5) {
                     const u32x4 vf = v_frag(q, 4), kh = k_frag(q, 16 * W), kl = k_frag(q, 32 + 16 * W);
                     acc4[0] = mfma(kh, vf, acc4[0]);
                     if constexpr (DT) acc4[DT] = mfma(kf[4], vf, acc4[DT]);
                     acc4[0] = mfma(kl, vf, acc4[0]);
+                    if constexpr (BETA) {
+                        const u32x4 vl = v_frag(q, 4, 1);
+                        acc4[0] = mfma(kh, vl, acc4[0]);
+                        if constexpr (DT) acc4[DT] = mfma(kf[4], vl, acc4[DT]);
+                        acc4[0] = mfma(kl, vl, acc4[0]);
+                    }
                 }
             }
         }
@@ -492,6 +579,15 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
             auto leave_tail = [&](float *u, f32x4 a) {
                 if (g < 2) *reinterpret_cast<f32x2 *>(u + 32 + 2 * g) = f32x2{(a[0] + a[1]) * fact[0], (a[2] + a[3]) * fact[1]};
             };
+            if constexpr (BETA) {
+                const float *ca = my_cols + kFromAnchor * L::kCols + lm;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int ct = 0; ct < 2 + DT; ++ct) acc[i][ct] *= ca[16 * (2 * i + W)];
+#pragma unroll
+                for (int i = 0; i < 1 + DT; ++i) acc4[i] *= ca[NX == 5 ? 64 : 0];
+            }
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 float *u = s_u + (16 * (2 * i + W) + lm) * US;
@@ -513,11 +609,16 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
         const Pieces qp = pieces(recompute_per_chunk(tid));
         const float *u_of = reinterpret_cast<const float *>(smem);       // of chunk c: + c * kWave / 4
         auto state_at = [&](int c, int i) { return u_of + c * (L::kOne / 4) + qp.n[i] * US + 4 * qp.c[i]; };
-        auto decay_at = [&](int c, int i, int what) { return *reinterpret_cast<const f32x4 *>(s_decay + (4 * c + what) * US + 4 * qp.c[i]); };
+        auto decay_at = [&](int c, int i, int what) {
+            f32x4 d = *reinterpret_cast<const f32x4 *>(s_decay + (4 * c + what) * US + 4 * qp.c[i]);
+            if constexpr (BETA) d *= s_cols[(4 * c + what) * L::kCols + qp.n[i]];
+            return d;
+        };
         // ---- the span's own state for the spans behind it ----
         auto flags_of = [&]() { return ARG->flags + (size_t)afresh(bh) * ARG->nspans * NW; };
         auto view_state = [&]() { return view(ARG->ws_state + (size_t)afresh(bh) * ARG->nspans * dk * dv, (uint32_t)ARG->nspans * ne4); };
         auto view_lgam = [&]() { return view(ARG->ws_lgam + (size_t)afresh(bh) * ARG->nspans * dk, 4u * (uint32_t)(ARG->nspans * dk)); };
+        auto view_lgam_b = [&]() { return view(ARG->ws_lgam_b + (size_t)afresh(bh) * ARG->nspans * dv, (uint32_t)ARG->nspans * dv4); };
         const bool gives = sp + 1 < ARG->nspans;
         if (gives) {
             const Rsrc b_state = view_state(), b_lgam = view_lgam();
@@ -535,6 +636,17 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                 for (int c = 0; c < NC; ++c) sum += s_decay[(4 * c + kLogDecay) * US + tid];
                 publish(b_lgam, 4u * (uint32_t)tid, 4u * (uint32_t)(sp * dk), sum * kLn2);
             }
+            if constexpr (BETA) {
+                if (w == 0) {       // (the wave whose flag stands for the decays)
+                    const Rsrc b_lgam_b = view_lgam_b();
+                    for (int n = tid; n < dv; n += 64) {
+                        float sum = 0.f;
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) sum += s_cols[(4 * c + kLogDecay) * L::kCols + n];
+                        publish(b_lgam_b, 4u * (uint32_t)n, (uint32_t)sp * dv4, sum * kLn2);
+                    }
+                }
+            }
         }
         // ---- O^T = V^T A^T: lane (lm, g) accumulates O[i = 16 t + lm][n = 16 x + 4 g + r] ----
         f32x4 o[2][NX];
@@ -544,9 +656,10 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
             const int tr_row = lm >> 2, tr_col = 4 * (lm & 3);       // transposing reads: token-in-4 and column quad of this lane
             const uint16_t *vtr = s_v + (4 * g + tr_row) * HD::NV + tr_col;
             const int v_swz = DT ? 0 : 16 * ((2 * g + (tr_row >> 1)) & 3);     // (rows of 128 bytes: tiles change places, see load_to_lds)
-            auto v_frag = [&](int q32, int x) {   // slot (g, e) of step q32 = token 32 q32 + 16 (e / 4) + 4 g + e % 4
-                const u32x2 lo = lds_read_tr(vtr + 32 * q32 * HD::NV + ((16 * x) ^ v_swz));
-                const u32x2 hi = lds_read_tr(vtr + (32 * q32 + 16) * HD::NV + ((16 * x) ^ v_swz));
+            // slot (g, e) of step q32 = token 32 q32 + 16 (e / 4) + 4 g + e % 4; part 1: the lo rows
+            auto v_frag = [&](int q32, int x, int part = 0) {
+                const u32x2 lo = lds_read_tr(vtr + (32 * q32 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz));
+                const u32x2 hi = lds_read_tr(vtr + (32 * q32 + 16 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz));
                 return u32x4{lo[0], lo[1], hi[0], hi[1]};
             };
 #pragma unroll
@@ -562,6 +675,13 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                     o[1][x] = mfma(vf, pah[1 + q], o[1][x]);
                     if (q == 0) o[0][x] = mfma(vf, pal[0], o[0][x]);
                     o[1][x] = mfma(vf, pal[1 + q], o[1][x]);
+                    if constexpr (BETA) {
+                        const u32x4 vl = v_frag(q, x, 1);
+                        if (q == 0) o[0][x] = mfma(vl, pah[0], o[0][x]);
+                        o[1][x] = mfma(vl, pah[1 + q], o[1][x]);
+                        if (q == 0) o[0][x] = mfma(vl, pal[0], o[0][x]);
+                        o[1][x] = mfma(vl, pal[1 + q], o[1][x]);
+                    }
                 }
         }
         if (gives) {
@@ -577,6 +697,9 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
         // ---- the state entering the span ----
         if (sp > 0 && 64 * w < kQuads) {
             const Rsrc b_state = view_state(), b_lgam = view_lgam();
+            float wb[BETA ? KQ : 1];   // the value column's part of the weight
+#pragma unroll
+            for (int i = 0; i < (BETA ? KQ : 1); ++i) wb[i] = 0.f;
             f32x4 wl[KQ], ref[KQ];     // log2 of the weight of the next span; the same behind the nearest spans that were all zero
 #pragma unroll
             for (int i = 0; i < KQ; ++i) wl[i] = ref[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -610,6 +733,7 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                 if (!ok) break;
                 asm volatile("" ::: "memory");
                 f32x4 u[N][KQ], d[N][KQ];
+                float db[N][BETA ? KQ : 1];
 #pragma unroll
                 for (int n = 0; n < N; ++n) {
                     const uint32_t at = (uint32_t)max(r0 - n, 0);
@@ -618,6 +742,7 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
 #pragma unroll
                         for (int r = 0; r < 4; ++r) u[n][i][r] = published(b_state, qp.at[i], at * ne4 + r * dv4);
                         d[n][i] = published4(b_lgam, qp.at_dk[i], at * 4u * (uint32_t)dk);
+                        if constexpr (BETA) db[n][i] = published(view_lgam_b(), 4u * (uint32_t)min(qp.n[i], dv - 1), at * dv4);
                     }
                 }
 #pragma unroll
@@ -627,9 +752,10 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                     for (int i = 0; i < KQ; ++i) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            S[i][r] = fmaf(exp2_fast(wl[i][r]), u[n][i][r], S[i][r]);
+                            S[i][r] = fmaf(exp2_fast(BETA ? wl[i][r] + wb[BETA ? i : 0] : wl[i][r]), u[n][i][r], S[i][r]);
                             wl[i][r] += d[n][i][r] * kLog2e;
                         }
+                        if constexpr (BETA) wb[i] += db[n][i] * kLog2e;
                         const bool zero = S[i][0] == 0.f && S[i][1] == 0.f && S[i][2] == 0.f && S[i][3] == 0.f;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) ref[i][r] = zero ? wl[i][r] : ref[i][r];
@@ -646,12 +772,15 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                     const uint32_t tok = (uint32_t)scan_token(ARG->scan_dir, s, T, ARG->grid_h, ARG->grid_w);
 #pragma unroll
                     for (int i = 0; i < KQ; ++i) {
-                        const float x = bf16_bits_to_float(fetch<uint16_t>(bv, tok * dv2 + 2u * (uint32_t)min(qp.n[i], dv - 1)));
+                        const uint32_t at_v = tok * dv2 + 2u * (uint32_t)min(qp.n[i], dv - 1);
+                        const float x = bf16_bits_to_float(fetch<uint16_t>(bv, at_v));
+                        float beta = 0.f;
+                        if constexpr (BETA) beta = fetch<float>(view_v(ARG->log_beta, 4), 2u * at_v) * kLog2e;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const uint32_t at = tok * dk2 + 2u * (uint32_t)min(4 * qp.c[i] + r, dk - 1);
                             const float a = FUSE ? gate1(bf16_bits_to_float(fetch<uint16_t>(bg, at))) : fetch<float>(bg, 2u * at) * kLog2e;
-                            S[i][r] = fmaf(exp2_fast(a), S[i][r], bf16_bits_to_float(fetch<uint16_t>(bk, at)) * x);
+                            S[i][r] = fmaf(exp2_fast(BETA ? a + beta : a), S[i][r], bf16_bits_to_float(fetch<uint16_t>(bk, at)) * x);
                         }
                     }
                 }
@@ -660,7 +789,7 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
 #pragma unroll
                 for (int i = 0; i < KQ; ++i)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) S[i][r] = fmaf(exp2_fast(wl[i][r]), fetch<float>(b_init, qp.at[i] + r * dv4), S[i][r]);
+                    for (int r = 0; r < 4; ++r) S[i][r] = fmaf(exp2_fast(BETA ? wl[i][r] + wb[BETA ? i : 0] : wl[i][r]), fetch<float>(b_init, qp.at[i] + r * dv4), S[i][r]);
             }
         }
         constexpr int NB = KQ == 1 ? 2 : 4;       // chunks whose reads go together (registers)
@@ -781,6 +910,12 @@ __global__ __launch_bounds__(128 * NC, 4) void chunk_pair_kernel(OnePassParams) 
                     }
                 }
                 const Rsrc bo = view_out();
+                if constexpr (BETA) {
+#pragma unroll
+                    for (int x = 0; x < NX; ++x)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) o[t][x][r] *= exp2_fast(fminf(cx[t][x][r], kMaxExp2));
+                }
                 if constexpr (ACC) {
 #pragma unroll
                     for (int x = 0; x < NX; ++x) o[t][x] += prev[t][x];
@@ -811,10 +946,10 @@ __global__ __launch_bounds__(256) void clear_flags_kernel(flag_t *flags, long lo
     for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) flags[i] = 0;
 }
 
-template <typename HD, int NC, bool FUSE, bool ACC, typename TOut>
+template <typename HD, int NC, bool FUSE, bool ACC, typename TOut, bool BETA = false>
 hipError_t launch_one(const OnePassParams &p, hipStream_t stream) {
-    using L = WLayout<HD, NC, FUSE>;
-    auto kernel = chunk_pair_kernel<HD, NC, FUSE, ACC, TOut>;
+    using L = WLayout<HD, NC, FUSE, BETA>;
+    auto kernel = chunk_pair_kernel<HD, NC, FUSE, ACC, TOut, BETA>;
     static std::atomic<bool> configured[kMaxDevices] = {};  // per instantiation and device
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), L::kBytes, configured);
     if (e != hipSuccess) return e;
@@ -825,6 +960,10 @@ hipError_t launch_one(const OnePassParams &p, hipStream_t stream) {
 template <typename HD, int NC>
 hipError_t launch_heads(const OnePassParams &p, hipStream_t stream) {
     const bool bf16 = p.out_dtype == GLA_DT_BF16;
+    if constexpr (NC == 4) {
+        if (p.log_beta != nullptr)
+            return bf16 ? launch_one<HD, 4, false, false, uint16_t, true>(p, stream) : launch_one<HD, 4, false, false, float, true>(p, stream);
+    }
     if (p.z_gate != nullptr)
         return bf16 ? launch_one<HD, NC, true, false, uint16_t>(p, stream) : launch_one<HD, NC, true, false, float>(p, stream);
     if (p.accumulate) return launch_one<HD, NC, false, true, float>(p, stream);   // host checks fp32 out
@@ -835,7 +974,7 @@ hipError_t launch_heads(const OnePassParams &p, hipStream_t stream) {
 
 // (Smaller heads would leave most of the tiles empty, and stay with the kernels that have classes for them.)
 bool onepass_covers(const Params &p) {
-    return !two_sided(p) && p.dk > 16 && p.dk <= 36 && p.dv > 32 && p.dv <= 72;
+    return (!two_sided(p) || (p.z_gate == nullptr && p.z_beta == nullptr)) && p.dk > 16 && p.dk <= 36 && p.dv > 32 && p.dv <= 72;
 }
 
 hipError_t launch_onepass(const OnePassParams &p, int chunks, hipStream_t stream) {

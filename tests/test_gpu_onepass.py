@@ -90,6 +90,27 @@ def test_gate_prologue_and_epilogue(B, H, gh, gw, dk, dv):
         near(fin, ref_fin)
 
 
+@pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64), (20, 40), (36, 40), (28, 72)])
+@pytest.mark.parametrize("B,H,gh,gw", [(2, 3, 16, 15), (4, 8, 5, 117), (2, 16, 64, 11), (8, 16, 9, 65)])
+def test_two_sided_gate(dk, dv, B, H, gh, gw):
+    """One span, spans of four chunks with a last one of one token or one chunk, two rounds of groups; both memory orders, an
+    initial state, no polls in one of them."""
+    from oracle import gla_oracle_gates as go
+    d = gi.make_gate_inputs(B, H, gh * gw, dk, dv, "bf16", seed=dk + gh)
+    s0 = np.random.default_rng(5).standard_normal((B, H, dk, dv)).astype(np.float32)
+    for scan, layout, out_dtype, polls in ((1, 0, torch.float32, POLLS), (2, 1, torch.bfloat16, POLLS), (0, 0, torch.float32, 0)):
+        if polls == 0 and gh * gw * B * H > 25000:
+            continue        # (what the wait leaves to be formed from the inputs takes its time)
+        gla.gla_set_option(gla.OPT_LOOK_BACK_POLLS, polls)
+        ref, ref_fin = go.gla_fwd_gates(d["q"], d["k"], d["v"], d["log_alpha"], d["log_beta"], gh, gw, scan, initial_state=s0)
+        t = upload(d, "q", "k", "v", "log_alpha") + [torch.from_numpy(d["log_beta"]).cuda()]
+        if layout == 1:
+            t = [x.transpose(1, 2).contiguous() for x in t]
+        out, fin = gla.gla_fwd_gates(*t, gh, gw, scan, layout=layout, initial_state=torch.from_numpy(s0).cuda(), out_dtype=out_dtype)
+        near(out if layout == 0 else out.transpose(1, 2), ref, out_dtype == torch.bfloat16)
+        near(fin, ref_fin)
+
+
 @pytest.mark.parametrize("fused", [False, True])
 @pytest.mark.parametrize("scan", [0, 3])
 def test_a_wait_that_runs_out(scan, fused):
