@@ -175,37 +175,62 @@ int hilo_chunks_per_span(int bh, int nchunks, bool epilogue) {
 // Bytes of the flags of a single-launch plan (two waves a chunk), which lie behind the sums of the gates
 size_t onepass_flag_bytes(size_t bh, size_t nspans, int chunks) { return align_up(bh * nspans * 2 * chunks * sizeof(unsigned long long), 256); }
 
-// Chunks a work-group of the single-launch forward kernels (4 or 8), or 0 where the call stays on the others: a span is then that
-// many chunks.  Eight chunks fill a compute unit, so up to 2048 are one round of work-groups, all loads in flight at once.  Time of the
-// two-pass kernels over that of these (36 / 72 channels, sequences x chunks; S: 32 / 64 channels, E: with the epilogue):
-//     spans of 4   16 x 4 1.14 (S 1.11, E 1.18), 128 x 4 1.10, but 192 x 4 1.03 and 0.95 to 0.97 for sums and [B,T,H,d], 256 x 4 0.98;
-//                  16 x 5 1.10, 16 x 16 1.03, 6 x 64 1.12, 32 x 32 1.21, 128 x 8 1.29; E: 32 x 8 0.90, 16 x 24 1.03, 16 x 64 1.16;
+// Heads of up to 32 / 64 channels
+bool small_heads(const Params &p) { return p.dk <= 32 && p.dv <= 64; }
+
+// Chunks that a work-group of the single-launch forward kernels holds (4 or 8), or 0 where the call stays on the others.  Eight chunks fill
+// a compute unit, so up to 2048 are one round of work-groups, all loads in flight at once.  Time of the two-pass kernels over
+// that of these (36 / 72 channels, sequences x chunks; S: 32 / 64 channels, E: with the epilogue):
+//     groups of 4  16 x 4 1.14 (S 1.11, E 1.18), 128 x 4 1.10, but 192 x 4 1.03 and 0.95 to 0.97 for sums and [B,T,H,d], 256 x 4 0.98;
+//                  64 x 8 1.18, 32 x 32 1.16, 128 x 8 1.29; S: 16 x 20 1.14, 16 x 32 1.16; E: 16 x 24 1.03, 16 x 64 1.16;
 //                  two groups on a unit 96 x 17 1.16 to 1.31
-//     spans of 8   16 x 100 1.20, 32 x 64 1.26 (E 1.33), 128 x 16 1.38, 128 x 5 1.13 but 192 x 5 0.87, 256 x 8 0.93 (E 1.20)
+//     groups of 8  16 x 100 1.20, 32 x 64 1.26 (E 1.33), 128 x 16 1.38, 128 x 5 1.13 but 192 x 5 0.87, 256 x 8 0.93 (E 1.20)
 //     two rounds   32 x 100 1.08, 32 x 128 1.11 (E 1.00), 64 x 64 1.14, 96 x 32 1.00, 16 x 256 1.03 (column scan 1.2), but 64 x 43 0.93,
 //                  128 x 17 0.87, 192 x 16 1.05 (column scan 0.85); three and more 0.87 to 1.11
+// Sequences of up to three chunks, which would leave waves idle, take 0.6 to 0.97.  Of longer ones, smaller calls stay with the others
+// although the forward call alone would gain (16 x 8 16.2 us, 14.6 here; 16 x 20 19.8, 17.4): the walks of the backward call that takes the
+// span states want spans of one or two chunks there (both calls: 16 x 8 39.9 us, here 44.4; 16 x 20 52.5, here 52.5 to 58; [B,T,H,d]
+// 32 x 13 55.5 and 64.4), and in spans that short these kernels gain nothing (16 x 8 18.0 us, 16 x 20 19.3, 16 x 27 22.8 for 20.7) but for
+// few of them a sequence (64 x 5 1.11, both calls 1.03) and small heads (16 x 20, both calls: 44.6 us, here 42.8).
 // The two-sided gate has room for four chunks on a compute unit, in one group: 16 x 4 1.29 (S 1.05), 256 x 4 1.17 (S 1.01), 512 x 4 1.17 (S 0.83),
 // 16 x 16 1.02 (column scan 0.87), 32 x 9 1.28 (S 1.13), 64 x 16 1.73 (S 1.52), and in several rounds 128 x 9 1.17 (S 1.00), 32 x 64 1.43,
 // 16 x 256 1.38, 128 x 32 1.40 (S 1.16), but 192 x 5 0.74 and 256 x 16 0.87, whose sequences the other kernels walk in one pass.
-// Sequences of up to three chunks, which would leave waves idle, take 0.6 to 0.97.  The fewest chunks of a plain call (48) are where
-// its work-groups begin to count: below, either kernel waits for its launches (16.3 us, 13.7 here), and such calls stay with
-// the fp16 engine.
 int onepass_chunks_per_group(const Params &p, int nchunks) {
     if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || !onepass_covers(p)) return 0;
     const long long bh = (long long)p.B * p.H, total = bh * nchunks;
     const bool epilogue = p.r_pre != nullptr;
     auto groups = [&](int chunks) { return bh * ((nchunks + chunks - 1) / chunks); };
     if (two_sided(p)) {
-        if (nchunks <= 4) return nchunks == 4 && (bh <= 128 || p.dk > 32 || p.dv > 64) && launch_fits(bh, 512) ? 4 : 0;
+        if (nchunks <= 4) return nchunks == 4 && (bh <= 128 || !small_heads(p)) && launch_fits(bh, 512) ? 4 : 0;
         return bh <= 128 && total >= 288 && groups(4) <= bh * kMaxChainedSpans ? 4 : 0;
     }
     if (nchunks <= 4) return nchunks == 4 && bh <= 128 ? 4 : 0;
-    if (total < (epilogue ? 384 : 48)) return 0;
+    if (total < (epilogue ? 384 : small_heads(p) ? 288 : nchunks <= 10 ? 320 : 513)) return 0;
     if (groups(4) <= 256) return 4;
     if (bh > 128) return epilogue && groups(8) <= 256 && (nchunks == 7 || nchunks == 8) ? 8 : 0;
     if (groups(8) <= 256) return 8;
     if (groups(4) <= 512) return 4;
     return groups(8) <= 512 && total >= 2990 && p.z_gate == nullptr ? 8 : 0;
+}
+
+// Whether the backward pass takes whole chunks although the forward call's states are there.  Forward and backward call, with the walks
+// over spans cut for them and with these kernels: 6 x 100 61.8 and 58.2 us, 16 x 43 61.8 and 59.3, 32 x 32 68.9 and 66.5, 64 x 16 66.0 and
+// 64.4, 64 x 10 56.9 and 56.0, but 64 x 6 46.5 and 50.6, 32 x 16 55.9 and 55.7 ([B,T,H,d] 32 x 13 55.5 and 64.4), 128 x 5 53.4 and 55.4;
+// 32 / 64 channels: 32 x 24 53.4 and 50.3, 128 x 8 52.3 and 51.6, 6 x 75 58.4 and 54.6, but 64 x 10 46.1 and 48.1, 6 x 52 46.0 and 49.
+bool onepass_back_with_states(const Params &p, int nchunks, long long total) {
+    return small_heads(p) ? total >= 720 || (nchunks >= 64 && total >= 400) : total >= 560 && nchunks >= 8;
+}
+
+// Chunks a span of those kernels: what a group holds, the most there can be, is the fastest for the forward call (64 x 24 24.1 us in spans
+// of 8, 26.3 of 6); where the walks of the backward pass may follow (onepass_back_takes), which go back over these spans, as short as leaves
+// one group a compute unit (64 x 24, both calls: 81.6 us in spans of 6, 89.1 of 8; 64 x 5 46.1 of 2, 54.9 of 4; S: 32 x 12 43.0 and 46.2).
+int onepass_chunks_per_span(const Params &p, int nchunks, int chunks) {
+    if (nchunks <= chunks) return nchunks;
+    const long long bh = (long long)p.B * p.H, total = bh * nchunks;
+    if (two_sided(p) || p.r_pre != nullptr || bh > 256) return chunks;
+    if (chunks == 4 && onepass_back_with_states(p, nchunks, total)) return chunks;
+    const int spans = (int)(256 / bh), c = (nchunks + spans - 1) / spans;
+    return c < 2 ? 2 : c < chunks ? c : chunks;       // (spans of one chunk leave no room for the flags)
 }
 
 // Whether the backward pass runs on the kernels that take whole chunks, four on a compute unit (`reuse`: the other kernels would
@@ -214,13 +239,13 @@ int onepass_chunks_per_group(const Params &p, int nchunks) {
 //     one span     16 x 4 1.40 (S 1.31, R 1.27), 256 x 4 1.26 (R 1.21), 512 x 4 1.13 (S 1.02), 16 x 3 1.20, 256 x 3 1.10, 320 x 3 0.98,
 //                  two chunks and fewer leave waves idle: 16 x 2 0.97, 1 chunk 0.7
 //     several      32 x 9 1.07 (S 0.89), 16 x 24 1.12 (S 1.04), 32 x 32 1.27, 16 x 64 1.30, 128 x 8 1.21, but 16 x 16 0.96 and 16 x 5
-//                  0.87, where two launches are all there is (R: 16 x 5 1.09, 16 x 64 1.04, 1 x 32 0.85)
+//                  0.87, where two launches are all there is (R: onepass_back_with_states)
 //     more groups than compute units 0.6 to 0.98: what a group loads and stores has nothing beside it there
 bool onepass_back_takes(const Params &p, bool reuse) {
     if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || two_sided(p) || !onepass_covers(p)) return false;
     const long long bh = (long long)p.B * p.H, nchunks = (p.T + kChunk - 1) / kChunk, total = bh * nchunks;
     if (nchunks <= 4) return nchunks == 4 ? bh <= 512 : nchunks == 3 && bh <= 256;
-    return bh * ((nchunks + 3) / 4) <= 256 && total >= (reuse ? 64 : (p.dk <= 32 && p.dv <= 64 ? 384 : 288));
+    return bh * ((nchunks + 3) / 4) <= 256 && (reuse ? onepass_back_with_states(p, nchunks, total) : total >= (small_heads(p) ? 384 : 288));
 }
 
 // A value that no earlier call's flags hold, nor (but for one chance in 2^64) memory that never held any
@@ -318,11 +343,12 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     if (use_onepass != nullptr) {
         // (without flags a sequence of one span needs no room; the bound over all plans holds these)
         const int c = use_mfma && g_opt_engine != GLA_ENGINE_MFMA_FP16 ? onepass_chunks_per_group(p, nchunks) : 0;
-        const size_t spans = c > 0 ? (size_t)((nchunks + c - 1) / c) : 1;
+        const int span = c > 0 ? onepass_chunks_per_span(p, nchunks, c) : 1;
+        const size_t spans = c > 0 ? (size_t)((nchunks + span - 1) / span) : 1;
         const bool fits = spans == 1 || plan_workspace_bytes(bh, spans, p.dk, p.dv) + onepass_flag_bytes(bh, spans, c) <= ws_limit;
         *use_onepass = fits ? c : 0;
         if (*use_onepass > 0) {
-            cps = c;
+            cps = span;
             if (use_fast != nullptr) *use_fast = false;
         }
     }

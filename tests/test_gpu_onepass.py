@@ -1,7 +1,8 @@
-"""The kernels that take whole chunks, forwards and backwards.  The single-launch forward kernels (a span's chunks on chip from the first load to the last store, states handed on through
-flags) at their edges: head sizes around the 16-channel units, the tail and the 16-column tiles, spans of 4 and of 8 chunks, ragged
-last chunks and spans, grids whose columns are shorter than a tile, both memory orders, an initial state, slow gates (every
-earlier span is looked at), sums over scan orders, gate prologue and epilogue; a wait that runs out, and replays of a graph.
+"""The kernels that take whole chunks, forwards and backwards.  The single-launch forward kernels (a span's chunks on chip from the first
+load to the last store, states handed on through flags) at their edges: head sizes around the 16-channel units, the tail and the
+16-column tiles, groups of 4 and of 8 chunks, filled or not, ragged last chunks and spans, grids whose columns are shorter than a tile,
+both memory orders, an initial state, slow gates (every earlier span is looked at), sums over scan orders, gate prologue and epilogue;
+a wait that runs out, and replays of a graph.
 
 Tolerance: as for the other kernels with split operands, 2e-4 of the RMS (an operand pair carries 16 bits, a product is off by at
 most 4 * 2^-17 of itself, and an output's largest value is about six times its RMS); a bf16 store adds at most half a unit of its
@@ -35,9 +36,10 @@ def near(got, want, bf16=False, tol=TOL):
     assert np.abs(got - want).max() / rms <= tol * max(1.0, top / rms / 6) + (2.0 ** -8 * top / rms if bf16 else 0.0)
 
 
-# (sequences as B x H, grid): one span; spans of 4 with a ragged last chunk or a last span of one chunk; the same of 8 (more than
-# 256 groups of 4); two groups on a compute unit; two rounds of groups
-PLANS = [(2, 2, 16, 16), (2, 3, 50, 13), (2, 3, 3, 219), (1, 6, 41, 16), (8, 16, 5, 91), (4, 16, 64, 17), (6, 16, 25, 43), (2, 16, 100, 65)]
+# (sequences as B x H, grid): one span; spans of two chunks with a ragged last one; of 4 (small heads 3); of 4 with a last span of one
+# chunk; full ones; spans of 5 in groups that could hold 8, with a last one of two chunks and with none; two rounds of groups
+PLANS = [(2, 2, 16, 16), (4, 16, 50, 7), (2, 16, 3, 365), (1, 6, 97, 64), (8, 16, 5, 91), (4, 16, 64, 17), (8, 16, 4, 151), (6, 16, 25, 43),
+         (2, 16, 100, 65)]
 
 
 @pytest.mark.parametrize("dk,dv,B,H,gh,gw", [(*h, *c) for h in ((36, 72), (32, 64)) for c in PLANS] +
@@ -57,7 +59,7 @@ def test_plans_and_heads(dk, dv, B, H, gh, gw):
 
 
 @pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
-@pytest.mark.parametrize("B,H,gh,gw,scans", [(2, 3, 50, 13, (0, 3)), (2, 16, 64, 64, (1, 2))])
+@pytest.mark.parametrize("B,H,gh,gw,scans", [(4, 16, 50, 7, (0, 3)), (2, 16, 64, 64, (1, 2))])
 def test_sums_and_their_states(B, H, gh, gw, scans, dk, dv):
     """Sums over scan orders; the last order's span states serve the backward call."""
     from oracle import gla_oracle
@@ -116,7 +118,7 @@ def test_two_sided_gate(dk, dv, B, H, gh, gw):
 def test_a_wait_that_runs_out(scan, fused):
     """No polls at all: what a span does not find at once it forms from the inputs."""
     from oracle import gla_oracle
-    B, H, gh, gw, dk, dv = 1, 7, 20, 33, 36, 72
+    B, H, gh, gw, dk, dv = 1, 7, 20, 254, 36, 72
     d = gi.make_fused_inputs(B, H, gh * gw, dk, dv, "bf16", seed=8)
     gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_MFMA)
     gla.gla_set_option(gla.OPT_LOOK_BACK_POLLS, 0)
