@@ -130,21 +130,26 @@ __global__ __launch_bounds__(NT, 4) void chunk_back_kernel(BackParams) {
         asm volatile("" ::: "memory");
     };
     if (tid < 4 * NC) s_meet[tid] = 0;
-    __syncthreads();
 
+    // what the first loads need, all at once: a group's first access to a line of its arguments takes as long as one to memory
+    int B = args->B, H = args->H, T = args->T, dk = args->dk, dv = args->dv, grid_h = args->grid_h, grid_w = args->grid_w,
+        scan_dir = args->scan_dir, nspans = args->nspans, st_k = args->st_k, st_v = args->st_v;
+    long long sb_k = args->sb_k, sh_k = args->sh_k, sb_v = args->sb_v, sh_v = args->sh_v;
+    const void *from_v = args->v, *from_o = args->d_out, *from_k = args->k, *from_q = args->q, *from_gate = args->log_alpha;
+    asm volatile("" : "+s"(B), "+s"(H), "+s"(T), "+s"(dk), "+s"(dv), "+s"(grid_h), "+s"(grid_w), "+s"(scan_dir), "+s"(nspans),
+                 "+s"(st_k), "+s"(st_v), "+s"(sb_k), "+s"(sh_k), "+s"(sb_v), "+s"(sh_v), "+s"(from_v), "+s"(from_o), "+s"(from_k), "+s"(from_q), "+s"(from_gate));
+    __syncthreads();           // (the counters of meet are there)
     int blk = blockIdx.x;      // contiguous ranges of spans per XCD
     {
-        const int nb = gridDim.x;
+        const int nb = B * H * nspans;
         if ((nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
     }
-    const int nspans = ARG->nspans;
     const int bh = blk / nspans, sp = blk - bh * nspans;
-    const int dk = ARG->dk, dv = ARG->dv, T = ARG->T;
     const int s_begin = sp * NC * kChunk, s_end = min(T, s_begin + NC * kChunk);
     const int c_begin = s_begin + (w >> 2) * kChunk;
-    const size_t base_k = (size_t)(bh / ARG->H) * (size_t)ARG->sb_k + (size_t)(bh % ARG->H) * (size_t)ARG->sh_k;
-    const size_t base_v = (size_t)(bh / ARG->H) * (size_t)ARG->sb_v + (size_t)(bh % ARG->H) * (size_t)ARG->sh_v;
-    const uint32_t dk2 = 2u * (uint32_t)ARG->st_k, dv2 = 2u * (uint32_t)ARG->st_v;   // bytes from one bf16 row to the next
+    const int batch = bh / H, head = bh - batch * H;
+    const size_t base_k = (size_t)batch * (size_t)sb_k + (size_t)head * (size_t)sh_k, base_v = (size_t)batch * (size_t)sb_v + (size_t)head * (size_t)sh_v;
+    const uint32_t dk2 = 2u * (uint32_t)st_k, dv2 = 2u * (uint32_t)st_v;   // bytes from one bf16 row to the next
     const uint32_t bytes_k = (uint32_t)(T - 1) * dk2 + 2u * (uint32_t)dk, bytes_v = (uint32_t)(T - 1) * dv2 + 2u * (uint32_t)dv;
     auto view_k = [&](const void *x, uint32_t bytes) { return view(static_cast<const char *>(x) + afresh(base_k) * bytes, bytes_k / 2 * bytes); };
     auto view_v = [&](const void *x, uint32_t bytes) { return view(static_cast<const char *>(x) + afresh(base_v) * bytes, bytes_v / 2 * bytes); };
@@ -161,14 +166,14 @@ __global__ __launch_bounds__(NT, 4) void chunk_back_kernel(BackParams) {
         LANE;
         int tok;
         {
-            const int col_len = ARG->scan_dir >= 2 ? ARG->grid_h : 1;       // (uniform)
-            const int s0 = min(c_begin + lane, s_end - 1), s = (ARG->scan_dir & 1) ? T - 1 - s0 : s0;
+            const int col_len = scan_dir >= 2 ? grid_h : 1;       // (uniform)
+            const int s0 = min(c_begin + lane, s_end - 1), s = (scan_dir & 1) ? T - 1 - s0 : s0;
             const int tc = s / col_len;
-            tok = (s - tc * col_len) * ARG->grid_w + tc;
+            tok = (s - tc * col_len) * grid_w + tc;
         }
         auto token_of = [&](int j) { return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * j, tok); };
         {
-            const Rsrc bv = view_v(ARG->v, 2), bo = view_v(ARG->d_out, 2);
+            const Rsrc bv = view_v(from_v, 2), bo = view_v(from_o, 2);
 #pragma unroll
             for (int i = 0; i < (VP + 3) / 4; ++i) {
                 if (4 * i + tile < VP) {
@@ -184,7 +189,7 @@ __global__ __launch_bounds__(NT, 4) void chunk_back_kernel(BackParams) {
         const uint32_t tk = token_of(16 * tile + lm);
         rowk = there ? tk * dk2 : kNowhere / 2;
         rowv = there ? tk * dv2 : kNowhere / 2;
-        const Rsrc bg = view_k(ARG->log_alpha, 4), bk = view_k(ARG->k, 2), bq = view_k(ARG->q, 2);
+        const Rsrc bg = view_k(from_gate, 4), bk = view_k(from_k, 2), bq = view_k(from_q, 2);
 #pragma unroll
         for (int u = 0; u < 2; ++u) la[u] = fetch<f32x4>(bg, f32_at(rowk, chb(u, g)));
         if constexpr (DT) lat = fetch<float>(bg, f32_at(rowk, tcb(g)));
