@@ -144,11 +144,11 @@ typedef enum {
                                  (or up to 36 and 65 to 80 value columns) of a column scan or of [B,T,H,d] tensors from
                                  3000 chunks of 64 tokens on, over all batches and heads; in gla_fwd_static only if their plan fits its array.
                                  Of heads of 17 to 36 key channels and 33 to 72 value columns, forward calls with one gate from about
-                                 512 chunks (320 for sequences of up to ten, 288 for up to 32 / 64 channels, 384 with the output epilogue)
-                                 up to about 2048, and larger plain ones of up to 128 sequences up to 4096, run on kernels with the
-                                 bf16 hi/lo operands that read their inputs once, in one launch; so do sequences of four chunks and, from
-                                 288 chunks on, the two-sided gate's of up to 128 sequences (not with GLA_OPT_CHUNKS_PER_SPAN or
-                                 GLA_CARRY_KERNEL set) */
+                                 512 chunks (320 for sequences of up to ten, 288 for up to 32 / 64 channels; with the output epilogue
+                                 48 to 192) up to about 2048, and larger ones of up to 128 sequences up to 4096, run on kernels with the
+                                 bf16 hi/lo operands that read their inputs once, in one launch; so do sequences of four chunks (with the
+                                 epilogue of three) and, from 288 chunks on, the two-sided gate's of up to 128 sequences (not with
+                                 GLA_OPT_CHUNKS_PER_SPAN or GLA_CARRY_KERNEL set) */
     GLA_ENGINE_RECURRENT = 1, /* fp32 token-by-token arithmetic inside each span; any dtype, any gates */
     GLA_ENGINE_MFMA = 2,      /* bf16 hi/lo MFMA chunk form (Sec. 3.5) in every pass, or in the one there is; bf16 inputs only */
     GLA_ENGINE_MFMA_FP16 = 3  /* fp16 operands in both passes of the plain forward call and of gla_fwd_fused without

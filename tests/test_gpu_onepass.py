@@ -37,9 +37,10 @@ def near(got, want, bf16=False, tol=TOL):
 
 
 # (sequences as B x H, grid): one span; spans of two chunks with a ragged last one; of 4 (small heads 3); of 4 with a last span of one
-# chunk; full ones; spans of 5 in groups that could hold 8, with a last one of two chunks and with none; two rounds of groups
+# chunk; full ones; spans of 5 in groups that could hold 8, with a last one of two chunks and with none; two rounds of groups;
+# one span of 6 chunks; many sequences of four (small heads)
 PLANS = [(2, 2, 16, 16), (4, 16, 50, 7), (2, 16, 3, 365), (1, 6, 97, 64), (8, 16, 5, 91), (4, 16, 64, 17), (8, 16, 4, 151), (6, 16, 25, 43),
-         (2, 16, 100, 65)]
+         (2, 16, 100, 65), (10, 16, 5, 72), (16, 16, 8, 30)]
 
 
 @pytest.mark.parametrize("dk,dv,B,H,gh,gw", [(*h, *c) for h in ((36, 72), (32, 64)) for c in PLANS] +
@@ -74,7 +75,8 @@ def test_sums_and_their_states(B, H, gh, gw, scans, dk, dv):
 
 
 @pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64), (20, 40)])
-@pytest.mark.parametrize("B,H,gh,gw", [(2, 3, 16, 15), (4, 16, 40, 13), (8, 16, 23, 37), (16, 16, 8, 61)])
+@pytest.mark.parametrize("B,H,gh,gw", [(2, 3, 16, 15), (4, 16, 40, 13), (8, 16, 23, 37), (16, 16, 8, 61), (2, 3, 11, 16), (2, 6, 13, 41), (12, 16, 35, 22),
+                                       (24, 16, 15, 34)])
 def test_gate_prologue_and_epilogue(B, H, gh, gw, dk, dv):
     from oracle import gla_oracle_fused as fo
     d = gi.make_fused_inputs(B, H, gh * gw, dk, dv, "bf16", seed=7)
