@@ -21,11 +21,12 @@
 // forms its part of the entering state from the inputs, token by token: every wait ends, and the result does not depend on it.
 // Operands are pairs of bf16 (hi + remainder; v as given), so products carry 16 bits; states, decays and sums are fp32.
 //
-// What bounds it on MI355X (36 / 72 channels, 1024 chunks in 256 groups of 4, 21 us): the rows of all groups come at the
-// memory's rate for 8 us, then 9 us of dependent stages (scores and U_c 3, publishing and looking back 4, outputs 2), then the
-// stores.  Against a state pass and an output pass, which read k, v and the gates twice: 1024 chunks 26.0 -> 22.5 us a call, 2048 36.5 ->
-// 28.5, with gate prologue and epilogue 45.5 -> 32.2, 4096 65.4 -> 59.5, and of those in a column scan whose gates hardly decay 90 -> 75 (a
-// column's neighbours are loaded at the same time, so the lines that they share are fetched once).
+// What bounds it on MI355X (36 / 72 channels, 1024 chunks in 256 groups of 4, 20 us): the rows of all groups come at the
+// memory's rate until 7 us, then 9 us of dependent stages (scores and U_c 3, publishing and looking back 4, outputs 2), then the
+// stores; at 4096 chunks two rounds of 28 us.  Against a state pass and an output pass, which read k, v and the gates twice (calls): 1024
+// chunks 29.1 -> 21.7 us, 2048 with gate prologue and epilogue 43.4 -> 30.0, 4096 70.7 -> 65.4, and of those in a column scan whose gates
+// hardly decay 89.8 -> 77.4 (a column's neighbours are loaded at the same time, so the lines that they share are fetched once); 1024 with the
+// two-sided gate 45.4 -> 26.2.
 // Why this shape: 128 registers and 20 KB of LDS a chunk, so 16 waves and 8 chunks on a compute unit (a wave per chunk with 256
 // registers: 72 us at 4096 chunks where this took 64, and 31 at 1024 where this took 25).  Straight-line code for waves whose
 // chunk is not there, arguments and lane numbers loaded afresh in each stage: with branches around the stages the registers
