@@ -181,7 +181,10 @@ bool small_heads(const Params &p) { return p.dk <= 32 && p.dv <= 64; }
 // Chunks that a work-group of the single-launch forward kernels holds (4 or 8), or 0 where the call stays on the others.  Eight chunks fill
 // a compute unit, so up to 2048 are one round of work-groups, all loads in flight at once.  Below: time of the two-pass kernels over
 // that of these, in sequences x chunks (36 / 72 channels; S: 32 / 64 channels), bf16 row scan and fp32 column scan where there are two.
-// A sequence's spans number at most kMaxChainedSpans: with slow gates every one of them is looked at.
+// A sequence has at most kMaxChainedSpans spans, since with gates that decay by nothing (z = 6) every earlier one is looked at (1 x 512 with 32 / 64
+// channels in 128 spans: z = 0 2.99, z = 3 2.01, z = 6 0.88; 2 x 1024 1.24, 1.22, 0.94), and in several rounds half as many, in calls whose
+// sequences lie within one or two of the eight ranges of spans that the XCDs work through in order: z = 6 3 x 1024 0.28, 6 x 512 0.50, but
+// 8 x 512 1.08, 16 x 256 1.06.
 
 // With the output epilogue (the two-pass kernels take two fills and a pass for it):
 //     4 chunks      16 1.34, 256 1.16, 512 1.11, 1920 1.03 (S 16 1.50, 510 1.19, 1920 1.23); 3 chunks 64 1.10, 192 1.06, but 288 0.95, 384 0.98
@@ -249,7 +252,9 @@ int onepass_plain_chunks(const Params &p, int nchunks) {
 int onepass_chunks_per_group(const Params &p, int nchunks) {
     if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || !onepass_covers(p)) return 0;
     const int c = two_sided(p) ? onepass_two_sided_chunks(p, nchunks) : p.r_pre != nullptr ? onepass_epilogue_chunks(p, nchunks) : onepass_plain_chunks(p, nchunks);
-    return c > 0 && nchunks <= c * kMaxChainedSpans ? c : 0;
+    if (c == 0 || nchunks <= c) return c;
+    const long long bh = (long long)p.B * p.H, spans = (nchunks + c - 1) / c, resident = c == 8 || two_sided(p) ? 256 : 512;
+    return bh * spans <= resident ? (spans <= kMaxChainedSpans ? c : 0) : (spans <= kMaxChainedSpans / 2 && bh >= 8 ? c : 0);
 }
 
 // Whether the backward pass takes whole chunks although the forward call's states are there.  Forward and backward call, with the walks
