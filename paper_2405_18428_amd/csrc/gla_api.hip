@@ -408,6 +408,14 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     return GLA_OK;
 }
 
+// Whether the kernels that need the state entering a span chain the local states of the spans before it themselves; else the carry
+// kernel has left (or will leave) the entering states in their place.  The single-launch kernels (`onepass`) only ever leave local
+// states, however many spans there are, and none of the last span.
+bool chains_in_output(const Params &p, bool use_mfma, int onepass = 0) {
+    if (!use_mfma || p.nspans <= 1) return false;
+    return onepass > 0 || g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS || (g_opt_carry == GLA_CARRY_AUTO && p.nspans <= kMaxChainedSpans);
+}
+
 void set_dense_bhtd_strides(Params &p) {
     p.st_k = p.dk; p.sh_k = (long long)p.T * p.dk; p.sb_k = (long long)p.H * p.T * p.dk;
     p.st_v = p.dv; p.sh_v = (long long)p.T * p.dv; p.sb_v = (long long)p.H * p.T * p.dv;
@@ -498,9 +506,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
     if (st != GLA_OK) return st;
     // MFMA engine with few spans per head: every kernel that needs the state entering its span chains the local
     // states itself (as the forward output pass does); otherwise the carry kernel chains them in place
-    base.chain_in_output = use_mfma && base.nspans > 1 &&
-                           (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
-                            (g_opt_carry == GLA_CARRY_AUTO && base.nspans <= kMaxChainedSpans));
+    base.chain_in_output = chains_in_output(base, use_mfma);
     const bool one_walk = use_mfma && !g_opt_bwd_split;     // one reversed walk for dk, dv and the gate gradient
     auto span = [&](const Params &p, SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
@@ -536,7 +542,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
     if (reuse) {
         // The forward call on the same tensors ran this very state pass.  Its workspace holds either the chained
         // states S_start(r) (carry kernel) or the local states U_r and log Gamma_r (chained inside its output
-        // pass), by the rule that also sets base.chain_in_output.
+        // pass, or left by the single-launch kernels).
         Params pf = base;
         pf.scan_dir = scan_dir;
         bool same_engine, fwd_fast = false;
@@ -549,9 +555,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         pa.ws_lgam = pf.ws_lgam;
         pa.nspans = pf.nspans;
         pa.span_len = pf.span_len;
-        pa.chain_in_output = use_mfma && pa.nspans > 1 &&
-                             (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
-                              (g_opt_carry == GLA_CARRY_AUTO && pa.nspans <= kMaxChainedSpans));
+        pa.chain_in_output = chains_in_output(pa, use_mfma, fwd_onepass);
     }
 
     // 2. states of the reversed recurrence G_s = q_s^T dO_s + diag(alpha_{s+1}) G_{s+1}: the forward recurrence
@@ -631,9 +635,7 @@ int run_bwd_gates(const void *q, const void *k, const void *v, const float *log_
     st = choose_engine_and_plan(base, workspace, use_mfma);
     if (st != GLA_OK) return st;
     // as in run_bwd: with the MFMA engine and few spans every kernel chains the span states it needs itself
-    base.chain_in_output = use_mfma && base.nspans > 1 &&
-                           (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
-                            (g_opt_carry == GLA_CARRY_AUTO && base.nspans <= kMaxChainedSpans));
+    base.chain_in_output = chains_in_output(base, use_mfma);
     const bool one_walk = use_mfma && !g_opt_bwd_split;     // one reversed walk for dk, dv and both gate gradients
     auto span = [&](const Params &p, SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
@@ -776,9 +778,7 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
         if (events) (void)hipEventRecord(events->ev[i], stream);
     };
 
-    p.chain_in_output = use_mfma && p.nspans > 1 &&
-                        (g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS ||
-                         (g_opt_carry == GLA_CARRY_AUTO && p.nspans <= kMaxChainedSpans));
+    p.chain_in_output = chains_in_output(p, use_mfma, use_onepass);
 
     hipError_t e = hipSuccess;
     mark(0);

@@ -163,6 +163,22 @@ def test_gradients(dk, dv, B, H, gh, gw):
             assert np.abs(got[3].cpu().numpy() - want[3]).max() <= TOL * 64 * size
 
 
+@pytest.mark.parametrize("chunks", [288, 320, 399])
+def test_one_long_sequence_and_its_states(chunks):
+    """One sequence of 32 / 64 channels: whatever number of spans the forward call cut it into (up to 200 of them were two chunks long, more
+    than the other kernels chain themselves), the backward call that takes its states finds local ones."""
+    from oracle import gla_oracle
+    dk, dv, gh, gw = 32, 64, chunks, 64
+    d = gi.make_inputs(1, 1, gh * gw, dk, dv, "bf16", seed=chunks, z_mean=1.5)
+    t = upload(d, "q", "k", "v", "log_alpha")
+    w = torch.from_numpy(np.random.default_rng(9).standard_normal((1, 1, gh * gw, dv)).astype(np.float32)).bfloat16()
+    want = gla_oracle.gla_bwd(d["q"], d["k"], d["v"], d["log_alpha"], w.float().numpy(), gh, gw, 0)
+    ws = torch.full((gla.gla_fwd_workspace_bytes(1, 1, gh * gw, dk, dv, gla.DT_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+    gla.gla_fwd_ex(*t, gh, gw, 0, workspace=ws)
+    for got, ref in zip(gla.gla_bwd(*t, w.cuda(), gh, gw, 0, fwd_workspace=ws)[:3], want[:3]):
+        near(got, ref)
+
+
 def test_replays_do_not_take_old_states():
     """A recorded call has one nonce for all replays: other inputs in the same buffers, and calls outside the graph on the same
     workspace, must not be answered from the states that the flags of an earlier replay stand for."""
