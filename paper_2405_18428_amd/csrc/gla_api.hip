@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "gla_common.h"
+#include "gla_onepass_plan.h"
 
 namespace gla {
 namespace {
@@ -20,10 +21,6 @@ std::atomic<int> g_opt_carry{GLA_CARRY_AUTO};
 std::atomic<int> g_opt_bwd_split{0};
 std::atomic<int> g_opt_range_fallback{1};
 std::atomic<int> g_opt_look_back_polls{1 << 15};     // (tens of milliseconds)
-
-// Most spans per (batch, head) that the output pass chains by itself: work-group r reads the r local states
-// before it, so the reads grow with the square of the span count while a carry kernel's grow linearly.
-constexpr int kMaxChainedSpans = 128; // beyond this the reads of a slowly decaying chain outgrow the carry kernel
 
 struct Scratch {
     void *ptr = nullptr;
@@ -172,124 +169,11 @@ int hilo_chunks_per_span(int bh, int nchunks, bool epilogue) {
     return best > 0 ? best : nchunks;        // (more than 1536 sequences)
 }
 
-// Bytes of the flags of a single-launch plan (two waves a chunk), which lie behind the sums of the gates
-size_t onepass_flag_bytes(size_t bh, size_t nspans, int chunks) { return align_up(bh * nspans * 2 * chunks * sizeof(unsigned long long), 256); }
-
-// Heads of up to 32 / 64 channels
-bool small_heads(const Params &p) { return p.dk <= 32 && p.dv <= 64; }
-
-// Chunks that a work-group of the single-launch forward kernels holds (4 or 8), or 0 where the call stays on the others.  Eight chunks fill
-// a compute unit, so up to 2048 are one round of work-groups, all loads in flight at once.  Below: time of the two-pass kernels over
-// that of these, in sequences x chunks (36 / 72 channels; S: 32 / 64 channels), bf16 row scan and fp32 column scan where there are two.
-// A sequence has at most kMaxChainedSpans spans, since with gates that decay by nothing (z = 6) every earlier one is looked at (1 x 512 with 32 / 64
-// channels in 128 spans: z = 0 2.99, z = 3 2.01, z = 6 0.88; 2 x 1024 1.24, 1.22, 0.94), and in several rounds half as many, in calls whose
-// sequences lie within one or two of the eight ranges of spans that the XCDs work through in order: z = 6 3 x 1024 0.28, 6 x 512 0.50, but
-// 8 x 512 1.08, 16 x 256 1.06.
-
-// With the output epilogue (the two-pass kernels take two fills and a pass for it):
-//     4 chunks      16 1.34, 256 1.16, 512 1.11, 1920 1.03 (S 16 1.50, 510 1.19, 1920 1.23); 3 chunks 64 1.10, 192 1.06, but 288 0.95, 384 0.98
-//                   (S 192 1.20, 288 0.97); 2 chunks 192 0.89 (S 0.96)
-//     groups of 4   3 x 16 1.11 1.04, 6 x 12 1.14 1.06, 16 x 8 1.05, 48 x 5 1.02, 32 x 12 1.36, but 16 x 5 0.99, 16 x 6 1.01 0.98, 32 x 5 0.99
-//                   (S 12 x 6 1.14 1.07); 160 x 9 1.35
-//     groups of 8   192 x 6 1.11, 256 x 6 1.10, 256 x 8 1.28, but 192 x 5 1.00 (S 1.34); 6 x 300 1.49
-//     rounds        16 x 256 1.07 1.12, 32 x 128 1.08 1.18, 128 x 24 1.07 1.15, 160 x 24 1.20 1.28, 192 x 16 1.15 1.12, 64 x 43 1.02 1.04, but 256 x 32
-//                   0.94 0.92, 256 x 12 0.87; in fours 192 x 12 1.14, but 192 x 9 0.95, 256 x 12 1.03 0.97, 32 x 128 with slow gates 0.81, 512 x 8 0.89,
-//                   304 x 6 0.97 (sequences from 256 on stay in one pass each, 304 x 12 1.22 for all that); S, in fours: 96 x 32 1.47, 192 x 16 1.58, 126 x 32 1.18, 252 x 9 1.24, 510 x 8 1.09, but 510 x 6 0.95, 510 x 5 0.80
-int onepass_epilogue_chunks(const Params &p, int nchunks) {
-    const long long bh = (long long)p.B * p.H, total = bh * nchunks;
-    const bool small = small_heads(p);
-    auto groups = [&](int chunks) { return bh * ((nchunks + chunks - 1) / chunks); };
-    if (nchunks <= 4) return (nchunks == 4 && launch_fits(bh, 512)) || (nchunks == 3 && bh <= 256) ? 4 : 0;
-    if (total < (small ? 48 : nchunks >= 8 ? 72 : 192)) return 0;
-    if (groups(4) <= 256) return 4;
-    if (bh > 128 && nchunks <= 8) {
-        if (bh <= 256) return small || nchunks >= 6 ? 8 : 0;
-        return small && nchunks == 8 && bh <= 512 ? 4 : 0;
-    }
-    if (groups(8) <= 256) return 8;
-    if (groups(4) <= 512) return 4;
-    if (small) return groups(4) <= 1024 ? 4 : 0;
-    if (bh >= 256) return 0;
-    if (nchunks < 16) return (nchunks == 11 || nchunks == 12) && groups(4) <= 1024 ? 4 : 0;
-    return groups(8) <= 512 ? 8 : 0;
-}
-
-// With the two-sided gate there is room for four chunks on a compute unit, in one group: 16 x 4 1.29 (S 1.05), 256 x 4 1.17 (S 1.01), 512 x 4
-// 1.17 (S 0.83), 16 x 16 1.02 (column scan 0.87), 32 x 9 1.28 (S 1.13), 64 x 16 1.73 (S 1.52), and in several rounds 128 x 9 1.17 (S 1.00),
-// 32 x 64 1.43, 16 x 256 1.38, 128 x 32 1.40 (S 1.16), but 192 x 5 0.74 and 256 x 16 0.87, whose sequences the other kernels walk in one pass.
-int onepass_two_sided_chunks(const Params &p, int nchunks) {
-    const long long bh = (long long)p.B * p.H;
-    if (nchunks <= 4) return nchunks == 4 && (bh <= 128 || !small_heads(p)) && launch_fits(bh, 512) ? 4 : 0;
-    return bh <= 128 && bh * nchunks >= 288 ? 4 : 0;
-}
-
-// Of the plain call the backward call may take the span states, so this is a matter of both:
-//     4 chunks      16 1.14, 128 1.10, but 192 1.02 0.97, 256 0.97 0.94 (S 96 1.15, 240 1.05, 360 1.03, 600 1.10; both calls 1.05 to 1.01)
-//     groups of 4   64 x 8 1.18, 32 x 32 1.16, 128 x 8 1.29; S: 16 x 20 1.14, 16 x 32 1.16; two groups on a unit 96 x 17 1.16 to 1.31
-//     groups of 8   16 x 100 1.20, 32 x 64 1.26, 128 x 16 1.38, 128 x 5 1.13; 136 x 6 1.35 1.57, 168 x 6 1.33 1.57, 168 x 7 1.46 1.64 (both calls 1.11 and
-//                   1.24), where the other plan has one round and a half, but 176 x 6 0.96 1.03, 144 x 5 0.96, 256 x 7 0.93 1.04 (S 0.94);
-//                   192 x 7 1.00 1.08, 224 x 8 1.01 1.10 (S 1.02 1.04)
-//     two rounds    32 x 100 1.08, 32 x 128 1.15 1.18, 64 x 64 1.14, 96 x 32 1.15 1.14, 16 x 256 1.10 1.16, but 64 x 43 0.93,
-//                   128 x 17 0.91, 192 x 16 1.29 0.95; three and more 0.87 to 1.11
-// Sequences of up to three chunks, which would leave waves idle, take 0.6 to 1.0.  Of longer ones, smaller calls stay with the others
-// although the forward call alone would gain (16 x 8 16.2 us, 14.6 here; 16 x 20 19.8, 17.4): the walks of the backward call that takes the
-// span states want spans of one or two chunks there (both calls: 16 x 8 39.9 us, here 44.4; 16 x 20 52.5, here 52.5 to 58; [B,T,H,d]
-// 32 x 13 55.5 and 64.4), and in spans that short these kernels gain nothing (16 x 8 18.0 us, 16 x 20 19.3, 16 x 27 22.8 for 20.7) but for
-// few of them a sequence (64 x 5 1.11, both calls 1.03) and small heads (16 x 20, both calls: 44.6 us, here 42.8).
-int onepass_plain_chunks(const Params &p, int nchunks) {
-    const long long bh = (long long)p.B * p.H, total = bh * nchunks;
-    const bool small = small_heads(p);
-    auto groups = [&](int chunks) { return bh * ((nchunks + chunks - 1) / chunks); };
-    if (nchunks <= 4) return nchunks == 4 && bh <= (small ? 640 : 128) ? 4 : 0;
-    if (total < (small ? 288 : nchunks <= 10 ? 320 : 513)) return 0;
-    if (groups(4) <= 256) return 4;
-    if (bh > 128) return nchunks <= 8 && bh <= (nchunks == 8 ? 256 : nchunks == 7 ? 192 : nchunks == 6 ? 170 : 0) ? 8 : 0;
-    if (groups(8) <= 256) return 8;
-    if (groups(4) <= 512) return 4;
-    return groups(8) <= 512 && total >= 2990 && p.z_gate == nullptr ? 8 : 0;
-}
-
-int onepass_chunks_per_group(const Params &p, int nchunks) {
-    if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || !onepass_covers(p)) return 0;
-    const int c = two_sided(p) ? onepass_two_sided_chunks(p, nchunks) : p.r_pre != nullptr ? onepass_epilogue_chunks(p, nchunks) : onepass_plain_chunks(p, nchunks);
-    if (c == 0 || nchunks <= c) return c;
-    const long long bh = (long long)p.B * p.H, spans = (nchunks + c - 1) / c, resident = c == 8 || two_sided(p) ? 256 : 512;
-    return bh * spans <= resident ? (spans <= kMaxChainedSpans ? c : 0) : (spans <= kMaxChainedSpans / 2 && bh >= 8 ? c : 0);
-}
-
-// Whether the backward pass takes whole chunks although the forward call's states are there.  Forward and backward call, with the walks
-// over spans cut for them and with these kernels: 6 x 100 61.8 and 58.2 us, 16 x 43 61.8 and 59.3, 32 x 32 68.9 and 66.5, 64 x 16 66.0 and
-// 64.4, 64 x 10 56.9 and 56.0, but 64 x 6 46.5 and 50.6, 32 x 16 55.9 and 55.7 ([B,T,H,d] 32 x 13 55.5 and 64.4), 128 x 5 53.4 and 55.4;
-// 32 / 64 channels: 32 x 24 53.4 and 50.3, 128 x 8 52.3 and 51.6, 6 x 75 58.4 and 54.6, but 64 x 10 46.1 and 48.1, 6 x 52 46.0 and 49.
-bool onepass_back_with_states(const Params &p, int nchunks, long long total) {
-    return small_heads(p) ? total >= 720 || (nchunks >= 64 && total >= 400) : total >= 560 && nchunks >= 8;
-}
-
-// Chunks a span of those kernels: what a group holds, the most there can be, is the fastest for the forward call (64 x 24 24.1 us in spans
-// of 8, 26.3 of 6); where the walks of the backward pass may follow (onepass_back_takes), which go back over these spans, as short as leaves
-// one group a compute unit (64 x 24, both calls: 81.6 us in spans of 6, 89.1 of 8; 64 x 5 46.1 of 2, 54.9 of 4; S: 32 x 12 43.0 and 46.2).
-int onepass_chunks_per_span(const Params &p, int nchunks, int chunks) {
-    if (nchunks <= chunks) return nchunks;
-    const long long bh = (long long)p.B * p.H, total = bh * nchunks;
-    if (two_sided(p) || p.r_pre != nullptr || bh > 256) return chunks;
-    if (chunks == 4 && onepass_back_with_states(p, nchunks, total)) return chunks;
-    const int spans = (int)(256 / bh), c = (nchunks + spans - 1) / spans;
-    return c < 2 ? 2 : c < chunks ? c : chunks;       // (spans of one chunk leave no room for the flags)
-}
-
-// Whether the backward pass runs on the kernels that take whole chunks, four on a compute unit (`reuse`: the other kernels would
-// find the forward states in the forward call's workspace).  Time of the walks over that of these (36 / 72 channels, sequences x
-// chunks; S: 32 / 64 channels, R: with the forward call's states, that call included):
-//     one span     16 x 4 1.40 (S 1.31, R 1.27), 256 x 4 1.26 (R 1.21), 512 x 4 1.13 (S 1.02), 16 x 3 1.20, 256 x 3 1.10, 320 x 3 0.98,
-//                  two chunks and fewer leave waves idle: 16 x 2 0.97, 1 chunk 0.7
-//     several      32 x 9 1.07 (S 0.89), 16 x 24 1.12 (S 1.04), 32 x 32 1.27, 16 x 64 1.30, 128 x 8 1.21, but 16 x 16 0.96 and 16 x 5
-//                  0.87, where two launches are all there is (R: onepass_back_with_states)
-//     more groups than compute units 0.6 to 0.98: what a group loads and stores has nothing beside it there
-bool onepass_back_takes(const Params &p, bool reuse) {
-    if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || two_sided(p) || !onepass_covers(p)) return false;
-    const long long bh = (long long)p.B * p.H, nchunks = (p.T + kChunk - 1) / kChunk, total = bh * nchunks;
-    if (nchunks <= 4) return nchunks == 4 ? bh <= 512 : nchunks == 3 && bh <= 256;
-    return bh * ((nchunks + 3) / 4) <= 256 && (reuse ? onepass_back_with_states(p, nchunks, total) : total >= (small_heads(p) ? 384 : 288));
+// The call as those rules see it; nothing where an option asks for another plan, or the kernels do not cover it
+bool onepass_call(const Params &p, OnePassCall &call) {
+    if (g_opt_chunks_per_span > 0 || g_opt_carry == GLA_CARRY_KERNEL || !onepass_covers(p)) return false;
+    call = {(long long)p.B * p.H, (p.T + kChunk - 1) / kChunk, p.dk <= 32 && p.dv <= 64, two_sided(p), p.z_gate != nullptr, p.r_pre != nullptr};
+    return true;
 }
 
 // A value that no earlier call's flags hold, nor (but for one chance in 2^64) memory that never held any
@@ -386,8 +270,9 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     }
     if (use_onepass != nullptr) {
         // (without flags a sequence of one span needs no room; the bound over all plans holds these)
-        const int c = use_mfma && g_opt_engine != GLA_ENGINE_MFMA_FP16 ? onepass_chunks_per_group(p, nchunks) : 0;
-        const int span = c > 0 ? onepass_chunks_per_span(p, nchunks, c) : 1;
+        OnePassCall call;
+        const int c = use_mfma && g_opt_engine != GLA_ENGINE_MFMA_FP16 && onepass_call(p, call) ? onepass_chunks_per_group(call) : 0;
+        const int span = c > 0 ? onepass_chunks_per_span(call, c) : 1;
         const size_t spans = c > 0 ? (size_t)((nchunks + span - 1) / span) : 1;
         const bool fits = spans == 1 || plan_workspace_bytes(bh, spans, p.dk, p.dv) + onepass_flag_bytes(bh, spans, c) <= ws_limit;
         *use_onepass = fits ? c : 0;
@@ -521,7 +406,8 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         return launch_carry(p, stream);
     };
 
-    if (one_walk && onepass_back_takes(base, fwd_workspace != nullptr)) {
+    OnePassCall call;
+    if (one_walk && onepass_call(base, call) && onepass_back_takes(call, fwd_workspace != nullptr)) {
         BackParams pc{base};
         const int nchunks = (T + kChunk - 1) / kChunk;
         pc.q = q; pc.k = k; pc.v = v; pc.log_alpha = log_alpha; pc.scan_dir = scan_dir; pc.d_out = d_out;
