@@ -271,13 +271,13 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
     if (use_onepass != nullptr) {
         // (without flags a sequence of one span needs no room; the bound over all plans holds these)
         OnePassCall call;
-        const int c = use_mfma && g_opt_engine != GLA_ENGINE_MFMA_FP16 && onepass_call(p, call) ? onepass_chunks_per_group(call) : 0;
-        const int span = c > 0 ? onepass_chunks_per_span(call, c) : 1;
-        const size_t spans = c > 0 ? (size_t)((nchunks + span - 1) / span) : 1;
-        const bool fits = spans == 1 || plan_workspace_bytes(bh, spans, p.dk, p.dv) + onepass_flag_bytes(bh, spans, c) <= ws_limit;
-        *use_onepass = fits ? c : 0;
+        OnePassPlan plan{0, 0};
+        if (use_mfma && g_opt_engine != GLA_ENGINE_MFMA_FP16 && onepass_call(p, call)) plan = onepass_plan(call);
+        const size_t spans = plan.chunks > 0 ? (size_t)((nchunks + plan.span - 1) / plan.span) : 1;
+        const bool fits = spans == 1 || plan_workspace_bytes(bh, spans, p.dk, p.dv) + onepass_flag_bytes(bh, spans, plan.chunks) <= ws_limit;
+        *use_onepass = fits ? plan.chunks : 0;
         if (*use_onepass > 0) {
-            cps = span;
+            cps = plan.span;
             if (use_fast != nullptr) *use_fast = false;
         }
     }

@@ -23,10 +23,6 @@ inline size_t onepass_flag_bytes(size_t bh, size_t nspans, int chunks) { return 
 // Chunks that a work-group of the single-launch forward kernels holds (4 or 8), or 0 where the call stays on the others.  Eight chunks fill
 // a compute unit, so up to 2048 are one round of work-groups, all loads in flight at once.  Below: time of the two-pass kernels over
 // that of these, in sequences x chunks (36 / 72 channels; S: 32 / 64 channels), bf16 row scan and fp32 column scan where there are two.
-// A sequence has at most kMaxChainedSpans spans, since with gates that decay by nothing (z = 6) every earlier one is looked at (1 x 512 with 32 / 64
-// channels in 128 spans: z = 0 2.99, z = 3 2.01, z = 6 0.88; 2 x 1024 1.24, 1.22, 0.94), and in several rounds half as many, in calls whose
-// sequences lie within one or two of the eight ranges of spans that the XCDs work through in order: z = 6 3 x 1024 0.28, 6 x 512 0.50, but
-// 8 x 512 1.08, 16 x 256 1.06.
 
 // With the output epilogue (the two-pass kernels take two fills and a pass for it):
 //     4 chunks      16 1.34, 256 1.16, 512 1.11, 1920 1.03 (S 16 1.50, 510 1.19, 1920 1.23); 3 chunks 64 1.10, 192 1.06, but 288 0.95, 384 0.98
@@ -94,11 +90,34 @@ inline int onepass_plain_chunks(const OnePassCall &p) {
     return groups(8) <= 512 && total >= 2990 && !p.prologue ? 8 : 0;
 }
 
+inline int onepass_resident(const OnePassCall &p, int chunks) { return chunks == 8 || p.two_sided ? 256 : 512; }     // groups at once
+
+// Most spans of a sequence where all groups are resident at once.  With gates that decay by nothing (z = 6) every earlier span is looked at,
+// four a trip to memory (of about 1 us) in groups of eight, two in groups of four; the two-pass kernels take 16 or 32, and a kernel of its own above
+// kMaxChainedSpans.  Their time over that of these, z = 0, 3 and 6, fours and in their place eights:
+//     36 / 72 channels   4 x 192 (48 spans of 4) 1.20 1.06 0.99 (1.03 1.17 1.28), 3 x 256 (64) 1.29 1.01 0.90 (1.11 1.14 1.23), 2 x 320 (80) 1.30 1.06 0.90
+//                        (1.17 1.25 1.38), 2 x 512 (128) 1.19 1.00 0.73 (1.12 1.18 1.29); eights 2 x 700 (88) 1.18 1.21 1.11, 2 x 1024 (128) 1.26 1.23 0.98
+//     32 / 64            2 x 256 (64) 1.30 1.04 1.00 (0.94 1.00 1.15), 2 x 320 (80) 1.40 1.07 0.89 (1.06 1.01 1.03), 2 x 512 (128) 1.37 1.04 0.72
+//                        (1.03 0.97 0.93), 1 x 512 (128) 3.14 2.01 0.89 (2.20 1.89 1.19); eights 4 x 512 (64) 1.25 1.21 1.03, but 2 x 700 (88) 1.15 1.11
+//                        0.88, 2 x 1024 (128) 1.25 1.21 0.80
+//     epilogue           2 x 256 (64) 1.45 1.23 1.13, 3 x 320 (80) 1.38 1.17 0.97 (1.16 1.23 1.33), 1 x 512 (128) 2.33 1.60 0.68 (1.81 1.63 1.09), eights
+//                        2 x 1024 (128) 1.38 1.39 1.16; 32 / 64: 2 x 512 (128) 2.67 1.96 1.04, eights 2 x 1024 2.16 2.00 1.11
+//     two-sided gate     2 x 400 (100) 1.80 1.41 1.01, 2 x 512 (128) 1.72 1.38 0.94, and one sequence, which the others cut into more than
+//                        kMaxChainedSpans spans, 1 x 320 (80) 2.18 1.45 0.77; 32 / 64: 1 x 400 (100) 2.39 1.83 1.03, 1 x 512 (128) 2.62 2.00 0.97
+inline int onepass_most_spans(const OnePassCall &p, int chunks) {
+    if (p.two_sided) return p.bh > 1 || p.small ? 100 : 0;
+    if (p.epilogue) return chunks == 4 && !p.small ? 64 : kMaxChainedSpans;
+    return p.small ? 64 : chunks == 4 ? 48 : kMaxChainedSpans;
+}
+
 inline int onepass_chunks_per_group(const OnePassCall &p) {
     const int nchunks = p.nchunks, c = p.two_sided ? onepass_two_sided_chunks(p) : p.epilogue ? onepass_epilogue_chunks(p) : onepass_plain_chunks(p);
     if (c == 0 || nchunks <= c) return c;
-    const long long bh = p.bh, spans = (nchunks + c - 1) / c, resident = c == 8 || p.two_sided ? 256 : 512;
-    return bh * spans <= resident ? (spans <= kMaxChainedSpans ? c : 0) : (spans <= kMaxChainedSpans / 2 && bh >= 8 ? c : 0);
+    auto spans = [&](int chunks) { return (nchunks + chunks - 1) / chunks; };
+    if (p.bh * spans(c) > onepass_resident(p, c)) return spans(c) <= kMaxChainedSpans / 2 && p.bh >= 8 ? c : 0;
+    if (spans(c) <= onepass_most_spans(p, c)) return c;
+    const bool eights = c == 4 && !p.two_sided && spans(4) <= kMaxChainedSpans && p.bh * spans(8) <= onepass_resident(p, 8);
+    return eights && spans(8) <= onepass_most_spans(p, 8) ? 8 : 0;
 }
 
 // Whether the backward pass takes whole chunks although the forward call's states are there.  Forward and backward call, with the walks
@@ -108,19 +127,6 @@ inline int onepass_chunks_per_group(const OnePassCall &p) {
 inline bool onepass_back_with_states(const OnePassCall &p) {
     const long long nchunks = p.nchunks, total = p.bh * nchunks;
     return p.small ? total >= 720 || (nchunks >= 64 && total >= 400) : total >= 560 && nchunks >= 8;
-}
-
-// Chunks a span of those kernels: what a group holds, the most there can be, is the fastest for the forward call (64 x 24 24.1 us in spans
-// of 8, 26.3 of 6); where the walks of the backward pass may follow (onepass_back_takes), which go back over these spans, as short as leaves
-// one group a compute unit (64 x 24, both calls: 81.6 us in spans of 6, 89.1 of 8; 64 x 5 46.1 of 2, 54.9 of 4; S: 32 x 12 43.0 and 46.2).
-inline int onepass_chunks_per_span(const OnePassCall &p, int chunks) {
-    const int nchunks = p.nchunks;
-    if (nchunks <= chunks) return nchunks;
-    const long long bh = p.bh;
-    if (p.two_sided || p.epilogue || bh > 256) return chunks;
-    if (chunks == 4 && onepass_back_with_states(p)) return chunks;
-    const int spans = (int)(256 / bh), c = (nchunks + spans - 1) / spans;
-    return c < 2 ? 2 : c < chunks ? c : chunks;       // (spans of one chunk leave no room for the flags)
 }
 
 // Whether the backward pass runs on the kernels that take whole chunks, four on a compute unit (`reuse`: the other kernels would
@@ -136,6 +142,32 @@ inline bool onepass_back_takes(const OnePassCall &p, bool reuse) {
     const long long bh = p.bh, nchunks = p.nchunks, total = bh * nchunks;
     if (nchunks <= 4) return nchunks == 4 ? bh <= 512 : nchunks == 3 && bh <= 256;
     return bh * ((nchunks + 3) / 4) <= 256 && (reuse ? onepass_back_with_states(p) : total >= (p.small ? 384 : 288));
+}
+
+// How the call is cut: chunks that a group holds (0: the call stays on the other kernels) and chunks of a span, of which a group takes one.
+// What a group holds is the fastest for the forward call (64 x 24 24.1 us in spans of 8, 26.3 of 6).  Where the walks of the backward pass may
+// follow, which go back over these spans, they are as short as leaves one group a compute unit (64 x 24, both calls: 81.6 us in spans of 6, 89.1
+// of 8; 64 x 5 46.1 of 2, 54.9 of 4; S: 32 x 12 43.0 and 46.2), but not so many that looking back takes longer (S, both calls, z = 3: 3 x 128 63.4
+// us in 64 spans of 2, 54.7 in 43 of 3; 1 x 320 in 107 of 3 and 46 of 7, forward call 29.6 and 22.3).  A few sequences where the two do not
+// agree stay on the other kernels (S, z = 3: 2 x 192 63.4 us in 96 of 2, 60.0 in 48 of 4, 56.4 there; 3 x 400 86.9 in 50 of 8, 77.3 there).
+struct OnePassPlan {
+    int chunks, span;
+};
+inline OnePassPlan onepass_plan(const OnePassCall &p) {
+    const int nchunks = p.nchunks, chunks = onepass_chunks_per_group(p);
+    if (chunks == 0 || nchunks <= chunks) return {chunks, chunks > 0 ? nchunks : 0};
+    const bool walks = !p.two_sided && !p.epilogue && p.bh <= 256 && !(chunks == 4 && onepass_back_with_states(p)) && !onepass_back_takes(p, true);
+    if (!walks) return {chunks, chunks};
+    auto cut = [&](int parts) { return (nchunks + parts - 1) / parts; };
+    int span = cut((int)(256 / p.bh));
+    span = span < 2 ? 2 : span < chunks ? span : chunks;                      // (spans of one chunk leave no room for the flags)
+    if (chunks == 4 && cut(span) > 30 && span < chunks) {
+        if (p.bh > 5) return {0, 0};      // (S, z = 3: 6 x 63 in 32 spans of 2 49.7 us, in 21 of 3 51.9, 48.3 there)
+        ++span;
+    }
+    if (chunks == 8 && p.bh == 1 && span < cut(48)) span = cut(48) < chunks ? cut(48) : chunks;
+    if (cut(span) > (chunks == 4 ? 48 : onepass_most_spans(p, 8))) return {0, 0};
+    return {chunks, span};
 }
 
 }  // namespace gla
