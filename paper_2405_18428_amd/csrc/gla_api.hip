@@ -190,7 +190,7 @@ unsigned long long next_nonce() {
 // plain_plan: the plan of the plain forward pass, whatever kernels the call itself runs on (the last scan order of a sum, whose
 // span states gla_bwd_reuse takes on that plan).
 int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use_fast = nullptr,
-                           size_t ws_limit = ~(size_t)0, bool plain_plan = false, int *use_onepass = nullptr) {
+                           size_t ws_limit = ~(size_t)0, bool plain_plan = false, OnePassPlan *onepass = nullptr) {
     if (g_opt_engine == GLA_ENGINE_RECURRENT) {
         use_mfma = false;
     } else if (g_opt_engine == GLA_ENGINE_MFMA || g_opt_engine == GLA_ENGINE_MFMA_FP16) {
@@ -268,16 +268,15 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
             cps = other;
         }
     }
-    if (use_onepass != nullptr) {
+    if (onepass != nullptr) {
         // (without flags a sequence of one span needs no room; the bound over all plans holds these)
         OnePassCall call;
-        OnePassPlan plan{0, 0};
-        if (use_mfma && g_opt_engine != GLA_ENGINE_MFMA_FP16 && onepass_call(p, call)) plan = onepass_plan(call);
-        const size_t spans = plan.chunks > 0 ? (size_t)((nchunks + plan.span - 1) / plan.span) : 1;
-        const bool fits = spans == 1 || plan_workspace_bytes(bh, spans, p.dk, p.dv) + onepass_flag_bytes(bh, spans, plan.chunks) <= ws_limit;
-        *use_onepass = fits ? plan.chunks : 0;
-        if (*use_onepass > 0) {
-            cps = plan.span;
+        *onepass = {0, 0};
+        if (use_mfma && g_opt_engine != GLA_ENGINE_MFMA_FP16 && onepass_call(p, call)) *onepass = onepass_plan(call);
+        const size_t spans = onepass->chunks > 0 ? (size_t)((nchunks + onepass->span - 1) / onepass->span) : 1;
+        if (spans > 1 && plan_workspace_bytes(bh, spans, p.dk, p.dv) + onepass_flag_bytes(bh, spans, onepass->chunks) > ws_limit) *onepass = {0, 0};
+        if (onepass->chunks > 0) {
+            cps = onepass->span;
             if (use_fast != nullptr) *use_fast = false;
         }
     }
@@ -296,9 +295,9 @@ int choose_engine_and_plan(Params &p, void *workspace, bool &use_mfma, bool *use
 // Whether the kernels that need the state entering a span chain the local states of the spans before it themselves; else the carry
 // kernel has left (or will leave) the entering states in their place.  The single-launch kernels (`onepass`) only ever leave local
 // states, however many spans there are, and none of the last span.
-bool chains_in_output(const Params &p, bool use_mfma, int onepass = 0) {
+bool chains_in_output(const Params &p, bool use_mfma, bool onepass = false) {
     if (!use_mfma || p.nspans <= 1) return false;
-    return onepass > 0 || g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS || (g_opt_carry == GLA_CARRY_AUTO && p.nspans <= kMaxChainedSpans);
+    return onepass || g_opt_carry == GLA_CARRY_IN_OUTPUT_PASS || (g_opt_carry == GLA_CARRY_AUTO && p.nspans <= kMaxChainedSpans);
 }
 
 void set_dense_bhtd_strides(Params &p) {
@@ -432,7 +431,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         Params pf = base;
         pf.scan_dir = scan_dir;
         bool same_engine, fwd_fast = false;
-        int fwd_onepass = 0;
+        OnePassPlan fwd_onepass;
         if (choose_engine_and_plan(pf, const_cast<void *>(fwd_workspace), same_engine, &fwd_fast, ~(size_t)0, false, &fwd_onepass) != GLA_OK)
             return GLA_ERR_HIP;
         // either way the states are read where they are: the row-read kernel chains local states itself.
@@ -441,7 +440,7 @@ int run_bwd(const void *q, const void *k, const void *v, const float *log_alpha,
         pa.ws_lgam = pf.ws_lgam;
         pa.nspans = pf.nspans;
         pa.span_len = pf.span_len;
-        pa.chain_in_output = chains_in_output(pa, use_mfma, fwd_onepass);
+        pa.chain_in_output = chains_in_output(pa, use_mfma, fwd_onepass.chunks > 0);
     }
 
     // 2. states of the reversed recurrence G_s = q_s^T dO_s + diag(alpha_{s+1}) G_{s+1}: the forward recurrence
@@ -652,10 +651,10 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
     }
 
     bool use_mfma, use_fast = false;
-    int use_onepass = 0;
-    st = choose_engine_and_plan(p, workspace, use_mfma, &use_fast, plan_sized_workspace ? ws_bytes : ~(size_t)0, accumulate == 2, &use_onepass);
+    OnePassPlan onepass;
+    st = choose_engine_and_plan(p, workspace, use_mfma, &use_fast, plan_sized_workspace ? ws_bytes : ~(size_t)0, accumulate == 2, &onepass);
     if (st != GLA_OK) return st;
-    if (plan_sized_workspace && use_onepass == 0 && ws_bytes < plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv))
+    if (plan_sized_workspace && onepass.chunks == 0 && ws_bytes < plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv))
         return GLA_ERR_WORKSPACE;
     auto span = [&](SpanMode mode) {
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
@@ -664,18 +663,18 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
         if (events) (void)hipEventRecord(events->ev[i], stream);
     };
 
-    p.chain_in_output = chains_in_output(p, use_mfma, use_onepass);
+    p.chain_in_output = chains_in_output(p, use_mfma, onepass.chunks > 0);
 
     hipError_t e = hipSuccess;
     mark(0);
-    if (use_onepass > 0) {
+    if (onepass.chunks > 0) {
         mark(1);
         mark(2);
         OnePassParams pw{p};
         pw.flags = reinterpret_cast<unsigned long long *>(p.ws_fail);       // (behind the sums of the gates)
         pw.nonce = next_nonce();
         pw.polls = g_opt_look_back_polls;
-        e = launch_onepass(pw, use_onepass, stream);
+        e = launch_onepass(pw, onepass.chunks, stream);
         mark(3);
         return e == hipSuccess ? GLA_OK : GLA_ERR_HIP;
     }
@@ -730,10 +729,10 @@ size_t static_plan_bytes(int B, int H, int T, int dk, int dv) {
     bool use_mfma;
     alignas(256) static unsigned char layout_base[256];   // only offsets from it are formed, nothing is accessed
     bool use_fast = false;
-    int use_onepass = 0;
-    if (choose_engine_and_plan(p, layout_base, use_mfma, &use_fast, kStaticScratchBytes, false, &use_onepass) != GLA_OK) return ~(size_t)0;
+    OnePassPlan onepass;
+    if (choose_engine_and_plan(p, layout_base, use_mfma, &use_fast, kStaticScratchBytes, false, &onepass) != GLA_OK) return ~(size_t)0;
     // (a single-launch plan has been compared with the room, which its flags need as well)
-    return use_onepass > 0 ? 0 : plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv);
+    return onepass.chunks > 0 ? 0 : plan_workspace_bytes((size_t)B * H, (size_t)p.nspans, dk, dv);
 }
 
 }  // namespace

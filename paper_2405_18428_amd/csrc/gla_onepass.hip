@@ -16,9 +16,11 @@
 // decay leaves nothing of the earlier ones, turns every U_c into P_c, and each wave adds q~ P_c and stores.
 //
 // Looking back: a wave publishes its part of the span's state with device-scope stores, waits for them to arrive, and stores
-// the call's nonce behind them; the same wave of a later span polls for that nonce.  A span only waits for earlier ones, which
-// are dispatched before it and wait for nothing before they publish.  Should a poll run out all the same (`polls`), the wave
-// forms its part of the entering state from the inputs, token by token: every wait ends, and the result does not depend on it.
+// the call's nonce behind them; the same wave of a later span polls for that nonce.  A span waits for nothing before it publishes, and then
+// only for earlier spans of its sequence.  These have smaller work-group numbers, are earlier ones of the same XCD, or are at the end of the range of
+// spans of the XCD before (onepass_block), whose own waits go the same way, so the earliest span that has not published can always go on.  That holds while the GPU starts groups
+// in the order of their numbers and has room for them; where something else is in the way, a poll can run out (`polls`), and the wave forms its part of
+// the entering state from the inputs, token by token: every wait ends, and the result then differs in the order of the sum only.
 // Operands are pairs of bf16 (hi + remainder; v as given), so products carry 16 bits; states, decays and sums are fp32.
 //
 // What bounds it on MI355X (36 / 72 channels, 1024 chunks in 256 groups of 4, 20 us): the rows of all groups come at the
@@ -36,6 +38,7 @@
 
 #include "gla_common.h"
 #include "gla_mfma_util.h"
+#include "gla_onepass_plan.h"
 
 namespace gla {
 namespace {
@@ -154,11 +157,7 @@ __global__ __launch_bounds__(128 * NC, BETA ? 2 : 4) void chunk_pair_kernel(OneP
     asm volatile("" : "+s"(B), "+s"(H), "+s"(T), "+s"(dk), "+s"(dv), "+s"(grid_h), "+s"(grid_w), "+s"(scan_dir), "+s"(nspans), "+s"(span_len),
                  "+s"(st_k), "+s"(st_v), "+s"(sb_k), "+s"(sh_k), "+s"(sb_v), "+s"(sh_v), "+s"(initial), "+s"(from_v), "+s"(from_k), "+s"(from_q), "+s"(from_gate));
     __syncthreads();           // (the counters of meet are there)
-    int blk = blockIdx.x;      // contiguous ranges of spans per XCD
-    {
-        const int nb = B * H * nspans;
-        if ((nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
-    }
+    const int blk = onepass_block((int)blockIdx.x, B * H * nspans, onepass_in_ranges(B * H, nspans, onepass_resident(NC, BETA)));
     const int bh = blk / nspans, sp = blk - bh * nspans;
     const int s_begin = sp * span_len, s_end = min(T, s_begin + span_len);
 

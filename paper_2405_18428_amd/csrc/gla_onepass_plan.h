@@ -30,8 +30,9 @@ inline size_t onepass_flag_bytes(size_t bh, size_t nspans, int chunks) { return 
 //     groups of 4   3 x 16 1.11 1.04, 6 x 12 1.14 1.06, 16 x 8 1.05, 48 x 5 1.02, 32 x 12 1.36, but 16 x 5 0.99, 16 x 6 1.01 0.98, 32 x 5 0.99
 //                   (S 12 x 6 1.14 1.07); 160 x 9 1.35
 //     groups of 8   192 x 6 1.11, 256 x 6 1.10, 256 x 8 1.28, but 192 x 5 1.00 (S 1.34); 6 x 300 1.49
-//     rounds        16 x 256 1.07 1.12, 32 x 128 1.08 1.18, 128 x 24 1.07 1.15, 160 x 24 1.20 1.28, 192 x 16 1.15 1.12, 64 x 43 1.02 1.04, but 256 x 32
-//                   0.94 0.92, 256 x 12 0.87; in fours 192 x 12 1.14, but 192 x 9 0.95, 256 x 12 1.03 0.97, 32 x 128 with slow gates 0.81, 512 x 8 0.89,
+//     rounds        16 x 256 1.07 1.12, 32 x 128 1.08 1.18, 128 x 24 1.07 1.15, 160 x 24 1.20 1.28, 192 x 16 1.15 1.12, but 64 x 43 1.01 1.03, 256 x 32
+//                   0.94 0.92, 256 x 12 0.87, and where the second round is less than half full, or a few long sequences (row scans, z = 0 and 3) 16 x 160 0.89 0.94,
+//                   32 x 80 0.93 0.97, 48 x 48 0.94 0.98, 16 x 192 0.95 0.97, 32 x 96 0.99 1.02, 16 x 208 0.99 1.05; in fours 192 x 12 1.14, but 192 x 9 0.95, 256 x 12 1.03 0.97, 32 x 128 with slow gates 0.81, 512 x 8 0.89,
 //                   304 x 6 0.97 (sequences from 256 on stay in one pass each, 304 x 12 1.22 for all that); S, in fours: 96 x 32 1.47, 192 x 16 1.58, 126 x 32 1.18, 252 x 9 1.24, 510 x 8 1.09, but 510 x 6 0.95, 510 x 5 0.80
 inline int onepass_epilogue_chunks(const OnePassCall &p) {
     const int nchunks = p.nchunks;
@@ -50,7 +51,7 @@ inline int onepass_epilogue_chunks(const OnePassCall &p) {
     if (small) return groups(4) <= 1024 ? 4 : 0;
     if (bh >= 256) return 0;
     if (nchunks < 16) return (nchunks == 11 || nchunks == 12) && groups(4) <= 1024 ? 4 : 0;
-    return groups(8) <= 512 ? 8 : 0;
+    return groups(8) <= 512 && total >= (nchunks > 128 ? 3300 : 2990) ? 8 : 0;
 }
 
 // With the two-sided gate there is room for four chunks on a compute unit, in one group: 16 x 4 1.29 (S 1.05), 256 x 4 1.17 (S 1.01), 512 x 4
@@ -90,7 +91,7 @@ inline int onepass_plain_chunks(const OnePassCall &p) {
     return groups(8) <= 512 && total >= 2990 && !p.prologue ? 8 : 0;
 }
 
-inline int onepass_resident(const OnePassCall &p, int chunks) { return chunks == 8 || p.two_sided ? 256 : 512; }     // groups at once
+constexpr int onepass_resident(int chunks, bool two_sided) { return chunks == 8 || two_sided ? 256 : 512; }     // groups at once
 
 // Most spans of a sequence where all groups are resident at once.  With gates that decay by nothing (z = 6) every earlier span is looked at,
 // four a trip to memory (of about 1 us) in groups of eight, two in groups of four; the two-pass kernels take 16 or 32, and a kernel of its own above
@@ -110,15 +111,46 @@ inline int onepass_most_spans(const OnePassCall &p, int chunks) {
     return p.small ? 64 : chunks == 4 ? 48 : kMaxChainedSpans;
 }
 
+// The same in several rounds, where a group that looks back keeps its place on a unit from the groups of the next round.  `aligned`: the
+// sequences lie whole within the ranges of spans that the XCDs work through (onepass_block).  z = 0, 3 and 6:
+//     two-sided gate   aligned 24 x 192 (48 spans) 1.39 1.14 1.03 (S 1.20 1.07 1.02), 16 x 256 (64) 1.36 1.07 0.84; else, in two rounds,
+//                      12 x 160 (40) 1.49 1.18 1.00 (S 1.33 1.15 1.04), and in more 26 x 96 (24) 1.38 1.17 1.17 (S 1.21 1.09 1.09), 60 x 128 (32) 1.32
+//                      0.96 0.91, 18 x 256 (64) 1.31 0.94 0.73
+//     epilogue, S      up to a round and a half 12 x 224 (56 spans) 1.25 1.03 0.94; in more, aligned 24 x 160 (40) 1.27 1.10 1.05, 16 x 256 (64)
+//                      1.22 1.01 0.85 (in eights 1.16 1.15 1.09), else 26 x 128 (32) 1.25 1.04 0.97, 18 x 192 (48) 1.27 1.01 0.89 (1.16 1.11 1.10)
+//     eights           aligned 8 x 512 (64) 1.13 1.13 1.07 (S 1.11 1.11 0.97); else 12 x 320 (40) 1.10 1.08 0.99 (S 1.10 1.05 0.94), 10 x 384 (48)
+//                      1.10 1.06 0.96 (S 1.10 1.03 0.91)
+inline int onepass_most_spans_in_rounds(const OnePassCall &p, int chunks) {
+    const bool aligned = p.bh % 8 == 0;
+    if (chunks == 8) return aligned ? 64 : 40;
+    if (p.two_sided) return aligned ? 48 : p.bh * ((p.nchunks + 3) / 4) <= 512 ? 40 : 24;
+    return p.bh * ((p.nchunks + 3) / 4) <= 768 ? 56 : aligned ? 40 : 32;
+}
+
 inline int onepass_chunks_per_group(const OnePassCall &p) {
     const int nchunks = p.nchunks, c = p.two_sided ? onepass_two_sided_chunks(p) : p.epilogue ? onepass_epilogue_chunks(p) : onepass_plain_chunks(p);
     if (c == 0 || nchunks <= c) return c;
     auto spans = [&](int chunks) { return (nchunks + chunks - 1) / chunks; };
-    if (p.bh * spans(c) > onepass_resident(p, c)) return spans(c) <= kMaxChainedSpans / 2 && p.bh >= 8 ? c : 0;
+    if (p.bh * spans(c) > onepass_resident(c, p.two_sided)) {
+        if (p.bh < 8) return 0;
+        if (spans(c) <= onepass_most_spans_in_rounds(p, c)) return c;
+        const bool eights = c == 4 && !p.two_sided && p.bh * nchunks >= 2990 && p.bh * spans(8) <= 2 * onepass_resident(8, p.two_sided);
+        return eights && spans(8) <= onepass_most_spans_in_rounds(p, 8) ? 8 : 0;
+    }
     if (spans(c) <= onepass_most_spans(p, c)) return c;
-    const bool eights = c == 4 && !p.two_sided && spans(4) <= kMaxChainedSpans && p.bh * spans(8) <= onepass_resident(p, 8);
+    const bool eights = c == 4 && !p.two_sided && spans(4) <= kMaxChainedSpans && p.bh * spans(8) <= onepass_resident(8, p.two_sided);
     return eights && spans(8) <= onepass_most_spans(p, 8) ? 8 : 0;
 }
+
+// The span that a work-group takes, of all sequences' spans one behind the other.  Work-groups go to the eight XCDs in turn, and each XCD starts its own in
+// the order of their numbers.  `ranges`: an XCD gets a contiguous eighth of the spans, so that what neighbours share comes from one L2.  The
+// first spans of a range then look back at the last ones of the range before, which is well while all groups are resident, or where no sequence
+// goes over from one range to the next; else those are a round away or more, and places on an XCD's units wait for them: up to a round and a half
+// a few, in more all (forward call over that of two passes, z = 3, in ranges and with spans in the order of the work-groups: two-sided 18 x 62, 288
+// groups, 1.12 and 1.01, 12 x 128, 384, 1.18 and 1.07, 18 x 96, 432, 0.95 and 1.12, 12 x 160, 480, 0.90 and 1.17, 126 x 16, 504, 1.14 and 1.56, 30 x 256
+// 0.49 and 0.95; one gate 36 x 112, 504, 0.92 and 1.18, 12 x 320, 480, 0.88 and 1.08).  Whole sequences in order: 16 x 256 with slow gates 0.96, in ranges 1.08.
+constexpr bool onepass_in_ranges(int bh, int spans, int resident) { return bh * spans <= resident * 3 / 2 || (bh & 7) == 0; }
+constexpr int onepass_block(int block, int blocks, bool ranges) { return ranges && (blocks & 7) == 0 ? (block & 7) * (blocks >> 3) + (block >> 3) : block; }
 
 // Whether the backward pass takes whole chunks although the forward call's states are there.  Forward and backward call, with the walks
 // over spans cut for them and with these kernels: 6 x 100 61.8 and 58.2 us, 16 x 43 61.8 and 59.3, 32 x 32 68.9 and 66.5, 64 x 16 66.0 and
@@ -161,7 +193,7 @@ inline OnePassPlan onepass_plan(const OnePassCall &p) {
     auto cut = [&](int parts) { return (nchunks + parts - 1) / parts; };
     int span = cut((int)(256 / p.bh));
     span = span < 2 ? 2 : span < chunks ? span : chunks;                      // (spans of one chunk leave no room for the flags)
-    if (chunks == 4 && cut(span) > 30 && span < chunks) {
+    if (chunks == 4 && span == 2 && cut(span) > 30) {
         if (p.bh > 5) return {0, 0};      // (S, z = 3: 6 x 63 in 32 spans of 2 49.7 us, in 21 of 3 51.9, 48.3 there)
         ++span;
     }

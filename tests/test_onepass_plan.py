@@ -9,6 +9,8 @@ import pytest
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2405_18428_amd", "csrc")
 SOURCE = r"""
 #include "gla_onepass_plan.h"
+#include <algorithm>
+#include <vector>
 using namespace gla;
 namespace {
 // calls of 1 to 700 sequences (and a few more) of 1 to 1400 chunks, of every kind; false from `holds` ends the sweep
@@ -38,7 +40,28 @@ long long shapes() {
 long long look_back() {
     return sweep([](const OnePassCall &c, OnePassPlan p, long long spans) {
         const bool one_round = c.bh * spans <= (p.chunks == 8 || c.two_sided ? 256 : 512);
-        return spans <= kMaxChainedSpans && (spans == 1 || !one_round || spans <= onepass_most_spans(c, p.chunks));
+        return spans <= kMaxChainedSpans && (spans == 1 || spans <= (one_round ? onepass_most_spans(c, p.chunks) : onepass_most_spans_in_rounds(c, p.chunks)));
+    });
+}
+// Every span is taken once.  Work-group numbers go to the eight XCDs in turn, and an XCD starts its own in order, `resident` of all at a time (one a compute
+// unit; two in fours with one gate).  A span's predecessor has a smaller number, of the same XCD or the one before it, or is the last of the XCD range
+// before: such waits only go from one range to the one before, so they end, and they are for calls of a round and a half at most.
+long long handed_out() {
+    std::vector<int> group(1 << 16);
+    return sweep([&](const OnePassCall &c, OnePassPlan p, long long spans) {
+        const long long blocks = c.bh * spans, resident = p.chunks == 8 || c.two_sided ? 256 : 512;
+        if (spans == 1 || blocks > (1 << 16) || (c.bh % 7 > 1 && c.nchunks % 5 > 1)) return spans == 1 || blocks <= (1 << 16);     // (some of them)
+        std::fill(group.begin(), group.begin() + blocks, -1);
+        for (int b = 0; b < blocks; ++b) {
+            const int s = onepass_block(b, (int)blocks, onepass_in_ranges((int)c.bh, (int)spans, onepass_resident(p.chunks, c.two_sided)));
+            if (s < 0 || s >= blocks || group[s] >= 0) return false;
+            group[s] = b;
+        }
+        for (int s = 0; s < blocks; ++s) {
+            if (s % spans == 0 || group[s - 1] == group[s] - 1 || group[s - 1] == group[s] - 8) continue;
+            if (group[s - 1] % 8 != group[s] % 8 - 1 || blocks > resident * 3 / 2) return false;
+        }
+        return true;
     });
 }
 // states, sums of the gates and flags of the plan within the bound of one span a chunk (gla_fwd_workspace_bytes)
@@ -65,10 +88,10 @@ def plans(tmp_path_factory):
     return ctypes.CDLL(str(where / "plan.so"))
 
 
-@pytest.mark.parametrize("what", ["shapes", "look_back", "room"])
+@pytest.mark.parametrize("what", ["shapes", "look_back", "handed_out", "room"])
 def test_every_plan(plans, what):
-    """Groups, spans and threads as the kernels take them; at most as many spans a sequence as its look-back was measured for; room for the
-    flags.  (A negative count: kind, sequences and chunks of the first call that breaks it.)"""
+    """Groups, spans and threads as the kernels take them; at most as many spans a sequence as its look-back was measured for; no group
+    waits for one that is started after it; room for the flags.  (A negative count: kind, sequences and chunks of the first call that breaks it.)"""
     f = getattr(plans, what)
     f.restype = ctypes.c_longlong
-    assert f() > 100000
+    assert f() > 50000
