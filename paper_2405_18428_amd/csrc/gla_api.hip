@@ -1,8 +1,10 @@
 // Host side of the C ABI declared in include/gla.h: argument validation, launch
 // plan, library-owned scratch for gla_fwd, and the timing aid.
+#include <time.h>
+#include <unistd.h>
+
 #include <atomic>
 #include <mutex>
-#include <random>
 #include <vector>
 
 #include "gla_common.h"
@@ -176,9 +178,21 @@ bool onepass_call(const Params &p, OnePassCall &call) {
     return true;
 }
 
+// Where this process's nonces begin: anywhere, so that flags which another process left in memory do not pass for its own.  (Nothing here
+// throws: the callers are C entry points.)
+unsigned long long first_nonce() {
+    unsigned long long n = 0;
+    if (getentropy(&n, sizeof n) != 0) {
+        struct timespec now = {};
+        (void)clock_gettime(CLOCK_REALTIME, &now);
+        n = ((unsigned long long)now.tv_sec * 1000000000ull + (unsigned long long)now.tv_nsec) * 0x9e3779b97f4a7c15ull ^ (unsigned long long)getpid() << 32;
+    }
+    return n;
+}
+
 // A value that no earlier call's flags hold, nor (but for one chance in 2^64) memory that never held any
 unsigned long long next_nonce() {
-    static std::atomic<unsigned long long> last{(unsigned long long)std::random_device{}() << 32 | std::random_device{}()};
+    static std::atomic<unsigned long long> last{first_nonce()};
     const unsigned long long n = ++last;
     return n != 0 ? n : ++last;       // (0 is what clears them)
 }

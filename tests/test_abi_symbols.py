@@ -141,3 +141,10 @@ def test_static_scratch_takes_long_sequences(engine, B, H, T, dk, dv):
         assert lib.gla_fwd_static(ok, ok, ok, ok, B, H, T, dk, dv, T // 64, 64, 0, ok, None, None) == 6
     finally:
         gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
+
+
+def test_nothing_random_that_throws(lib):
+    """The entry points are C functions: an exception that leaves one ends the process.  std::random_device throws where the system's
+    random source fails, so the library must not bind to it."""
+    with open(gla.library_path(), "rb") as f:
+        assert b"random_device" not in f.read()
