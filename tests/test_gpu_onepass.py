@@ -133,12 +133,172 @@ def test_a_wait_that_runs_out(scan, fused):
         near(fin, ref_fin)
 
 
+@pytest.mark.parametrize("dk,dv,B,H,gh,gw", [(36, 72, 4, 25, 24, 24), (32, 64, 4, 25, 24, 24), (20, 40, 4, 25, 9, 61), (32, 64, 2, 8, 20, 64)])
+def test_a_wait_that_runs_out_in_other_kernels(dk, dv, B, H, gh, gw):
+    """The same in groups of eight (100 sequences of nine chunks, two spans) and, of small heads, of four: an initial state in [B,T,H,d], sums
+    over scan orders, and the epilogue, whose rows are on their way to LDS meanwhile.  Waits that end well give the same."""
+    from oracle import gla_oracle, gla_oracle_fused as fo
+    d = gi.make_fused_inputs(B, H, gh * gw, dk, dv, "bf16", seed=dk + gw)
+    s0 = np.random.default_rng(5).standard_normal((B, H, dk, dv)).astype(np.float32)
+    q, k, v, z, r = upload(d, "q", "k", "v", "z", "r")
+    lnw, lnb = (torch.from_numpy(d[n]).cuda() for n in ("ln_w", "ln_b"))
+    la = torch.nn.functional.logsigmoid(z.float()) / 16
+    log_alpha = la.cpu().numpy()
+    order = lambda s, **more: gla_oracle.gla_fwd(d["q"], d["k"], d["v"], log_alpha, gh, gw, s, **more)
+    want, want_fin = order(3, initial_state=s0)
+    total = order(0)[0] + order(2)[0]
+    mixed, mixed_fin = fo.gla_fused(d["q"], d["k"], d["v"], d["z"], 16.0, d["r"], d["ln_w"], d["ln_b"], 1e-5, gh, gw, 1)
+    for polls in (0, POLLS):
+        gla.gla_set_option(gla.OPT_LOOK_BACK_POLLS, polls)
+        t = [x.transpose(1, 2).contiguous() for x in (q, k, v, la)]
+        out, fin = gla.gla_fwd_layout(*t, gh, gw, 3, layout=1, initial_state=torch.from_numpy(s0).cuda())
+        near(out.transpose(1, 2), want)
+        near(fin, want_fin)
+        near(gla.gla_fwd_multi(q, k, v, la, gh, gw, scan_dirs=[0, 2]), total)
+        out, fin = gla.gla_fwd_fused(q, k, v, z, 16.0, gh, gw, 1, r_pre=r, ln_weight=lnw, ln_bias=lnb, ln_eps=1e-5)
+        near(out, mixed, tol=2e-3)
+        near(fin, mixed_fin)
+
+
+@pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
+@pytest.mark.parametrize("step", [0, 20, 31, 32, 63])
+@pytest.mark.parametrize("B,H,chunks", [(1, 16, 4), (1, 16, 40)])
+def test_gate_of_exactly_zero(dk, dv, B, H, chunks, step):
+    """log_alpha = -inf (a pre-activation as low; log_beta = -inf) on some channels at one step: the limits of the operands do not cover it, but
+    nothing is lost to NaN, and what does not hang on that chunk is right: outputs and dq from seven chunks on, whose earlier steps have decayed to
+    less than TOL, dk and dv of the chunks behind it."""
+    from oracle import gla_oracle, gla_oracle_gates as go
+    gh, gw = chunks, 64
+    at, behind = 64 * (1 if chunks == 4 else 2) + step, 64 * (2 if chunks == 4 else 3)
+    d = gi.make_gate_inputs(B, H, gh * gw, dk, dv, "bf16", seed=7)
+    open_beta = d["log_beta"].copy()
+    d["log_alpha"][:, :, at, [0, 5, 17, 31]] = -np.inf
+    d["log_beta"][:, :, at, [1, 16, 39, 63]] = -np.inf
+    q, k, v, la = upload(d, "q", "k", "v", "log_alpha")
+    z = torch.randn(B, H, gh * gw, dk, device="cuda").bfloat16()
+    z[:, :, at, [0, 5, 17, 31]] = -3e38
+    w = torch.from_numpy(np.random.default_rng(9).standard_normal((B, H, gh * gw, dv)).astype(np.float32)).bfloat16()
+    finite = lambda *t: all(bool(torch.isfinite(x).all()) for x in t)
+    ws = torch.empty(gla.gla_fwd_workspace_bytes(B, H, gh * gw, dk, dv, gla.DT_BF16), dtype=torch.uint8, device="cuda")
+    out, fin = gla.gla_fwd_ex(q, k, v, la, gh, gw, 0, workspace=ws)
+    assert finite(out, fin)
+    assert finite(*gla.gla_fwd_fused(q, k, v, z, 16.0, gh, gw, 0, r_pre=v, ln_eps=1e-5))
+    for keep in (None, ws):
+        grads = gla.gla_bwd(q, k, v, la, w.cuda(), gh, gw, 0, fwd_workspace=keep)
+        assert finite(*grads)
+        want = gla_oracle.gla_bwd(d["q"], d["k"], d["v"], d["log_alpha"], w.float().numpy(), gh, gw, 0)
+        for g, r in zip(grads[1:3], want[1:3]):
+            near(g[:, :, behind:], r[:, :, behind:])
+        if chunks > 9:
+            near(grads[0][:, :, 9 * 64:], want[0][:, :, 9 * 64:])
+    alpha_only = torch.from_numpy(open_beta).cuda()
+    open_alpha = np.where(np.isinf(d["log_alpha"]), np.float32(-0.1), d["log_alpha"])
+    for a, b, na, nb in ((la, alpha_only, d["log_alpha"], open_beta),
+                         (torch.from_numpy(open_alpha).cuda(), torch.from_numpy(d["log_beta"]).cuda(), open_alpha, d["log_beta"])):
+        got, got_fin = gla.gla_fwd_gates(q, k, v, a, b, gh, gw, 0)
+        assert finite(got, got_fin)
+        if chunks > 9:
+            ref, ref_fin = go.gla_fwd_gates(d["q"], d["k"], d["v"], na, nb, gh, gw, 0)
+            near(got[:, :, 9 * 64:], ref[:, :, 9 * 64:])
+            near(got_fin, ref_fin)
+    if chunks > 9:
+        ref, ref_fin = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, 0)
+        near(out[:, :, 9 * 64:], ref[:, :, 9 * 64:])
+        near(fin, ref_fin)
+
+
+@pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
+@pytest.mark.parametrize("B,H,chunks", [(1, 8, 80), (2, 8, 80)])
+def test_chain_behind_zeros(dk, dv, B, H, chunks):
+    """No keys in the last 60 chunks: what is left of the first ones has decayed far below the 2^-40 at which a chain of span states stops, but it
+    is all there is (groups of four and of eight; the gate on both sides).  Backwards the same: no gradient from chunk 4 to 63, so that dv and dk
+    of these chunks come from the last ones, and dq of the last from the first."""
+    from oracle import gla_oracle, gla_oracle_gates as go
+    gh, gw = chunks, 64
+    d = gi.make_gate_inputs(B, H, gh * gw, dk, dv, "bf16", seed=21, z_mean=1.5)
+    d["k"][:, :, 20 * 64:] = 0.0
+    d["k_bits"] = gi.round_to_bf16_bits(d["k"])
+    w = np.random.default_rng(9).standard_normal((B, H, gh * gw, dv)).astype(np.float32)
+    w[:, :, 4 * 64:64 * 64] = 0.0
+    w = torch.from_numpy(w).bfloat16()
+    q, k, v, la = upload(d, "q", "k", "v", "log_alpha")
+    lb = torch.from_numpy(d["log_beta"]).cuda()
+    one, both = gla_oracle.gla_fwd(d["q"], d["k"], d["v"], d["log_alpha"], gh, gw, 0), go.gla_fwd_gates(
+        d["q"], d["k"], d["v"], d["log_alpha"], d["log_beta"] / 16, gh, gw, 0)
+    assert 0.0 < np.abs(one[1]).max() < 2.0 ** -50 and 0.0 < np.abs(both[1]).max() < 2.0 ** -50
+    out, fin = gla.gla_fwd_ex(q, k, v, la, gh, gw, 0)
+    last = slice((chunks - 1) * 64, None)
+    near(fin, one[1])
+    near(out[:, :, last], one[0][:, :, last])
+    out, fin = gla.gla_fwd_gates(q, k, v, la, lb / 16, gh, gw, 0)
+    near(fin, both[1])
+    near(out[:, :, last], both[0][:, :, last])
+    want = gla_oracle.gla_bwd(d["q"], d["k"], d["v"], d["log_alpha"], w.float().numpy(), gh, gw, 0)
+    got = gla.gla_bwd(q, k, v, la, w.cuda(), gh, gw, 0)
+    near(got[0][:, :, last], want[0][:, :, last])
+    for g, r in zip(got[1:3], want[1:3]):
+        assert 0.0 < np.abs(r[:, :, 8 * 64:9 * 64]).max() < 2.0 ** -50
+        near(g[:, :, 8 * 64:9 * 64], r[:, :, 8 * 64:9 * 64])
+
+
+@pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
+@pytest.mark.parametrize("two_sided,bh,chunks", [(False, 36, 112), (True, 50, 32), (False, 12, 250), (True, 40, 64), (True, 12, 128)])
+def test_several_rounds(two_sided, bh, chunks, dk, dv):
+    """Groups in several rounds, of spans in order (work-groups a multiple of eight, sequences not), in ranges of whole sequences, and in ranges that
+    sequences straddle, with slow gates: as the two-pass kernels have it (which GLA_CARRY_KERNEL asks for)."""
+    g = torch.Generator(device="cuda").manual_seed(bh)
+    T = 64 * chunks
+    q, k, v = (torch.randn(1, bh, T, d, generator=g, device="cuda").bfloat16() for d in (dk, dk, dv))
+    gate = lambda d: torch.nn.functional.logsigmoid(torch.randn(1, bh, T, d, generator=g, device="cuda") + 4.0) / 16
+    more = (gate(dk), gate(dv)) if two_sided else (gate(dk),)
+    call = gla.gla_fwd_gates if two_sided else gla.gla_fwd_ex
+    try:
+        gla.gla_set_option(gla.OPT_CARRY, gla.CARRY_KERNEL)
+        gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_MFMA)
+        want = [x.cpu().numpy() for x in call(q, k, v, *more, chunks, 64, 2)]
+    finally:
+        gla.gla_set_option(gla.OPT_CARRY, gla.CARRY_AUTO)
+        gla.gla_set_option(gla.OPT_ENGINE, gla.ENGINE_AUTO)
+    for got, ref in zip(call(q, k, v, *more, chunks, 64, 2), want):
+        near(got, ref, tol=2 * TOL)
+
+
+def test_two_streams():
+    """Calls that wait inside a launch, on two streams at once, each with a workspace of its own: every result as it is alone.  Groups of eight that fill
+    the chip beside groups of four, slow gates, so that every group waits; a poll that runs out changes the last bits only."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    calls = []
+    for bh, chunks, dk, dv in ((16, 100, 36, 72), (6, 120, 32, 64), (16, 256, 36, 72)):
+        T = 64 * chunks
+        t = [torch.randn(1, bh, T, d, generator=g, device="cuda").bfloat16() for d in (dk, dk, dv)]
+        t.append(torch.nn.functional.logsigmoid(torch.randn(1, bh, T, dk, generator=g, device="cuda") + 4.0) / 16)
+        ws = torch.empty(gla.gla_fwd_workspace_bytes(1, bh, T, dk, dv, gla.DT_BF16), dtype=torch.uint8, device="cuda")
+        calls.append((t, chunks, ws, gla.gla_fwd_ex(*t, chunks, 64, 0, workspace=ws)))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for pair in ((0, 1), (2, 0), (1, 2)):
+        torch.cuda.synchronize()
+        kept = []
+        for _ in range(8):
+            for c, stream in zip(pair, streams):
+                t, chunks, ws, _want = calls[c]
+                with torch.cuda.stream(stream):
+                    kept.append((c, gla.gla_fwd_ex(*t, chunks, 64, 0, workspace=ws)))
+        torch.cuda.synchronize()
+        for c, got in kept:
+            for x, ref in zip(got, calls[c][3]):
+                assert float((x - ref).abs().max() / ref.square().mean().sqrt()) <= TOL
+
+
 # (one span of three and of four chunks, ragged; several spans, with a last one of one token and with one of four chunks; two rounds
 # of one-span groups; short columns)
 BACK = [(2, 3, 14, 13), (2, 3, 3, 84), (1, 6, 16, 16), (18, 16, 5, 37), (8, 16, 11, 35), (2, 16, 9, 57), (4, 16, 64, 15), (16, 16, 32, 7)]
 
 
-@pytest.mark.parametrize("dk,dv,B,H,gh,gw", [(*h, *c) for h in ((36, 72), (32, 64)) for c in BACK] +
+# (129 to 256 sequences of 6, 7 and 8 chunks: one span each in the forward call, several in the walks that follow it)
+ONE_SPAN = [(10, 16, 5, 72), (12, 16, 7, 61), (16, 16, 8, 61)]
+
+
+@pytest.mark.parametrize("dk,dv,B,H,gh,gw", [(*h, *c) for h in ((36, 72), (32, 64)) for c in BACK + ONE_SPAN] +
                          [(*h, *c) for h in ((20, 40), (36, 40), (28, 72)) for c in BACK[:5]])
 def test_gradients(dk, dv, B, H, gh, gw):
     """All four gradients, both memory orders, with and without the forward call's workspace; slow gates in every other case.  The gate
@@ -201,3 +361,11 @@ def test_replays_do_not_take_old_states():
         got = gla.gla_fwd_ex(*sets[1 - i], gh, gw, 2, workspace=ws)
         torch.cuda.synchronize()
         assert torch.equal(got[0], want[1 - i][0])
+    # one replay behind the other, so that the flags of the one before are there unless the call clears them
+    for i in (0, 1, 0, 0, 1, 1, 0):
+        for x, y in zip(t, sets[i]):
+            x.copy_(y)
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[i][0]) and torch.equal(fin, want[i][1]), i
