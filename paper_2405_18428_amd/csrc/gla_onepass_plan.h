@@ -113,7 +113,7 @@ inline int onepass_most_spans(const OnePassCall &p, int chunks) {
 
 // The same in several rounds, where a group that looks back keeps its place on a unit from the groups of the next round.  `aligned`: the
 // sequences lie whole within the ranges of spans that the XCDs work through (onepass_block).  z = 0, 3 and 6:
-//     two-sided gate   aligned 24 x 192 (48 spans) 1.39 1.14 1.03 (S 1.20 1.07 1.02), 16 x 256 (64) 1.36 1.07 0.84; else, in two rounds,
+//     two-sided gate   aligned 24 x 192 (48 spans) 1.39 1.14 1.03 (S 1.20 1.07 1.02), 16 x 256 (64) 1.36 1.07 0.84 (kept for the former two); else, in two rounds,
 //                      12 x 160 (40) 1.49 1.18 1.00 (S 1.33 1.15 1.04), and in more 26 x 96 (24) 1.38 1.17 1.17 (S 1.21 1.09 1.09), 60 x 128 (32) 1.32
 //                      0.96 0.91, 18 x 256 (64) 1.31 0.94 0.73
 //     epilogue, S      up to a round and a half 12 x 224 (56 spans) 1.25 1.03 0.94; in more, aligned 24 x 160 (40) 1.27 1.10 1.05, 16 x 256 (64)
@@ -123,7 +123,7 @@ inline int onepass_most_spans(const OnePassCall &p, int chunks) {
 inline int onepass_most_spans_in_rounds(const OnePassCall &p, int chunks) {
     const bool aligned = p.bh % 8 == 0;
     if (chunks == 8) return aligned ? 64 : 40;
-    if (p.two_sided) return aligned ? 48 : p.bh * ((p.nchunks + 3) / 4) <= 512 ? 40 : 24;
+    if (p.two_sided) return aligned ? 64 : p.bh * ((p.nchunks + 3) / 4) <= 512 ? 40 : 24;
     return p.bh * ((p.nchunks + 3) / 4) <= 768 ? 56 : aligned ? 40 : 32;
 }
 
