@@ -699,7 +699,8 @@ def main():
                                                        f"FETCH_SIZE / WRITE_SIZE of this command, committed; not re-measured here)",
         "algorithmic_bytes": alg_bytes, "kernel_ms": round(float(phase[dom]), 5),
         "kernel_achieved": round(kernel_achieved, 1), "kernel_frac": round(kernel_achieved / HBM_PEAK_GBS, 4),
-        "phase_ms": {n: round(float(x), 5) for n, x in zip(names + ["whole_call"], phase)},
+        # (phases that the plan skips are left out: a call in one launch has none but its output kernel)
+        "phase_ms": {n: round(float(x), 5) for n, x in zip(names + ["whole_call"], phase) if x > 0},
         "whole_path_frac": round(achieved / HBM_PEAK_GBS, 4),
         "measured_copy_gbs": round(copy_gbs, 1),
         "frac_of_measured_copy": round(achieved / copy_gbs, 4),

@@ -609,6 +609,7 @@ struct FusedArgs {
 
 struct PhaseEvents {
     hipEvent_t ev[4];
+    bool recorded[4];       // the first and, behind every phase that runs, one
 };
 
 int run(const void *q, const void *k, const void *v, const float *log_alpha,
@@ -674,7 +675,7 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
         return use_mfma ? launch_mfma_span(p, mode, stream) : launch_recurrent_span(p, mode, stream);
     };
     auto mark = [&](int i) {
-        if (events) (void)hipEventRecord(events->ev[i], stream);
+        if (events) events->recorded[i] = hipEventRecord(events->ev[i], stream) == hipSuccess;
     };
 
     p.chain_in_output = chains_in_output(p, use_mfma, onepass.chunks > 0);
@@ -682,8 +683,6 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
     hipError_t e = hipSuccess;
     mark(0);
     if (onepass.chunks > 0) {
-        mark(1);
-        mark(2);
         OnePassParams pw{p};
         pw.flags = reinterpret_cast<unsigned long long *>(p.ws_fail);       // (behind the sums of the gates)
         pw.nonce = next_nonce();
@@ -695,13 +694,13 @@ int run(const void *q, const void *k, const void *v, const float *log_alpha,
     if (p.nspans > 1) {
         e = use_fast ? launch_fast_state(p, stream) : span(kModeState);
         if (e != hipSuccess) return GLA_ERR_HIP;
+        mark(1);
     }
-    mark(1);
     if (p.nspans > 1 && !p.chain_in_output) {
         e = launch_carry(p, stream);
         if (e != hipSuccess) return GLA_ERR_HIP;
+        mark(2);
     }
-    mark(2);
     if (use_fast) {
         // fp16 output pass; the spans whose gates or operands leave its range raise their flags and are
         // recomputed by the bf16 hi/lo pass (work-groups of unflagged spans return at once)
@@ -1036,9 +1035,11 @@ int gla_fwd_timed(const void *q, const void *k, const void *v, const float *log_
     if (status == GLA_OK) {
         for (int i = 0; i < done; ++i) {
             float ms = 0.f;
-            for (int j = 0; j < 3; ++j) {
-                if (hipEventElapsedTime(&ms, evs[i].ev[j], evs[i].ev[j + 1]) != hipSuccess) status = GLA_ERR_HIP;
+            for (int j = 0, from = 0; j < 3; ++j) {
+                if (!evs[i].recorded[j + 1]) continue;       // (a phase that the plan skips)
+                if (hipEventElapsedTime(&ms, evs[i].ev[from], evs[i].ev[j + 1]) != hipSuccess) status = GLA_ERR_HIP;
                 sum[j] += ms;
+                from = j + 1;
             }
             if (hipEventElapsedTime(&ms, evs[i].ev[0], evs[i].ev[3]) != hipSuccess) status = GLA_ERR_HIP;
             sum[3] += ms;

@@ -339,6 +339,22 @@ def test_one_long_sequence_and_its_states(chunks):
         near(got, ref)
 
 
+def test_phases_of_one_launch():
+    """gla_fwd_timed: the phases that a call in one launch does not have take no time; those of a call in two passes do."""
+    B, H, gh, gw, dk, dv = 1, 16, 40, 64, 36, 72
+    t = upload(gi.make_inputs(B, H, gh * gw, dk, dv, "bf16", seed=2), "q", "k", "v", "log_alpha")
+    ws = torch.empty(gla.gla_fwd_workspace_bytes(B, H, gh * gw, dk, dv, gla.DT_BF16), dtype=torch.uint8, device="cuda")
+    out, fin = gla.gla_fwd_ex(*t, gh, gw, 0, workspace=ws)
+    ms = gla.gla_fwd_timed(*t, gh, gw, 0, out, fin, ws, iters=3)
+    assert ms[0] == 0 and ms[1] == 0 and 0 < ms[2] <= ms[3]
+    try:
+        gla.gla_set_option(gla.OPT_CARRY, gla.CARRY_KERNEL)
+        ms = gla.gla_fwd_timed(*t, gh, gw, 0, out, fin, ws, iters=3)
+    finally:
+        gla.gla_set_option(gla.OPT_CARRY, gla.CARRY_AUTO)
+    assert all(0 < m < ms[3] for m in ms[:3])
+
+
 def test_replays_do_not_take_old_states():
     """A recorded call has one nonce for all replays: other inputs in the same buffers, and calls outside the graph on the same
     workspace, must not be answered from the states that the flags of an earlier replay stand for."""
