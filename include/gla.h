@@ -57,6 +57,7 @@
  *    whenever z > -20).  GLA_ENGINE_RECURRENT has no such limit.  Beyond it, up to a gate
  *    of exactly zero (log_alpha = -inf), what that channel adds inside the 64-step chunk is
  *    lost or wrong, but finite: later chunks lack it as far as it would not have decayed.
+ *    With the two-sided gate the bound is on the sum of both sides' |log|, and what lies beyond it need not be finite.
  *  - fp16 MFMA engine (what GLA_ENGINE_AUTO takes for the plain forward pass, and for
  *    gla_fwd_fused without the output epilogue, on bf16 inputs with 17..64 key
  *    channels and more than four chunks, unless the single-launch kernels take the call (see gla_engine), or
@@ -83,9 +84,11 @@
  *    of magnitude smaller than the earlier ones lose the decayed remainder of
  *    the earlier ones.  GLA_CARRY_KERNEL has no cut-off.
  *
- * The entry points that take a caller workspace only enqueue kernels, with one
- * exception: the first use of a kernel instantiation on a device raises its
- * dynamic-LDS limit (hipFuncSetAttribute).  Before capturing calls into a HIP
+ * The entry points that take a caller workspace only enqueue kernels, with two
+ * exceptions: the first use of a kernel instantiation on a device raises its
+ * dynamic-LDS limit (hipFuncSetAttribute), and a forward call in one launch asks
+ * whether its stream is being recorded (hipStreamIsCapturing; a recorded call has
+ * one small kernel more, which clears its flags).  Before capturing calls into a HIP
  * graph, or entering a region that must not touch the runtime, run each call
  * once with the same shapes and options.
  */
@@ -145,10 +148,12 @@ typedef enum {
                                  3000 chunks of 64 tokens on, over all batches and heads; in gla_fwd_static only if their plan fits its array.
                                  Of heads of 17 to 36 key channels and 33 to 72 value columns, forward calls with one gate from about
                                  512 chunks (320 for sequences of up to ten, 288 for up to 32 / 64 channels; with the output epilogue
-                                 48 to 192) up to about 2048, and larger ones of up to 128 sequences up to 4096, run on kernels with the
-                                 bf16 hi/lo operands that read their inputs once, in one launch; so do sequences of four chunks (with the
-                                 epilogue of three) and, from 288 chunks on, the two-sided gate's of up to 128 sequences (not with
-                                 GLA_OPT_CHUNKS_PER_SPAN or GLA_CARRY_KERNEL set) */
+                                 48 to 192) up to about 2048, and larger ones of 8 to 128 sequences up to 4096 (from about 3000), run on
+                                 kernels with the bf16 hi/lo operands that read their inputs once, in one launch; so do sequences of four
+                                 chunks (with the epilogue of three) and, from 288 chunks on, the two-sided gate's of up to 128 sequences.
+                                 Long sequences only up to a number of spans (of four or eight chunks) that depends on the kind of call: 48 to
+                                 128, and 24 to 64 where not all spans are worked on at once.  Not with
+                                 GLA_OPT_CHUNKS_PER_SPAN or GLA_CARRY_KERNEL set */
     GLA_ENGINE_RECURRENT = 1, /* fp32 token-by-token arithmetic inside each span; any dtype, any gates */
     GLA_ENGINE_MFMA = 2,      /* bf16 hi/lo MFMA chunk form (Sec. 3.5) in every pass, or in the one there is; bf16 inputs only */
     GLA_ENGINE_MFMA_FP16 = 3  /* fp16 operands in both passes of the plain forward call and of gla_fwd_fused without
@@ -196,8 +201,10 @@ int gla_fwd(const void *q, const void *k, const void *v, const float *log_alpha,
  * allocating library routine; the kernels it launches are gla_fwd's.
  *
  * GLA_ERR_WORKSPACE if the launch plan of the problem needs more than the array holds
- * (B * H * spans * (dk * dv + dk + dv) floats, spans = 64-token chunks / chunks per
+ * (B * H * spans * (dk * dv + dk + dv + 1) floats, spans = 64-token chunks / chunks per
  * work-group; the DiG-XL/2 shape at 2048 px uses about 7 MiB); nothing is enqueued then.
+ * (A call in one launch needs some bytes more for its flags, and runs in two passes where
+ * those do not fit.)
  * All calls on one GPU share that GPU's array: calls that overlap on one GPU (different
  * streams or threads) race.  Nothing in it needs clearing between calls: every call
  * writes the span states before it reads them.  As for every entry point that takes a
@@ -326,6 +333,10 @@ size_t gla_bwd_gates_workspace_bytes(int B, int H, int T, int dk, int dv, int qk
  *
  * Everything else as gla_bwd; `workspace` must be a different buffer.  The library cannot
  * check that the forward workspace belongs to these tensors: a stale one gives wrong dq.
+ * Of a (batch, head) sequence that left the range of the fp16 MFMA engine (see above) the forward
+ * call's outputs are right, but the span states that its fp16 passes left are not: where gates
+ * close that fast, take gla_bwd, or GLA_ENGINE_MFMA for both calls; dq and dlog_alpha of such a
+ * sequence can be wrong or not finite otherwise.
  */
 int gla_bwd_reuse(const void *q, const void *k, const void *v, const float *log_alpha, const void *d_out,
                   int B, int H, int T, int dk, int dv, int grid_h, int grid_w, int scan_dir, int qkv_dtype,
@@ -435,7 +446,8 @@ size_t gla_fwd_workspace_bytes(int B, int H, int T, int dk, int dv, int qkv_dtyp
  * (Sec. 3.5 cut into spans: local span states, carry across spans, outputs) and
  * returns mean milliseconds per call in phase_ms (HOST pointer to 4 floats:
  * span-state kernel, carry kernel, output kernel, whole call).  Synchronises
- * the stream before returning.  Phases a plan skips report 0.
+ * the stream before returning.  Phases a plan skips report 0 (a call in one launch has
+ * an output kernel only).
  */
 int gla_fwd_timed(const void *q, const void *k, const void *v, const float *log_alpha,
                   int B, int H, int T, int dk, int dv, int grid_h, int grid_w, int scan_dir,

@@ -20,7 +20,7 @@ struct OnePassCall {
 // Bytes of the flags of a single-launch plan (two waves a chunk), which lie behind the sums of the gates
 inline size_t onepass_flag_bytes(size_t bh, size_t nspans, int chunks) { return (bh * nspans * 2 * chunks * sizeof(unsigned long long) + 255) / 256 * 256; }
 
-// Chunks that a work-group of the single-launch forward kernels holds (4 or 8), or 0 where the call stays on the others.  Eight chunks fill
+// The next three functions: chunks that a work-group of the single-launch forward kernels holds (4 or 8), or 0 where the call stays on the others.  Eight chunks fill
 // a compute unit, so up to 2048 are one round of work-groups, all loads in flight at once.  Below: time of the two-pass kernels over
 // that of these, in sequences x chunks (36 / 72 channels; S: 32 / 64 channels), bf16 row scan and fp32 column scan where there are two.
 
@@ -50,7 +50,9 @@ inline int onepass_epilogue_chunks(const OnePassCall &p) {
     if (groups(4) <= 512) return 4;
     if (small) return groups(4) <= 1024 ? 4 : 0;
     if (bh >= 256) return 0;
+    // three groups of four with at most one place empty (9 and 10 chunks leave more of them idle, 13 to 15 begin a fourth)
     if (nchunks < 16) return (nchunks == 11 || nchunks == 12) && groups(4) <= 1024 ? 4 : 0;
+    // (a second round that is at least half full; of long sequences somewhat more, since its groups look back further)
     return groups(8) <= 512 && total >= (nchunks > 128 ? 3300 : 2990) ? 8 : 0;
 }
 
@@ -85,9 +87,12 @@ inline int onepass_plain_chunks(const OnePassCall &p) {
     if (nchunks <= 4) return nchunks == 4 && bh <= (small ? 640 : 128) ? 4 : 0;
     if (total < (small ? 288 : nchunks <= 10 ? 320 : 513)) return 0;
     if (groups(4) <= 256) return 4;
+    // One group of eight a sequence, one round.  What it costs does not fall with the places that are empty, so six chunks pay only while the other plan
+    // cuts them into three spans (up to 512 of them, 170 sequences; then into two), seven a little longer
     if (bh > 128) return nchunks <= 8 && bh <= (nchunks == 8 ? 256 : nchunks == 7 ? 192 : nchunks == 6 ? 170 : 0) ? 8 : 0;
     if (groups(8) <= 256) return 8;
     if (groups(4) <= 512) return 4;
+    // (a second round that is about half full: 2048 chunks and 942 more)
     return groups(8) <= 512 && total >= 2990 && !p.prologue ? 8 : 0;
 }
 
