@@ -37,22 +37,13 @@
 #include <type_traits>
 
 #include "gla_common.h"
-#include "gla_mfma_util.h"
 #include "gla_onepass_plan.h"
+#include "gla_onepass_util.h"
 
 namespace gla {
 namespace {
 
 typedef unsigned long long flag_t;
-
-// Head classes: DT groups of four tail channels behind the 32 of a contraction step, NX tiles of 16 value columns, of which
-// NV columns exist.
-struct HeadsXL {
-    static constexpr int DT = 1, NX = 5, NV = 72;
-};
-struct HeadsS {
-    static constexpr int DT = 0, NX = 4, NV = 64;
-};
 
 template <typename HD, int NC, bool FUSE, bool BETA>
 struct WLayout {
@@ -71,15 +62,6 @@ struct WLayout {
     static constexpr int kBytes = oLn + (FUSE ? 2 * 16 * HD::NX * 4 : 0);
     static_assert(kBytes <= 160 * 1024 / (BETA ? 4 / NC : 8 / NC), "16 waves on a compute unit, 8 with the two-sided gate");
 };
-// what the totals of a chunk's tiles become: 2^(b_C), 2^(b_m), 2^(b_C - b_m), b_C
-enum { kDecay, kToAnchor, kFromAnchor, kLogDecay };
-
-// 16 bytes a lane from the view to LDS, lane i's at `lds` + 16 i
-__device__ inline void load_to_lds(Rsrc r, void *lds, uint32_t at) {
-    typedef __attribute__((address_space(3))) void *lds_ptr;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)lds, 16, (int)at, 0, 0, 0);
-}
-
 // Accesses at device scope (sc1): past the L1s and past the L2s, of which every XCD has one of its own
 constexpr int kDeviceScope = 16;
 __device__ inline void publish(Rsrc r, uint32_t at, uint32_t from, float x) {
@@ -92,19 +74,7 @@ __device__ inline f32x4 published4(Rsrc r, uint32_t at, uint32_t from) {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, (int)from, kDeviceScope));
 }
 
-// Identity that the optimiser cannot see through, of a value that the whole wave shares
-template <typename V>
-__device__ inline V afresh(V x) {
-    asm volatile("" : "+s"(x));
-    return x;
-}
-
-// This lane, afresh in every stage: what is derived from it is not carried from one to the next in registers.
-#define LANE [[maybe_unused]] const int lane = recompute_per_chunk(threadIdx.x) & 63, lm = lane & 15, g = lane >> 4
-
-// The kernel's arguments, loaded where they are used: all of them at once do not fit the scalar registers.
 typedef const __attribute__((address_space(4))) OnePassParams *Args;
-#define ARG afresh(args)
 
 // FUSE = the gate prologue and the optional output epilogue; ACC = rows are added to the fp32 rows already in `out`; BETA = the
 // two-sided gate (log_beta): with c_j the prefix sums of log2 beta per value column, v~_i = v_i 2^(c_m - c_i) takes the place of v as
@@ -433,6 +403,18 @@ __global__ __launch_bounds__(128 * NC, BETA ? 2 : 4) void chunk_pair_kernel(OneP
             }
         }
         meet();
+        // This lane, and its operand of the products with v: transposing reads of columns 16 x + lm, slot (g, e) of step q32 = token
+        // 32 q32 + 16 (e / 4) + 4 g + e % 4; part 1: the lo rows.  (Rows of 128 bytes: tiles change places, see load_to_lds.)
+#define TR_LANE \
+        LANE; \
+        const int tr_row = lm >> 2, tr_col = 4 * (lm & 3);     /* token-in-4 and column quad of this lane */ \
+        const uint16_t *vtr = s_v + (4 * g + tr_row) * HD::NV + tr_col; \
+        const int v_swz = DT ? 0 : 16 * ((2 * g + (tr_row >> 1)) & 3); \
+        auto v_frag = [&](int q32, int x, int part = 0) { \
+            const u32x2 lo = lds_read_tr(vtr + (32 * q32 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz)); \
+            const u32x2 hi = lds_read_tr(vtr + (32 * q32 + 16 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz)); \
+            return u32x4{lo[0], lo[1], hi[0], hi[1]}; \
+        }
         // slots hi, hi, lo, lo of a tail channel's pair
         auto tail_operand = [](uint32_t pair) {
             return u32x4{__builtin_amdgcn_perm(pair, pair, 0x01000100u), __builtin_amdgcn_perm(pair, pair, 0x03020302u), 0, 0};
@@ -440,16 +422,7 @@ __global__ __launch_bounds__(128 * NC, BETA ? 2 : 4) void chunk_pair_kernel(OneP
         u32x4 pah[3], pal[3];                          // scores of tile W; of tile 3 - W, tokens 0 .. 31 and 32 .. 63
         f32x4 acc[2][2 + DT], acc4[1 + DT];            // column tiles W and W + 2; of tile 4 the channels of tile W, and the tail's
         {
-            LANE;
-            const int tr_row = lm >> 2, tr_col = 4 * (lm & 3);       // transposing reads: token-in-4 and column quad of this lane
-            const uint16_t *vtr = s_v + (4 * g + tr_row) * HD::NV + tr_col;
-            const int v_swz = DT ? 0 : 16 * ((2 * g + (tr_row >> 1)) & 3);     // (rows of 128 bytes: tiles change places, see load_to_lds)
-            // slot (g, e) of step q32 = token 32 q32 + 16 (e / 4) + 4 g + e % 4; part 1: the lo rows
-            auto v_frag = [&](int q32, int x, int part = 0) {
-                const u32x2 lo = lds_read_tr(vtr + (32 * q32 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz));
-                const u32x2 hi = lds_read_tr(vtr + (32 * q32 + 16 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz));
-                return u32x4{lo[0], lo[1], hi[0], hi[1]};
-            };
+            TR_LANE;
             // (the totals of the tiles have been read)
             if (W == 0 && lane < US) {
                 float *d = my_decay + lane;
@@ -662,16 +635,7 @@ __global__ __launch_bounds__(128 * NC, BETA ? 2 : 4) void chunk_pair_kernel(OneP
         f32x4 o[2][NX];
         auto view_out = [&]() { return view_v(ARG->out, sizeof(TOut)); };
         {
-            LANE;
-            const int tr_row = lm >> 2, tr_col = 4 * (lm & 3);       // transposing reads: token-in-4 and column quad of this lane
-            const uint16_t *vtr = s_v + (4 * g + tr_row) * HD::NV + tr_col;
-            const int v_swz = DT ? 0 : 16 * ((2 * g + (tr_row >> 1)) & 3);     // (rows of 128 bytes: tiles change places, see load_to_lds)
-            // slot (g, e) of step q32 = token 32 q32 + 16 (e / 4) + 4 g + e % 4; part 1: the lo rows
-            auto v_frag = [&](int q32, int x, int part = 0) {
-                const u32x2 lo = lds_read_tr(vtr + (32 * q32 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz));
-                const u32x2 hi = lds_read_tr(vtr + (32 * q32 + 16 + kChunk * part) * HD::NV + ((16 * x) ^ v_swz));
-                return u32x4{lo[0], lo[1], hi[0], hi[1]};
-            };
+            TR_LANE;
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll

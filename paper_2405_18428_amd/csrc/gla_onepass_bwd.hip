@@ -23,17 +23,11 @@
 #include <type_traits>
 
 #include "gla_common.h"
-#include "gla_mfma_util.h"
+#include "gla_onepass_util.h"
 
 namespace gla {
 namespace {
 
-struct HeadsXL {
-    static constexpr int DT = 1, NX = 5, NV = 72;
-};
-struct HeadsS {
-    static constexpr int DT = 0, NX = 4, NV = 64;
-};
 enum { kWhole, kStates, kOutputs };      // sequences of one span; the spans' states; the gradients from them
 
 constexpr int NC = 4, NT = 256 * NC;
@@ -53,21 +47,8 @@ struct BLayout {
     static constexpr int kBytes = oMeet + 4 * NC * 4;
     static_assert(kBytes <= 160 * 1024, "one group a compute unit");
 };
-enum { kDecay, kToAnchor, kFromAnchor, kLogDecay };
 
-__device__ inline void load_to_lds(Rsrc r, void *lds, uint32_t at) {
-    typedef __attribute__((address_space(3))) void *lds_ptr;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)lds, 16, (int)at, 0, 0, 0);
-}
-template <typename V>
-__device__ inline V afresh(V x) {
-    asm volatile("" : "+s"(x));
-    return x;
-}
 typedef const __attribute__((address_space(4))) BackParams *Args;
-#define ARG afresh(args)
-// This lane, afresh in every stage: what is derived from it is not carried from one to the next in registers.
-#define LANE [[maybe_unused]] const int lane = recompute_per_chunk(threadIdx.x) & 63, lm = lane & 15, g = lane >> 4
 
 // Inclusive sums over the lanes from this one to the last of its 16 (row_scan16x4 the other way round)
 __device__ inline void row_suffix16x4(float &a, float &b, float &c, float &d) {
