@@ -73,7 +73,8 @@ inline int onepass_two_sided_chunks(const OnePassCall &p) {
 //                   1.24), where the other plan has one round and a half, but 176 x 6 0.96 1.03, 144 x 5 0.96, 256 x 7 0.93 1.04 (S 0.94);
 //                   192 x 7 1.00 1.08, 224 x 8 1.01 1.10 (S 1.02 1.04)
 //     two rounds    32 x 100 1.08, 32 x 128 1.15 1.18, 64 x 64 1.14, 96 x 32 1.15 1.14, 16 x 256 1.10 1.16, but 64 x 43 0.93,
-//                   128 x 17 0.91, 192 x 16 1.29 0.95; three and more 0.87 to 1.11
+//                   128 x 17 0.91, 192 x 16 1.29 0.95; three and more 0.87 to 1.11; S (z = 0, 3, 6) 12 x 256 1.02 0.95 0.90, 10 x 320 1.01 0.94 0.85, 8 x 400
+//                   1.00 0.96 0.86, but 14 x 240 1.05 1.03 0.96, 18 x 200 1.13 1.12 1.07, 12 x 320 1.09 1.04 0.93
 // Sequences of up to three chunks, which would leave waves idle, take 0.6 to 1.0.  Of longer ones, smaller calls stay with the others
 // although the forward call alone would gain (16 x 8 16.2 us, 14.6 here; 16 x 20 19.8, 17.4): the walks of the backward call that takes the
 // span states want spans of one or two chunks there (both calls: 16 x 8 39.9 us, here 44.4; 16 x 20 52.5, here 52.5 to 58; [B,T,H,d]
@@ -92,8 +93,8 @@ inline int onepass_plain_chunks(const OnePassCall &p) {
     if (bh > 128) return nchunks <= 8 && bh <= (nchunks == 8 ? 256 : nchunks == 7 ? 192 : nchunks == 6 ? 170 : 0) ? 8 : 0;
     if (groups(8) <= 256) return 8;
     if (groups(4) <= 512) return 4;
-    // (a second round that is about half full: 2048 chunks and 942 more)
-    return groups(8) <= 512 && total >= 2990 && !p.prologue ? 8 : 0;
+    // (a second round that is about half full: 2048 chunks and 942 more; of long sequences of small heads somewhat more, as with the epilogue)
+    return groups(8) <= 512 && total >= (small && nchunks > 128 ? 3300 : 2990) && !p.prologue ? 8 : 0;
 }
 
 constexpr int onepass_resident(int chunks, bool two_sided) { return chunks == 8 || two_sided ? 256 : 512; }     // groups at once

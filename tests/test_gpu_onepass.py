@@ -242,7 +242,7 @@ def test_chain_behind_zeros(dk, dv, B, H, chunks):
 
 
 @pytest.mark.parametrize("dk,dv", [(36, 72), (32, 64)])
-@pytest.mark.parametrize("two_sided,bh,chunks", [(False, 36, 112), (True, 50, 32), (False, 12, 250), (True, 40, 64), (True, 12, 128)])
+@pytest.mark.parametrize("two_sided,bh,chunks", [(False, 36, 112), (True, 50, 32), (False, 12, 288), (True, 40, 64), (True, 12, 128)])
 def test_several_rounds(two_sided, bh, chunks, dk, dv):
     """Groups in several rounds, of spans in order (work-groups a multiple of eight, sequences not), in ranges of whole sequences, and in ranges that
     sequences straddle, with slow gates: as the two-pass kernels have it (which GLA_CARRY_KERNEL asks for)."""
